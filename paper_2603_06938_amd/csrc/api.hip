@@ -60,7 +60,11 @@ static swimba_status check_mixer(const swimba_dims *d)
     return SWIMBA_OK;
 }
 
-static void layout_of(const swimba_dims *d, swimba_ws_layout *o)
+// Scratch of the fp32 chain behind the stage arrays (offsets from the workspace's start)
+struct ChainF32Layout {
+    size_t cop, bop, gop, hseg, aseg;
+};
+static void layout_of(const swimba_dims *d, swimba_ws_layout *o, ChainF32Layout *cf = nullptr)
 {
     const Shape s = make_shape(d);
     const size_t T = (size_t)s.B * s.L;
@@ -94,6 +98,17 @@ static void layout_of(const swimba_dims *d, swimba_ws_layout *o)
     if (mf) off = align_up(off + (size_t)s.B * s.nc * s.H * s.Q * sizeof(float), 256);
     o->hmid = off;
     if (mf) off = align_up(off + (size_t)s.B * (PASS_SPLIT_MAX_SEGMENTS - 1) * s.H * s.P * s.N * sizeof(float), 256);
+    if (!mf) {
+        size_t ops, g, seg, dec;
+        chain_f32_sizes(d, &ops, &g, &seg, &dec);
+        ChainF32Layout l;
+        l.cop = off;  off = align_up(off + ops, 256);
+        l.bop = off;  off = align_up(off + ops, 256);
+        l.gop = off;  off = align_up(off + g, 256);
+        l.hseg = off; off = align_up(off + seg, 256);
+        l.aseg = off; off = align_up(off + dec, 256);
+        if (cf) *cf = l;
+    }
     o->total = off > 0 ? off : 256;
 }
 
@@ -186,6 +201,7 @@ struct Ws {
     float *states;
     void *states_lp, *cmix, *bmix_t8, *bmix_frag, *cb;
     float *cs2, *fdec, *cdec, *hmid;
+    float *cop, *bop, *gop, *hseg, *aseg;   // fp32 chain
 };
 
 static swimba_status carve(const swimba_dims *d, void *workspace, size_t bytes, Ws *ws)
@@ -193,7 +209,8 @@ static swimba_status carve(const swimba_dims *d, void *workspace, size_t bytes, 
     swimba_status st = check_mixer(d);
     if (st != SWIMBA_OK) return st;
     swimba_ws_layout lo;
-    layout_of(d, &lo);
+    ChainF32Layout cf = {0, 0, 0, 0, 0};
+    layout_of(d, &lo, &cf);
     if (!workspace || bytes < lo.total || ((uintptr_t)workspace & 255u)) return SWIMBA_ERR_WORKSPACE;
     char *p = (char *)workspace;
     ws->idx = (int32_t *)(p + lo.topk_idx);
@@ -210,6 +227,11 @@ static swimba_status carve(const swimba_dims *d, void *workspace, size_t bytes, 
     ws->fdec = mf ? (float *)(p + lo.fdec) : nullptr;
     ws->cdec = mf ? (float *)(p + lo.cdec) : nullptr;
     ws->hmid = mf ? (float *)(p + lo.hmid) : nullptr;
+    ws->cop = mf ? nullptr : (float *)(p + cf.cop);
+    ws->bop = mf ? nullptr : (float *)(p + cf.bop);
+    ws->gop = mf ? nullptr : (float *)(p + cf.gop);
+    ws->hseg = mf ? nullptr : (float *)(p + cf.hseg);
+    ws->aseg = mf ? nullptr : (float *)(p + cf.aseg);
     return SWIMBA_OK;
 }
 
@@ -538,14 +560,12 @@ swimba_status swimba_mixer_fwd(const swimba_dims *dims, const void *x, const voi
     const Shape s = make_shape(dims);
     const bool mf = use_mfma_path(dims);
     if (T > 0) {
+        if (!mf)
+            return launch_chain_f32(s, dims->io_dtype, x, dt, A, D, B_experts, C_experts, router_logits, nullptr, h0, y,
+                                    h_final, topk_idx ? topk_idx : ws.idx, topk_w ? topk_w : ws.w, ws.cop, ws.bop, ws.gop,
+                                    ws.hseg, ws.aseg, stream);
         // On the bf16 MFMA path the mix kernel routes the tokens itself and the chunk-state
         // kernel computes the cumsum itself: two launches fewer.
-        if (!mf) {
-            st = swimba_stage_router(dims, router_logits, workspace, workspace_bytes, hip_stream);
-            if (st != SWIMBA_OK) return st;
-            st = swimba_stage_cumsum(dims, dt, A, workspace, workspace_bytes, hip_stream);
-            if (st != SWIMBA_OK) return st;
-        }
         const bool chunk_mix = use_chunk_mix(dims, false);
         st = chunk_mix ? swimba_stage_mix_chunk(dims, B_experts, C_experts, router_logits, workspace, workspace_bytes,
                                                 hip_stream)
@@ -580,7 +600,7 @@ swimba_status swimba_mixer_fwd(const swimba_dims *dims, const void *x, const voi
             return launch_pass64_mfma(s, x, dt, D, ws.cmix, ws.bmix_t8, ws.cb, ws.cs2, ws.fdec, ws.cdec, h0, h_final, y,
                                       stream, nseg, ws.hmid);
         }
-        if (mf && s.nc <= OUTPUT_LOOKBACK_MAX_CHUNKS) {
+        if (s.nc <= OUTPUT_LOOKBACK_MAX_CHUNKS) {
             // short sequences: no scan launch; the G^T tiles ride in the chunk-state launch and every
             // workgroup of the output kernel carries the state up to its own chunk
             st = launch_chunk_state_mfma(s, x, dt, A, ws.bmix_t8, ws.cs, ws.states_lp, stream, 1, ws.cmix,
@@ -1068,12 +1088,8 @@ static swimba_status mixer_selected_core(const swimba_dims *dims, const void *x,
             }
             st = launch_chunk_state_mfma(s, x, dt, A, ws.bmix_t8, ws.cs, ws.states_lp, stream);
         } else {
-            st = launch_slot_ids(ws.idx, T, dims->top_k, stream);
-            if (st != SWIMBA_OK) return st;
-            st = launch_cumsum(s, dims->io_dtype, dt, A, ws.cs, stream);
-            if (st != SWIMBA_OK) return st;
-            st = launch_chunk_state_generic(s, dims->io_dtype, x, dt, B_sel, ws.idx, w_sel, ws.cs, ws.states,
-                                            stream);
+            return launch_chain_f32(s, dims->io_dtype, x, dt, A, D, B_sel, C_sel, nullptr, w_sel, h0, y, h_final, nullptr,
+                                    nullptr, ws.cop, ws.bop, ws.gop, ws.hseg, ws.aseg, stream);
         }
         if (st != SWIMBA_OK) return st;
     }
@@ -1082,12 +1098,8 @@ static swimba_status mixer_selected_core(const swimba_dims *dims, const void *x,
                 : launch_state_scan(s, h0, h_final, ws.states, nullptr, ws.cs, stream);
         if (st != SWIMBA_OK) return st;
     }
-    if (T > 0) {
-        st = mf ? launch_output_mfma(s, x, dt, D, ws.cmix, ws.cb, ws.cs, ws.states_lp, y, nullptr, 0, 0, stream)
-                : launch_output_generic(s, dims->io_dtype, x, dt, D, B_sel, C_sel, ws.idx, w_sel, w_sel, ws.cs,
-                                        ws.states, y, nullptr, 0, 0, stream);
-        if (st != SWIMBA_OK) return st;
-    }
+    if (T > 0)
+        return launch_output_mfma(s, x, dt, D, ws.cmix, ws.cb, ws.cs, ws.states_lp, y, nullptr, 0, 0, stream);
     return SWIMBA_OK;
 }
 
@@ -1165,7 +1177,6 @@ swimba_status swimba_mixer_fwd_proj(const swimba_dims *dims, int32_t d_model, co
                                 dims->io_dtype, u, W_B, W_C, router_logits, bsel, csel, ws.idx, ws.w,
                                 (int32_t *)(base + ml.counts), (int32_t *)(base + ml.lists), 1, stream);
         if (st != SWIMBA_OK) return st;
-        // the selection leaves the workspace before the fp32 kernels reuse its place for slot ids
         if (topk_idx || topk_w) {
             const size_t cnt = (size_t)T * dims->top_k;
             hipError_t e = hipSuccess;

@@ -1,0 +1,581 @@
+// SSD forward in fp32 arithmetic for any (P, N) within the library limits, on v_mfma_f32_32x32x2_f32
+// (paper, background section on SSD: matrix work inside chunks, a linear recurrence between chunks;
+// Theorem 1: the mixed streams feed one plain SSM).  fp32 io, and bf16 io at the sizes the bf16 MFMA
+// kernels do not take.
+//
+// The result does not depend on the chunk length, so the kernels walk their own steps of 64 tokens:
+// the work inside a step grows with its length, the states between steps never leave registers.
+//   mix_ops_kernel    (batch, step, group): routes 64 tokens, mixes their B and C rows in fp32 and
+//                     writes them, and the masked products G = C B^T, in the register layout of the
+//                     operands the chain reads.  Shared by the heads of the group.
+//   chain_f32_kernel  (batch, segment, head, 32 channels): walks the steps of a segment with the state in
+//                     accumulator registers.  A wave owns 32 of the N state columns; its accumulator rows
+//                     n = 8a + 4kg + b of channel p are at the same time the B operand of the readout
+//                     contraction, so the state passes through neither LDS nor memory.
+//                       Y[i][p]   = sum_n (exp(cs_i) C[i][n]) S[n][p]  +  sum_{j<=i} M[i][j] x[j][p]
+//                       S[n][p]  <- exp(cs_last) S[n][p] + sum_j B[j][n] (dt_j exp(cs_last - cs_j) x[j][p])
+//                       M[i][j]   = G[i][j] exp(cs_i - cs_j) dt_j          (every exponent <= 0)
+//                     The readout is split over the state columns, the 12 blocks of M over the waves, and
+//                     the four partial Y tiles are added in a fixed order: 76 MFMAs per wave and step
+//                     (N = 128) whatever the wave.
+// Where batch x heads x slices alone would leave compute units idle, a sequence is walked as several
+// segments: one launch sums each segment's own contribution to the state (state part only), and a
+// segment of the output launch starts from the sum of those in front of it (the recurrence is linear
+// in the state).
+//
+// Bound: the f32 matrix pipe (157 TFLOP/s); 64-cycle MFMAs, one operand register per MFMA, so LDS and
+// L2 are far from their limits.
+#include "common.hpp"
+#include "mfma_util.hpp"
+
+#include <atomic>
+
+namespace swimba {
+
+constexpr int CF_STEP = 64;            // tokens per step
+constexpr int CF_MIX_THREADS = 512;
+constexpr int CF_XS = CF_STEP + 4;     // row stride of the transposed x tile (floats)
+constexpr int CF_GBLK = 12;            // 4-column blocks of the masked 64 x 64 product: 4 of tile row 0, 8 of tile row 1
+
+typedef float __attribute__((ext_vector_type(4))) cf_f32x4_t;
+
+__device__ __forceinline__ f32x16_t mfma_f32(float a, float b, f32x16_t c)
+{
+    return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
+}
+
+// four consecutive elements as fp32
+__device__ __forceinline__ float4 load4(const float *p) { return *reinterpret_cast<const float4 *>(p); }
+__device__ __forceinline__ float4 load4(const bf16 *p)
+{
+    const uint2 u = *reinterpret_cast<const uint2 *>(p);
+    return make_float4(bf_lo(u.x), bf_hi(u.x), bf_lo(u.y), bf_hi(u.y));
+}
+
+// Operand arrays, per (batch, step, group), N padded to NT tiles of 32 columns:
+//   cop (2, NT, 4, 64, 4)  [I][nt][a][lane][b] = C[32 I + lane%32][32 nt + 8a + 4(lane/32) + b]
+//   bop (NT, 8, 64, 4)     [nt][q][lane][b]    = B[8q + 4(lane/32) + b][32 nt + lane%32]
+//   gop (12, 64, 4)        [blk][lane][b]      = (j <= i) C[i] . B[j], blk < 4: i = lane%32, q = blk, else i = 32 + lane%32,
+//                          q = blk - 4; j = 8q + 4(lane/32) + b
+template <typename T>
+__global__ void __launch_bounds__(CF_MIX_THREADS)
+mix_ops_kernel(const T *__restrict__ Be, const T *__restrict__ Ce, const T *__restrict__ logits,
+               int32_t *__restrict__ idx_out, float *__restrict__ w_out, const float *__restrict__ w_sel,
+               float *__restrict__ cop, float *__restrict__ bop, float *__restrict__ gop, Shape s, int NT)
+{
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    const int K = s.K, NP = 32 * NT, RS = NP + 4;        // row stride of the mixed rows
+    int32_t *s_idx = reinterpret_cast<int32_t *>(smem_raw);                 // [64][K]
+    float *s_w = reinterpret_cast<float *>(s_idx + CF_STEP * K);             // [64][K]
+    float *s_B = s_w + CF_STEP * K;                                          // [64][RS]
+    float *s_C = s_B + CF_STEP * RS;                                         // [64][RS]
+    const int g = blockIdx.x % s.G;
+    const int c = (blockIdx.x / s.G) % s.nc;
+    const int b = blockIdx.x / (s.G * s.nc);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int valid = min(CF_STEP, s.L - c * CF_STEP);
+    const int64_t tok0 = (int64_t)b * s.L + (int64_t)c * CF_STEP;
+    const bool sel = (w_sel != nullptr);
+
+    if (tid < CF_STEP) {
+        const int64_t t = tok0 + min(tid, valid - 1);
+        int32_t *ix = s_idx + tid * K;
+        float *wx = s_w + tid * K;
+        if (sel) {
+            for (int r = 0; r < K; ++r) { ix[r] = r; wx[r] = w_sel[t * K + r]; }
+        } else {
+            const T *gl = logits + t * s.E;
+            if (s.E <= 16) {
+                float v[16];
+#pragma unroll
+                for (int e = 0; e < 16; ++e) v[e] = to_float(gl[min(e, s.E - 1)]);
+                // every load is in flight before the first is used; the routing then reads them from LDS
+                float *row = s_B + tid * 17;
+#pragma unroll
+                for (int e = 0; e < 16; ++e) row[e] = v[e];
+                route_token([&](int e) { return row[e]; }, s.E, K, ix, wx);
+            } else {
+                route_token([&](int e) { return to_float(gl[e]); }, s.E, K, ix, wx);
+            }
+            if (g == 0 && tid < valid)
+                for (int r = 0; r < K; ++r) { idx_out[t * K + r] = ix[r]; w_out[t * K + r] = wx[r]; }
+        }
+        if (tid >= valid)
+            for (int r = 0; r < K; ++r) wx[r] = 0.f;     // rows past the end of the sequence mix to zero
+    }
+    __syncthreads();
+
+    // ---- mixed rows: a lane takes quads of 4 columns, four (token, quad) units of both streams at a time ----
+    const int rowsE = sel ? K : s.E;
+    const int64_t estride = (int64_t)s.G * s.N, tokstride = rowsE * estride;
+    const T *Bg = Be + (tok0 * rowsE * s.G + g) * s.N;
+    const T *Cg = Ce + (tok0 * rowsE * s.G + g) * s.N;
+    const int QPR = NP / 4, units = CF_STEP * QPR;       // units is a multiple of 512
+    const bool vec = (s.N % 4 == 0);
+    for (int u0 = tid; u0 < units; u0 += 4 * CF_MIX_THREADS) {
+        float4 ab[4], ac[4];
+#pragma unroll
+        for (int m = 0; m < 4; ++m) ab[m] = ac[m] = make_float4(0.f, 0.f, 0.f, 0.f);
+        for (int r = 0; r < K; ++r) {
+            float4 vb[4], vc[4];
+            float ww[4];
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+                const int u = min(u0 + m * CF_MIX_THREADS, units - 1);
+                const int j = u / QPR, n = (u % QPR) * 4;
+                const int64_t o = min(j, valid - 1) * tokstride + s_idx[j * K + r] * estride;
+                ww[m] = s_w[j * K + r];
+                if (vec) {
+                    const int nn = min(n, s.N - 4);
+                    vb[m] = load4(Bg + o + nn);
+                    vc[m] = load4(Cg + o + nn);
+                } else {
+                    float t[8];
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const int nn = min(n + q, s.N - 1);
+                        t[q] = to_float(Bg[o + nn]);
+                        t[4 + q] = to_float(Cg[o + nn]);
+                    }
+                    vb[m] = make_float4(t[0], t[1], t[2], t[3]);
+                    vc[m] = make_float4(t[4], t[5], t[6], t[7]);
+                }
+            }
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+                ab[m].x += ww[m] * vb[m].x; ab[m].y += ww[m] * vb[m].y; ab[m].z += ww[m] * vb[m].z; ab[m].w += ww[m] * vb[m].w;
+                ac[m].x += ww[m] * vc[m].x; ac[m].y += ww[m] * vc[m].y; ac[m].z += ww[m] * vc[m].z; ac[m].w += ww[m] * vc[m].w;
+            }
+        }
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+            const int u = u0 + m * CF_MIX_THREADS;
+            if (u < units) {
+                const int j = u / QPR, n = (u % QPR) * 4;
+                float *fb = reinterpret_cast<float *>(&ab[m]), *fc = reinterpret_cast<float *>(&ac[m]);
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    if (n + q >= s.N) fb[q] = fc[q] = 0.f;          // padding columns
+                *reinterpret_cast<float4 *>(s_B + j * RS + n) = ab[m];
+                *reinterpret_cast<float4 *>(s_C + j * RS + n) = ac[m];
+            }
+        }
+    }
+    __syncthreads();
+
+    const int64_t bcg = blockIdx.x;
+    float4 *co = reinterpret_cast<float4 *>(cop) + bcg * (2 * NT * 4 * 64);
+    float4 *bo = reinterpret_cast<float4 *>(bop) + bcg * (NT * 8 * 64);
+    float4 *go = reinterpret_cast<float4 *>(gop) + bcg * (CF_GBLK * 64);
+    // ---- G^T[j][i] = B[j] . C[i] in 16 x 16 tiles (v_mfma_f32_16x16x4_f32): lane (i = lane%16, kq = lane/16) ends
+    // ---- with four consecutive j of one i, which is a float4 of gop.  Tiles right of the diagonal are zero. ----
+    {
+        const int l16 = lane & 15, kq = lane >> 4;
+        for (int t = wave; t < 12; t += CF_MIX_THREADS / 64) {
+            // tile rows 0, 1 have columns J = 0, 1; rows 2, 3 columns 0..3
+            const int I = t < 4 ? t >> 1 : 2 + ((t - 4) >> 2), J = t < 4 ? t & 1 : (t - 4) & 3;
+            cf_f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+            if (J <= I) {
+                const float *br = s_B + (16 * J + l16) * RS + 4 * kq, *cr = s_C + (16 * I + l16) * RS + 4 * kq;
+                for (int k = 0; k < NP; k += 16) {
+                    const float4 av = *reinterpret_cast<const float4 *>(br + k);
+                    const float4 bv = *reinterpret_cast<const float4 *>(cr + k);
+                    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av.x, bv.x, acc, 0, 0, 0);
+                    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av.y, bv.y, acc, 0, 0, 0);
+                    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av.z, bv.z, acc, 0, 0, 0);
+                    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av.w, bv.w, acc, 0, 0, 0);
+                }
+            }
+            const int i = 16 * I + l16, j0 = 16 * J + 4 * kq;
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (j0 + q > i) acc[q] = 0.f;
+            const int blk = (i >> 5) * 4 + (j0 >> 3);
+            go[blk * 64 + ((j0 >> 2) & 1) * 32 + (i & 31)] = make_float4(acc[0], acc[1], acc[2], acc[3]);
+        }
+    }
+    for (int u = tid; u < 2 * NT * 4 * 64; u += CF_MIX_THREADS) {
+        const int ln = u & 63, a = (u >> 6) & 3, nt = (u >> 8) % NT, I = (u >> 8) / NT;
+        co[u] = *reinterpret_cast<const float4 *>(s_C + (32 * I + (ln & 31)) * RS + 32 * nt + 8 * a + 4 * (ln >> 5));
+    }
+    for (int u = tid; u < NT * 8 * 64; u += CF_MIX_THREADS) {
+        const int ln = u & 63, q = (u >> 6) & 7, nt = u >> 9;
+        const float *src = s_B + (8 * q + 4 * (ln >> 5)) * RS + 32 * nt + (ln & 31);
+        bo[u] = make_float4(src[0], src[RS], src[2 * RS], src[3 * RS]);
+    }
+}
+
+// NTW: 32-column state tiles per wave (N <= 128 * NTW).  OUT: y (and h_final); otherwise the state part only:
+// the segment's own contribution to the state (from zero) into hseg, its total decay (log2) into aseg.
+template <typename T, int NTW, bool OUT>
+__global__ void __launch_bounds__(256, NTW == 1 ? 2 : 1)
+chain_f32_kernel(const T *__restrict__ x, const T *__restrict__ dt, const float *__restrict__ A,
+                 const float *__restrict__ D, const float *__restrict__ cop, const float *__restrict__ bop,
+                 const float *__restrict__ gop, const float *__restrict__ h0, float *__restrict__ h_final,
+                 float *__restrict__ hseg, float *__restrict__ aseg, T *__restrict__ y, Shape s, int NT, int nslice,
+                 int nrun, int nseg, int steps_per_seg, int total, int nblocks)
+{
+    __shared__ __align__(16) float s_x[2][32 * CF_XS];           // x^T of a step: [channel][token]
+    __shared__ __align__(16) float s_cs[2][CF_STEP], s_dt[2][CF_STEP], s_c[2][CF_STEP];
+    __shared__ __align__(16) float s_y[OUT ? 4 : 1][OUT ? CF_STEP * 32 : 1];   // partial Y per wave: [token][channel]
+
+    // (batch, segment, head, slice), neighbours (heads of one group) on one XCD: they read the same operands
+    const int lid = xcd_logical_id(blockIdx.x, nblocks);
+    if (lid >= total) return;
+    const int sl = lid % nslice;
+    const int h = (lid / nslice) % s.H;
+    const int seg = (lid / (nslice * s.H)) % nrun;
+    const int b = lid / (nslice * s.H * nrun);
+    const int g = (h * s.G) / s.H;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l32 = lane & 31, kg = lane >> 5;
+    const int c_begin = seg * steps_per_seg, c_end = min(s.nc, c_begin + steps_per_seg);
+    const int p0 = 32 * sl, P = s.P;
+    const float Ah = A[h] * LOG2E;
+    const float dsk = (OUT && D) ? D[h] : 0.f;
+
+    // ---- running state: rows n = 32 nt + 8a + 4kg + b, column p0 + l32, in register 4a + b ----
+    f32x16_t st[NTW];
+    const int p = p0 + l32;
+    auto state_at = [&](const float *base, int nt, int a, int q) -> float {      // base: one (P, N) state
+        const int n = 32 * nt + 8 * a + 4 * kg + q;
+        return (p < P && n < s.N) ? base[(int64_t)p * s.N + n] : 0.f;
+    };
+#pragma unroll
+    for (int k = 0; k < NTW; ++k) {
+        const int nt = wave * NTW + k;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) st[k][v] = 0.f;
+        if (OUT && h0) {
+            const float *hp = h0 + ((int64_t)b * s.H + h) * P * s.N;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) st[k][v] = state_at(hp, nt, v >> 2, v & 3);
+        }
+    }
+    if (OUT) {
+        for (int q = 0; q < seg; ++q) {                  // the state in front of this segment
+            const int64_t o = ((int64_t)b * (nseg - 1) + q) * s.H + h;
+            const float a = fast_exp2(aseg[o]);
+            const float *hp = hseg + o * P * s.N;
+#pragma unroll
+            for (int k = 0; k < NTW; ++k)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) st[k][v] = a * st[k][v] + state_at(hp, wave * NTW + k, v >> 2, v & 3);
+        }
+    }
+
+    // ---- loads of a step; every one is clamped and unconditional ----
+    const int xj = tid >> 2, xp = (tid & 3) * 8;         // this thread's token and 8 channels of the x tile
+    const bool vecx = (P % 8 == 0);
+    float xn[8];
+    float dtn = 0.f;
+    auto load_x = [&](int c) __attribute__((always_inline)) {
+        const int valid = min(CF_STEP, s.L - c * CF_STEP);
+        const int64_t t0 = (int64_t)b * s.L + (int64_t)c * CF_STEP;
+        const T *xr = x + ((t0 + min(xj, valid - 1)) * s.H + h) * P + p0;
+        if (vecx) {
+            const int pc = (p0 + xp < P) ? xp : 0;
+            const float4 v0 = load4(xr + pc), v1 = load4(xr + pc + 4);
+            xn[0] = v0.x; xn[1] = v0.y; xn[2] = v0.z; xn[3] = v0.w; xn[4] = v1.x; xn[5] = v1.y; xn[6] = v1.z; xn[7] = v1.w;
+        } else {
+#pragma unroll
+            for (int q = 0; q < 8; ++q) xn[q] = to_float(xr[min(xp + q, P - 1 - p0)]);
+        }
+        dtn = to_float(dt[(t0 + min(lane, valid - 1)) * s.H + h]);
+    };
+    float4 cr[NTW][2][4], br[NTW][8], gr[3];
+    const int64_t bg0 = ((int64_t)b * s.nc) * s.G + g;
+    auto load_c = [&](int c) __attribute__((always_inline)) {
+        const float4 *src = reinterpret_cast<const float4 *>(cop) + (bg0 + (int64_t)c * s.G) * (2 * NT * 4 * 64) + lane;
+#pragma unroll
+        for (int k = 0; k < NTW; ++k)
+#pragma unroll
+            for (int I = 0; I < 2; ++I)
+#pragma unroll
+                for (int a = 0; a < 4; ++a)
+                    cr[k][I][a] = src[((I * NT + min(wave * NTW + k, NT - 1)) * 4 + a) * 64];
+    };
+    auto load_b = [&](int c) __attribute__((always_inline)) {
+        const float4 *src = reinterpret_cast<const float4 *>(bop) + (bg0 + (int64_t)c * s.G) * (NT * 8 * 64) + lane;
+#pragma unroll
+        for (int k = 0; k < NTW; ++k)
+#pragma unroll
+            for (int q = 0; q < 8; ++q) br[k][q] = src[(min(wave * NTW + k, NT - 1) * 8 + q) * 64];
+    };
+    auto load_g = [&](int c) __attribute__((always_inline)) {
+        const float4 *src = reinterpret_cast<const float4 *>(gop) + (bg0 + (int64_t)c * s.G) * (CF_GBLK * 64) + lane;
+#pragma unroll
+        for (int t = 0; t < 3; ++t) gr[t] = src[(3 * wave + t) * 64];
+    };
+    // x^T tile and tables of step c (in the registers) into buffer buf
+    auto stage = [&](int c, int buf) __attribute__((always_inline)) {
+        const int valid = min(CF_STEP, s.L - c * CF_STEP);
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+            s_x[buf][(xp + q) * CF_XS + xj] = (xj < valid && p0 + xp + q < P) ? xn[q] : 0.f;
+        if (wave == 3) {
+            const float dv = (lane < valid) ? dtn : 0.f;
+            float cs = dv * Ah;
+#pragma unroll
+            for (int off = 1; off < 64; off <<= 1) {
+                const float v = __shfl_up(cs, off);
+                if (lane >= off) cs += v;
+            }
+            const float last = __shfl(cs, 63);
+            s_cs[buf][lane] = cs;
+            s_dt[buf][lane] = dv;
+            s_c[buf][lane] = dv * fast_exp2(last - cs);
+        }
+    };
+
+    float atot = 0.f;
+    load_x(c_begin);
+    if (OUT) { load_c(c_begin); load_g(c_begin); }
+    load_b(c_begin);
+    stage(c_begin, 0);
+    for (int c = c_begin; c < c_end; ++c) {
+        const int buf = (c - c_begin) & 1;
+        const int cn = min(c + 1, c_end - 1);
+        float xc[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) xc[q] = xn[q];
+        lds_barrier();                                   // step c is staged
+        load_x(cn);
+        const float *sx = s_x[buf] + l32 * CF_XS + 4 * kg;
+        const float cs_last = s_cs[buf][CF_STEP - 1];
+        f32x16_t yt[2];
+        if (OUT) {
+#pragma unroll
+            for (int v = 0; v < 16; ++v) yt[0][v] = yt[1][v] = 0.f;
+            const float ci[2] = {s_cs[buf][l32], s_cs[buf][32 + l32]};
+            const float ei[2] = {fast_exp2(ci[0]), fast_exp2(ci[1])};
+#pragma unroll
+            for (int k = 0; k < NTW; ++k)
+                if (wave * NTW + k < NT) {               // wave-uniform
+#pragma unroll
+                    for (int a = 0; a < 4; ++a) {
+                        const float4 u0 = cr[k][0][a], u1 = cr[k][1][a];
+                        yt[0] = mfma_f32(u0.x * ei[0], st[k][4 * a + 0], yt[0]);
+                        yt[1] = mfma_f32(u1.x * ei[1], st[k][4 * a + 0], yt[1]);
+                        yt[0] = mfma_f32(u0.y * ei[0], st[k][4 * a + 1], yt[0]);
+                        yt[1] = mfma_f32(u1.y * ei[1], st[k][4 * a + 1], yt[1]);
+                        yt[0] = mfma_f32(u0.z * ei[0], st[k][4 * a + 2], yt[0]);
+                        yt[1] = mfma_f32(u1.z * ei[1], st[k][4 * a + 2], yt[1]);
+                        yt[0] = mfma_f32(u0.w * ei[0], st[k][4 * a + 3], yt[0]);
+                        yt[1] = mfma_f32(u1.w * ei[1], st[k][4 * a + 3], yt[1]);
+                    }
+                }
+            load_c(cn);
+            // the wave's three 8-token blocks of M (block ids 3 wave .. + 2)
+#pragma unroll
+            for (int t = 0; t < 3; ++t) {
+                const int id = 3 * wave + t;
+                const bool up = id >= 4;                 // wave-uniform
+                const int q = up ? id - 4 : id;
+                const float4 cj = *reinterpret_cast<const float4 *>(&s_cs[buf][8 * q + 4 * kg]);
+                const float4 dj = *reinterpret_cast<const float4 *>(&s_dt[buf][8 * q + 4 * kg]);
+                const float4 xv = *reinterpret_cast<const float4 *>(sx + 8 * q);
+                const float cii = up ? ci[1] : ci[0];
+                // entries with j > i are zero in G; the clamp keeps their factor finite
+                const float m0 = gr[t].x * (dj.x * fast_exp2(fminf(cii - cj.x, 0.f)));
+                const float m1 = gr[t].y * (dj.y * fast_exp2(fminf(cii - cj.y, 0.f)));
+                const float m2 = gr[t].z * (dj.z * fast_exp2(fminf(cii - cj.z, 0.f)));
+                const float m3 = gr[t].w * (dj.w * fast_exp2(fminf(cii - cj.w, 0.f)));
+                if (up) {
+                    yt[1] = mfma_f32(m0, xv.x, yt[1]);
+                    yt[1] = mfma_f32(m1, xv.y, yt[1]);
+                    yt[1] = mfma_f32(m2, xv.z, yt[1]);
+                    yt[1] = mfma_f32(m3, xv.w, yt[1]);
+                } else {
+                    yt[0] = mfma_f32(m0, xv.x, yt[0]);
+                    yt[0] = mfma_f32(m1, xv.y, yt[0]);
+                    yt[0] = mfma_f32(m2, xv.z, yt[0]);
+                    yt[0] = mfma_f32(m3, xv.w, yt[0]);
+                }
+            }
+            load_g(cn);
+        } else {
+            atot += cs_last;
+        }
+        // ---- state ----
+        {
+            const float dec = fast_exp2(cs_last);
+#pragma unroll
+            for (int k = 0; k < NTW; ++k)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) st[k][v] *= dec;
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                const float4 cj = *reinterpret_cast<const float4 *>(&s_c[buf][8 * q + 4 * kg]);
+                const float4 xv = *reinterpret_cast<const float4 *>(sx + 8 * q);
+                const float x0 = xv.x * cj.x, x1 = xv.y * cj.y, x2 = xv.z * cj.z, x3 = xv.w * cj.w;
+#pragma unroll
+                for (int k = 0; k < NTW; ++k) {
+                    if (wave * NTW + k >= NT) continue;  // wave-uniform
+                    st[k] = mfma_f32(br[k][q].x, x0, st[k]);
+                    st[k] = mfma_f32(br[k][q].y, x1, st[k]);
+                    st[k] = mfma_f32(br[k][q].z, x2, st[k]);
+                    st[k] = mfma_f32(br[k][q].w, x3, st[k]);
+                }
+            }
+            load_b(cn);
+        }
+        if (OUT) {
+            // the partial tiles of the four waves meet in LDS (those of the previous step were added up in front
+            // of the barrier at the top)
+#pragma unroll
+            for (int I = 0; I < 2; ++I)
+#pragma unroll
+                for (int v = 0; v < 16; ++v)
+                    s_y[wave][(32 * I + 8 * (v >> 2) + 4 * kg + (v & 3)) * 32 + l32] = yt[I][v];
+        }
+        stage(cn, buf ^ 1);
+        if (OUT) {
+            lds_barrier();
+            const int valid = min(CF_STEP, s.L - c * CF_STEP);
+            if (xj < valid && p0 + xp < P) {
+                float r[8];
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    const float4 a0 = *reinterpret_cast<const float4 *>(&s_y[0][xj * 32 + xp + 4 * q]);
+                    const float4 a1 = *reinterpret_cast<const float4 *>(&s_y[1][xj * 32 + xp + 4 * q]);
+                    const float4 a2 = *reinterpret_cast<const float4 *>(&s_y[2][xj * 32 + xp + 4 * q]);
+                    const float4 a3 = *reinterpret_cast<const float4 *>(&s_y[3][xj * 32 + xp + 4 * q]);
+                    r[4 * q + 0] = (a0.x + a1.x) + (a2.x + a3.x) + dsk * xc[4 * q + 0];
+                    r[4 * q + 1] = (a0.y + a1.y) + (a2.y + a3.y) + dsk * xc[4 * q + 1];
+                    r[4 * q + 2] = (a0.z + a1.z) + (a2.z + a3.z) + dsk * xc[4 * q + 2];
+                    r[4 * q + 3] = (a0.w + a1.w) + (a2.w + a3.w) + dsk * xc[4 * q + 3];
+                }
+                T *yr = y + (((int64_t)b * s.L + (int64_t)c * CF_STEP + xj) * s.H + h) * P + p0 + xp;
+                if (vecx) {
+                    if constexpr (sizeof(T) == 4) {
+                        *reinterpret_cast<float4 *>(yr) = make_float4(r[0], r[1], r[2], r[3]);
+                        *reinterpret_cast<float4 *>(yr + 4) = make_float4(r[4], r[5], r[6], r[7]);
+                    } else {
+                        *reinterpret_cast<uint4 *>(yr) = pack8(r);
+                    }
+                } else {
+#pragma unroll
+                    for (int q = 0; q < 8; ++q)
+                        if (p0 + xp + q < P) yr[q] = from_float<T>(r[q]);
+                }
+            }
+        }
+    }
+    float *dst = OUT ? (seg == nseg - 1 && h_final ? h_final + ((int64_t)b * s.H + h) * P * s.N : nullptr)
+                     : hseg + (((int64_t)b * (nseg - 1) + seg) * s.H + h) * P * s.N;
+    if (dst && p < P) {
+#pragma unroll
+        for (int k = 0; k < NTW; ++k)
+#pragma unroll
+            for (int a = 0; a < 4; ++a) {
+                const int n = 32 * (wave * NTW + k) + 8 * a + 4 * kg;
+                float *q = dst + (int64_t)p * s.N + n;
+                if (s.N % 4 == 0) {
+                    if (n < s.N)
+                        *reinterpret_cast<float4 *>(q) = make_float4(st[k][4 * a], st[k][4 * a + 1], st[k][4 * a + 2], st[k][4 * a + 3]);
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (n + e < s.N) q[e] = st[k][4 * a + e];
+                }
+            }
+    }
+    if (!OUT && sl == 0 && tid == 0) aseg[((int64_t)b * (nseg - 1) + seg) * s.H + h] = atot;
+}
+
+// Segments a sequence is walked in.  A chain keeps a quarter of a compute unit's two resident workgroups busy
+// for its whole segment, so short of about 1.5 workgroups per compute unit the chip idles; the extra
+// launch (state part of all segments but the last, 2/5 of the work) pays from four steps per segment on.
+int chain_f32_segments(int64_t B, int64_t L, int64_t H, int64_t P)
+{
+    const int64_t steps = (L + CF_STEP - 1) / CF_STEP, chains = B * H * ((P + 31) / 32);
+    if (chains == 0) return 1;
+    int nseg = 1;
+    while (nseg < CHAIN_F32_MAX_SEGMENTS && chains * nseg < 384 && steps >= 8 * (int64_t)nseg) nseg *= 2;
+    return nseg;
+}
+
+void chain_f32_sizes(const swimba_dims *d, size_t *ops, size_t *g, size_t *seg, size_t *dec)
+{
+    const size_t nc = ((size_t)d->seqlen + CF_STEP - 1) / CF_STEP, NT = ((size_t)d->dstate + 31) / 32;
+    const size_t items = (size_t)d->batch * nc * d->ngroups;
+    const size_t nseg = chain_f32_segments(d->batch, d->seqlen, d->nheads, d->headdim);
+    *ops = items * CF_STEP * NT * 32 * sizeof(float);
+    *g = items * CF_GBLK * 64 * 16;
+    *dec = (size_t)d->batch * (nseg - 1) * d->nheads * sizeof(float);
+    *seg = (size_t)d->batch * (nseg - 1) * d->nheads * d->headdim * d->dstate * sizeof(float);
+}
+
+template <typename T, int NTW>
+static void launch_chain_t(const Shape &s, const void *x, const void *dt, const float *A, const float *D, const float *cop,
+                           const float *bop, const float *gop, const float *h0, float *h_final, float *hseg,
+                           float *aseg, void *y, int NT, int nseg, hipStream_t st)
+{
+    const int nslice = (s.P + 31) / 32, sps = (s.nc + nseg - 1) / nseg;
+    const int used = (s.nc + sps - 1) / sps;             // segments that have steps
+    if (used > 1) {
+        const int total = s.B * (used - 1) * s.H * nslice, nblocks = xcd_padded(total);
+        hipLaunchKernelGGL((chain_f32_kernel<T, NTW, false>), dim3(nblocks), dim3(256), 0, st, (const T *)x, (const T *)dt,
+                           A, D, cop, bop, gop, h0, h_final, hseg, aseg, (T *)y, s, NT, nslice, used - 1, used, sps, total,
+                           nblocks);
+    }
+    const int total = s.B * used * s.H * nslice, nblocks = xcd_padded(total);
+    hipLaunchKernelGGL((chain_f32_kernel<T, NTW, true>), dim3(nblocks), dim3(256), 0, st, (const T *)x, (const T *)dt, A,
+                       D, cop, bop, gop, h0, h_final, hseg, aseg, (T *)y, s, NT, nslice, used, used, sps, total, nblocks);
+}
+
+template <typename T>
+static swimba_status launch_f32_t(const Shape &s, const void *x, const void *dt, const float *A, const float *D,
+                                  const void *Be, const void *Ce, const void *logits, const float *w_sel,
+                                  const float *h0, void *y, float *h_final, int32_t *idx, float *w, float *cop,
+                                  float *bop, float *gop, float *hseg, float *aseg, int nseg, hipStream_t st)
+{
+    const int NT = (s.N + 31) / 32;
+    const size_t shm = (size_t)CF_STEP * s.K * 8 + (size_t)2 * CF_STEP * (32 * NT + 4) * sizeof(float);
+    // more than 64 KB of dynamic LDS has to be allowed once per device
+    static std::atomic<uint64_t> attr_set{0};            // one bit per device ordinal
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) { set_last_hip_error((int)e); return SWIMBA_ERR_HIP; }
+    const uint64_t bit = 1ull << (dev & 63);
+    if (!(attr_set.load(std::memory_order_acquire) & bit)) {
+        constexpr size_t most = (size_t)CF_STEP * SWIMBA_MAX_TOPK * 8 + (size_t)2 * CF_STEP * (SWIMBA_MAX_DSTATE + 4) * sizeof(float);
+        e = hipFuncSetAttribute((const void *)mix_ops_kernel<T>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)most);
+        if (e != hipSuccess) { set_last_hip_error((int)e); return SWIMBA_ERR_HIP; }
+        attr_set.fetch_or(bit, std::memory_order_release);
+    }
+    hipLaunchKernelGGL(mix_ops_kernel<T>, dim3((unsigned)((int64_t)s.B * s.nc * s.G)), dim3(CF_MIX_THREADS), shm, st,
+                       (const T *)Be, (const T *)Ce, (const T *)logits, idx, w, w_sel, cop, bop, gop, s, NT);
+    SWIMBA_CHECK_LAUNCH();
+    if (NT <= 4)
+        launch_chain_t<T, 1>(s, x, dt, A, D, cop, bop, gop, h0, h_final, hseg, aseg, y, NT, nseg, st);
+    else
+        launch_chain_t<T, 2>(s, x, dt, A, D, cop, bop, gop, h0, h_final, hseg, aseg, y, NT, nseg, st);
+    SWIMBA_CHECK_LAUNCH();
+    return SWIMBA_OK;
+}
+
+// logits / idx / w: routing inside (w_sel == nullptr); w_sel: rows of the selected experts with given weights
+swimba_status launch_chain_f32(const Shape &s0, int io_dtype, const void *x, const void *dt, const float *A,
+                               const float *D, const void *Be, const void *Ce, const void *logits, const float *w_sel,
+                               const float *h0, void *y, float *h_final, int32_t *idx, float *w, float *cop, float *bop,
+                               float *gop, float *hseg, float *aseg, hipStream_t st)
+{
+    Shape s = s0;
+    s.Q = CF_STEP;
+    s.nc = (s.L + CF_STEP - 1) / CF_STEP;
+    if ((int64_t)s.B * s.nc == 0) return SWIMBA_OK;
+    const int nseg = chain_f32_segments(s.B, s.L, s.H, s.P);
+    if ((int64_t)s.B * s.nc * s.G > 0x7fffffffll || (int64_t)s.B * nseg * s.H * ((s.P + 31) / 32) > 0x7ffffff0ll)
+        return SWIMBA_ERR_UNSUPPORTED;
+    if (io_dtype == SWIMBA_BF16)
+        return launch_f32_t<bf16>(s, x, dt, A, D, Be, Ce, logits, w_sel, h0, y, h_final, idx, w, cop, bop, gop, hseg, aseg,
+                                  nseg, st);
+    return launch_f32_t<float>(s, x, dt, A, D, Be, Ce, logits, w_sel, h0, y, h_final, idx, w, cop, bop, gop, hseg, aseg,
+                               nseg, st);
+}
+
+}  // namespace swimba
