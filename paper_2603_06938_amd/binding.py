@@ -1,4 +1,5 @@
-"""Thin ctypes binding of libswimba.so: argument marshalling only.
+"""Thin binding of libswimba.so: argument marshalling only.  The forwards and decode steps marshal in
+native code (csrc/native.cpp), everything else through ctypes.
 
 Every function has the name and the argument order of the C entry point it
 calls (include/swimba.h); torch is used for device memory, dtypes and the
@@ -20,6 +21,7 @@ SWIMBA_F32, SWIMBA_BF16 = 0, 1
 MAX_TOPK = 16
 
 _lib = None
+_native = None      # the module of csrc/native.cpp, once loaded
 
 
 class SwimbaError(RuntimeError):
@@ -150,6 +152,17 @@ def _load():
     return _lib
 
 
+def _load_native():
+    """The calls a program makes every step run their checks and allocations natively (csrc/native.cpp)."""
+    global _native
+    if _native is None:
+        _load()
+        from . import _native as module
+        module.classes(MixerOut, StepOut, SwimbaError)
+        _native = module
+    return _native
+
+
 def library_loaded() -> bool:
     return _lib is not None
 
@@ -247,47 +260,13 @@ class MixerOut(NamedTuple):
 def swimba_mixer_fwd(x, dt, A, D, B_experts, C_experts, router_logits, top_k: int, chunk: int,
                      h0=None, *, y=None, h_final=None, topk_idx=None, topk_w=None, workspace=None,
                      want_h_final: bool = True, want_topk: bool = False) -> MixerOut:
-    d = dims_of(x, B_experts, top_k, chunk)
-    B, L, H, P, N, G, E = d.batch, d.seqlen, d.nheads, d.headdim, d.dstate, d.ngroups, d.nexperts
-    io = x.dtype
-    dev = x.device
-    if workspace is None:
-        workspace = alloc_workspace(d, dev)
-    if y is None:
-        y = torch.empty_like(x)
-    if h_final is None and want_h_final:
-        h_final = torch.empty((B, H, P, N), dtype=torch.float32, device=dev)
-    if want_topk and topk_idx is None:
-        topk_idx = torch.empty((B, L, top_k), dtype=torch.int32, device=dev)
-    if want_topk and topk_w is None:
-        topk_w = torch.empty((B, L, top_k), dtype=torch.float32, device=dev)
-    st = _load().swimba_mixer_fwd(
-        ctypes.byref(d), _ptr(x, "x", io, (B, L, H, P)), _ptr(dt, "dt", io, (B, L, H)),
-        _ptr(A, "A", torch.float32, (H,)), _ptr(D, "D", torch.float32, (H,)),
-        _ptr(B_experts, "B_experts", io, (B, L, E, G, N)),
-        _ptr(C_experts, "C_experts", io, (B, L, E, G, N)),
-        _ptr(router_logits, "router_logits", io, (B, L, E)),
-        _ptr(h0, "h0", torch.float32, (B, H, P, N)), _ptr(y, "y", io, (B, L, H, P)),
-        _ptr(h_final, "h_final", torch.float32, (B, H, P, N)),
-        _ptr(topk_idx, "topk_idx", torch.int32, (B, L, top_k)),
-        _ptr(topk_w, "topk_w", torch.float32, (B, L, top_k)),
-        _ptr(workspace, "workspace", torch.uint8), workspace.numel(), _stream())
-    _check(st, "swimba_mixer_fwd")
-    return MixerOut(y, h_final, topk_idx, topk_w)
+    return (_native or _load_native()).mixer_fwd(x, dt, A, D, B_experts, C_experts, router_logits, top_k, chunk, h0, y,
+                                                 h_final, topk_idx, topk_w, workspace, want_h_final, want_topk)
 
 
 def swimba_router_linear(u, W_g, router_logits=None) -> torch.Tensor:
     """u (..., Dm), W_g (E, Dm) -> routing logits (..., E) in the io dtype."""
-    Dm = u.shape[-1]
-    E = W_g.shape[0]
-    tokens = u.numel() // Dm if Dm else 0
-    if router_logits is None:
-        router_logits = torch.empty(tuple(u.shape[:-1]) + (E,), dtype=u.dtype, device=u.device)
-    st = _load().swimba_router_linear(tokens, Dm, E, _io_code(u), _ptr(u, "u"), _ptr(W_g, "W_g", u.dtype, (E, Dm)),
-                                      _ptr(router_logits, "router_logits", u.dtype, tuple(u.shape[:-1]) + (E,)),
-                                      _stream())
-    _check(st, "swimba_router_linear")
-    return router_logits
+    return (_native or _load_native()).router_linear(u, W_g, router_logits)
 
 
 def swimba_expert_proj_workspace_bytes(dims: swimba_dims, d_model: int) -> int:
@@ -401,56 +380,15 @@ def swimba_mixer_fwd_xe_proj(u, W_B, W_C, W_X, dt, A, D, router_logits, top_k: i
                              h_final=None, workspace=None, want_h_final: bool = True,
                              want_topk: bool = False) -> MixerOut:
     """Token features -> y with one projected input stream per expert (projection + expert-X forward in one call)."""
-    B, L, Dm = u.shape
-    E, G, N, _ = W_B.shape
-    _, H, P, _ = W_X.shape
-    io, dev = u.dtype, u.device
-    d = make_dims(B, L, H, P, N, G, E, top_k, chunk, _io_code(u))
-    if workspace is None:
-        n = swimba_mixer_xe_proj_workspace_bytes(d, Dm)
-        if n == 0:
-            raise SwimbaError(2, "swimba_mixer_xe_proj_workspace_bytes")
-        workspace = torch.empty(n, dtype=torch.uint8, device=dev)
-    if y is None:
-        y = torch.empty((B, L, H, P), dtype=io, device=dev)
-    if h_final is None and want_h_final:
-        h_final = torch.empty((B, H, P, N), dtype=torch.float32, device=dev)
-    topk_idx = torch.empty((B, L, top_k), dtype=torch.int32, device=dev) if want_topk else None
-    topk_w = torch.empty((B, L, top_k), dtype=torch.float32, device=dev) if want_topk else None
-    st = _load().swimba_mixer_fwd_xe_proj(
-        ctypes.byref(d), Dm, _ptr(u, "u", io, (B, L, Dm)), _ptr(W_B, "W_B", io, (E, G, N, Dm)),
-        _ptr(W_C, "W_C", io, (E, G, N, Dm)), _ptr(W_X, "W_X", io, (E, H, P, Dm)), _ptr(dt, "dt", io, (B, L, H)),
-        _ptr(A, "A", torch.float32, (H,)), _ptr(D, "D", torch.float32, (H,)),
-        _ptr(router_logits, "router_logits", io, (B, L, E)), _ptr(h0, "h0", torch.float32, (B, H, P, N)),
-        _ptr(y, "y", io, (B, L, H, P)), _ptr(h_final, "h_final", torch.float32, (B, H, P, N)),
-        _ptr(topk_idx, "topk_idx", torch.int32, (B, L, top_k)), _ptr(topk_w, "topk_w", torch.float32, (B, L, top_k)),
-        _ptr(workspace, "workspace", torch.uint8), workspace.numel(), _stream())
-    _check(st, "swimba_mixer_fwd_xe_proj")
-    return MixerOut(y, h_final, topk_idx, topk_w)
+    return (_native or _load_native()).mixer_fwd_xe_proj(u, W_B, W_C, W_X, dt, A, D, router_logits, top_k, chunk, h0, y,
+                                                         h_final, workspace, want_h_final, want_topk)
 
 
 def swimba_mixer_fwd_selected(x, dt, A, D, B_sel, C_sel, topk_w, chunk: int, h0=None, *, y=None, h_final=None,
                               workspace=None, want_h_final: bool = True) -> MixerOut:
     """Mixer forward on the selected experts' streams B_sel/C_sel (B,L,k,G,N) with given weights (B,L,k)."""
-    B, L, H, P = x.shape
-    _, _, K, G, N = B_sel.shape
-    io, dev = x.dtype, x.device
-    d = make_dims(B, L, H, P, N, G, K, K, chunk, _io_code(x))
-    if workspace is None:
-        workspace = alloc_workspace(d, dev)
-    if y is None:
-        y = torch.empty_like(x)
-    if h_final is None and want_h_final:
-        h_final = torch.empty((B, H, P, N), dtype=torch.float32, device=dev)
-    st = _load().swimba_mixer_fwd_selected(
-        ctypes.byref(d), _ptr(x, "x", io, (B, L, H, P)), _ptr(dt, "dt", io, (B, L, H)),
-        _ptr(A, "A", torch.float32, (H,)), _ptr(D, "D", torch.float32, (H,)),
-        _ptr(B_sel, "B_sel", io, (B, L, K, G, N)), _ptr(C_sel, "C_sel", io, (B, L, K, G, N)),
-        _ptr(topk_w, "topk_w", torch.float32, (B, L, K)), _ptr(h0, "h0", torch.float32, (B, H, P, N)),
-        _ptr(y, "y", io, (B, L, H, P)), _ptr(h_final, "h_final", torch.float32, (B, H, P, N)),
-        _ptr(workspace, "workspace", torch.uint8), workspace.numel(), _stream())
-    _check(st, "swimba_mixer_fwd_selected")
-    return MixerOut(y, h_final, None, None)
+    return (_native or _load_native()).mixer_fwd_selected(x, dt, A, D, B_sel, C_sel, topk_w, chunk, h0, y, h_final,
+                                                          workspace, want_h_final)
 
 
 def swimba_mixer_proj_workspace_bytes(dims: swimba_dims, d_model: int) -> int:
@@ -461,32 +399,8 @@ def swimba_mixer_fwd_proj(u, W_B, W_C, x, dt, A, D, router_logits, top_k: int, c
                           h_final=None, workspace=None, want_h_final: bool = True,
                           want_topk: bool = False) -> MixerOut:
     """In-projection of the selected experts and the mixer forward in one call; u (B,L,Dm), W (E,G,N,Dm)."""
-    B, L, H, P = x.shape
-    E, G, N, Dm = W_B.shape
-    io, dev = x.dtype, x.device
-    d = make_dims(B, L, H, P, N, G, E, top_k, chunk, _io_code(x))
-    if workspace is None:
-        n = swimba_mixer_proj_workspace_bytes(d, Dm)
-        if n == 0:
-            alloc_workspace(d, dev)   # raises with the status of the dims
-            raise SwimbaError(2, "swimba_mixer_proj_workspace_bytes")
-        workspace = torch.empty(n, dtype=torch.uint8, device=dev)
-    if y is None:
-        y = torch.empty_like(x)
-    if h_final is None and want_h_final:
-        h_final = torch.empty((B, H, P, N), dtype=torch.float32, device=dev)
-    topk_idx = torch.empty((B, L, top_k), dtype=torch.int32, device=dev) if want_topk else None
-    topk_w = torch.empty((B, L, top_k), dtype=torch.float32, device=dev) if want_topk else None
-    st = _load().swimba_mixer_fwd_proj(
-        ctypes.byref(d), Dm, _ptr(u, "u", io, (B, L, Dm)), _ptr(W_B, "W_B", io, (E, G, N, Dm)),
-        _ptr(W_C, "W_C", io, (E, G, N, Dm)), _ptr(x, "x", io, (B, L, H, P)), _ptr(dt, "dt", io, (B, L, H)),
-        _ptr(A, "A", torch.float32, (H,)), _ptr(D, "D", torch.float32, (H,)),
-        _ptr(router_logits, "router_logits", io, (B, L, E)), _ptr(h0, "h0", torch.float32, (B, H, P, N)),
-        _ptr(y, "y", io, (B, L, H, P)), _ptr(h_final, "h_final", torch.float32, (B, H, P, N)),
-        _ptr(topk_idx, "topk_idx", torch.int32, (B, L, top_k)), _ptr(topk_w, "topk_w", torch.float32, (B, L, top_k)),
-        _ptr(workspace, "workspace", torch.uint8), workspace.numel(), _stream())
-    _check(st, "swimba_mixer_fwd_proj")
-    return MixerOut(y, h_final, topk_idx, topk_w)
+    return (_native or _load_native()).mixer_fwd_proj(u, W_B, W_C, x, dt, A, D, router_logits, top_k, chunk, h0, y,
+                                                      h_final, workspace, want_h_final, want_topk)
 
 
 def swimba_mixer_xe_workspace_bytes(dims: swimba_dims) -> int:
@@ -760,28 +674,8 @@ def swimba_step(state, x, dt, A, D, B_experts, C_experts, router_logits, top_k: 
                 state_out=None, y=None, topk_idx=None, workspace=None, want_topk: bool = False) -> StepOut:
     """state (B,H,P,N) fp32, x (B,H,P), dt (B,H), B/C_experts (B,E,G,N), router_logits (B,E).
     state_out defaults to `state` (in place)."""
-    B, H, P = x.shape
-    _, E, G, N = B_experts.shape
-    io = x.dtype
-    d = make_dims(B, 1, H, P, N, G, E, top_k, 0, _io_code(x))
-    if state_out is None:
-        state_out = state
-    if y is None:
-        y = torch.empty_like(x)
-    if want_topk and topk_idx is None:
-        topk_idx = torch.empty((B, top_k), dtype=torch.int32, device=x.device)
-    if workspace is None:
-        workspace = torch.empty(max(swimba_step_workspace_bytes(d), 256), dtype=torch.uint8, device=x.device)
-    st = _load().swimba_step(
-        ctypes.byref(d), _ptr(state, "state", torch.float32, (B, H, P, N)),
-        _ptr(state_out, "state_out", torch.float32, (B, H, P, N)), _ptr(x, "x", io, (B, H, P)),
-        _ptr(dt, "dt", io, (B, H)), _ptr(A, "A", torch.float32, (H,)), _ptr(D, "D", torch.float32, (H,)),
-        _ptr(B_experts, "B_experts", io, (B, E, G, N)), _ptr(C_experts, "C_experts", io, (B, E, G, N)),
-        _ptr(router_logits, "router_logits", io, (B, E)), _ptr(y, "y", io, (B, H, P)),
-        _ptr(topk_idx, "topk_idx", torch.int32, (B, top_k)),
-        _ptr(workspace, "workspace", torch.uint8), workspace.numel(), _stream())
-    _check(st, "swimba_step")
-    return StepOut(y, state_out, topk_idx)
+    return (_native or _load_native()).step(state, x, dt, A, D, B_experts, C_experts, router_logits, top_k, state_out, y,
+                                            topk_idx, workspace, want_topk)
 
 
 def swimba_step_static(state, x, dt, A, D, B_experts, C_experts, router_logits, top_k: int, y, *,
@@ -826,28 +720,5 @@ def swimba_step_multi(state, x, dt, A, D, B_experts, C_experts, router_logits, t
                       state_out=None, y=None, topk_idx=None, workspace=None, want_topk: bool = False) -> StepOut:
     """L decode tokens per sequence in one call: state (B,H,P,N) fp32, x (B,L,H,P), dt (B,L,H),
     B/C_experts (B,L,E,G,N), router_logits (B,L,E).  state_out defaults to `state` (in place)."""
-    B, L, H, P = x.shape
-    _, _, E, G, N = B_experts.shape
-    io = x.dtype
-    d = make_dims(B, L, H, P, N, G, E, top_k, 0, _io_code(x))
-    if state_out is None:
-        state_out = state
-    if y is None:
-        y = torch.empty_like(x)
-    if want_topk and topk_idx is None:
-        topk_idx = torch.empty((B, L, top_k), dtype=torch.int32, device=x.device)
-    if workspace is None:
-        n = swimba_step_multi_workspace_bytes(d)
-        if n == 0:
-            raise SwimbaError(4 if L > 0 else 2, "swimba_step_multi_workspace_bytes")
-        workspace = torch.empty(n, dtype=torch.uint8, device=x.device)
-    st = _load().swimba_step_multi(
-        ctypes.byref(d), _ptr(state, "state", torch.float32, (B, H, P, N)),
-        _ptr(state_out, "state_out", torch.float32, (B, H, P, N)), _ptr(x, "x", io, (B, L, H, P)),
-        _ptr(dt, "dt", io, (B, L, H)), _ptr(A, "A", torch.float32, (H,)), _ptr(D, "D", torch.float32, (H,)),
-        _ptr(B_experts, "B_experts", io, (B, L, E, G, N)), _ptr(C_experts, "C_experts", io, (B, L, E, G, N)),
-        _ptr(router_logits, "router_logits", io, (B, L, E)), _ptr(y, "y", io, (B, L, H, P)),
-        _ptr(topk_idx, "topk_idx", torch.int32, (B, L, top_k)),
-        _ptr(workspace, "workspace", torch.uint8), workspace.numel(), _stream())
-    _check(st, "swimba_step_multi")
-    return StepOut(y, state_out, topk_idx)
+    return (_native or _load_native()).step_multi(state, x, dt, A, D, B_experts, C_experts, router_logits, top_k,
+                                                  state_out, y, topk_idx, workspace, want_topk)
