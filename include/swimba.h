@@ -471,7 +471,8 @@ swimba_status swimba_mixer_fwd_proj(const swimba_dims *dims, int32_t d_model, co
  *   y (B,H,P) io [out];  topk_idx (B,k) int32 [out] NULL = not wanted
  *   workspace: >= swimba_step_workspace_bytes(dims) bytes (the mixed streams of the
  *             step, B*G*N*2 fp32), 256-byte aligned; 0 from the query = invalid dims
- * Two kernels are enqueued (routing + mixing, then the state update).  Arithmetic is fp32.
+ * One kernel is enqueued for N a power of two from 16 to 256 and up to 16 experts, otherwise two
+ * (routing + mixing, then the state update).  Arithmetic is fp32.
  */
 size_t swimba_step_workspace_bytes(const swimba_dims *dims);
 swimba_status swimba_step(const swimba_dims *dims, const float *state_in, float *state_out,

@@ -113,7 +113,7 @@ static void layout_of(const swimba_dims *d, swimba_ws_layout *o, ChainF32Layout 
 }
 
 // compute units of the current device (0 if the query fails); asked once
-static int device_cus()
+int device_cus()
 {
     static std::atomic<int> ncu_cache{0};
     int ncu = ncu_cache.load(std::memory_order_relaxed);

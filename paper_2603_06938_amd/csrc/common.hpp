@@ -55,6 +55,7 @@ inline bool use_mfma_path(const swimba_dims *d)
 }
 
 void set_last_hip_error(int e);
+int device_cus();   // compute units of the current device (0 if the query fails)
 
 #define SWIMBA_CHECK_LAUNCH()                                  \
     do {                                                       \

@@ -1,0 +1,49 @@
+"""Decode steps at the edges of the one-launch kernel: every state size it takes and one it does not, head
+dimensions that leave a register row or a block partly empty, 16 and 17 experts (with and without
+routing inside the update), 16 and 17 tokens (one launch and two), tied logits; against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import swimba_oracle as orc
+from paper_2603_06938_amd import binding as sw
+from paper_2603_06938_amd import synth
+from gpu_util import TOL, host, rel_errors, to_device
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("cfg", [
+    # B, L, H, P, N, G, E, k, io
+    (2, 1, 4, 64, 16, 2, 16, 4, "bf16"),
+    (1, 16, 3, 24, 32, 1, 16, 16, "f32"),
+    (2, 17, 2, 65, 64, 1, 5, 2, "bf16"),
+    (1, 3, 2, 100, 256, 2, 17, 3, "f32"),
+    (2, 33, 4, 64, 128, 4, 40, 2, "bf16"),
+    (40, 1, 64, 64, 128, 8, 8, 2, "bf16"),     # more than one round of blocks
+    (2, 2, 2, 1, 128, 1, 1, 1, "f32"),
+    (1, 6, 2, 64, 80, 1, 8, 2, "bf16"),        # a state size with an update launch per token
+], ids=lambda c: "B%dL%dH%dP%dN%dG%dE%dk%d%s" % c)
+def test_step_sizes_match_oracle(cfg):
+    B, L, H, P, N, G, E, k, io = cfg
+    w = synth.Workload("sizes", B, L, H, P, N, G, E, k, 0, io, 7)
+    p = synth.make_decode_inputs(w, seed=sum(cfg[:8]))
+    p["router_logits"] = np.round(p["router_logits"] * 2) / 2          # ties: the lower index goes first
+    p["D"] = np.linspace(-1, 1, H).astype(np.float32)
+    d = to_device(p, io)
+    args = [d[q] for q in ("x", "dt", "A", "D", "B_experts", "C_experts", "router_logits")]
+    if L == 1:
+        args = [a[:, 0].contiguous() if i not in (2, 3) else a for i, a in enumerate(args)]
+        out = sw.swimba_step(d["state"], *args, k, want_topk=True)
+    else:
+        out = sw.swimba_step_multi(d["state"], *args, k, want_topk=True)
+    torch.cuda.synchronize()
+    ref = orc.mixer_fwd(p["x"], p["dt"], p["A"], p["D"], p["B_experts"], p["C_experts"], p["router_logits"], k,
+                        h0=p["state"].astype(np.float64))
+    np.testing.assert_array_equal(out.topk_idx.cpu().numpy().reshape(B, L, k), ref["topk_idx"])
+    assert out.state.data_ptr() == d["state"].data_ptr()
+    l2, linf = rel_errors(host(out.state), ref["h_final"], (0, 1))
+    assert l2 <= 1e-5 and linf <= 1e-5, ("state", l2, linf)   # fp32 arithmetic on both io types
+    # whole-output norm: with few tokens and channels a (batch, head) slice is a handful of cancelling scalars
+    l2, linf = rel_errors(host(out.y).reshape(B, L, H, P), ref["y"], ())
+    assert l2 <= TOL[io] and linf <= TOL[io], ("y", l2, linf)
