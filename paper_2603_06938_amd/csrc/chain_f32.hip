@@ -568,7 +568,9 @@ swimba_status launch_chain_f32(const Shape &s0, int io_dtype, const void *x, con
     s.Q = CF_STEP;
     s.nc = (s.L + CF_STEP - 1) / CF_STEP;
     if ((int64_t)s.B * s.nc == 0) return SWIMBA_OK;
-    const int nseg = chain_f32_segments(s.B, s.L, s.H, s.P);
+    // With the final state written over the initial one, only a single segment may read h0: the last segment of a
+    // sequence can end before another one has started.
+    const int nseg = h0 && h0 == h_final ? 1 : chain_f32_segments(s.B, s.L, s.H, s.P);
     if ((int64_t)s.B * s.nc * s.G > 0x7fffffffll || (int64_t)s.B * nseg * s.H * ((s.P + 31) / 32) > 0x7ffffff0ll)
         return SWIMBA_ERR_UNSUPPORTED;
     if (io_dtype == SWIMBA_BF16)

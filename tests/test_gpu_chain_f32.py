@@ -1,0 +1,83 @@
+"""The fp32 chain at its edges: lengths around its steps of 64 tokens, one to eight segments with a short and an
+empty last one, head and state sizes around its tiles of 32, one and two state tiles per wave, 16 and 17
+experts, bf16 io at sizes outside the bf16 kernels, and the final state written over the initial one;
+against the oracle in double.
+
+Tolerance: an output is a sum of at most N + 64 products per step with the state carried in fp32, so its
+relative error stays below about sqrt(steps * (N + 64)) * 2^-24 = 4e-6 for the longest sequence here, plus the
+exponentials of fp32 sums (2^-23 times a sum of up to 10): 1e-5 for the whole-output norm; bf16 io: y's
+rounding, 2^-8."""
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import swimba_oracle as orc
+from paper_2603_06938_amd import binding as sw
+from paper_2603_06938_amd import synth
+from gpu_util import host, to_device
+
+pytestmark = pytest.mark.gpu
+BAR = {"f32": 1e-5, "bf16": 2.0 ** -8}
+
+
+def inputs(B, L, H, P, N, G, E, k, io):
+    w = synth.Workload("chain", B, L, H, P, N, G, E, k, 64, io, 7)
+    p = synth.make_inputs(w, seed=B + 3 * L + 5 * H + 7 * P + 11 * N + 13 * E)
+    p["D"] = np.linspace(-1, 1, H).astype(np.float32)
+    h0 = (0.1 * np.random.default_rng(L).standard_normal((B, H, P, N))).astype(np.float32)
+    return p, h0
+
+
+def rel(got, ref):
+    return np.linalg.norm(got - ref) / np.linalg.norm(ref)
+
+
+def check(y, hf, p, k, h0, io):
+    ref = orc.mixer_fwd(p["x"], p["dt"], p["A"], p["D"], p["B_experts"], p["C_experts"], p["router_logits"], k,
+                        h0=h0)
+    assert rel(host(y), ref["y"]) <= BAR[io]
+    assert rel(host(hf), ref["h_final"]) <= 1e-5
+
+
+@pytest.mark.parametrize("cfg", [
+    # B, L, H, P, N, G, E, k, io
+    (1, 1, 1, 1, 1, 1, 1, 1, "f32"),
+    (2, 63, 2, 31, 33, 1, 4, 2, "f32"),
+    (2, 64, 4, 32, 32, 2, 16, 3, "f32"),
+    (1, 65, 3, 33, 126, 3, 17, 2, "f32"),
+    (1, 511, 2, 64, 128, 1, 8, 2, "f32"),
+    (1, 513, 2, 40, 129, 1, 8, 2, "f32"),      # two state tiles per wave
+    (1, 577, 4, 32, 256, 2, 8, 2, "f32"),      # ten steps in two segments
+    (1, 1100, 2, 64, 64, 1, 5, 5, "f32"),      # 18 steps in four segments, the last one short
+    (1, 2100, 2, 16, 48, 1, 8, 2, "f32"),      # 33 steps in eight: five each, the last one empty
+    (1, 600, 2, 24, 80, 1, 8, 2, "f32"),
+    (1, 600, 2, 128, 60, 1, 8, 2, "bf16"),     # outside the bf16 kernels
+    (1, 70, 2, 20, 160, 2, 8, 2, "bf16"),
+], ids=lambda c: "B%dL%dH%dP%dN%dG%dE%dk%d%s" % c)
+def test_chain_sizes(cfg):
+    k, io = cfg[7], cfg[8]
+    p, h0 = inputs(*cfg)
+    d = to_device(p, io)
+    args = [d[q] for q in ("x", "dt", "A", "D", "B_experts", "C_experts", "router_logits")]
+    for h in (None, h0):
+        out = sw.swimba_mixer_fwd(*args, k, 64, None if h is None else torch.from_numpy(h).cuda())
+        torch.cuda.synchronize()
+        check(out.y, out.h_final, p, k, h, io)
+
+
+def test_final_state_over_the_initial_one():
+    B, L, H, P, N, G, E, k = 2, 700, 4, 64, 128, 1, 8, 2
+    p, h0 = inputs(B, L, H, P, N, G, E, k, "f32")
+    d = to_device(p, "f32")
+    state = torch.from_numpy(h0).cuda()
+    y = torch.empty_like(d["x"])
+    dims = sw.dims_of(d["x"], d["B_experts"], k, 64)
+    ws = sw.alloc_workspace(dims, "cuda:0")
+    ptrs = [d[q].data_ptr() for q in ("x", "dt", "A", "D", "B_experts", "C_experts", "router_logits")]
+    status = sw._load().swimba_mixer_fwd(ctypes.byref(dims), *ptrs, state.data_ptr(), y.data_ptr(), state.data_ptr(),
+                                         None, None, ws.data_ptr(), ws.numel(), torch.cuda.current_stream().cuda_stream)
+    assert status == 0
+    torch.cuda.synchronize()
+    check(y, state, p, k, h0, "f32")
