@@ -14,7 +14,7 @@
 //                     contraction, so the state passes through neither LDS nor memory.
 //                       Y[i][p]   = sum_n (exp(cs_i) C[i][n]) S[n][p]  +  sum_{j<=i} M[i][j] x[j][p]
 //                       S[n][p]  <- exp(cs_last) S[n][p] + sum_j B[j][n] (dt_j exp(cs_last - cs_j) x[j][p])
-//                       M[i][j]   = G[i][j] exp(cs_i - cs_j) dt_j          (every exponent <= 0)
+//                       M[i][j]   = G[i][j] dt_j exp(cs_i - cs_j)
 //                     The readout is split over the state columns, the 12 blocks of M over the waves, and
 //                     the four partial Y tiles are added in a fixed order: 76 MFMAs per wave and step
 //                     (N = 128) whatever the wave.
@@ -378,11 +378,12 @@ chain_f32_kernel(const T *__restrict__ x, const T *__restrict__ dt, const float 
                 const float4 dj = *reinterpret_cast<const float4 *>(&s_dt[buf][8 * q + 4 * kg]);
                 const float4 xv = *reinterpret_cast<const float4 *>(sx + 8 * q);
                 const float cii = up ? ci[1] : ci[0];
-                // entries with j > i are zero in G; the clamp keeps their factor finite
-                const float m0 = gr[t].x * (dj.x * fast_exp2(fminf(cii - cj.x, 0.f)));
-                const float m1 = gr[t].y * (dj.y * fast_exp2(fminf(cii - cj.y, 0.f)));
-                const float m2 = gr[t].z * (dj.z * fast_exp2(fminf(cii - cj.z, 0.f)));
-                const float m3 = gr[t].w * (dj.w * fast_exp2(fminf(cii - cj.w, 0.f)));
+                // entries with j > i are zero in G; the clamp keeps their factor finite and, at 127, leaves the others
+                // alone where a state grows (A > 0)
+                const float m0 = (gr[t].x * dj.x) * fast_exp2(fminf(cii - cj.x, 127.f));
+                const float m1 = (gr[t].y * dj.y) * fast_exp2(fminf(cii - cj.y, 127.f));
+                const float m2 = (gr[t].z * dj.z) * fast_exp2(fminf(cii - cj.z, 127.f));
+                const float m3 = (gr[t].w * dj.w) * fast_exp2(fminf(cii - cj.w, 127.f));
                 if (up) {
                     yt[1] = mfma_f32(m0, xv.x, yt[1]);
                     yt[1] = mfma_f32(m1, xv.y, yt[1]);

@@ -67,6 +67,18 @@ def test_chain_sizes(cfg):
         check(out.y, out.h_final, p, k, h, io)
 
 
+def test_growing_state():
+    """A positive A (and a negative dt) is outside the model but not refused: the factors of M exceed 1."""
+    p, h0 = inputs(1, 200, 4, 32, 64, 1, 8, 2, "f32")
+    p["A"] = np.array([0.5, -0.5, 2.0, -2.0], np.float32)
+    p["dt"][:, 50:60] *= -1
+    d = to_device(p, "f32")
+    args = [d[q] for q in ("x", "dt", "A", "D", "B_experts", "C_experts", "router_logits")]
+    out = sw.swimba_mixer_fwd(*args, 2, 64, torch.from_numpy(h0).cuda())
+    torch.cuda.synchronize()
+    check(out.y, out.h_final, p, 2, h0, "f32")
+
+
 def test_final_state_over_the_initial_one():
     B, L, H, P, N, G, E, k = 2, 700, 4, 64, 128, 1, 8, 2
     p, h0 = inputs(B, L, H, P, N, G, E, k, "f32")
