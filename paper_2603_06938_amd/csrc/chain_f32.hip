@@ -35,6 +35,7 @@ namespace swimba {
 constexpr int CF_STEP = 64;            // tokens per step
 constexpr int CF_MIX_THREADS = 512;
 constexpr int CF_XS = CF_STEP + 4;     // row stride of the transposed x tile (floats)
+constexpr int CF_YS = 36;              // row stride of the partial Y tiles (floats)
 constexpr int CF_GBLK = 12;            // 4-column blocks of the masked 64 x 64 product: 4 of tile row 0, 8 of tile row 1
 
 typedef float __attribute__((ext_vector_type(4))) cf_f32x4_t;
@@ -42,6 +43,23 @@ typedef float __attribute__((ext_vector_type(4))) cf_f32x4_t;
 __device__ __forceinline__ f32x16_t mfma_f32(float a, float b, f32x16_t c)
 {
     return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
+}
+
+// Inclusive sum over the 64 lanes in register moves (DPP): four shifted additions inside rows of 16, then the last
+// lane of a row onto the next one and of the lower half onto the upper.  No LDS pass: one wave scans while the
+// others wait at the step's barrier, and six shuffles would cost it six LDS latencies.
+__device__ __forceinline__ float wave_scan(float v)
+{
+#define CF_SCAN(ctrl, rows)                                                                                              \
+    v += __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), ctrl, rows, 0xf, false))
+    CF_SCAN(0x111, 0xf);   // row_shr:1
+    CF_SCAN(0x112, 0xf);   // row_shr:2
+    CF_SCAN(0x114, 0xf);   // row_shr:4
+    CF_SCAN(0x118, 0xf);   // row_shr:8
+    CF_SCAN(0x142, 0xa);   // row_bcast:15 into rows 1 and 3
+    CF_SCAN(0x143, 0xc);   // row_bcast:31 into rows 2 and 3
+#undef CF_SCAN
+    return v;
 }
 
 // four consecutive elements as fp32
@@ -218,7 +236,7 @@ chain_f32_kernel(const T *__restrict__ x, const T *__restrict__ dt, const float 
 {
     __shared__ __align__(16) float s_x[2][32 * CF_XS];           // x^T of a step: [channel][token]
     __shared__ __align__(16) float s_cs[2][CF_STEP], s_dt[2][CF_STEP], s_c[2][CF_STEP];
-    __shared__ __align__(16) float s_y[OUT ? 4 : 1][OUT ? CF_STEP * 32 : 1];   // partial Y per wave: [token][channel]
+    __shared__ __align__(16) float s_y[OUT ? 4 : 1][OUT ? CF_STEP * CF_YS : 1];   // partial Y per wave: [token][channel]
 
     // (batch, segment, head, slice), neighbours (heads of one group) on one XCD: they read the same operands
     const int lid = xcd_logical_id(blockIdx.x, nblocks);
@@ -307,7 +325,7 @@ chain_f32_kernel(const T *__restrict__ x, const T *__restrict__ dt, const float 
     auto load_g = [&](int c) __attribute__((always_inline)) {
         const float4 *src = reinterpret_cast<const float4 *>(gop) + (bg0 + (int64_t)c * s.G) * (CF_GBLK * 64) + lane;
 #pragma unroll
-        for (int t = 0; t < 3; ++t) gr[t] = src[(3 * wave + t) * 64];
+        for (int t = 0; t < 3; ++t) gr[t] = src[(t > 0 ? 3 + 2 * wave + t : wave) * 64];
     };
     // x^T tile and tables of step c (in the registers) into buffer buf
     auto stage = [&](int c, int buf) __attribute__((always_inline)) {
@@ -317,13 +335,8 @@ chain_f32_kernel(const T *__restrict__ x, const T *__restrict__ dt, const float 
             s_x[buf][(xp + q) * CF_XS + xj] = (xj < valid && p0 + xp + q < P) ? xn[q] : 0.f;
         if (wave == 3) {
             const float dv = (lane < valid) ? dtn : 0.f;
-            float cs = dv * Ah;
-#pragma unroll
-            for (int off = 1; off < 64; off <<= 1) {
-                const float v = __shfl_up(cs, off);
-                if (lane >= off) cs += v;
-            }
-            const float last = __shfl(cs, 63);
+            const float cs = wave_scan(dv * Ah);
+            const float last = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(cs), 63));
             s_cs[buf][lane] = cs;
             s_dt[buf][lane] = dv;
             s_c[buf][lane] = dv * fast_exp2(last - cs);
@@ -345,7 +358,7 @@ chain_f32_kernel(const T *__restrict__ x, const T *__restrict__ dt, const float 
         load_x(cn);
         const float *sx = s_x[buf] + l32 * CF_XS + 4 * kg;
         const float cs_last = s_cs[buf][CF_STEP - 1];
-        f32x16_t yt[2];
+        f32x16_t yt[2];                                  // Y^T: rows are channels, so a lane holds four of one token
         if (OUT) {
 #pragma unroll
             for (int v = 0; v < 16; ++v) yt[0][v] = yt[1][v] = 0.f;
@@ -357,44 +370,34 @@ chain_f32_kernel(const T *__restrict__ x, const T *__restrict__ dt, const float 
 #pragma unroll
                     for (int a = 0; a < 4; ++a) {
                         const float4 u0 = cr[k][0][a], u1 = cr[k][1][a];
-                        yt[0] = mfma_f32(u0.x * ei[0], st[k][4 * a + 0], yt[0]);
-                        yt[1] = mfma_f32(u1.x * ei[1], st[k][4 * a + 0], yt[1]);
-                        yt[0] = mfma_f32(u0.y * ei[0], st[k][4 * a + 1], yt[0]);
-                        yt[1] = mfma_f32(u1.y * ei[1], st[k][4 * a + 1], yt[1]);
-                        yt[0] = mfma_f32(u0.z * ei[0], st[k][4 * a + 2], yt[0]);
-                        yt[1] = mfma_f32(u1.z * ei[1], st[k][4 * a + 2], yt[1]);
-                        yt[0] = mfma_f32(u0.w * ei[0], st[k][4 * a + 3], yt[0]);
-                        yt[1] = mfma_f32(u1.w * ei[1], st[k][4 * a + 3], yt[1]);
+                        yt[0] = mfma_f32(st[k][4 * a + 0], u0.x * ei[0], yt[0]);
+                        yt[1] = mfma_f32(st[k][4 * a + 0], u1.x * ei[1], yt[1]);
+                        yt[0] = mfma_f32(st[k][4 * a + 1], u0.y * ei[0], yt[0]);
+                        yt[1] = mfma_f32(st[k][4 * a + 1], u1.y * ei[1], yt[1]);
+                        yt[0] = mfma_f32(st[k][4 * a + 2], u0.z * ei[0], yt[0]);
+                        yt[1] = mfma_f32(st[k][4 * a + 2], u1.z * ei[1], yt[1]);
+                        yt[0] = mfma_f32(st[k][4 * a + 3], u0.w * ei[0], yt[0]);
+                        yt[1] = mfma_f32(st[k][4 * a + 3], u1.w * ei[1], yt[1]);
                     }
                 }
             load_c(cn);
-            // the wave's three 8-token blocks of M (block ids 3 wave .. + 2)
+            // the wave's 8-token blocks of M: one of tile row 0 and two of tile row 1, the same code in every wave
 #pragma unroll
             for (int t = 0; t < 3; ++t) {
-                const int id = 3 * wave + t;
-                const bool up = id >= 4;                 // wave-uniform
-                const int q = up ? id - 4 : id;
+                const int I = t > 0, q = t > 0 ? 2 * wave + t - 1 : wave;
                 const float4 cj = *reinterpret_cast<const float4 *>(&s_cs[buf][8 * q + 4 * kg]);
                 const float4 dj = *reinterpret_cast<const float4 *>(&s_dt[buf][8 * q + 4 * kg]);
                 const float4 xv = *reinterpret_cast<const float4 *>(sx + 8 * q);
-                const float cii = up ? ci[1] : ci[0];
                 // entries with j > i are zero in G; the clamp keeps their factor finite and, at 127, leaves the others
                 // alone where a state grows (A > 0)
-                const float m0 = (gr[t].x * dj.x) * fast_exp2(fminf(cii - cj.x, 127.f));
-                const float m1 = (gr[t].y * dj.y) * fast_exp2(fminf(cii - cj.y, 127.f));
-                const float m2 = (gr[t].z * dj.z) * fast_exp2(fminf(cii - cj.z, 127.f));
-                const float m3 = (gr[t].w * dj.w) * fast_exp2(fminf(cii - cj.w, 127.f));
-                if (up) {
-                    yt[1] = mfma_f32(m0, xv.x, yt[1]);
-                    yt[1] = mfma_f32(m1, xv.y, yt[1]);
-                    yt[1] = mfma_f32(m2, xv.z, yt[1]);
-                    yt[1] = mfma_f32(m3, xv.w, yt[1]);
-                } else {
-                    yt[0] = mfma_f32(m0, xv.x, yt[0]);
-                    yt[0] = mfma_f32(m1, xv.y, yt[0]);
-                    yt[0] = mfma_f32(m2, xv.z, yt[0]);
-                    yt[0] = mfma_f32(m3, xv.w, yt[0]);
-                }
+                const float m0 = (gr[t].x * dj.x) * fast_exp2(fminf(ci[I] - cj.x, 127.f));
+                const float m1 = (gr[t].y * dj.y) * fast_exp2(fminf(ci[I] - cj.y, 127.f));
+                const float m2 = (gr[t].z * dj.z) * fast_exp2(fminf(ci[I] - cj.z, 127.f));
+                const float m3 = (gr[t].w * dj.w) * fast_exp2(fminf(ci[I] - cj.w, 127.f));
+                yt[I] = mfma_f32(xv.x, m0, yt[I]);
+                yt[I] = mfma_f32(xv.y, m1, yt[I]);
+                yt[I] = mfma_f32(xv.z, m2, yt[I]);
+                yt[I] = mfma_f32(xv.w, m3, yt[I]);
             }
             load_g(cn);
         } else {
@@ -408,17 +411,16 @@ chain_f32_kernel(const T *__restrict__ x, const T *__restrict__ dt, const float 
 #pragma unroll
                 for (int v = 0; v < 16; ++v) st[k][v] *= dec;
 #pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                const float4 cj = *reinterpret_cast<const float4 *>(&s_c[buf][8 * q + 4 * kg]);
-                const float4 xv = *reinterpret_cast<const float4 *>(sx + 8 * q);
-                const float x0 = xv.x * cj.x, x1 = xv.y * cj.y, x2 = xv.z * cj.z, x3 = xv.w * cj.w;
+            for (int k = 0; k < NTW; ++k) {
+                if (wave * NTW + k >= NT) continue;      // wave-uniform; outside the token loop, whose LDS reads overlap
 #pragma unroll
-                for (int k = 0; k < NTW; ++k) {
-                    if (wave * NTW + k >= NT) continue;  // wave-uniform
-                    st[k] = mfma_f32(br[k][q].x, x0, st[k]);
-                    st[k] = mfma_f32(br[k][q].y, x1, st[k]);
-                    st[k] = mfma_f32(br[k][q].z, x2, st[k]);
-                    st[k] = mfma_f32(br[k][q].w, x3, st[k]);
+                for (int q = 0; q < 8; ++q) {
+                    const float4 cj = *reinterpret_cast<const float4 *>(&s_c[buf][8 * q + 4 * kg]);
+                    const float4 xv = *reinterpret_cast<const float4 *>(sx + 8 * q);
+                    st[k] = mfma_f32(br[k][q].x, xv.x * cj.x, st[k]);
+                    st[k] = mfma_f32(br[k][q].y, xv.y * cj.y, st[k]);
+                    st[k] = mfma_f32(br[k][q].z, xv.z * cj.z, st[k]);
+                    st[k] = mfma_f32(br[k][q].w, xv.w * cj.w, st[k]);
                 }
             }
             load_b(cn);
@@ -429,8 +431,9 @@ chain_f32_kernel(const T *__restrict__ x, const T *__restrict__ dt, const float 
 #pragma unroll
             for (int I = 0; I < 2; ++I)
 #pragma unroll
-                for (int v = 0; v < 16; ++v)
-                    s_y[wave][(32 * I + 8 * (v >> 2) + 4 * kg + (v & 3)) * 32 + l32] = yt[I][v];
+                for (int a = 0; a < 4; ++a)
+                    *reinterpret_cast<float4 *>(&s_y[wave][(32 * I + l32) * CF_YS + 8 * a + 4 * kg]) =
+                        make_float4(yt[I][4 * a], yt[I][4 * a + 1], yt[I][4 * a + 2], yt[I][4 * a + 3]);
         }
         stage(cn, buf ^ 1);
         if (OUT) {
@@ -440,10 +443,10 @@ chain_f32_kernel(const T *__restrict__ x, const T *__restrict__ dt, const float 
                 float r[8];
 #pragma unroll
                 for (int q = 0; q < 2; ++q) {
-                    const float4 a0 = *reinterpret_cast<const float4 *>(&s_y[0][xj * 32 + xp + 4 * q]);
-                    const float4 a1 = *reinterpret_cast<const float4 *>(&s_y[1][xj * 32 + xp + 4 * q]);
-                    const float4 a2 = *reinterpret_cast<const float4 *>(&s_y[2][xj * 32 + xp + 4 * q]);
-                    const float4 a3 = *reinterpret_cast<const float4 *>(&s_y[3][xj * 32 + xp + 4 * q]);
+                    const float4 a0 = *reinterpret_cast<const float4 *>(&s_y[0][xj * CF_YS + xp + 4 * q]);
+                    const float4 a1 = *reinterpret_cast<const float4 *>(&s_y[1][xj * CF_YS + xp + 4 * q]);
+                    const float4 a2 = *reinterpret_cast<const float4 *>(&s_y[2][xj * CF_YS + xp + 4 * q]);
+                    const float4 a3 = *reinterpret_cast<const float4 *>(&s_y[3][xj * CF_YS + xp + 4 * q]);
                     r[4 * q + 0] = (a0.x + a1.x) + (a2.x + a3.x) + dsk * xc[4 * q + 0];
                     r[4 * q + 1] = (a0.y + a1.y) + (a2.y + a3.y) + dsk * xc[4 * q + 1];
                     r[4 * q + 2] = (a0.z + a1.z) + (a2.z + a3.z) + dsk * xc[4 * q + 2];
