@@ -75,7 +75,9 @@ __device__ __forceinline__ float4 load4(const bf16 *p)
 //   bop (NT, 8, 64, 4)     [nt][q][lane][b]    = B[8q + 4(lane/32) + b][32 nt + lane%32]
 //   gop (12, 64, 4)        [blk][lane][b]      = (j <= i) C[i] . B[j], blk < 4: i = lane%32, q = blk, else i = 32 + lane%32,
 //                          q = blk - 4; j = 8q + 4(lane/32) + b
-template <typename T>
+// PARTS = 4: four workgroups share a step, each with 16 of its tokens as rows of C and of G; it mixes the B rows
+// that these meet, so B is read 2.5 times, by compute units that would have none of the steps.
+template <typename T, int PARTS>
 __global__ void __launch_bounds__(CF_MIX_THREADS)
 mix_ops_kernel(const T *__restrict__ Be, const T *__restrict__ Ce, const T *__restrict__ logits,
                int32_t *__restrict__ idx_out, float *__restrict__ w_out, const float *__restrict__ w_sel,
@@ -87,9 +89,11 @@ mix_ops_kernel(const T *__restrict__ Be, const T *__restrict__ Ce, const T *__re
     float *s_w = reinterpret_cast<float *>(s_idx + CF_STEP * K);             // [64][K]
     float *s_B = s_w + CF_STEP * K;                                          // [64][RS]
     float *s_C = s_B + CF_STEP * RS;                                         // [64][RS]
-    const int g = blockIdx.x % s.G;
-    const int c = (blockIdx.x / s.G) % s.nc;
-    const int b = blockIdx.x / (s.G * s.nc);
+    constexpr int R = CF_STEP / PARTS;                   // rows of C and G in this workgroup
+    const int part = blockIdx.x % PARTS, r0 = part * R, item = blockIdx.x / PARTS;
+    const int g = item % s.G;
+    const int c = (item / s.G) % s.nc;
+    const int b = item / (s.G * s.nc);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int valid = min(CF_STEP, s.L - c * CF_STEP);
@@ -116,7 +120,7 @@ mix_ops_kernel(const T *__restrict__ Be, const T *__restrict__ Ce, const T *__re
             } else {
                 route_token([&](int e) { return to_float(gl[e]); }, s.E, K, ix, wx);
             }
-            if (g == 0 && tid < valid)
+            if (g == 0 && tid < valid && tid >= r0 && tid < r0 + R)
                 for (int r = 0; r < K; ++r) { idx_out[t * K + r] = ix[r]; w_out[t * K + r] = wx[r]; }
         }
         if (tid >= valid)
@@ -124,65 +128,57 @@ mix_ops_kernel(const T *__restrict__ Be, const T *__restrict__ Ce, const T *__re
     }
     __syncthreads();
 
-    // ---- mixed rows: a lane takes quads of 4 columns, four (token, quad) units of both streams at a time ----
+    // ---- mixed rows: a lane takes quads of 4 columns of one stream, eight at a time; C rows [r0, r0 + R), then the B
+    // ---- rows up to the last of them ----
     const int rowsE = sel ? K : s.E;
     const int64_t estride = (int64_t)s.G * s.N, tokstride = rowsE * estride;
     const T *Bg = Be + (tok0 * rowsE * s.G + g) * s.N;
     const T *Cg = Ce + (tok0 * rowsE * s.G + g) * s.N;
-    const int QPR = NP / 4, units = CF_STEP * QPR;       // units is a multiple of 512
+    const int QPR = NP / 4, units = (R + r0 + R) * QPR;
     const bool vec = (s.N % 4 == 0);
-    for (int u0 = tid; u0 < units; u0 += 4 * CF_MIX_THREADS) {
-        float4 ab[4], ac[4];
+    for (int u0 = tid; u0 < units; u0 += 8 * CF_MIX_THREADS) {
+        float4 am[8];
 #pragma unroll
-        for (int m = 0; m < 4; ++m) ab[m] = ac[m] = make_float4(0.f, 0.f, 0.f, 0.f);
+        for (int m = 0; m < 8; ++m) am[m] = make_float4(0.f, 0.f, 0.f, 0.f);
         for (int r = 0; r < K; ++r) {
-            float4 vb[4], vc[4];
-            float ww[4];
+            float4 v[8];
+            float ww[8];
 #pragma unroll
-            for (int m = 0; m < 4; ++m) {
+            for (int m = 0; m < 8; ++m) {
                 const int u = min(u0 + m * CF_MIX_THREADS, units - 1);
-                const int j = u / QPR, n = (u % QPR) * 4;
-                const int64_t o = min(j, valid - 1) * tokstride + s_idx[j * K + r] * estride;
+                const int rr = u / QPR, n = (u % QPR) * 4, j = rr < R ? r0 + rr : rr - R;
+                const T *src = (rr < R ? Cg : Bg) + min(j, valid - 1) * tokstride + s_idx[j * K + r] * estride;
                 ww[m] = s_w[j * K + r];
                 if (vec) {
-                    const int nn = min(n, s.N - 4);
-                    vb[m] = load4(Bg + o + nn);
-                    vc[m] = load4(Cg + o + nn);
+                    v[m] = load4(src + min(n, s.N - 4));
                 } else {
-                    float t[8];
+                    float t[4];
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const int nn = min(n + q, s.N - 1);
-                        t[q] = to_float(Bg[o + nn]);
-                        t[4 + q] = to_float(Cg[o + nn]);
-                    }
-                    vb[m] = make_float4(t[0], t[1], t[2], t[3]);
-                    vc[m] = make_float4(t[4], t[5], t[6], t[7]);
+                    for (int q = 0; q < 4; ++q) t[q] = to_float(src[min(n + q, s.N - 1)]);
+                    v[m] = make_float4(t[0], t[1], t[2], t[3]);
                 }
             }
 #pragma unroll
-            for (int m = 0; m < 4; ++m) {
-                ab[m].x += ww[m] * vb[m].x; ab[m].y += ww[m] * vb[m].y; ab[m].z += ww[m] * vb[m].z; ab[m].w += ww[m] * vb[m].w;
-                ac[m].x += ww[m] * vc[m].x; ac[m].y += ww[m] * vc[m].y; ac[m].z += ww[m] * vc[m].z; ac[m].w += ww[m] * vc[m].w;
+            for (int m = 0; m < 8; ++m) {
+                am[m].x += ww[m] * v[m].x; am[m].y += ww[m] * v[m].y; am[m].z += ww[m] * v[m].z; am[m].w += ww[m] * v[m].w;
             }
         }
 #pragma unroll
-        for (int m = 0; m < 4; ++m) {
+        for (int m = 0; m < 8; ++m) {
             const int u = u0 + m * CF_MIX_THREADS;
             if (u < units) {
-                const int j = u / QPR, n = (u % QPR) * 4;
-                float *fb = reinterpret_cast<float *>(&ab[m]), *fc = reinterpret_cast<float *>(&ac[m]);
+                const int rr = u / QPR, n = (u % QPR) * 4;
+                float *f = reinterpret_cast<float *>(&am[m]);
 #pragma unroll
                 for (int q = 0; q < 4; ++q)
-                    if (n + q >= s.N) fb[q] = fc[q] = 0.f;          // padding columns
-                *reinterpret_cast<float4 *>(s_B + j * RS + n) = ab[m];
-                *reinterpret_cast<float4 *>(s_C + j * RS + n) = ac[m];
+                    if (n + q >= s.N) f[q] = 0.f;                   // padding columns
+                *reinterpret_cast<float4 *>((rr < R ? s_C + (r0 + rr) * RS : s_B + (rr - R) * RS) + n) = am[m];
             }
         }
     }
     __syncthreads();
 
-    const int64_t bcg = blockIdx.x;
+    const int64_t bcg = item;
     float4 *co = reinterpret_cast<float4 *>(cop) + bcg * (2 * NT * 4 * 64);
     float4 *bo = reinterpret_cast<float4 *>(bop) + bcg * (NT * 8 * 64);
     float4 *go = reinterpret_cast<float4 *>(gop) + bcg * (CF_GBLK * 64);
@@ -190,7 +186,9 @@ mix_ops_kernel(const T *__restrict__ Be, const T *__restrict__ Ce, const T *__re
     // ---- with four consecutive j of one i, which is a float4 of gop.  Tiles right of the diagonal are zero. ----
     {
         const int l16 = lane & 15, kq = lane >> 4;
-        for (int t = wave; t < 12; t += CF_MIX_THREADS / 64) {
+        const int t_begin = PARTS == 1 ? 0 : part < 2 ? 2 * part : 4 * part - 4;
+        const int t_end = PARTS == 1 ? 12 : part < 2 ? t_begin + 2 : t_begin + 4;
+        for (int t = t_begin + wave; t < t_end; t += CF_MIX_THREADS / 64) {
             // tile rows 0, 1 have columns J = 0, 1; rows 2, 3 columns 0..3
             const int I = t < 4 ? t >> 1 : 2 + ((t - 4) >> 2), J = t < 4 ? t & 1 : (t - 4) & 3;
             cf_f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
@@ -213,14 +211,16 @@ mix_ops_kernel(const T *__restrict__ Be, const T *__restrict__ Ce, const T *__re
             go[blk * 64 + ((j0 >> 2) & 1) * 32 + (i & 31)] = make_float4(acc[0], acc[1], acc[2], acc[3]);
         }
     }
-    for (int u = tid; u < 2 * NT * 4 * 64; u += CF_MIX_THREADS) {
-        const int ln = u & 63, a = (u >> 6) & 3, nt = (u >> 8) % NT, I = (u >> 8) / NT;
-        co[u] = *reinterpret_cast<const float4 *>(s_C + (32 * I + (ln & 31)) * RS + 32 * nt + 8 * a + 4 * (ln >> 5));
+    for (int u = tid; u < R * NT * 8; u += CF_MIX_THREADS) {
+        const int row = r0 + u % R, kg = (u / R) & 1, a = (u / R >> 1) & 3, nt = u / R >> 3;
+        co[(((row >> 5) * NT + nt) * 4 + a) * 64 + kg * 32 + (row & 31)] =
+            *reinterpret_cast<const float4 *>(s_C + row * RS + 32 * nt + 8 * a + 4 * kg);
     }
-    for (int u = tid; u < NT * 8 * 64; u += CF_MIX_THREADS) {
-        const int ln = u & 63, q = (u >> 6) & 7, nt = u >> 9;
+    constexpr int QS = R / 8;
+    for (int u = tid; u < NT * QS * 64; u += CF_MIX_THREADS) {
+        const int ln = u & 63, q = r0 / 8 + (u >> 6) % QS, nt = (u >> 6) / QS;
         const float *src = s_B + (8 * q + 4 * (ln >> 5)) * RS + 32 * nt + (ln & 31);
-        bo[u] = make_float4(src[0], src[RS], src[2 * RS], src[3 * RS]);
+        bo[(nt * 8 + q) * 64 + ln] = make_float4(src[0], src[RS], src[2 * RS], src[3 * RS]);
     }
 }
 
@@ -257,6 +257,10 @@ chain_f32_kernel(const T *__restrict__ x, const T *__restrict__ dt, const float 
     // ---- running state: rows n = 32 nt + 8a + 4kg + b, column p0 + l32, in register 4a + b ----
     f32x16_t st[NTW];
     const int p = p0 + l32;
+    // a segment's contribution in hseg: (batch, segment, head, slice), then [nt][a][lane], the registers as they are
+    auto hseg_frag = [&](int q) __attribute__((always_inline)) {
+        return reinterpret_cast<float4 *>(hseg) + ((((int64_t)b * (nseg - 1) + q) * s.H + h) * nslice + sl) * (NT * 256) + lane;
+    };
     auto state_at = [&](const float *base, int nt, int a, int q) -> float {      // base: one (P, N) state
         const int n = 32 * nt + 8 * a + 4 * kg + q;
         return (p < P && n < s.N) ? base[(int64_t)p * s.N + n] : 0.f;
@@ -273,14 +277,34 @@ chain_f32_kernel(const T *__restrict__ x, const T *__restrict__ dt, const float 
         }
     }
     if (OUT) {
-        for (int q = 0; q < seg; ++q) {                  // the state in front of this segment
-            const int64_t o = ((int64_t)b * (nseg - 1) + q) * s.H + h;
-            const float a = fast_exp2(aseg[o]);
-            const float *hp = hseg + o * P * s.N;
+        // the state in front of this segment, four contributions requested together
+        for (int q0 = 0; q0 < seg; q0 += 4) {
+            float dec[4];
+            float4 v[4][NTW][4];
 #pragma unroll
-            for (int k = 0; k < NTW; ++k)
+            for (int u = 0; u < 4; ++u) {
+                const int q = min(q0 + u, seg - 1);
+                const float4 *hp = hseg_frag(q);
+                dec[u] = aseg[((int64_t)b * (nseg - 1) + q) * s.H + h];
 #pragma unroll
-                for (int v = 0; v < 16; ++v) st[k][v] = a * st[k][v] + state_at(hp, wave * NTW + k, v >> 2, v & 3);
+                for (int k = 0; k < NTW; ++k)
+#pragma unroll
+                    for (int a = 0; a < 4; ++a) v[u][k][a] = hp[(min(wave * NTW + k, NT - 1) * 4 + a) * 64];
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                if (q0 + u >= seg) continue;
+                const float d = fast_exp2(dec[u]);
+#pragma unroll
+                for (int k = 0; k < NTW; ++k)
+#pragma unroll
+                    for (int a = 0; a < 4; ++a) {
+                        st[k][4 * a + 0] = d * st[k][4 * a + 0] + v[u][k][a].x;
+                        st[k][4 * a + 1] = d * st[k][4 * a + 1] + v[u][k][a].y;
+                        st[k][4 * a + 2] = d * st[k][4 * a + 2] + v[u][k][a].z;
+                        st[k][4 * a + 3] = d * st[k][4 * a + 3] + v[u][k][a].w;
+                    }
+            }
         }
     }
 
@@ -303,7 +327,9 @@ chain_f32_kernel(const T *__restrict__ x, const T *__restrict__ dt, const float 
         }
         dtn = to_float(dt[(t0 + min(lane, valid - 1)) * s.H + h]);
     };
-    float4 cr[NTW][2][4], br[NTW][8], gr[3];
+    // In the state part alone the B operand of the next step has no readout to arrive behind: it gets registers of
+    // its own (brn) and is requested a whole step ahead.
+    float4 cr[NTW][2][4], br[NTW][8], brn[NTW][8], gr[3];
     const int64_t bg0 = ((int64_t)b * s.nc) * s.G + g;
     auto load_c = [&](int c) __attribute__((always_inline)) {
         const float4 *src = reinterpret_cast<const float4 *>(cop) + (bg0 + (int64_t)c * s.G) * (2 * NT * 4 * 64) + lane;
@@ -315,7 +341,7 @@ chain_f32_kernel(const T *__restrict__ x, const T *__restrict__ dt, const float 
                 for (int a = 0; a < 4; ++a)
                     cr[k][I][a] = src[((I * NT + min(wave * NTW + k, NT - 1)) * 4 + a) * 64];
     };
-    auto load_b = [&](int c) __attribute__((always_inline)) {
+    auto load_b = [&](int c, float4 (&br)[NTW][8]) __attribute__((always_inline)) {
         const float4 *src = reinterpret_cast<const float4 *>(bop) + (bg0 + (int64_t)c * s.G) * (NT * 8 * 64) + lane;
 #pragma unroll
         for (int k = 0; k < NTW; ++k)
@@ -346,9 +372,9 @@ chain_f32_kernel(const T *__restrict__ x, const T *__restrict__ dt, const float 
     float atot = 0.f;
     load_x(c_begin);
     if (OUT) { load_c(c_begin); load_g(c_begin); }
-    load_b(c_begin);
+    load_b(c_begin, br);
     stage(c_begin, 0);
-    for (int c = c_begin; c < c_end; ++c) {
+    auto step = [&](int c, float4 (&br)[NTW][8], float4 (&brn)[NTW][8]) __attribute__((always_inline)) {
         const int buf = (c - c_begin) & 1;
         const int cn = min(c + 1, c_end - 1);
         float xc[8];
@@ -356,6 +382,7 @@ chain_f32_kernel(const T *__restrict__ x, const T *__restrict__ dt, const float 
         for (int q = 0; q < 8; ++q) xc[q] = xn[q];
         lds_barrier();                                   // step c is staged
         load_x(cn);
+        if (!OUT) load_b(cn, brn);
         const float *sx = s_x[buf] + l32 * CF_XS + 4 * kg;
         const float cs_last = s_cs[buf][CF_STEP - 1];
         f32x16_t yt[2];                                  // Y^T: rows are channels, so a lane holds four of one token
@@ -423,7 +450,7 @@ chain_f32_kernel(const T *__restrict__ x, const T *__restrict__ dt, const float 
                     st[k] = mfma_f32(br[k][q].w, xv.w * cj.w, st[k]);
                 }
             }
-            load_b(cn);
+            if (OUT) load_b(cn, br);
         }
         if (OUT) {
             // the partial tiles of the four waves meet in LDS (those of the previous step were added up in front
@@ -467,9 +494,27 @@ chain_f32_kernel(const T *__restrict__ x, const T *__restrict__ dt, const float 
                 }
             }
         }
+    };
+    if (OUT) {
+        for (int c = c_begin; c < c_end; ++c) step(c, br, br);
+    } else {
+        for (int c = c_begin; c < c_end; c += 2) {
+            step(c, br, brn);
+            if (c + 1 < c_end) step(c + 1, brn, br);
+        }
     }
-    float *dst = OUT ? (seg == nseg - 1 && h_final ? h_final + ((int64_t)b * s.H + h) * P * s.N : nullptr)
-                     : hseg + (((int64_t)b * (nseg - 1) + seg) * s.H + h) * P * s.N;
+    if (!OUT) {
+        float4 *dst = hseg_frag(seg);
+#pragma unroll
+        for (int k = 0; k < NTW; ++k) {
+            if (wave * NTW + k >= NT) continue;          // wave-uniform
+#pragma unroll
+            for (int a = 0; a < 4; ++a)
+                dst[((wave * NTW + k) * 4 + a) * 64] =
+                    make_float4(st[k][4 * a], st[k][4 * a + 1], st[k][4 * a + 2], st[k][4 * a + 3]);
+        }
+    }
+    float *dst = OUT && seg == nseg - 1 && h_final ? h_final + ((int64_t)b * s.H + h) * P * s.N : nullptr;
     if (dst && p < P) {
 #pragma unroll
         for (int k = 0; k < NTW; ++k)
@@ -499,6 +544,11 @@ int chain_f32_segments(int64_t B, int64_t L, int64_t H, int64_t P)
     if (chains == 0) return 1;
     int nseg = 1;
     while (nseg < CHAIN_F32_MAX_SEGMENTS && chains * nseg < 384 && steps >= 8 * (int64_t)nseg) nseg *= 2;
+    // Some compute units then hold one chain more than others and set the time: twice as many chains of half the
+    // length where that takes a fifth off the fullest unit (96 chains of 32 steps: 4 segments 113 us, 8 102;
+    // 128 chains, where it takes nothing off: 113 and 125).
+    const int64_t cus = 256, full = (chains * nseg + cus - 1) / cus, full2 = (2 * chains * nseg + cus - 1) / cus;
+    if (nseg > 1 && nseg < CHAIN_F32_MAX_SEGMENTS && steps >= 8 * (int64_t)nseg && 10 * full2 <= 16 * full) nseg *= 2;
     return nseg;
 }
 
@@ -510,7 +560,7 @@ void chain_f32_sizes(const swimba_dims *d, size_t *ops, size_t *g, size_t *seg, 
     *ops = items * CF_STEP * NT * 32 * sizeof(float);
     *g = items * CF_GBLK * 64 * 16;
     *dec = (size_t)d->batch * (nseg - 1) * d->nheads * sizeof(float);
-    *seg = (size_t)d->batch * (nseg - 1) * d->nheads * d->headdim * d->dstate * sizeof(float);
+    *seg = (size_t)d->batch * (nseg - 1) * d->nheads * ((d->headdim + 31) / 32) * NT * 1024 * sizeof(float);
 }
 
 template <typename T, int NTW>
@@ -547,12 +597,20 @@ static swimba_status launch_f32_t(const Shape &s, const void *x, const void *dt,
     const uint64_t bit = 1ull << (dev & 63);
     if (!(attr_set.load(std::memory_order_acquire) & bit)) {
         constexpr size_t most = (size_t)CF_STEP * SWIMBA_MAX_TOPK * 8 + (size_t)2 * CF_STEP * (SWIMBA_MAX_DSTATE + 4) * sizeof(float);
-        e = hipFuncSetAttribute((const void *)mix_ops_kernel<T>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)most);
+        e = hipFuncSetAttribute((const void *)mix_ops_kernel<T, 1>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)most);
+        if (e == hipSuccess)
+            e = hipFuncSetAttribute((const void *)mix_ops_kernel<T, 4>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)most);
         if (e != hipSuccess) { set_last_hip_error((int)e); return SWIMBA_ERR_HIP; }
         attr_set.fetch_or(bit, std::memory_order_release);
     }
-    hipLaunchKernelGGL(mix_ops_kernel<T>, dim3((unsigned)((int64_t)s.B * s.nc * s.G)), dim3(CF_MIX_THREADS), shm, st,
-                       (const T *)Be, (const T *)Ce, (const T *)logits, idx, w, w_sel, cop, bop, gop, s, NT);
+    const int64_t items = (int64_t)s.B * s.nc * s.G;
+    // Up to a quarter as many steps as compute units (64 here) four workgroups share one, each on a unit of its own.
+    if (items <= device_cus() / 4)
+        hipLaunchKernelGGL((mix_ops_kernel<T, 4>), dim3((unsigned)items * 4), dim3(CF_MIX_THREADS), shm, st, (const T *)Be,
+                           (const T *)Ce, (const T *)logits, idx, w, w_sel, cop, bop, gop, s, NT);
+    else
+        hipLaunchKernelGGL((mix_ops_kernel<T, 1>), dim3((unsigned)items), dim3(CF_MIX_THREADS), shm, st, (const T *)Be,
+                           (const T *)Ce, (const T *)logits, idx, w, w_sel, cop, bop, gop, s, NT);
     SWIMBA_CHECK_LAUNCH();
     if (NT <= 4)
         launch_chain_t<T, 1>(s, x, dt, A, D, cop, bop, gop, h0, h_final, hseg, aseg, y, NT, nseg, st);

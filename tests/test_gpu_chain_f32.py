@@ -52,6 +52,7 @@ def check(y, hf, p, k, h0, io):
     (1, 577, 4, 32, 256, 2, 8, 2, "f32"),      # ten steps in two segments
     (1, 1100, 2, 64, 64, 1, 5, 5, "f32"),      # 18 steps in four segments, the last one short
     (1, 2100, 2, 16, 48, 1, 8, 2, "f32"),      # 33 steps in eight: five each, the last one empty
+    (2, 2050, 48, 8, 12, 2, 4, 2, "f32"),      # 96 chains in eight segments, more steps than mix in four parts
     (1, 600, 2, 24, 80, 1, 8, 2, "f32"),
     (1, 600, 2, 128, 60, 1, 8, 2, "bf16"),     # outside the bf16 kernels
     (1, 70, 2, 20, 160, 2, 8, 2, "bf16"),
