@@ -8,8 +8,11 @@
 #include <c10/hip/HIPStream.h>
 
 #include "swimba.h"
+#include "unlocked.hpp"
 
 namespace {
+
+using swimba::unlocked;
 
 PyObject *g_mixer_out = nullptr, *g_step_out = nullptr, *g_error = nullptr;   // classes of the Python module
 
@@ -129,6 +132,7 @@ at::Device gpu_of(const at::Tensor &t, const char *name)
     return t.device();
 }
 
+// asked for while the lock is held: the query can throw
 void *stream() { return c10::hip::getCurrentHIPStream().stream(); }
 
 void check(swimba_status st, const char *where)
@@ -158,16 +162,6 @@ PyObject *named(PyObject *cls, std::initializer_list<Out *> outs)
     return r;
 }
 
-template <typename F>
-swimba_status unlocked(F f)
-{
-    swimba_status st;
-    Py_BEGIN_ALLOW_THREADS
-    st = f();
-    Py_END_ALLOW_THREADS
-    return st;
-}
-
 swimba_dims dims_of(int64_t B, int64_t L, int64_t H, int64_t P, int64_t N, int64_t G, int64_t E, int32_t k, int32_t Q,
                     int32_t io)
 {
@@ -195,9 +189,10 @@ PyObject *mixer_fwd(PyObject *const *a)
     hf.take(a[11], truth(a[15]), "h_final", f32, {B, H, P, N}, dev);
     idx.take(a[12], topk, "topk_idx", at::kInt, {B, L, k}, dev);
     w.take(a[13], topk, "topk_w", f32, {B, L, k}, dev);
+    void *const hs = stream();
     check(unlocked([&] {
               return swimba_mixer_fwd(&d, px, pdt, (float *)pA, (float *)pD, pB, pC, pg, (float *)ph, y.data,
-                                      (float *)hf.data, (int32_t *)idx.data, (float *)w.data, ws.data, ws.bytes, stream());
+                                      (float *)hf.data, (int32_t *)idx.data, (float *)w.data, ws.data, ws.bytes, hs);
           }), "swimba_mixer_fwd");
     return named(g_mixer_out, {&y, &hf, &idx, &w});
 }
@@ -216,8 +211,9 @@ PyObject *router_linear(PyObject *const *a)
     Out g;
     g.take(a[2], true, "router_logits", io, shape, gpu_of(u, "u"));
     const int64_t tokens = Dm ? u.numel() / Dm : 0;
+    void *const hs = stream();
     check(unlocked([&] {
-              return swimba_router_linear(tokens, (int32_t)Dm, (int32_t)E, code, pu, pW, g.data, stream());
+              return swimba_router_linear(tokens, (int32_t)Dm, (int32_t)E, code, pu, pW, g.data, hs);
           }), "swimba_router_linear");
     return g.release();
 }
@@ -241,9 +237,10 @@ PyObject *mixer_fwd_selected(PyObject *const *a)
     hf.take(a[10], truth(a[12]), "h_final", f32, {B, H, P, N}, dev);
     none1.obj = Py_NewRef(Py_None);
     none2.obj = Py_NewRef(Py_None);
+    void *const hs = stream();
     check(unlocked([&] {
               return swimba_mixer_fwd_selected(&d, px, pdt, (float *)pA, (float *)pD, pB, pC, (float *)pw, (float *)ph,
-                                               y.data, (float *)hf.data, ws.data, ws.bytes, stream());
+                                               y.data, (float *)hf.data, ws.data, ws.bytes, hs);
           }), "swimba_mixer_fwd_selected");
     return named(g_mixer_out, {&y, &hf, &none1, &none2});
 }
@@ -269,10 +266,11 @@ PyObject *mixer_fwd_proj(PyObject *const *a)
     hf.take(a[12], truth(a[14]), "h_final", f32, {B, H, P, N}, dev);
     idx.take(Py_None, topk, "topk_idx", at::kInt, {B, L, k}, dev);
     w.take(Py_None, topk, "topk_w", f32, {B, L, k}, dev);
+    void *const hs = stream();
     check(unlocked([&] {
               return swimba_mixer_fwd_proj(&d, (int32_t)Dm, pu, pWB, pWC, px, pdt, (float *)pA, (float *)pD, pg,
                                            (float *)ph, y.data, (float *)hf.data, (int32_t *)idx.data, (float *)w.data,
-                                           ws.data, ws.bytes, stream());
+                                           ws.data, ws.bytes, hs);
           }), "swimba_mixer_fwd_proj");
     return named(g_mixer_out, {&y, &hf, &idx, &w});
 }
@@ -299,10 +297,11 @@ PyObject *mixer_fwd_xe_proj(PyObject *const *a)
     hf.take(a[12], truth(a[14]), "h_final", f32, {B, H, P, N}, dev);
     idx.take(Py_None, topk, "topk_idx", at::kInt, {B, L, k}, dev);
     w.take(Py_None, topk, "topk_w", f32, {B, L, k}, dev);
+    void *const hs = stream();
     check(unlocked([&] {
               return swimba_mixer_fwd_xe_proj(&d, (int32_t)Dm, pu, pWB, pWC, pWX, pdt, (float *)pA, (float *)pD, pg,
                                               (float *)ph, y.data, (float *)hf.data, (int32_t *)idx.data,
-                                              (float *)w.data, ws.data, ws.bytes, stream());
+                                              (float *)w.data, ws.data, ws.bytes, hs);
           }), "swimba_mixer_fwd_xe_proj");
     return named(g_mixer_out, {&y, &hf, &idx, &w});
 }
@@ -340,10 +339,11 @@ PyObject *step(PyObject *const *a)
     y.take(a[10], true, "y", io, lead({H, P}), dev);
     idx.take(a[11], truth(a[13]), "topk_idx", at::kInt, lead({k}), dev);
     state.obj = Py_NewRef(so);
+    void *const hs = stream();
     check(unlocked([&] {
               return (MULTI ? swimba_step_multi : swimba_step)(&d, (float *)ps, (float *)pso, px, pdt, (float *)pA,
                                                                (float *)pD, pB, pC, pg, y.data, (int32_t *)idx.data,
-                                                               ws.data, ws.bytes, stream());
+                                                               ws.data, ws.bytes, hs);
           }), MULTI ? "swimba_step_multi" : "swimba_step");
     return named(g_step_out, {&y, &state, &idx});
 }
