@@ -3,6 +3,7 @@
 // shape / data_ptr, ctypes conversions, the stream query) took 18 us per decode step and 25 us per
 // forward on the host, more than the kernels of a small call take on the GPU.
 // CPython + libtorch; no kernels in here, and nothing is kept between calls.
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 #include <ATen/hip/EmptyTensor.h>
 #include <c10/hip/HIPStream.h>
@@ -358,8 +359,8 @@ PyObject *entry(PyObject *, PyObject *const *args, Py_ssize_t n)
     try {
         return F(args);
     } catch (const Raised &) {
-    } catch (const std::exception &e) {
-        PyErr_SetString(PyExc_RuntimeError, e.what());
+    } catch (...) {
+        torch::translate_exception_to_python(std::current_exception());   // torch.OutOfMemoryError and its like
     }
     return nullptr;
 }
