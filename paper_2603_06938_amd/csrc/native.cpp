@@ -107,15 +107,33 @@ struct Out {
     PyObject *release() { PyObject *o = obj; obj = nullptr; return o; }
 };
 
-// The caller's workspace, or one of `bytes` for this call.
+void check(swimba_status st, const char *where)
+{
+    if (st == SWIMBA_OK) return;
+    PyObject *e = PyObject_CallFunction(g_error, "is", (int)st, where);
+    if (e) {
+        PyErr_SetObject(g_error, e);
+        Py_DECREF(e);
+    }
+    throw Raised{};
+}
+
+// The caller's workspace, or one of `want` bytes for this call.  Sizes that the library refuses (want == 0): those of a
+// forward raise their status here, before an output is allocated for them; a decode call refuses them by itself.
 struct Workspace {
     at::TensorBase own;
     void *data = nullptr;
     size_t bytes = 0;
-    Workspace(PyObject *given, size_t want, at::Device dev)
+    Workspace(PyObject *given, size_t want, at::Device dev, const swimba_dims *forward = nullptr,
+              const char *query = nullptr)
     {
         if (given == Py_None) {
-            if (want == 0) return;   // the call refuses the sizes with their own status
+            if (want == 0) {
+                if (!forward) return;
+                swimba_ws_layout lo;
+                const swimba_status st = swimba_mixer_workspace_layout(forward, &lo);
+                check(st != SWIMBA_OK ? st : SWIMBA_ERR_SHAPE, query);
+            }
             own = at::detail::empty_cuda({(int64_t)want}, at::kByte, dev, std::nullopt);
             data = own.data_ptr();
             bytes = want;
@@ -135,17 +153,6 @@ at::Device gpu_of(const at::Tensor &t, const char *name)
 
 // asked for while the lock is held: the query can throw
 void *stream() { return c10::hip::getCurrentHIPStream().stream(); }
-
-void check(swimba_status st, const char *where)
-{
-    if (st == SWIMBA_OK) return;
-    PyObject *e = PyObject_CallFunction(g_error, "is", (int)st, where);
-    if (e) {
-        PyErr_SetObject(g_error, e);
-        Py_DECREF(e);
-    }
-    throw Raised{};
-}
 
 // MixerOut / StepOut: named tuples, made without their Python-level constructor
 PyObject *named(PyObject *cls, std::initializer_list<Out *> outs)
@@ -184,7 +191,8 @@ PyObject *mixer_fwd(PyObject *const *a)
     void *pA = ptr(a[2], "A", f32, {H}), *pD = ptr(a[3], "D", f32, {H});
     void *pB = ptr(a[4], "B_experts", io, {B, L, E, G, N}), *pC = ptr(a[5], "C_experts", io, {B, L, E, G, N});
     void *pg = ptr(a[6], "router_logits", io, {B, L, E}), *ph = ptr(a[9], "h0", f32, {B, H, P, N});
-    const Workspace ws(a[14], a[14] == Py_None ? swimba_mixer_workspace_bytes(&d) : 0, dev);
+    const Workspace ws(a[14], a[14] == Py_None ? swimba_mixer_workspace_bytes(&d) : 0, dev, &d,
+                       "swimba_mixer_workspace_bytes");
     Out y, hf, idx, w;
     y.take(a[10], true, "y", io, {B, L, H, P}, dev);
     hf.take(a[11], truth(a[15]), "h_final", f32, {B, H, P, N}, dev);
@@ -232,7 +240,8 @@ PyObject *mixer_fwd_selected(PyObject *const *a)
     void *pA = ptr(a[2], "A", f32, {H}), *pD = ptr(a[3], "D", f32, {H});
     void *pB = ptr(a[4], "B_sel", io, {B, L, K, G, N}), *pC = ptr(a[5], "C_sel", io, {B, L, K, G, N});
     void *pw = ptr(a[6], "topk_w", f32, {B, L, K}), *ph = ptr(a[8], "h0", f32, {B, H, P, N});
-    const Workspace ws(a[11], a[11] == Py_None ? swimba_mixer_workspace_bytes(&d) : 0, dev);
+    const Workspace ws(a[11], a[11] == Py_None ? swimba_mixer_workspace_bytes(&d) : 0, dev, &d,
+                       "swimba_mixer_workspace_bytes");
     Out y, hf, none1, none2;
     y.take(a[9], true, "y", io, {B, L, H, P}, dev);
     hf.take(a[10], truth(a[12]), "h_final", f32, {B, H, P, N}, dev);
@@ -261,7 +270,8 @@ PyObject *mixer_fwd_proj(PyObject *const *a)
     void *pWC = ptr(a[2], "W_C", io, {E, G, N, Dm}), *px = ptr(a[3], "x", io, {B, L, H, P});
     void *pdt = ptr(a[4], "dt", io, {B, L, H}), *pA = ptr(a[5], "A", f32, {H}), *pD = ptr(a[6], "D", f32, {H});
     void *pg = ptr(a[7], "router_logits", io, {B, L, E}), *ph = ptr(a[10], "h0", f32, {B, H, P, N});
-    const Workspace ws(a[13], a[13] == Py_None ? swimba_mixer_proj_workspace_bytes(&d, (int32_t)Dm) : 0, dev);
+    const Workspace ws(a[13], a[13] == Py_None ? swimba_mixer_proj_workspace_bytes(&d, (int32_t)Dm) : 0, dev, &d,
+                       "swimba_mixer_proj_workspace_bytes");
     Out y, hf, idx, w;
     y.take(a[11], true, "y", io, {B, L, H, P}, dev);
     hf.take(a[12], truth(a[14]), "h_final", f32, {B, H, P, N}, dev);
@@ -292,7 +302,8 @@ PyObject *mixer_fwd_xe_proj(PyObject *const *a)
     void *pWC = ptr(a[2], "W_C", io, {E, G, N, Dm}), *pWX = ptr(a[3], "W_X", io, {E, H, P, Dm});
     void *pdt = ptr(a[4], "dt", io, {B, L, H}), *pA = ptr(a[5], "A", f32, {H}), *pD = ptr(a[6], "D", f32, {H});
     void *pg = ptr(a[7], "router_logits", io, {B, L, E}), *ph = ptr(a[10], "h0", f32, {B, H, P, N});
-    const Workspace ws(a[13], a[13] == Py_None ? swimba_mixer_xe_proj_workspace_bytes(&d, (int32_t)Dm) : 0, dev);
+    const Workspace ws(a[13], a[13] == Py_None ? swimba_mixer_xe_proj_workspace_bytes(&d, (int32_t)Dm) : 0, dev, &d,
+                       "swimba_mixer_xe_proj_workspace_bytes");
     Out y, hf, idx, w;
     y.take(a[11], true, "y", io, {B, L, H, P}, dev);
     hf.take(a[12], truth(a[14]), "h_final", f32, {B, H, P, N}, dev);

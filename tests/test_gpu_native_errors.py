@@ -19,3 +19,18 @@ def test_out_of_memory_keeps_its_type():
             sw.swimba_router_linear(u, W)
     finally:
         torch.cuda.set_per_process_memory_fraction(1.0)
+
+
+@pytest.mark.parametrize("k,status", [(-1, 2), (0, 2), (5, 2), (17, 4)])
+def test_refused_sizes_raise_their_status(k, status):
+    """Before any output of that size is asked for."""
+    E = 4 if k < 17 else 32
+    x, dt = torch.zeros(1, 2, 3, 4, device="cuda:0"), torch.zeros(1, 2, 3, device="cuda:0")
+    A, Be, lg = torch.zeros(3, device="cuda:0"), torch.zeros(1, 2, E, 1, 4, device="cuda:0"), torch.zeros(1, 2, E, device="cuda:0")
+    W = torch.zeros(E, 1, 4, 8, device="cuda:0")
+    with pytest.raises(sw.SwimbaError) as e:
+        sw.swimba_mixer_fwd(x, dt, A, None, Be, Be, lg, k, 64, want_topk=True)
+    assert e.value.status == status
+    with pytest.raises(sw.SwimbaError) as e:
+        sw.swimba_mixer_fwd_proj(torch.zeros(1, 2, 8, device="cuda:0"), W, W, x, dt, A, None, lg, k, 64, want_topk=True)
+    assert e.value.status == status
