@@ -1,6 +1,7 @@
 """Builds libswimba.so (HIP, gfx950 only) and the host-side module _native.so in-tree."""
 from __future__ import annotations
 
+import importlib.util
 import os
 import subprocess
 import sys
@@ -56,7 +57,10 @@ def _link_native(obj, verbose):
 
 
 def build(verbose: bool = False) -> str:
-    """Compile every .hip under csrc/ and link the shared library; then the host-side module on top of it."""
+    """Compile every .hip under csrc/ and link the shared library; then the host-side module on top of it.
+
+    The C library needs nothing from torch: it is in place before the module is waited for, and where torch is not
+    installed it is all there is to build."""
     os.makedirs(OBJ, exist_ok=True)
     srcs = sources()
 
@@ -74,16 +78,18 @@ def build(verbose: bool = False) -> str:
         return obj
 
     with ThreadPoolExecutor(max_workers=min(8, len(srcs))) as ex:
-        native = ex.submit(_compile_native, verbose)
+        native = ex.submit(_compile_native, verbose) if importlib.util.find_spec("torch") else None
         objs = list(ex.map(cc, srcs))
-        native = native.result()
     tmp = LIB + ".tmp%d" % os.getpid()
     r = subprocess.run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp, *objs],
                        capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError("link failed:\n%s\n%s" % (r.stdout, r.stderr))
     os.replace(tmp, LIB)
-    _link_native(native, verbose)
+    if native is None:
+        print("torch is not installed: no Python module, libswimba.so only", file=sys.stderr)
+    else:
+        _link_native(native.result(), verbose)
     return LIB
 
 
