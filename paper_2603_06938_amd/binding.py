@@ -16,6 +16,7 @@ import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libswimba.so")
+NATIVE_PATH = os.path.join(_HERE, "_native.so")
 
 SWIMBA_F32, SWIMBA_BF16 = 0, 1
 MAX_TOPK = 16
@@ -157,6 +158,9 @@ def _load_native():
     global _native
     if _native is None:
         _load()
+        if not os.path.exists(NATIVE_PATH):
+            raise RuntimeError(
+                "_native.so is not built (%s); run `python -c 'import __graft_entry__ as g; g.build()'`" % NATIVE_PATH)
         from . import _native as module
         module.classes(MixerOut, StepOut, SwimbaError)
         _native = module

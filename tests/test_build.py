@@ -1,9 +1,12 @@
-"""The build's parts stand on their own: the C library does not wait for the Python module.  The compilers are stand-ins that write their output file."""
+"""The build's parts stand on their own: the C library does not wait for the Python module, and a part that is
+missing says how to build it.  The compilers are stand-ins that write their output file."""
 import os
 import stat
 
 import pytest
+import torch
 
+from paper_2603_06938_amd import binding as sw
 from paper_2603_06938_amd import build as b
 
 
@@ -33,3 +36,11 @@ def test_the_library_builds_without_torch(tree, monkeypatch):
     monkeypatch.setattr(b.importlib.util, "find_spec", lambda n, *a: None if n == "torch" else find(n, *a))
     monkeypatch.setattr(b, "_compile_native", lambda verbose: pytest.fail("compiled against torch"))
     assert b.build() == b.LIB and os.path.exists(b.LIB)
+
+
+def test_a_missing_module_says_what_to_run(tmp_path, monkeypatch):
+    monkeypatch.setattr(sw, "_native", None)
+    monkeypatch.setattr(sw, "NATIVE_PATH", str(tmp_path / "_native.so"))
+    t = torch.zeros(1, 2, 3, 4)
+    with pytest.raises(RuntimeError, match="not built.*g.build"):
+        sw.swimba_router_linear(t, t)
