@@ -62,7 +62,7 @@ static swimba_status check_mixer(const swimba_dims *d)
 
 // Scratch of the fp32 chain behind the stage arrays (offsets from the workspace's start)
 struct ChainF32Layout {
-    size_t cop, bop, gop, hseg, aseg;
+    size_t cop, bop, gop, hseg, aseg, hinit;
 };
 static void layout_of(const swimba_dims *d, swimba_ws_layout *o, ChainF32Layout *cf = nullptr)
 {
@@ -99,14 +99,15 @@ static void layout_of(const swimba_dims *d, swimba_ws_layout *o, ChainF32Layout 
     o->hmid = off;
     if (mf) off = align_up(off + (size_t)s.B * (PASS_SPLIT_MAX_SEGMENTS - 1) * s.H * s.P * s.N * sizeof(float), 256);
     if (!mf) {
-        size_t ops, g, seg, dec;
-        chain_f32_sizes(d, &ops, &g, &seg, &dec);
+        size_t ops, g, seg, dec, init;
+        chain_f32_sizes(d, &ops, &g, &seg, &dec, &init);
         ChainF32Layout l;
         l.cop = off;  off = align_up(off + ops, 256);
         l.bop = off;  off = align_up(off + ops, 256);
         l.gop = off;  off = align_up(off + g, 256);
         l.hseg = off; off = align_up(off + seg, 256);
         l.aseg = off; off = align_up(off + dec, 256);
+        l.hinit = off; off = align_up(off + init, 256);
         if (cf) *cf = l;
     }
     o->total = off > 0 ? off : 256;
@@ -201,7 +202,7 @@ struct Ws {
     float *states;
     void *states_lp, *cmix, *bmix_t8, *bmix_frag, *cb;
     float *cs2, *fdec, *cdec, *hmid;
-    float *cop, *bop, *gop, *hseg, *aseg;   // fp32 chain
+    float *cop, *bop, *gop, *hseg, *aseg, *hinit;   // fp32 chain
 };
 
 static swimba_status carve(const swimba_dims *d, void *workspace, size_t bytes, Ws *ws)
@@ -209,7 +210,7 @@ static swimba_status carve(const swimba_dims *d, void *workspace, size_t bytes, 
     swimba_status st = check_mixer(d);
     if (st != SWIMBA_OK) return st;
     swimba_ws_layout lo;
-    ChainF32Layout cf = {0, 0, 0, 0, 0};
+    ChainF32Layout cf = {0, 0, 0, 0, 0, 0};
     layout_of(d, &lo, &cf);
     if (!workspace || bytes < lo.total || ((uintptr_t)workspace & 255u)) return SWIMBA_ERR_WORKSPACE;
     char *p = (char *)workspace;
@@ -232,6 +233,7 @@ static swimba_status carve(const swimba_dims *d, void *workspace, size_t bytes, 
     ws->gop = mf ? nullptr : (float *)(p + cf.gop);
     ws->hseg = mf ? nullptr : (float *)(p + cf.hseg);
     ws->aseg = mf ? nullptr : (float *)(p + cf.aseg);
+    ws->hinit = mf ? nullptr : (float *)(p + cf.hinit);
     return SWIMBA_OK;
 }
 
@@ -563,7 +565,7 @@ swimba_status swimba_mixer_fwd(const swimba_dims *dims, const void *x, const voi
         if (!mf)
             return launch_chain_f32(s, dims->io_dtype, x, dt, A, D, B_experts, C_experts, router_logits, nullptr, h0, y,
                                     h_final, topk_idx ? topk_idx : ws.idx, topk_w ? topk_w : ws.w, ws.cop, ws.bop, ws.gop,
-                                    ws.hseg, ws.aseg, stream);
+                                    ws.hseg, ws.aseg, ws.hinit, stream);
         // On the bf16 MFMA path the mix kernel routes the tokens itself and the chunk-state
         // kernel computes the cumsum itself: two launches fewer.
         const bool chunk_mix = use_chunk_mix(dims, false);
@@ -1089,7 +1091,7 @@ static swimba_status mixer_selected_core(const swimba_dims *dims, const void *x,
             st = launch_chunk_state_mfma(s, x, dt, A, ws.bmix_t8, ws.cs, ws.states_lp, stream);
         } else {
             return launch_chain_f32(s, dims->io_dtype, x, dt, A, D, B_sel, C_sel, nullptr, w_sel, h0, y, h_final, nullptr,
-                                    nullptr, ws.cop, ws.bop, ws.gop, ws.hseg, ws.aseg, stream);
+                                    nullptr, ws.cop, ws.bop, ws.gop, ws.hseg, ws.aseg, ws.hinit, stream);
         }
         if (st != SWIMBA_OK) return st;
     }

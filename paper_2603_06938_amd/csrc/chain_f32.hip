@@ -225,12 +225,13 @@ mix_ops_kernel(const T *__restrict__ Be, const T *__restrict__ Ce, const T *__re
 }
 
 // NTW: 32-column state tiles per wave (N <= 128 * NTW).  OUT: y (and h_final); otherwise the state part only:
-// the segment's own contribution to the state (from zero) into hseg, its total decay (log2) into aseg.
+// the segment's own contribution to the state (from zero) into hseg, its total decay (log2) into aseg; with an h_final
+// it is segment 0's copy of h0 for the output launch, whose own h_final is the caller's h0.
 template <typename T, int NTW, bool OUT>
 __global__ void __launch_bounds__(256, NTW == 1 ? 2 : 1)
 chain_f32_kernel(const T *__restrict__ x, const T *__restrict__ dt, const float *__restrict__ A,
                  const float *__restrict__ D, const float *__restrict__ cop, const float *__restrict__ bop,
-                 const float *__restrict__ gop, const float *__restrict__ h0, float *__restrict__ h_final,
+                 const float *__restrict__ gop, const float *h0, float *h_final,
                  float *__restrict__ hseg, float *__restrict__ aseg, T *__restrict__ y, Shape s, int NT, int nslice,
                  int nrun, int nseg, int steps_per_seg, int total, int nblocks)
 {
@@ -275,6 +276,16 @@ chain_f32_kernel(const T *__restrict__ x, const T *__restrict__ dt, const float 
 #pragma unroll
             for (int v = 0; v < 16; ++v) st[k][v] = state_at(hp, nt, v >> 2, v & 3);
         }
+    }
+    if (!OUT && h_final && seg == 0 && p < P) {
+        const int64_t o = ((int64_t)b * s.H + h) * P * s.N;
+#pragma unroll
+        for (int k = 0; k < NTW; ++k)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int n = 32 * (wave * NTW + k) + 8 * (v >> 2) + 4 * kg + (v & 3);
+                if (n < s.N) h_final[o + (int64_t)p * s.N + n] = h0[o + (int64_t)p * s.N + n];
+            }
     }
     if (OUT) {
         // the state in front of this segment, four contributions requested together
@@ -552,7 +563,7 @@ int chain_f32_segments(int64_t B, int64_t L, int64_t H, int64_t P)
     return nseg;
 }
 
-void chain_f32_sizes(const swimba_dims *d, size_t *ops, size_t *g, size_t *seg, size_t *dec)
+void chain_f32_sizes(const swimba_dims *d, size_t *ops, size_t *g, size_t *seg, size_t *dec, size_t *init)
 {
     const size_t nc = ((size_t)d->seqlen + CF_STEP - 1) / CF_STEP, NT = ((size_t)d->dstate + 31) / 32;
     const size_t items = (size_t)d->batch * nc * d->ngroups;
@@ -561,20 +572,24 @@ void chain_f32_sizes(const swimba_dims *d, size_t *ops, size_t *g, size_t *seg, 
     *g = items * CF_GBLK * 64 * 16;
     *dec = (size_t)d->batch * (nseg - 1) * d->nheads * sizeof(float);
     *seg = (size_t)d->batch * (nseg - 1) * d->nheads * ((d->headdim + 31) / 32) * NT * 1024 * sizeof(float);
+    *init = nseg > 1 ? (size_t)d->batch * d->nheads * d->headdim * d->dstate * sizeof(float) : 0;
 }
 
 template <typename T, int NTW>
 static void launch_chain_t(const Shape &s, const void *x, const void *dt, const float *A, const float *D, const float *cop,
                            const float *bop, const float *gop, const float *h0, float *h_final, float *hseg,
-                           float *aseg, void *y, int NT, int nseg, hipStream_t st)
+                           float *aseg, float *hinit, void *y, int NT, int nseg, hipStream_t st)
 {
     const int nslice = (s.P + 31) / 32, sps = (s.nc + nseg - 1) / nseg;
     const int used = (s.nc + sps - 1) / sps;             // segments that have steps
     if (used > 1) {
+        // With the final state written over the initial one the segments of the output launch read a copy: the last
+        // segment of a sequence can end before another one has started.
+        float *copy = h0 && h0 == h_final ? hinit : nullptr;
         const int total = s.B * (used - 1) * s.H * nslice, nblocks = xcd_padded(total);
         hipLaunchKernelGGL((chain_f32_kernel<T, NTW, false>), dim3(nblocks), dim3(256), 0, st, (const T *)x, (const T *)dt,
-                           A, D, cop, bop, gop, h0, h_final, hseg, aseg, (T *)y, s, NT, nslice, used - 1, used, sps, total,
-                           nblocks);
+                           A, D, cop, bop, gop, h0, copy, hseg, aseg, (T *)y, s, NT, nslice, used - 1, used, sps, total, nblocks);
+        if (copy) h0 = copy;
     }
     const int total = s.B * used * s.H * nslice, nblocks = xcd_padded(total);
     hipLaunchKernelGGL((chain_f32_kernel<T, NTW, true>), dim3(nblocks), dim3(256), 0, st, (const T *)x, (const T *)dt, A,
@@ -585,7 +600,7 @@ template <typename T>
 static swimba_status launch_f32_t(const Shape &s, const void *x, const void *dt, const float *A, const float *D,
                                   const void *Be, const void *Ce, const void *logits, const float *w_sel,
                                   const float *h0, void *y, float *h_final, int32_t *idx, float *w, float *cop,
-                                  float *bop, float *gop, float *hseg, float *aseg, int nseg, hipStream_t st)
+                                  float *bop, float *gop, float *hseg, float *aseg, float *hinit, int nseg, hipStream_t st)
 {
     const int NT = (s.N + 31) / 32;
     const size_t shm = (size_t)CF_STEP * s.K * 8 + (size_t)2 * CF_STEP * (32 * NT + 4) * sizeof(float);
@@ -613,9 +628,9 @@ static swimba_status launch_f32_t(const Shape &s, const void *x, const void *dt,
                            (const T *)Ce, (const T *)logits, idx, w, w_sel, cop, bop, gop, s, NT);
     SWIMBA_CHECK_LAUNCH();
     if (NT <= 4)
-        launch_chain_t<T, 1>(s, x, dt, A, D, cop, bop, gop, h0, h_final, hseg, aseg, y, NT, nseg, st);
+        launch_chain_t<T, 1>(s, x, dt, A, D, cop, bop, gop, h0, h_final, hseg, aseg, hinit, y, NT, nseg, st);
     else
-        launch_chain_t<T, 2>(s, x, dt, A, D, cop, bop, gop, h0, h_final, hseg, aseg, y, NT, nseg, st);
+        launch_chain_t<T, 2>(s, x, dt, A, D, cop, bop, gop, h0, h_final, hseg, aseg, hinit, y, NT, nseg, st);
     SWIMBA_CHECK_LAUNCH();
     return SWIMBA_OK;
 }
@@ -624,22 +639,20 @@ static swimba_status launch_f32_t(const Shape &s, const void *x, const void *dt,
 swimba_status launch_chain_f32(const Shape &s0, int io_dtype, const void *x, const void *dt, const float *A,
                                const float *D, const void *Be, const void *Ce, const void *logits, const float *w_sel,
                                const float *h0, void *y, float *h_final, int32_t *idx, float *w, float *cop, float *bop,
-                               float *gop, float *hseg, float *aseg, hipStream_t st)
+                               float *gop, float *hseg, float *aseg, float *hinit, hipStream_t st)
 {
     Shape s = s0;
     s.Q = CF_STEP;
     s.nc = (s.L + CF_STEP - 1) / CF_STEP;
     if ((int64_t)s.B * s.nc == 0) return SWIMBA_OK;
-    // With the final state written over the initial one, only a single segment may read h0: the last segment of a
-    // sequence can end before another one has started.
-    const int nseg = h0 && h0 == h_final ? 1 : chain_f32_segments(s.B, s.L, s.H, s.P);
+    const int nseg = chain_f32_segments(s.B, s.L, s.H, s.P);
     if ((int64_t)s.B * s.nc * s.G > 0x7fffffffll || (int64_t)s.B * nseg * s.H * ((s.P + 31) / 32) > 0x7ffffff0ll)
         return SWIMBA_ERR_UNSUPPORTED;
     if (io_dtype == SWIMBA_BF16)
         return launch_f32_t<bf16>(s, x, dt, A, D, Be, Ce, logits, w_sel, h0, y, h_final, idx, w, cop, bop, gop, hseg, aseg,
-                                  nseg, st);
+                                  hinit, nseg, st);
     return launch_f32_t<float>(s, x, dt, A, D, Be, Ce, logits, w_sel, h0, y, h_final, idx, w, cop, bop, gop, hseg, aseg,
-                               nseg, st);
+                               hinit, nseg, st);
 }
 
 }  // namespace swimba

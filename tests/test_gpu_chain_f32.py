@@ -94,3 +94,24 @@ def test_final_state_over_the_initial_one():
     assert status == 0
     torch.cuda.synchronize()
     check(y, state, p, k, h0, "f32")
+
+
+@pytest.mark.parametrize("cfg", [
+    (1, 2100, 2, 16, 48, 1, 8, 2, "f32"),      # five steps a segment, the eighth empty
+    (2, 700, 4, 64, 128, 1, 8, 2, "f32"),
+    (1, 577, 4, 33, 240, 2, 8, 2, "f32"),      # a slice of one channel, two state tiles per wave
+    (1, 1100, 1, 24, 18, 1, 8, 2, "bf16"),
+    (1, 60, 1, 24, 18, 1, 8, 2, "f32"),        # one segment
+], ids=lambda c: "B%dL%dH%dP%dN%dG%dE%dk%d%s" % c)
+def test_a_state_in_place_gives_the_same_bits(cfg):
+    """The sequence is walked in the same segments whether or not the final state goes over the initial one."""
+    k = cfg[7]
+    p, h0 = inputs(*cfg)
+    d = to_device(p, cfg[8])
+    args = [d[q] for q in ("x", "dt", "A", "D", "B_experts", "C_experts", "router_logits")]
+    apart = sw.swimba_mixer_fwd(*args, k, 64, torch.from_numpy(h0).cuda())
+    state = torch.from_numpy(h0).cuda()
+    over = sw.swimba_mixer_fwd(*args, k, 64, state, h_final=state)
+    torch.cuda.synchronize()
+    assert over.h_final.data_ptr() == state.data_ptr()
+    assert torch.equal(over.y, apart.y) and torch.equal(state, apart.h_final)
