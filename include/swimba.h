@@ -156,6 +156,9 @@ swimba_status swimba_router_topk(int64_t tokens, int32_t nexperts, int32_t top_k
  * tiles also after the decay mask, and the state carried into a chunk are rounded to bf16
  * as operands; the recurrence between chunks itself runs in fp32 registers);
  * other bf16 shapes use the fp32 kernels.
+ * In fp32 arithmetic an input that is not finite reaches no token in front of its own, no other
+ * sequence and, in x (one channel) or dt (one head), nothing beside its channel or head.  The bf16
+ * MFMA kernels multiply tiles of 32 tokens and make no such promise.
  */
 swimba_status swimba_mixer_fwd(const swimba_dims *dims, const void *x, const void *dt,
                                const float *A, const float *D, const void *B_experts,

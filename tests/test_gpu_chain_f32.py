@@ -115,3 +115,34 @@ def test_a_state_in_place_gives_the_same_bits(cfg):
     torch.cuda.synchronize()
     assert over.h_final.data_ptr() == state.data_ptr()
     assert torch.equal(over.y, apart.y) and torch.equal(state, apart.h_final)
+
+
+@pytest.mark.parametrize("j", [5, 31, 32, 63, 64, 80, 330])
+@pytest.mark.parametrize("which", ["x_inf", "x_nan", "dt_inf", "dt_nan", "B_nan", "C_inf"])
+def test_values_that_are_not_finite_stay_causal(which, j):
+    """Uninitialised padding behind a sequence, say: tokens in front of it, other channels (x), other heads (dt)
+    and other sequences keep their values; its own token does not hide it."""
+    cfg = (2, 600, 4, 40, 48, 1, 8, 2, "f32")                       # two segments of five steps
+    B, L, H, P = cfg[:4]
+    p, h0 = inputs(*cfg)
+    d = to_device(p, "f32")
+    names = ("x", "dt", "A", "D", "B_experts", "C_experts", "router_logits")
+    h = torch.from_numpy(h0).cuda()
+    clean = sw.swimba_mixer_fwd(*[d[q] for q in names], 2, 64, h)
+    bad = float("inf") if which.endswith("inf") else float("nan")
+    hit = torch.zeros(B, L, H, P, dtype=torch.bool, device="cuda:0")
+    if which[0] == "x":
+        d["x"][1, j, 2, 33] = bad
+        hit[1, j:, 2, 33] = True
+    elif which[0] == "d":
+        d["dt"][1, j, 2] = bad
+        hit[1, j:, 2] = True
+    else:
+        d["B_experts" if which[0] == "B" else "C_experts"][1, j] = bad
+        hit[1, j:(None if which[0] == "B" else j + 1)] = True
+    out = sw.swimba_mixer_fwd(*[d[q] for q in names], 2, 64, h)
+    torch.cuda.synchronize()
+    assert not torch.isfinite(out.y[1, j][hit[1, j]]).any()
+    kept = ~hit
+    assert torch.isfinite(out.y[kept]).all()
+    assert rel(host(out.y[kept]), host(clean.y[kept])) <= 1e-6     # the sums are taken in another order
