@@ -512,10 +512,13 @@ swimba_status swimba_step_static(const swimba_dims *dims, const float *state_in,
  *   state_in/out (B,H,P,N) fp32 (may alias); x (B,L,H,P), dt (B,L,H), B/C_experts (B,L,E,G,N),
  *   router_logits (B,L,E), y (B,L,H,P) [out], topk_idx (B,L,k) [out, nullable]
  *   1 <= L <= SWIMBA_MAX_STEP_TOKENS; workspace >= swimba_step_multi_workspace_bytes(dims).
- * Arithmetic is fp32 like swimba_step.  From about 16 tokens per call on, swimba_mixer_fwd with
- * h0 = the state, h_final = the new state and a chunk of 64 is the faster way to the same result
- * where its bf16 MFMA path applies (at B = H = P = 64, N = 128: 150-160 us for any L up to 64,
- * against 146 / 254 / 450 us here for L = 16 / 32 / 64), at that path's bf16-operand accuracy.
+ * For N a power of two from 16 to 256 one kernel is enqueued for up to 16 experts and 16 tokens and two
+ * (routing + mixing, then the state update) beyond; for another N the second kernel runs once per
+ * token, and the state crosses memory as often.  Arithmetic is fp32 like swimba_step.  From about 32
+ * tokens per call on, swimba_mixer_fwd with h0 = the state, h_final = the new state and a chunk of 64 is
+ * the faster way to the same result where its bf16 MFMA path applies (at B = H = P = 64, N = 128:
+ * 126 / 132 / 140 us for L = 16 / 32 / 64, against 82 / 128 / 226 us here), at that path's
+ * bf16-operand accuracy.
  */
 size_t swimba_step_multi_workspace_bytes(const swimba_dims *dims);
 swimba_status swimba_step_multi(const swimba_dims *dims, const float *state_in, float *state_out,

@@ -1,9 +1,10 @@
 // Recurrent decode step of one or a few tokens per sequence (paper: selective SSM recurrence per channel,
-// with the router-mixed injection and readout of Theorem 1).  One launch where the state size is a
-// power of two and a row of lanes holds a token's logits (up to 16 experts): every block routes and mixes
-// its tokens while its piece of the fp32 state is on its way in, applies them to it and writes it back.
-// More experts: the same kernel behind a small one that routes and mixes (fp32 rows in the caller's
-// workspace).  Other state sizes: that small kernel and one update launch per token.
+// with the router-mixed injection and readout of Theorem 1).  State sizes that are a power of two: one launch where a
+// row of lanes holds a token's logits (up to 16 experts) and a block routes all tokens at once (up to 16): every
+// block routes and mixes its tokens while its piece of the fp32 state is on its way in, applies them to it and writes
+// it back.  More experts or tokens: the update behind a small kernel that routes and mixes (fp32 rows in the
+// caller's workspace); the state still crosses memory once.  Other state sizes: that small kernel and one update
+// launch per token.
 #include "common.hpp"
 
 #include <atomic>
@@ -127,25 +128,77 @@ __device__ __forceinline__ void route_row16(float v, int lane, int E, int K, int
     }
 }
 
-// Block = (b, h, slice of R * 256 / (N/4) state rows); lane -> 4 columns of R rows, held in registers over
-// the L tokens, so the state crosses memory once in each direction.  Every block routes and mixes its
-// sequence's tokens itself (rows of a group's B and C come from L2 for all but the first head); the state
-// loads are issued before that chain and the latency of both is the same one.  With bc (the output of
-// step_mix_kernel, for more experts than a row of lanes has) the rows come mixed.
+// Both kernels below: block = (b, h, slice of R * 256 / (N/4) state rows); lane -> 4 columns of R rows, held in
+// registers over the L tokens, so the state crosses memory once in each direction.
 // HBM-bound at a full batch, launch- and latency-bound for a few sequences.
+template <int N, int R>
+struct StepRows {
+    static constexpr int LPR = N / 4;                       // lanes of a state row
+    static constexpr int STRIDE = STEP_THREADS / LPR;       // rows of one register
+    static constexpr int ROWS = R * STRIDE;
+    static_assert(R <= LPR, "every row sum has a lane");
+    // the row whose sum a lane ends up with (see group_sums)
+    static constexpr int LOGR = R == 1 ? 0 : R == 2 ? 1 : R == 4 ? 2 : 3;
+    static constexpr int SHIFT = (LPR == 64 ? 6 : LPR == 32 ? 5 : LPR == 16 ? 4 : LPR == 8 ? 3 : 2) - LOGR;
+
+    int lane, r0, n4, p0, P, myrow;
+    bool mine;
+    f32x4_t v[R];
+
+    __device__ __forceinline__ StepRows(int tid, int p0_, int P_)
+        : lane(tid & 63), r0(tid / LPR), n4((tid % LPR) * 4), p0(p0_), P(P_)
+    {
+        myrow = ((lane % LPR) >> SHIFT) * STRIDE + r0;
+        mine = (lane & ((1 << SHIFT) - 1)) == 0 && p0 + myrow < P;
+    }
+    __device__ __forceinline__ void load(const float *state)       // state: the slice's first row
+    {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const uint32_t o = (uint32_t)(min(r * STRIDE + r0, P - 1 - p0) * N + n4);
+            v[r] = __builtin_nontemporal_load(reinterpret_cast<const f32x4_t *>(state + o));
+        }
+    }
+    __device__ __forceinline__ void store(float *state) const
+    {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int p = r * STRIDE + r0;
+            if (p0 + p < P) __builtin_nontemporal_store(v[r], reinterpret_cast<f32x4_t *>(state + (uint32_t)(p * N + n4)));
+        }
+    }
+    // one token: mixed rows b and c (N), inputs xr of the slice's rows; y: the token's output of this lane's row
+    template <typename T>
+    __device__ __forceinline__ void token(const float *b, const float *c, const float *xr, float dtv, float decay, float dsk, T *y)
+    {
+        const f32x4_t bm = *reinterpret_cast<const f32x4_t *>(b + n4);
+        const f32x4_t cm = *reinterpret_cast<const f32x4_t *>(c + n4);
+        float part[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const float u = dtv * xr[r * STRIDE + r0];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) v[r][q] = fmaf(u, bm[q], decay * v[r][q]);   // in place: no register moves
+            part[r] = (v[r][0] * cm[0] + v[r][1] * cm[1]) + (v[r][2] * cm[2] + v[r][3] * cm[3]);
+        }
+        const float tot = group_sums<LPR / 2>(part, lane);
+        if (mine) *y = from_float<T>(tot + dsk * xr[myrow]);
+    }
+};
+
+// Up to STEP_FUSED_TOKENS tokens of up to STEP_FUSED_EXPERTS experts.  Every block routes and mixes its
+// sequence's tokens itself (rows of a group's B and C come from L2 for all but the first head); the state
+// loads are issued before that chain and the latency of both is the same one.
 template <typename T, int N, int R>
 __global__ void __launch_bounds__(STEP_THREADS, R > 4 ? 7 : 8)
 step_fused_kernel(const float *state_in, float *state_out, const T *__restrict__ x, const T *__restrict__ dt,
                   const float *__restrict__ A, const float *__restrict__ D, const T *__restrict__ Be,
                   const T *__restrict__ Ce, const T *__restrict__ logits, T *__restrict__ y,
-                  int32_t *__restrict__ idx_out, const float *__restrict__ bc, Shape s, int slices, int t0, int L)
+                  int32_t *__restrict__ idx_out, Shape s, int slices)
 {
-    constexpr int LPR = N / 4;                       // lanes of a state row
-    constexpr int STRIDE = STEP_THREADS / LPR;       // rows of one register
-    constexpr int ROWS = R * STRIDE;
-    static_assert(R <= LPR, "every row sum has a lane");
+    constexpr int LPR = StepRows<N, R>::LPR, ROWS = StepRows<N, R>::ROWS;
     extern __shared__ __align__(16) float smem[];
-    const int K = s.K, E = s.E, P = s.P;
+    const int K = s.K, E = s.E, P = s.P, L = s.L;
     float *s_b = smem, *s_c = s_b + L * N, *s_x = s_c + L * N, *s_dt = s_x + L * ROWS, *s_a = s_dt + L;
     float *s_w = s_a + L;
     int32_t *s_i = (int32_t *)(s_w + L * K);
@@ -155,15 +208,14 @@ step_fused_kernel(const float *state_in, float *state_out, const T *__restrict__
     const int g = (h * s.G) / s.H;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int n4 = (tid % LPR) * 4, r0 = tid / LPR;
     const int p0 = sl * ROWS;
     const int64_t base = (((int64_t)b * s.H + h) * P + p0) * N;
-    const int64_t tok = (int64_t)b * s.L + t0;       // first token of this launch
+    const int64_t tok = (int64_t)b * L;
 
     // logits first: memory operations retire in order, and the router waits for them
     const int e16 = lane & 15;
     const int rt = wave * 4 + (lane >> 4);           // the token this row of lanes routes
-    const float lg = !bc && rt < L && e16 < E ? to_float(logits[(tok + rt) * E + e16]) : -INFINITY;
+    const float lg = rt < L && e16 < E ? to_float(logits[(tok + rt) * E + e16]) : -INFINITY;
 #pragma unroll 1
     for (int i = tid; i < L * ROWS; i += STEP_THREADS) {
         const int t = i / ROWS, p = p0 + i % ROWS;
@@ -174,27 +226,15 @@ step_fused_kernel(const float *state_in, float *state_out, const T *__restrict__
         s_dt[tid] = dtv;
         s_a[tid] = expf(dtv * A[h]);
     }
-    f32x4_t v[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const uint32_t o = (uint32_t)(min(r * STRIDE + r0, P - 1 - p0) * N + n4);
-        v[r] = __builtin_nontemporal_load(reinterpret_cast<const f32x4_t *>(state_in + base + o));
-    }
-    if (!bc) {
-        if (rt < L) route_row16(lg, lane, E, K, s_i + rt * K, s_w + rt * K);
-        lds_barrier();
-        if (idx_out && h == 0 && sl == 0 && tid < L * K) idx_out[tok * K + tid] = s_i[tid];
-    }
+    StepRows<N, R> rows(tid, p0, P);
+    rows.load(state_in + base);
+    if (rt < L) route_row16(lg, lane, E, K, s_i + rt * K, s_w + rt * K);
+    lds_barrier();
+    if (idx_out && h == 0 && sl == 0 && tid < L * K) idx_out[tok * K + tid] = s_i[tid];
     // mixed rows of the L tokens: 4 columns of B or C per thread and turn
 #pragma unroll 1
     for (int i = tid; i < L * 2 * LPR; i += STEP_THREADS) {
         const int t = i / (2 * LPR), c = (i / LPR) & 1, n = (i % LPR) * 4;
-        float *dst = (c ? s_c : s_b) + t * N + n;
-        if (bc) {
-            *reinterpret_cast<f32x4_t *>(dst) =
-                *reinterpret_cast<const f32x4_t *>(bc + (((tok + t) * s.G + g) * 2 + c) * N + n);
-            continue;
-        }
         const T *src = (c ? Ce : Be) + ((tok + t) * E * s.G + g) * N + n;
         float m[4] = {0.f, 0.f, 0.f, 0.f};
         for (int r = 0; r < K; ++r) {
@@ -205,62 +245,91 @@ step_fused_kernel(const float *state_in, float *state_out, const T *__restrict__
 #pragma unroll
             for (int q = 0; q < 4; ++q) m[q] += w * to_float(four.q[q]);
         }
-        *reinterpret_cast<f32x4_t *>(dst) = f32x4_t{m[0], m[1], m[2], m[3]};
+        *reinterpret_cast<f32x4_t *>((c ? s_c : s_b) + t * N + n) = f32x4_t{m[0], m[1], m[2], m[3]};
     }
     lds_barrier();
     const float dsk = D ? D[h] : 0.f;
-    // the row whose sum this lane ends up with (see group_sums)
-    constexpr int LOGR = R == 1 ? 0 : R == 2 ? 1 : R == 4 ? 2 : 3;
-    constexpr int SHIFT = (LPR == 64 ? 6 : LPR == 32 ? 5 : LPR == 16 ? 4 : LPR == 8 ? 3 : 2) - LOGR;
-    const int myrow = ((lane % LPR) >> SHIFT) * STRIDE + r0;
-    const bool mine = (lane & ((1 << SHIFT) - 1)) == 0 && p0 + myrow < P;
-    T *yr = y + (tok * s.H + h) * P + p0 + myrow;
+    T *yr = y + (tok * s.H + h) * P + p0 + rows.myrow;
 #pragma unroll 1
-    for (int t = 0; t < L; ++t) {
-        const f32x4_t bm = *reinterpret_cast<const f32x4_t *>(s_b + t * N + n4);
-        const f32x4_t cm = *reinterpret_cast<const f32x4_t *>(s_c + t * N + n4);
-        const float dtv = s_dt[t], decay = s_a[t];
-        float part[R];
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const float u = dtv * s_x[t * ROWS + r * STRIDE + r0];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) v[r][q] = decay * v[r][q] + u * bm[q];
-            part[r] = (v[r][0] * cm[0] + v[r][1] * cm[1]) + (v[r][2] * cm[2] + v[r][3] * cm[3]);
-        }
-        const float tot = group_sums<LPR / 2>(part, lane);
-        if (mine) yr[(int64_t)t * s.H * P] = from_float<T>(tot + dsk * s_x[t * ROWS + myrow]);
-    }
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const int p = r * STRIDE + r0;
-        if (p0 + p < P) __builtin_nontemporal_store(v[r], reinterpret_cast<f32x4_t *>(state_out + base + (uint32_t)(p * N + n4)));
-    }
+    for (int t = 0; t < L; ++t)
+        rows.token(s_b + t * N, s_c + t * N, s_x + t * ROWS, s_dt[t], s_a[t], dsk, yr + (int64_t)t * s.H * P);
+    rows.store(state_out + base);
 }
 
-// Sums over the 32 lanes of a half wave of NV values per lane at once (NV a power of two, at most
-// 16): every butterfly step halves the number of values a lane carries, so NV values cost
-// NV shuffles instead of 5 NV.  Returns sum number ((lane & 31) >> 1) % NV... see below: after
-// log2(NV) halving steps a lane holds the value whose index is given by its lane bits, the
-// remaining steps are plain xor reductions.  Value i ends up (complete) on the lanes whose bits
-// 4 .. 5-log2(NV) spell i.
-template <int NV>
-__device__ __forceinline__ float half_wave_sums(float (&v)[NV], int lane)
+// Any number of tokens and experts, behind step_mix_kernel: bc holds the mixed rows (B; C) of every token and group.
+// The tokens pass through LDS TG at a time, the next ones on their way while these are applied.
+template <typename T, int N, int R, int TG>
+__global__ void __launch_bounds__(STEP_THREADS, TG > 4 ? 4 : R > 4 ? 7 : 8)
+step_mixed_kernel(const float *state_in, float *state_out, const T *__restrict__ x, const T *__restrict__ dt,
+                  const float *__restrict__ A, const float *__restrict__ D, const float *__restrict__ bc,
+                  T *__restrict__ y, Shape s, int slices)
 {
-    int off = 16;
+    constexpr int ROWS = StepRows<N, R>::ROWS;
+    constexpr int NB = TG * 2 * N / 4 > STEP_THREADS ? TG * 2 * N / 4 / STEP_THREADS : 1;     // quads of bc per lane
+    constexpr int NX = TG * ROWS > STEP_THREADS ? TG * ROWS / STEP_THREADS : 1;
+    __shared__ __align__(16) float s_bc[TG * 2 * N], s_x[TG * ROWS];
+    __shared__ float s_dt[TG], s_a[TG];
+    const int P = s.P, L = s.L;
+    const int sl = blockIdx.x % slices;
+    const int h = (blockIdx.x / slices) % s.H;
+    const int b = blockIdx.x / (slices * s.H);
+    const int g = (h * s.G) / s.H;
+    const int tid = threadIdx.x;
+    const int p0 = sl * ROWS;
+    const int64_t base = (((int64_t)b * s.H + h) * P + p0) * N;
+    const int64_t tok = (int64_t)b * L;
+    const float Ah = A[h], dsk = D ? D[h] : 0.f;
+
+    f32x4_t nb[NB];
+    float nx[NX], ndt = 0.f;
+    // tokens past the last one are left out 256 lanes at a time and repeat the last one otherwise
+    auto load = [&](int t0) __attribute__((always_inline)) {
 #pragma unroll
-    for (int n = NV / 2; n >= 1; n >>= 1, off >>= 1) {
-        const bool hi = (lane & off) != 0;
-#pragma unroll
-        for (int j = 0; j < n; ++j) {
-            const float keep = hi ? v[n + j] : v[j];
-            const float send = hi ? v[j] : v[n + j];
-            v[j] = keep + __shfl_xor(send, off);
+        for (int i = 0; i < NB; ++i) {
+            const int o = (tid + i * STEP_THREADS) * 4;
+            if (t0 + i * STEP_THREADS * 4 / (2 * N) < L)
+                nb[i] = *reinterpret_cast<const f32x4_t *>(bc + ((tok + min(t0 + o / (2 * N), L - 1)) * s.G + g) * 2 * N + o % (2 * N));
         }
+#pragma unroll
+        for (int i = 0; i < NX; ++i) {
+            const int o = tid + i * STEP_THREADS;
+            if (t0 + i * STEP_THREADS / ROWS < L)
+                nx[i] = to_float(x[((tok + min(t0 + o / ROWS, L - 1)) * s.H + h) * P + min(p0 + o % ROWS, P - 1)]);
+        }
+        if (tid < TG) ndt = to_float(dt[(tok + min(t0 + tid, L - 1)) * s.H + h]);
+    };
+    auto stage = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+            const int o = (tid + i * STEP_THREADS) * 4;
+            if (o < TG * 2 * N) *reinterpret_cast<f32x4_t *>(s_bc + o) = nb[i];
+        }
+#pragma unroll
+        for (int i = 0; i < NX; ++i) {
+            const int o = tid + i * STEP_THREADS;
+            if (o < TG * ROWS) s_x[o] = nx[i];
+        }
+        if (tid < TG) {
+            s_dt[tid] = ndt;
+            s_a[tid] = expf(ndt * Ah);
+        }
+    };
+    load(0);
+    StepRows<N, R> rows(tid, p0, P);
+    rows.load(state_in + base);
+    T *yr = y + (tok * s.H + h) * P + p0 + rows.myrow;
+    for (int t0 = 0; t0 < L; t0 += TG) {
+        stage();
+        lds_barrier();
+        if (TG > 4 && t0 + TG < L) load(t0 + TG);             // (four tokens are the whole call)
+        const int n = min(TG, L - t0);
+#pragma unroll 1
+        for (int t = 0; t < n; ++t)
+            rows.token(s_bc + t * 2 * N, s_bc + t * 2 * N + N, s_x + t * ROWS, s_dt[t], s_a[t], dsk,
+                       yr + (int64_t)(t0 + t) * s.H * P);
+        lds_barrier();
     }
-    float r = v[0];
-    for (; off >= 1; off >>= 1) r += __shfl_xor(r, off);
-    return r;
+    rows.store(state_out + base);
 }
 
 // ---- state update, any N: block = (b, h), a wave walks one state row at a time ------------
@@ -297,40 +366,50 @@ step_update_generic_kernel(const float *state_in, float *state_out, const T *__r
     }
 }
 
-// Tokens go STEP_FUSED_TOKENS per launch (the mixed rows of a launch are in LDS).
 template <typename T, int N, int R>
-static void launch_fused(const Shape &s, const float *state_in, float *state_out, const void *x, const void *dt,
-                         const float *A, const float *D, const void *Be, const void *Ce, const void *logits, void *y,
-                         int32_t *idx, const float *bc, hipStream_t st)
+static void launch_rows(const Shape &s, const float *state_in, float *state_out, const void *x, const void *dt,
+                        const float *A, const float *D, const void *Be, const void *Ce, const void *logits, void *y,
+                        int32_t *idx, const float *bc, hipStream_t st)
 {
-    constexpr int ROWS = R * STEP_THREADS / (N / 4);
+    constexpr int ROWS = StepRows<N, R>::ROWS;
     const int slices = (s.P + ROWS - 1) / ROWS;
-    for (int t0 = 0; t0 < s.L; t0 += STEP_FUSED_TOKENS) {
-        const int L = s.L - t0 < STEP_FUSED_TOKENS ? s.L - t0 : STEP_FUSED_TOKENS;
-        const size_t lds = (size_t)L * (2 * N + ROWS + 2 + 2 * s.K) * sizeof(float);
-        hipLaunchKernelGGL((step_fused_kernel<T, N, R>), dim3((unsigned)(s.B * s.H * slices)), dim3(STEP_THREADS), lds,
-                           st, t0 == 0 ? state_in : state_out, state_out, (const T *)x, (const T *)dt, A, D,
-                           (const T *)Be, (const T *)Ce, (const T *)logits, (T *)y, idx, bc, s, slices, t0, L);
+    const dim3 grid((unsigned)(s.B * s.H * slices));
+    if (bc) {
+        auto kernel = s.L > 4 ? step_mixed_kernel<T, N, R, 16> : step_mixed_kernel<T, N, (R > 4 ? 4 : R), 4>;   // R <= 4 there
+        hipLaunchKernelGGL(kernel, grid, dim3(STEP_THREADS), 0, st, state_in, state_out, (const T *)x, (const T *)dt, A, D,
+                           bc, (T *)y, s, slices);
+        return;
     }
+    const size_t lds = (size_t)s.L * (2 * N + ROWS + 2 + 2 * s.K) * sizeof(float);
+    hipLaunchKernelGGL((step_fused_kernel<T, N, R>), grid, dim3(STEP_THREADS), lds, st, state_in, state_out, (const T *)x,
+                       (const T *)dt, A, D, (const T *)Be, (const T *)Ce, (const T *)logits, (T *)y, idx, s, slices);
 }
 
-// Four registers of rows per lane (16 KB of state per block at most) stream best: full batch of 64 sequences x
-// 64 heads 46.4 us (5.8 TB/s) against 52.6 with two and 49.4 with eight (one with one: 83.9).  Eight where every
-// block then finds a place at once (7 blocks per compute unit) and four would need a second round (24 sequences:
-// 16.9 against 19.5 us), and from five tokens on, where the routing and mixing that every block repeats
-// costs more than the rounds (8 tokens x 16 sequences: 16.2 against 17.3 us).
+// Registers of rows per lane.
+// Routing inside: four (16 KB of state per block at most) stream best: full batch of 64 sequences x 64 heads 46.4 us
+// (5.8 TB/s) against 52.6 with two and 49.4 with eight (one with one: 83.9).  Eight where every block then finds a
+// place at once (7 blocks per compute unit) and four would need a second round (24 sequences: 16.9 against 19.5 us),
+// and from five tokens on, where the routing and mixing that every block repeats costs more than the rounds
+// (8 tokens x 16 sequences: 16.2 against 17.3 us).
+// Rows that come mixed: up to four tokens four, as above (one token, 64 sequences x 64 heads: 57 us with two and
+// with four, 63 with one, 86 with eight).  With more the tokens' chain counts: as many rows as leave 1.5 blocks per
+// compute unit, and eight only from four blocks on.  64 tokens x 32 heads, one / two / four / eight registers:
+// 1 sequence 21.2 / 24.0 / 30.1 / 41.5 us, 4: 27.8 / 25.8 / 30.9 / 42.4, 16: 70 / 55 / 47.9 / 49.3, 64: 244 / 169 / 145 / 136.
 template <typename T, int N>
-static void launch_fused_rows(const Shape &s, const float *state_in, float *state_out, const void *x, const void *dt,
-                              const float *A, const float *D, const void *Be, const void *Ce, const void *logits,
-                              void *y, int32_t *idx, const float *bc, hipStream_t st)
+static void launch_update(const Shape &s, const float *state_in, float *state_out, const void *x, const void *dt,
+                          const float *A, const float *D, const void *Be, const void *Ce, const void *logits,
+                          void *y, int32_t *idx, const float *bc, hipStream_t st)
 {
     constexpr int STRIDE = STEP_THREADS / (N / 4);
     auto blocks = [&](int r) { return (int64_t)s.B * s.H * ((s.P + r * STRIDE - 1) / (r * STRIDE)); };
     const int ncu = device_cus();
-    int R = s.L > 4 || (blocks(4) > 8 * ncu && blocks(8) <= 7 * ncu) ? 8 : 4;
+    int R;
+    if (!bc) R = s.L > 4 || (blocks(4) > 8 * ncu && blocks(8) <= 7 * ncu) ? 8 : 4;
+    else if (s.L <= 4) R = 4;
+    else for (R = blocks(8) >= 4 * ncu ? 8 : 4; R > 1 && 2 * blocks(R) < 3 * ncu; R /= 2) {}
     while (R > 1 && (R / 2) * STRIDE >= s.P) R /= 2;
     auto go = [&](auto r) {
-        launch_fused<T, N, decltype(r)::value>(s, state_in, state_out, x, dt, A, D, Be, Ce, logits, y, idx, bc, st);
+        launch_rows<T, N, decltype(r)::value>(s, state_in, state_out, x, dt, A, D, Be, Ce, logits, y, idx, bc, st);
     };
     if (R >= 8 && N >= 32) go(std::integral_constant<int, N >= 32 ? 8 : 4>{});
     else if (R >= 4) go(std::integral_constant<int, 4>{});
@@ -348,7 +427,7 @@ static swimba_status launch_step_multi_t(const Shape &s, const float *state_in, 
 {
     const int64_t blocks = (int64_t)s.B * s.H;
     if (blocks == 0 || s.L == 0) return SWIMBA_OK;
-    const bool route_in_update = s.E <= STEP_FUSED_EXPERTS;
+    const bool route_in_update = s.E <= STEP_FUSED_EXPERTS && s.L <= STEP_FUSED_TOKENS;
     const bool rows = (s.N & (s.N - 1)) == 0 && s.N >= 16 && s.N <= 256 && blocks * s.P < (1ll << 31);
     if (!rows || !route_in_update) {
         Shape tok = s;             // the mix kernel sees B*L independent tokens
@@ -361,7 +440,7 @@ static swimba_status launch_step_multi_t(const Shape &s, const float *state_in, 
     if (rows) {
         const float *mixed = route_in_update ? nullptr : bc;
         auto fused = [&](auto n) {
-            launch_fused_rows<T, decltype(n)::value>(s, state_in, state_out, x, dt, A, D, Be, Ce, logits, y, idx, mixed, st);
+            launch_update<T, decltype(n)::value>(s, state_in, state_out, x, dt, A, D, Be, Ce, logits, y, idx, mixed, st);
         };
         switch (s.N) {
         case 16: fused(std::integral_constant<int, 16>{}); break;

@@ -1,6 +1,8 @@
 """Decode steps at the edges of the one-launch kernel: every state size it takes and one it does not, head
-dimensions that leave a register row or a block partly empty, 16 and 17 experts (with and without
-routing inside the update), 16 and 17 tokens (one launch and two), tied logits; against the oracle."""
+dimensions that leave a register row or a block partly empty, 16 and 17 experts and 16 and 17 tokens (with and
+without routing inside the update), tied logits; against the oracle."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -23,6 +25,15 @@ pytestmark = pytest.mark.gpu
     (40, 1, 64, 64, 128, 8, 8, 2, "bf16"),     # more than one round of blocks
     (2, 2, 2, 1, 128, 1, 1, 1, "f32"),
     (1, 6, 2, 64, 80, 1, 8, 2, "bf16"),        # a state size with an update launch per token
+    # rows that come mixed: four, five and sixteen tokens, whole and short groups of sixteen, every number of registers
+    (3, 4, 4, 40, 16, 2, 17, 2, "f32"),
+    (2, 5, 2, 64, 256, 1, 17, 2, "bf16"),
+    (1, 32, 4, 64, 16, 1, 8, 4, "bf16"),
+    (5, 64, 16, 30, 32, 2, 8, 2, "f32"),
+    (12, 31, 32, 64, 64, 1, 8, 2, "bf16"),
+    (8, 18, 24, 64, 128, 1, 20, 2, "f32"),
+    (64, 17, 16, 64, 128, 1, 4, 1, "bf16"),
+    (40, 16, 16, 33, 256, 1, 18, 1, "f32"),
 ], ids=lambda c: "B%dL%dH%dP%dN%dG%dE%dk%d%s" % c)
 def test_step_sizes_match_oracle(cfg):
     B, L, H, P, N, G, E, k, io = cfg
@@ -47,3 +58,25 @@ def test_step_sizes_match_oracle(cfg):
     # whole-output norm: with few tokens and channels a (batch, head) slice is a handful of cancelling scalars
     l2, linf = rel_errors(host(out.y).reshape(B, L, H, P), ref["y"], ())
     assert l2 <= TOL[io] and linf <= TOL[io], ("y", l2, linf)
+
+
+@pytest.mark.parametrize("E", [8, 17])
+@pytest.mark.parametrize("L", [17, 33, 64])
+def test_the_state_crosses_memory_once(L, E):
+    """However many tokens a call has, two kernels run: one that routes and mixes, one that updates the state."""
+    x = torch.randn(2, L, 4, 64, device="cuda:0")
+    dt, lg = torch.rand(2, L, 4, device="cuda:0"), torch.randn(2, L, E, device="cuda:0")
+    A, Be = -torch.ones(4, device="cuda:0"), torch.randn(2, L, E, 1, 128, device="cuda:0")
+    state = torch.zeros(2, 4, 64, 128, device="cuda:0")
+    dims = sw.make_dims(2, L, 4, 64, 128, 1, E, 2, 0, torch.float32)
+    ws = torch.empty(sw.swimba_step_multi_workspace_bytes(dims), dtype=torch.uint8, device="cuda:0")
+    y = torch.empty_like(x)
+    call = lambda: sw.swimba_step_multi(state, x, dt, A, None, Be, Be, lg, 2, y=y, workspace=ws)
+    call()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph):
+        call()
+    n = ctypes.c_size_t()
+    assert sw._load().hipGraphGetNodes(ctypes.c_void_p(graph.raw_cuda_graph()), None, ctypes.byref(n)) == 0
+    assert n.value == 2
