@@ -99,11 +99,11 @@ static void layout_of(const swimba_dims *d, swimba_ws_layout *o, ChainF32Layout 
     o->hmid = off;
     if (mf) off = align_up(off + (size_t)s.B * (PASS_SPLIT_MAX_SEGMENTS - 1) * s.H * s.P * s.N * sizeof(float), 256);
     if (!mf) {
-        size_t ops, g, seg, dec, init;
-        chain_f32_sizes(d, &ops, &g, &seg, &dec, &init);
+        size_t cop, bop, g, seg, dec, init;
+        chain_f32_sizes(d, &cop, &bop, &g, &seg, &dec, &init);
         ChainF32Layout l;
-        l.cop = off;  off = align_up(off + ops, 256);
-        l.bop = off;  off = align_up(off + ops, 256);
+        l.cop = off;  off = align_up(off + cop, 256);
+        l.bop = off;  off = align_up(off + bop, 256);
         l.gop = off;  off = align_up(off + g, 256);
         l.hseg = off; off = align_up(off + seg, 256);
         l.aseg = off; off = align_up(off + dec, 256);

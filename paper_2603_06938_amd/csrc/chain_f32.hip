@@ -71,18 +71,31 @@ __device__ __forceinline__ float4 load4(const bf16 *p)
     return make_float4(bf_lo(u.x), bf_hi(u.x), bf_lo(u.y), bf_hi(u.y));
 }
 
-// Operand arrays, per (batch, step, group), N padded to NT tiles of 32 columns:
-//   cop (2, NT, 4, 64, 4)  [I][nt][a][lane][b] = C[32 I + lane%32][32 nt + 8a + 4(lane/32) + b]
-//   bop (NT, 8, 64, 4)     [nt][q][lane][b]    = B[8q + 4(lane/32) + b][32 nt + lane%32]
-//   gop (12, 64, 4)        [blk][lane][b]      = (j <= i) C[i] . B[j], blk < 4: i = lane%32, q = blk, else i = 32 + lane%32,
+// Operand arrays, per (batch, step, group), N padded to NT tiles of 32 columns.  IT, QN and GB are 2, 8 and 12, and
+// less where a whole sequence is shorter than a step (chain_ops): a sequence of 16 tokens takes 8 KB a group, not 28.
+//   cop (IT, NT, 4, 64, 4) [I][nt][a][lane][b] = C[32 I + lane%32][32 nt + 8a + 4(lane/32) + b]
+//   bop (NT, QN, 64, 4)    [nt][q][lane][b]    = B[8q + 4(lane/32) + b][32 nt + lane%32]
+//   gop (GB, 64, 4)        [blk][lane][b]      = (j <= i) C[i] . B[j], blk < 4: i = lane%32, q = blk, else i = 32 + lane%32,
 //                          q = blk - 4; j = 8q + 4(lane/32) + b
+// Of a step that is not full only what its tokens need is written, and the chain reads nothing else: the tile rows of C
+// and of G and the blocks of eight B rows with a token in them.
+struct ChainOps {
+    int IT, QN, GB;
+};
+__host__ __device__ inline ChainOps chain_ops(int L)
+{
+    const int q = (L + 7) / 8;
+    return L > 32 ? ChainOps{2, q < 8 ? q : 8, CF_GBLK} : ChainOps{1, q, q};
+}
+
 // PARTS = 4: four workgroups share a step, each with 16 of its tokens as rows of C and of G; it mixes the B rows
 // that these meet, so B is read 2.5 times, by compute units that would have none of the steps.
+// gpb groups per workgroup: its tokens are routed once for all of them.
 template <typename T, int PARTS>
-__global__ void __launch_bounds__(CF_MIX_THREADS)
+__global__ void __launch_bounds__(CF_MIX_THREADS, PARTS == 1 ? 4 : 2)
 mix_ops_kernel(const T *__restrict__ Be, const T *__restrict__ Ce, const T *__restrict__ logits,
                int32_t *__restrict__ idx_out, float *__restrict__ w_out, const float *__restrict__ w_sel,
-               float *__restrict__ cop, float *__restrict__ bop, float *__restrict__ gop, Shape s, int NT)
+               float *__restrict__ cop, float *__restrict__ bop, float *__restrict__ gop, Shape s, int NT, int gpb)
 {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     const int K = s.K, NP = 32 * NT, RS = NP + 4;        // row stride of the mixed rows
@@ -91,64 +104,73 @@ mix_ops_kernel(const T *__restrict__ Be, const T *__restrict__ Ce, const T *__re
     float *s_B = s_w + CF_STEP * K;                                          // [64][RS]
     float *s_C = s_B + CF_STEP * RS;                                         // [64][RS]
     constexpr int R = CF_STEP / PARTS;                   // rows of C and G in this workgroup
-    const int part = blockIdx.x % PARTS, r0 = part * R, item = blockIdx.x / PARTS;
-    const int g = item % s.G;
-    const int c = (item / s.G) % s.nc;
-    const int b = item / (s.G * s.nc);
+    // quads of a lane in flight: with a step per workgroup two of these share a compute unit
+    constexpr int QF = PARTS == 1 ? 4 : 8;
+    const int part = blockIdx.x % PARTS, r0 = part * R, item = blockIdx.x / PARTS, gblocks = s.G / gpb;
+    const int g_begin = (item % gblocks) * gpb;
+    const int c = (item / gblocks) % s.nc;
+    const int b = item / (gblocks * s.nc);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int valid = min(CF_STEP, s.L - c * CF_STEP);
+    if (r0 >= valid) return;
     const int64_t tok0 = (int64_t)b * s.L + (int64_t)c * CF_STEP;
     const bool sel = (w_sel != nullptr);
+    const ChainOps ops = chain_ops(s.L);
 
-    if (tid < CF_STEP) {
-        const int64_t t = tok0 + min(tid, valid - 1);
+    // more than 16 experts: the step's logits, one piece of memory, pass through LDS; up to 16 go through registers
+    const int ES = s.E | 1;                              // row stride
+    if (!sel && s.E > 16) {
+        for (int i = tid; i < valid * s.E; i += CF_MIX_THREADS) s_B[i / s.E * ES + i % s.E] = to_float(logits[tok0 * s.E + i]);
+        __syncthreads();
+    }
+    if (tid < valid) {
+        const int64_t t = tok0 + tid;
         int32_t *ix = s_idx + tid * K;
         float *wx = s_w + tid * K;
         if (sel) {
             for (int r = 0; r < K; ++r) { ix[r] = r; wx[r] = w_sel[t * K + r]; }
         } else {
-            const T *gl = logits + t * s.E;
+            float *row = s_B + tid * (s.E > 16 ? ES : 17);
             if (s.E <= 16) {
+                const T *gl = logits + t * s.E;
                 float v[16];
 #pragma unroll
                 for (int e = 0; e < 16; ++e) v[e] = to_float(gl[min(e, s.E - 1)]);
-                // every load is in flight before the first is used; the routing then reads them from LDS
-                float *row = s_B + tid * 17;
+                // every load is in flight before the first is used
 #pragma unroll
                 for (int e = 0; e < 16; ++e) row[e] = v[e];
-                route_token([&](int e) { return row[e]; }, s.E, K, ix, wx);
-            } else {
-                route_token([&](int e) { return to_float(gl[e]); }, s.E, K, ix, wx);
             }
-            if (g == 0 && tid < valid && tid >= r0 && tid < r0 + R)
+            route_token([&](int e) { return row[e]; }, s.E, K, ix, wx);
+            if (g_begin == 0 && tid >= r0 && tid < r0 + R)
                 for (int r = 0; r < K; ++r) { idx_out[t * K + r] = ix[r]; w_out[t * K + r] = wx[r]; }
         }
-        if (tid >= valid)
-            for (int r = 0; r < K; ++r) wx[r] = 0.f;     // rows past the end of the sequence mix to zero
     }
     __syncthreads();
 
-    // ---- mixed rows: a lane takes quads of 4 columns of one stream, eight at a time; C rows [r0, r0 + R), then the B
-    // ---- rows up to the last of them ----
     const int rowsE = sel ? K : s.E;
     const int64_t estride = (int64_t)s.G * s.N, tokstride = rowsE * estride;
+    const bool vec = (s.N % 4 == 0);
+    const int rowsC = min(valid - r0, R), rowsB = min(valid, r0 + R);
+    const int QPR = NP / 4, units = (rowsC + rowsB) * QPR;
+    for (int g = g_begin; g < g_begin + gpb; ++g) {
+    // ---- mixed rows: a lane takes quads of 4 columns of one stream, QF at a time; C rows [r0, r0 + R), then the B
+    // ---- rows up to the last of them ----
     const T *Bg = Be + (tok0 * rowsE * s.G + g) * s.N;
     const T *Cg = Ce + (tok0 * rowsE * s.G + g) * s.N;
-    const int QPR = NP / 4, units = (R + r0 + R) * QPR;
-    const bool vec = (s.N % 4 == 0);
-    for (int u0 = tid; u0 < units; u0 += 8 * CF_MIX_THREADS) {
-        float4 am[8];
+    for (int u0 = 0; u0 < units; u0 += QF * CF_MIX_THREADS) {
+        float4 am[QF];
 #pragma unroll
-        for (int m = 0; m < 8; ++m) am[m] = make_float4(0.f, 0.f, 0.f, 0.f);
+        for (int m = 0; m < QF; ++m) am[m] = make_float4(0.f, 0.f, 0.f, 0.f);
         for (int r = 0; r < K; ++r) {
-            float4 v[8];
-            float ww[8];
+            float4 v[QF];
+            float ww[QF];
 #pragma unroll
-            for (int m = 0; m < 8; ++m) {
-                const int u = min(u0 + m * CF_MIX_THREADS, units - 1);
-                const int rr = u / QPR, n = (u % QPR) * 4, j = rr < R ? r0 + rr : rr - R;
-                const T *src = (rr < R ? Cg : Bg) + min(j, valid - 1) * tokstride + s_idx[j * K + r] * estride;
+            for (int m = 0; m < QF; ++m) {
+                if (u0 + m * CF_MIX_THREADS >= units) continue;          // uniform
+                const int u = min(u0 + m * CF_MIX_THREADS + tid, units - 1);
+                const int rr = u / QPR, n = (u % QPR) * 4, j = rr < rowsC ? r0 + rr : rr - rowsC;
+                const T *src = (rr < rowsC ? Cg : Bg) + j * tokstride + s_idx[j * K + r] * estride;
                 ww[m] = s_w[j * K + r];
                 if (vec) {
                     v[m] = load4(src + min(n, s.N - 4));
@@ -160,31 +182,33 @@ mix_ops_kernel(const T *__restrict__ Be, const T *__restrict__ Ce, const T *__re
                 }
             }
 #pragma unroll
-            for (int m = 0; m < 8; ++m) {
+            for (int m = 0; m < QF; ++m) {
+                if (u0 + m * CF_MIX_THREADS >= units) continue;
                 am[m].x += ww[m] * v[m].x; am[m].y += ww[m] * v[m].y; am[m].z += ww[m] * v[m].z; am[m].w += ww[m] * v[m].w;
             }
         }
 #pragma unroll
-        for (int m = 0; m < 8; ++m) {
-            const int u = u0 + m * CF_MIX_THREADS;
+        for (int m = 0; m < QF; ++m) {
+            const int u = u0 + m * CF_MIX_THREADS + tid;
             if (u < units) {
                 const int rr = u / QPR, n = (u % QPR) * 4;
                 float *f = reinterpret_cast<float *>(&am[m]);
 #pragma unroll
                 for (int q = 0; q < 4; ++q)
                     if (n + q >= s.N) f[q] = 0.f;                   // padding columns
-                *reinterpret_cast<float4 *>((rr < R ? s_C + (r0 + rr) * RS : s_B + (rr - R) * RS) + n) = am[m];
+                *reinterpret_cast<float4 *>((rr < rowsC ? s_C + (r0 + rr) * RS : s_B + (rr - rowsC) * RS) + n) = am[m];
             }
         }
     }
     __syncthreads();
 
-    const int64_t bcg = item;
-    float4 *co = reinterpret_cast<float4 *>(cop) + bcg * (2 * NT * 4 * 64);
-    float4 *bo = reinterpret_cast<float4 *>(bop) + bcg * (NT * 8 * 64);
-    float4 *go = reinterpret_cast<float4 *>(gop) + bcg * (CF_GBLK * 64);
+    const int64_t bcg = ((int64_t)b * s.nc + c) * s.G + g;
+    float4 *co = reinterpret_cast<float4 *>(cop) + bcg * (ops.IT * NT * 4 * 64);
+    float4 *bo = reinterpret_cast<float4 *>(bop) + bcg * (NT * ops.QN * 64);
+    float4 *go = reinterpret_cast<float4 *>(gop) + bcg * (ops.GB * 64);
     // ---- G^T[j][i] = B[j] . C[i] in 16 x 16 tiles (v_mfma_f32_16x16x4_f32): lane (i = lane%16, kq = lane/16) ends
-    // ---- with four consecutive j of one i, which is a float4 of gop.  Tiles right of the diagonal are zero. ----
+    // ---- with four consecutive j of one i, which is a float4 of gop.  Tiles right of the diagonal are zero.  Rows past
+    // ---- the end hold what LDS held: their entries are masked (j > i) or belong to no token. ----
     {
         const int l16 = lane & 15, kq = lane >> 4;
         const int t_begin = PARTS == 1 ? 0 : part < 2 ? 2 * part : 4 * part - 4;
@@ -192,6 +216,7 @@ mix_ops_kernel(const T *__restrict__ Be, const T *__restrict__ Ce, const T *__re
         for (int t = t_begin + wave; t < t_end; t += CF_MIX_THREADS / 64) {
             // tile rows 0, 1 have columns J = 0, 1; rows 2, 3 columns 0..3
             const int I = t < 4 ? t >> 1 : 2 + ((t - 4) >> 2), J = t < 4 ? t & 1 : (t - 4) & 3;
+            if (16 * I >= valid || 16 * J >= valid) continue;
             cf_f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
             if (J <= I) {
                 const float *br = s_B + (16 * J + l16) * RS + 4 * kq, *cr = s_C + (16 * I + l16) * RS + 4 * kq;
@@ -209,36 +234,43 @@ mix_ops_kernel(const T *__restrict__ Be, const T *__restrict__ Ce, const T *__re
             for (int q = 0; q < 4; ++q)
                 if (j0 + q > i) acc[q] = 0.f;
             const int blk = (i >> 5) * 4 + (j0 >> 3);
-            go[blk * 64 + ((j0 >> 2) & 1) * 32 + (i & 31)] = make_float4(acc[0], acc[1], acc[2], acc[3]);
+            if (blk < ops.GB) go[blk * 64 + ((j0 >> 2) & 1) * 32 + (i & 31)] = make_float4(acc[0], acc[1], acc[2], acc[3]);
         }
     }
-    for (int u = tid; u < R * NT * 8; u += CF_MIX_THREADS) {
-        const int row = r0 + u % R, kg = (u / R) & 1, a = (u / R >> 1) & 3, nt = u / R >> 3;
+    for (int u = tid; u < rowsC * NT * 8; u += CF_MIX_THREADS) {
+        const int row = r0 + u % rowsC, v = u / rowsC, kg = v & 1, a = (v >> 1) & 3, nt = v >> 3;
         co[(((row >> 5) * NT + nt) * 4 + a) * 64 + kg * 32 + (row & 31)] =
             *reinterpret_cast<const float4 *>(s_C + row * RS + 32 * nt + 8 * a + 4 * kg);
     }
-    constexpr int QS = R / 8;
+    const int QS = (rowsC + 7) / 8;                      // blocks of eight B rows in this workgroup
     for (int u = tid; u < NT * QS * 64; u += CF_MIX_THREADS) {
-        const int ln = u & 63, q = r0 / 8 + (u >> 6) % QS, nt = (u >> 6) / QS;
-        const float *src = s_B + (8 * q + 4 * (ln >> 5)) * RS + 32 * nt + (ln & 31);
-        bo[(nt * 8 + q) * 64 + ln] = make_float4(src[0], src[RS], src[2 * RS], src[3 * RS]);
+        const int ln = u & 63, q = r0 / 8 + (u >> 6) % QS, nt = (u >> 6) / QS, row = 8 * q + 4 * (ln >> 5);
+        const float *src = s_B + row * RS + 32 * nt + (ln & 31);
+        // rows past the end are multiplied by zeros of x: they have to be finite
+        bo[(nt * ops.QN + q) * 64 + ln] = make_float4(row < valid ? src[0] : 0.f, row + 1 < valid ? src[RS] : 0.f,
+                                                      row + 2 < valid ? src[2 * RS] : 0.f, row + 3 < valid ? src[3 * RS] : 0.f);
+    }
+    __syncthreads();                                     // the next group's rows
     }
 }
 
-// NTW: 32-column state tiles per wave (N <= 128 * NTW).  OUT: y (and h_final); otherwise the state part only:
+// NTW: 32-column state tiles per wave (N <= 128 * NTW).  ROWT: 32-token tile rows of a step (1: sequences of at most
+// 32 tokens).  OUT: y (and h_final); otherwise the state part only:
 // the segment's own contribution to the state (from zero) into hseg, its total decay (log2) into aseg; with an h_final
 // it is segment 0's copy of h0 for the output launch, whose own h_final is the caller's h0.
-template <typename T, int NTW, bool OUT>
-__global__ void __launch_bounds__(256, NTW == 1 ? 2 : 1)
+template <typename T, int NTW, bool OUT, int ROWT>
+__global__ void __launch_bounds__(256, NTW == 1 ? (ROWT == 1 ? 3 : 2) : 1)
 chain_f32_kernel(const T *__restrict__ x, const T *__restrict__ dt, const float *__restrict__ A,
                  const float *__restrict__ D, const float *__restrict__ cop, const float *__restrict__ bop,
                  const float *__restrict__ gop, const float *h0, float *h_final,
                  float *__restrict__ hseg, float *__restrict__ aseg, T *__restrict__ y, Shape s, int NT, int nslice,
                  int nrun, int nseg, int steps_per_seg, int total, int nblocks)
 {
+    constexpr int QT = 4 * ROWT;                                 // 8-token blocks of a step
+    static_assert(OUT || ROWT == 2, "segments are of whole steps");
     __shared__ __align__(16) float s_x[2][32 * CF_XS];           // x^T of a step: [channel][token]
     __shared__ __align__(16) float s_cs[2][CF_STEP], s_dt[2][CF_STEP], s_c[2][CF_STEP];
-    __shared__ __align__(16) float s_y[OUT ? 4 : 1][OUT ? CF_STEP * CF_YS : 1];   // partial Y per wave: [token][channel]
+    __shared__ __align__(16) float s_y[OUT ? 4 : 1][OUT ? 32 * ROWT * CF_YS : 1];   // partial Y per wave: [token][channel]
 
     // (batch, segment, head, slice), neighbours (heads of one group) on one XCD: they read the same operands
     const int lid = xcd_logical_id(blockIdx.x, nblocks);
@@ -344,29 +376,37 @@ chain_f32_kernel(const T *__restrict__ x, const T *__restrict__ dt, const float 
     };
     // In the state part alone the B operand of the next step has no readout to arrive behind: it gets registers of
     // its own (brn) and is requested a whole step ahead.
-    float4 cr[NTW][2][4], br[NTW][8], brn[NTW][8], gr[3];
+    float4 cr[NTW][ROWT][4], br[NTW][QT], brn[NTW][QT], gr[ROWT == 2 ? 3 : 1];
     const int64_t bg0 = ((int64_t)b * s.nc) * s.G + g;
+    const ChainOps ops = chain_ops(s.L);
+    // Tile rows and blocks without a token are not there: the last ones that are come in their place, for results
+    // that are not stored and products with zeros of x.
+    auto last_token = [&](int c) __attribute__((always_inline)) { return min(CF_STEP, s.L - c * CF_STEP) - 1; };
     auto load_c = [&](int c) __attribute__((always_inline)) {
-        const float4 *src = reinterpret_cast<const float4 *>(cop) + (bg0 + (int64_t)c * s.G) * (2 * NT * 4 * 64) + lane;
+        const float4 *src = reinterpret_cast<const float4 *>(cop) + (bg0 + (int64_t)c * s.G) * (ops.IT * NT * 4 * 64) + lane;
+        const int Il = last_token(c) >> 5;
 #pragma unroll
         for (int k = 0; k < NTW; ++k)
 #pragma unroll
-            for (int I = 0; I < 2; ++I)
+            for (int I = 0; I < ROWT; ++I)
 #pragma unroll
                 for (int a = 0; a < 4; ++a)
-                    cr[k][I][a] = src[((I * NT + min(wave * NTW + k, NT - 1)) * 4 + a) * 64];
+                    cr[k][I][a] = src[((min(I, Il) * NT + min(wave * NTW + k, NT - 1)) * 4 + a) * 64];
     };
-    auto load_b = [&](int c, float4 (&br)[NTW][8]) __attribute__((always_inline)) {
-        const float4 *src = reinterpret_cast<const float4 *>(bop) + (bg0 + (int64_t)c * s.G) * (NT * 8 * 64) + lane;
+    auto load_b = [&](int c, float4 (&br)[NTW][QT]) __attribute__((always_inline)) {
+        const float4 *src = reinterpret_cast<const float4 *>(bop) + (bg0 + (int64_t)c * s.G) * (NT * ops.QN * 64) + lane;
+        const int ql = last_token(c) >> 3;
 #pragma unroll
         for (int k = 0; k < NTW; ++k)
 #pragma unroll
-            for (int q = 0; q < 8; ++q) br[k][q] = src[(min(wave * NTW + k, NT - 1) * 8 + q) * 64];
+            for (int q = 0; q < QT; ++q) br[k][q] = src[(min(wave * NTW + k, NT - 1) * ops.QN + min(q, ql)) * 64];
     };
     auto load_g = [&](int c) __attribute__((always_inline)) {
-        const float4 *src = reinterpret_cast<const float4 *>(gop) + (bg0 + (int64_t)c * s.G) * (CF_GBLK * 64) + lane;
+        const float4 *src = reinterpret_cast<const float4 *>(gop) + (bg0 + (int64_t)c * s.G) * (ops.GB * 64) + lane;
+        const int ql = last_token(c) >> 3;
+        gr[0] = src[min(wave, ql) * 64];
 #pragma unroll
-        for (int t = 0; t < 3; ++t) gr[t] = src[(t > 0 ? 3 + 2 * wave + t : wave) * 64];
+        for (int t = 1; t < (ROWT == 2 ? 3 : 1); ++t) gr[t] = src[(ql > 3 ? 4 + min(2 * wave + t - 1, ql) : 0) * 64];
     };
     // x^T tile and tables of step c (in the registers) into buffer buf
     auto stage = [&](int c, int buf) __attribute__((always_inline)) {
@@ -386,7 +426,7 @@ chain_f32_kernel(const T *__restrict__ x, const T *__restrict__ dt, const float 
 
     float atot = 0.f;
     float odd = 0.f;                                     // NaN once zero times anything not finite has been added
-    auto step = [&](int c, float4 (&br)[NTW][8], float4 (&brn)[NTW][8], auto one_by_one) __attribute__((always_inline)) {
+    auto step = [&](int c, float4 (&br)[NTW][QT], float4 (&brn)[NTW][QT], auto one_by_one) __attribute__((always_inline)) {
         const int buf = (c - c_begin) & 1;
         const int cn = min(c + 1, c_end - 1);
         float xc[8];
@@ -402,32 +442,32 @@ chain_f32_kernel(const T *__restrict__ x, const T *__restrict__ dt, const float 
         if (!OUT) load_b(cn, brn);
         const float *sx = s_x[buf] + l32 * CF_XS + 4 * kg;
         const float cs_last = s_cs[buf][CF_STEP - 1];
-        f32x16_t yt[2];                                  // Y^T: rows are channels, so a lane holds four of one token
+        f32x16_t yt[ROWT];                               // Y^T: rows are channels, so a lane holds four of one token
         if (OUT) {
 #pragma unroll
-            for (int v = 0; v < 16; ++v) yt[0][v] = yt[1][v] = 0.f;
-            const float ci[2] = {s_cs[buf][l32], s_cs[buf][32 + l32]};
+            for (int v = 0; v < 16; ++v) yt[0][v] = yt[ROWT - 1][v] = 0.f;
+            const float ci[2] = {s_cs[buf][l32], s_cs[buf][32 * (ROWT - 1) + l32]};
             const float ei[2] = {fast_exp2(ci[0]), fast_exp2(ci[1])};
 #pragma unroll
             for (int k = 0; k < NTW; ++k)
                 if (wave * NTW + k < NT) {               // wave-uniform
 #pragma unroll
                     for (int a = 0; a < 4; ++a) {
-                        const float4 u0 = cr[k][0][a], u1 = cr[k][1][a];
+                        const float4 u0 = cr[k][0][a], u1 = cr[k][ROWT - 1][a];
                         yt[0] = mfma_f32(st[k][4 * a + 0], u0.x * ei[0], yt[0]);
-                        yt[1] = mfma_f32(st[k][4 * a + 0], u1.x * ei[1], yt[1]);
+                        if (ROWT == 2) yt[ROWT - 1] = mfma_f32(st[k][4 * a + 0], u1.x * ei[1], yt[ROWT - 1]);
                         yt[0] = mfma_f32(st[k][4 * a + 1], u0.y * ei[0], yt[0]);
-                        yt[1] = mfma_f32(st[k][4 * a + 1], u1.y * ei[1], yt[1]);
+                        if (ROWT == 2) yt[ROWT - 1] = mfma_f32(st[k][4 * a + 1], u1.y * ei[1], yt[ROWT - 1]);
                         yt[0] = mfma_f32(st[k][4 * a + 2], u0.z * ei[0], yt[0]);
-                        yt[1] = mfma_f32(st[k][4 * a + 2], u1.z * ei[1], yt[1]);
+                        if (ROWT == 2) yt[ROWT - 1] = mfma_f32(st[k][4 * a + 2], u1.z * ei[1], yt[ROWT - 1]);
                         yt[0] = mfma_f32(st[k][4 * a + 3], u0.w * ei[0], yt[0]);
-                        yt[1] = mfma_f32(st[k][4 * a + 3], u1.w * ei[1], yt[1]);
+                        if (ROWT == 2) yt[ROWT - 1] = mfma_f32(st[k][4 * a + 3], u1.w * ei[1], yt[ROWT - 1]);
                     }
                 }
             load_c(cn);
             // the wave's 8-token blocks of M: one of tile row 0 and two of tile row 1, the same code in every wave
 #pragma unroll
-            for (int t = 0; t < 3; ++t) {
+            for (int t = 0; t < (ROWT == 2 ? 3 : 1); ++t) {
                 const int I = t > 0, q = t > 0 ? 2 * wave + t - 1 : wave;
                 if constexpr (decltype(one_by_one)::value) {
 #pragma unroll 1
@@ -473,7 +513,7 @@ chain_f32_kernel(const T *__restrict__ x, const T *__restrict__ dt, const float 
             for (int k = 0; k < NTW; ++k) {
                 if (wave * NTW + k >= NT) continue;      // wave-uniform; outside the token loop, whose LDS reads overlap
 #pragma unroll
-                for (int q = 0; q < 8; ++q) {
+                for (int q = 0; q < QT; ++q) {
                     const float4 cj = *reinterpret_cast<const float4 *>(&s_c[buf][8 * q + 4 * kg]);
                     const float4 xv = *reinterpret_cast<const float4 *>(sx + 8 * q);
                     st[k] = mfma_f32(br[k][q].x, xv.x * cj.x, st[k]);
@@ -488,7 +528,7 @@ chain_f32_kernel(const T *__restrict__ x, const T *__restrict__ dt, const float 
             // the partial tiles of the four waves meet in LDS (those of the previous step were added up in front
             // of the barrier at the top)
 #pragma unroll
-            for (int I = 0; I < 2; ++I)
+            for (int I = 0; I < ROWT; ++I)
 #pragma unroll
                 for (int a = 0; a < 4; ++a)
                     *reinterpret_cast<float4 *>(&s_y[wave][(32 * I + l32) * CF_YS + 8 * a + 4 * kg]) =
@@ -598,13 +638,15 @@ int chain_f32_segments(int64_t B, int64_t L, int64_t H, int64_t P)
     return nseg;
 }
 
-void chain_f32_sizes(const swimba_dims *d, size_t *ops, size_t *g, size_t *seg, size_t *dec, size_t *init)
+void chain_f32_sizes(const swimba_dims *d, size_t *cop, size_t *bop, size_t *g, size_t *seg, size_t *dec, size_t *init)
 {
     const size_t nc = ((size_t)d->seqlen + CF_STEP - 1) / CF_STEP, NT = ((size_t)d->dstate + 31) / 32;
     const size_t items = (size_t)d->batch * nc * d->ngroups;
     const size_t nseg = chain_f32_segments(d->batch, d->seqlen, d->nheads, d->headdim);
-    *ops = items * CF_STEP * NT * 32 * sizeof(float);
-    *g = items * CF_GBLK * 64 * 16;
+    const ChainOps o = chain_ops(d->seqlen);
+    *cop = items * o.IT * NT * 4 * 64 * 16;
+    *bop = items * o.QN * NT * 64 * 16;
+    *g = items * o.GB * 64 * 16;
     *dec = (size_t)d->batch * (nseg - 1) * d->nheads * sizeof(float);
     *seg = (size_t)d->batch * (nseg - 1) * d->nheads * ((d->headdim + 31) / 32) * NT * 1024 * sizeof(float);
     *init = nseg > 1 ? (size_t)d->batch * d->nheads * d->headdim * d->dstate * sizeof(float) : 0;
@@ -622,13 +664,15 @@ static void launch_chain_t(const Shape &s, const void *x, const void *dt, const 
         // segment of a sequence can end before another one has started.
         float *copy = h0 && h0 == h_final ? hinit : nullptr;
         const int total = s.B * (used - 1) * s.H * nslice, nblocks = xcd_padded(total);
-        hipLaunchKernelGGL((chain_f32_kernel<T, NTW, false>), dim3(nblocks), dim3(256), 0, st, (const T *)x, (const T *)dt,
+        hipLaunchKernelGGL((chain_f32_kernel<T, NTW, false, 2>), dim3(nblocks), dim3(256), 0, st, (const T *)x, (const T *)dt,
                            A, D, cop, bop, gop, h0, copy, hseg, aseg, (T *)y, s, NT, nslice, used - 1, used, sps, total, nblocks);
         if (copy) h0 = copy;
     }
     const int total = s.B * used * s.H * nslice, nblocks = xcd_padded(total);
-    hipLaunchKernelGGL((chain_f32_kernel<T, NTW, true>), dim3(nblocks), dim3(256), 0, st, (const T *)x, (const T *)dt, A,
-                       D, cop, bop, gop, h0, h_final, hseg, aseg, (T *)y, s, NT, nslice, used, used, sps, total, nblocks);
+    // at most 32 tokens: one tile row, 36 MFMAs for 76 and three workgroups per compute unit
+    auto out = s.L > 32 ? chain_f32_kernel<T, NTW, true, 2> : chain_f32_kernel<T, NTW, true, 1>;
+    hipLaunchKernelGGL(out, dim3(nblocks), dim3(256), 0, st, (const T *)x, (const T *)dt, A, D, cop, bop, gop, h0, h_final,
+                       hseg, aseg, (T *)y, s, NT, nslice, used, used, sps, total, nblocks);
 }
 
 template <typename T>
@@ -638,7 +682,8 @@ static swimba_status launch_f32_t(const Shape &s, const void *x, const void *dt,
                                   float *bop, float *gop, float *hseg, float *aseg, float *hinit, int nseg, hipStream_t st)
 {
     const int NT = (s.N + 31) / 32;
-    const size_t shm = (size_t)CF_STEP * s.K * 8 + (size_t)2 * CF_STEP * (32 * NT + 4) * sizeof(float);
+    const size_t rows = (size_t)2 * CF_STEP * (32 * NT + 4), row_logits = w_sel ? 0 : (size_t)CF_STEP * (s.E | 1);
+    const size_t shm = (size_t)CF_STEP * s.K * 8 + (rows > row_logits ? rows : row_logits) * sizeof(float);
     // more than 64 KB of dynamic LDS has to be allowed once per device
     static std::atomic<uint64_t> attr_set{0};            // one bit per device ordinal
     int dev = 0;
@@ -655,12 +700,18 @@ static swimba_status launch_f32_t(const Shape &s, const void *x, const void *dt,
     }
     const int64_t items = (int64_t)s.B * s.nc * s.G;
     // Up to a quarter as many steps as compute units (64 here) four workgroups share one, each on a unit of its own.
-    if (items <= device_cus() / 4)
+    const int ncu = device_cus();
+    if (items <= ncu / 4)
         hipLaunchKernelGGL((mix_ops_kernel<T, 4>), dim3((unsigned)items * 4), dim3(CF_MIX_THREADS), shm, st, (const T *)Be,
-                           (const T *)Ce, (const T *)logits, idx, w, w_sel, cop, bop, gop, s, NT);
-    else
-        hipLaunchKernelGGL((mix_ops_kernel<T, 1>), dim3((unsigned)items), dim3(CF_MIX_THREADS), shm, st, (const T *)Be,
-                           (const T *)Ce, (const T *)logits, idx, w, w_sel, cop, bop, gop, s, NT);
+                           (const T *)Ce, (const T *)logits, idx, w, w_sel, cop, bop, gop, s, NT, 1);
+    else {
+        // groups share a workgroup and its routing as long as four workgroups per compute unit remain
+        int gpb = 1;
+        for (int n = 2; n <= s.G; ++n)
+            if (s.G % n == 0 && items / n >= 4 * ncu) gpb = n;
+        hipLaunchKernelGGL((mix_ops_kernel<T, 1>), dim3((unsigned)(items / gpb)), dim3(CF_MIX_THREADS), shm, st, (const T *)Be,
+                           (const T *)Ce, (const T *)logits, idx, w, w_sel, cop, bop, gop, s, NT, gpb);
+    }
     SWIMBA_CHECK_LAUNCH();
     if (NT <= 4)
         launch_chain_t<T, 1>(s, x, dt, A, D, cop, bop, gop, h0, h_final, hseg, aseg, hinit, y, NT, nseg, st);

@@ -117,13 +117,13 @@ def test_a_state_in_place_gives_the_same_bits(cfg):
     assert torch.equal(over.y, apart.y) and torch.equal(state, apart.h_final)
 
 
-@pytest.mark.parametrize("j", [5, 31, 32, 63, 64, 80, 330])
+@pytest.mark.parametrize("L,j", [(600, 5), (600, 31), (600, 32), (600, 63), (600, 64), (600, 80), (600, 330), (20, 5)])
 @pytest.mark.parametrize("which", ["x_inf", "x_nan", "dt_inf", "dt_nan", "B_nan", "C_inf"])
-def test_values_that_are_not_finite_stay_causal(which, j):
+def test_values_that_are_not_finite_stay_causal(which, L, j):
     """Uninitialised padding behind a sequence, say: tokens in front of it, other channels (x), other heads (dt)
     and other sequences keep their values; its own token does not hide it."""
-    cfg = (2, 600, 4, 40, 48, 1, 8, 2, "f32")                       # two segments of five steps
-    B, L, H, P = cfg[:4]
+    cfg = (2, L, 4, 40, 48, 1, 8, 2, "f32")                         # 600 tokens: two segments of five steps
+    B, _, H, P = cfg[:4]
     p, h0 = inputs(*cfg)
     d = to_device(p, "f32")
     names = ("x", "dt", "A", "D", "B_experts", "C_experts", "router_logits")
@@ -146,3 +146,35 @@ def test_values_that_are_not_finite_stay_causal(which, j):
     kept = ~hit
     assert torch.isfinite(out.y[kept]).all()
     assert rel(host(out.y[kept]), host(clean.y[kept])) <= 1e-6     # the sums are taken in another order
+
+
+@pytest.mark.parametrize("cfg", [
+    # B, L, H, P, N, G, E, k, io: steps that are not full, one and two tile rows, with and without other steps
+    (3, 1, 4, 8, 16, 2, 17, 2, "f32"),
+    (2, 7, 3, 33, 130, 3, 16, 2, "bf16"),
+    (2, 8, 2, 64, 128, 1, 256, 3, "f32"),
+    (70, 9, 2, 8, 8, 1, 5, 2, "f32"),          # more steps than four workgroups share
+    (2, 16, 2, 20, 32, 1, 8, 2, "f32"),
+    (70, 17, 4, 4, 40, 4, 40, 2, "f32"),
+    (2, 31, 2, 16, 16, 1, 8, 2, "f32"),
+    (70, 32, 2, 16, 60, 2, 8, 2, "bf16"),
+    (2, 33, 2, 32, 32, 1, 8, 2, "f32"),
+    (70, 49, 2, 8, 16, 1, 33, 2, "f32"),
+    (2, 145, 2, 40, 48, 1, 8, 2, "f32"),
+    (600, 5, 4, 4, 8, 4, 17, 2, "f32"),        # two groups share a workgroup
+    (160, 100, 8, 2, 4, 8, 8, 2, "f32"),
+    (1, 60, 2, 4, 4, 1, 256, 8, "f32"),        # logits that need more LDS than the rows
+], ids=lambda c: "B%dL%dH%dP%dN%dG%dE%dk%d%s" % c)
+def test_steps_that_are_not_full(cfg):
+    """From a workspace of NaN: the chain reads nothing that was not written for it, and sums nothing that is not finite."""
+    k, io = cfg[7], cfg[8]
+    p, h0 = inputs(*cfg)
+    d = to_device(p, io)
+    args = [d[q] for q in ("x", "dt", "A", "D", "B_experts", "C_experts", "router_logits")]
+    ws = sw.alloc_workspace(sw.dims_of(d["x"], d["B_experts"], k, 64), "cuda:0")
+    ws.fill_(255)
+    out = sw.swimba_mixer_fwd(*args, k, 64, torch.from_numpy(h0).cuda(), workspace=ws, want_topk=True)
+    torch.cuda.synchronize()
+    check(out.y, out.h_final, p, k, h0, io)
+    ref = orc.mixer_fwd(p["x"], p["dt"], p["A"], p["D"], p["B_experts"], p["C_experts"], p["router_logits"], k, h0=h0)
+    np.testing.assert_array_equal(out.topk_idx.cpu().numpy(), ref["topk_idx"])
