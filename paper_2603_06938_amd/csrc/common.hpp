@@ -87,7 +87,7 @@ swimba_status launch_mix_rows_mfma(const Shape &s, const void *Be, const void *C
                                    int32_t *idx, float *w, void *cmix, void *bfrag, void *bmix_t8,
                                    int sep_e, int slot, const float *w_sel, hipStream_t st);
 // fp32 arithmetic on the f32 matrix pipe, any (P, N) (chain_f32.hip)
-constexpr int CHAIN_F32_MAX_SEGMENTS = 8;
+constexpr int CHAIN_F32_MAX_SEGMENTS = 64;
 // bytes of its scratch arrays
 void chain_f32_sizes(const swimba_dims *d, size_t *cop, size_t *bop, size_t *g, size_t *seg, size_t *dec, size_t *init);
 swimba_status launch_chain_f32(const Shape &s, int io_dtype, const void *x, const void *dt, const float *A,

@@ -1,4 +1,4 @@
-"""The fp32 chain at its edges: lengths around its steps of 64 tokens, one to eight segments with a short and an
+"""The fp32 chain at its edges: lengths around its steps of 64 tokens, one to 64 segments with a short and an
 empty last one, head and state sizes around its tiles of 32, one and two state tiles per wave, 16 and 17
 experts, bf16 io at sizes outside the bf16 kernels, and the final state written over the initial one;
 against the oracle in double.
@@ -52,6 +52,8 @@ def check(y, hf, p, k, h0, io):
     (1, 577, 4, 32, 256, 2, 8, 2, "f32"),      # ten steps in two segments
     (1, 1100, 2, 64, 64, 1, 5, 5, "f32"),      # 18 steps in four segments, the last one short
     (1, 2100, 2, 16, 48, 1, 8, 2, "f32"),      # 33 steps in eight: five each, the last one empty
+    (1, 16623, 1, 16, 16, 1, 8, 2, "f32"),     # 260 steps in 64: five each, the last twelve empty
+    (2, 8200, 2, 33, 20, 1, 4, 2, "f32"),      # 129 steps in 32, a slice of one channel
     (2, 2050, 48, 8, 12, 2, 4, 2, "f32"),      # 96 chains in eight segments, more steps than mix in four parts
     (1, 600, 2, 24, 80, 1, 8, 2, "f32"),
     (1, 600, 2, 128, 60, 1, 8, 2, "bf16"),     # outside the bf16 kernels
