@@ -75,7 +75,8 @@ typedef struct {
 } swimba_dims;
 
 /* Byte offsets of the scratch arrays inside the workspace (for tests and
- * profiling of single stages; a plain caller only needs `total`). */
+ * profiling of single stages; a plain caller only needs `total`).  The fp32 forwards keep scratch of
+ * their own from `cs` on; only topk_idx and topk_w can be read after them. */
 typedef struct {
     size_t topk_idx;  /* (B,L,k) int32 : active experts, router order              */
     size_t topk_w;    /* (B,L,k) fp32  : their un-renormalised softmax weights      */

@@ -60,7 +60,8 @@ static swimba_status check_mixer(const swimba_dims *d)
     return SWIMBA_OK;
 }
 
-// Scratch of the fp32 chain behind the stage arrays (offsets from the workspace's start)
+// Scratch of the fp32 chain (offsets from the workspace's start).  It lies over cs and states: the forwards that run the
+// chain use neither, and the stage calls and the forwards by expert, which do, run no chain.
 struct ChainF32Layout {
     size_t cop, bop, gop, hseg, aseg, hinit;
 };
@@ -101,7 +102,9 @@ static void layout_of(const swimba_dims *d, swimba_ws_layout *o, ChainF32Layout 
     if (!mf) {
         size_t cop, bop, g, seg, dec, init;
         chain_f32_sizes(d, &cop, &bop, &g, &seg, &dec, &init);
+        const size_t stages = off;
         ChainF32Layout l;
+        off = o->cs;
         l.cop = off;  off = align_up(off + cop, 256);
         l.bop = off;  off = align_up(off + bop, 256);
         l.gop = off;  off = align_up(off + g, 256);
@@ -109,6 +112,7 @@ static void layout_of(const swimba_dims *d, swimba_ws_layout *o, ChainF32Layout 
         l.aseg = off; off = align_up(off + dec, 256);
         l.hinit = off; off = align_up(off + init, 256);
         if (cf) *cf = l;
+        if (off < stages) off = stages;
     }
     o->total = off > 0 ? off : 256;
 }

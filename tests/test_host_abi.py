@@ -54,6 +54,18 @@ def test_workspace_query_and_layout():
     assert lm.total - lm.cb >= 2 * 36 * 2048
 
 
+@pytest.mark.parametrize("kw,most", [
+    # cs and states are larger than the fp32 forward's own arrays, which lie over them
+    (dict(batch=8, seqlen=2048, nheads=24, headdim=64, dstate=128), 0),
+    # a sequence of 16 tokens: two of eight blocks of B rows, one of two tile rows of C and two of twelve blocks of G
+    (dict(batch=1024, seqlen=16, nheads=8, ngroups=8, chunk=16), 1024 * 8 * 8192),
+    (dict(batch=200, seqlen=2, nheads=8, headdim=1, dstate=8, ngroups=4, chunk=16), 200 * 4 * 6144),
+], ids=["states", "16 tokens", "2 tokens"])
+def test_fp32_workspace_is_shared_and_no_larger_than_its_tokens_need(kw, most):
+    lo = sw.swimba_mixer_workspace_layout(dims(**kw))
+    assert lo.total <= max(lo.states_lp, lo.cs + most + 6 * 256)
+
+
 @pytest.mark.parametrize("kw,status", [
     (dict(io_dtype=7), 3),
     (dict(nheads=0), 2), (dict(top_k=0), 2), (dict(top_k=5), 2), (dict(ngroups=3), 2),
