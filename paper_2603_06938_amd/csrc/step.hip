@@ -167,22 +167,22 @@ struct StepRows {
             if (p0 + p < P) __builtin_nontemporal_store(v[r], reinterpret_cast<f32x4_t *>(state + (uint32_t)(p * N + n4)));
         }
     }
-    // one token: mixed rows b and c (N), inputs xr of the slice's rows; y: the token's output of this lane's row
-    template <typename T>
-    __device__ __forceinline__ void token(const float *b, const float *c, const float *xr, float dtv, float decay, float dsk, T *y)
+    // one token: mixed rows b and c (N), x(row): inputs of the slice's rows; y: the token's output of this lane's row
+    template <typename T, typename X>
+    __device__ __forceinline__ void token(const float *b, const float *c, X x, float dtv, float decay, float dsk, T *y)
     {
         const f32x4_t bm = *reinterpret_cast<const f32x4_t *>(b + n4);
         const f32x4_t cm = *reinterpret_cast<const f32x4_t *>(c + n4);
         float part[R];
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            const float u = dtv * xr[r * STRIDE + r0];
+            const float u = dtv * x(r * STRIDE + r0);
 #pragma unroll
             for (int q = 0; q < 4; ++q) v[r][q] = fmaf(u, bm[q], decay * v[r][q]);   // in place: no register moves
             part[r] = (v[r][0] * cm[0] + v[r][1] * cm[1]) + (v[r][2] * cm[2] + v[r][3] * cm[3]);
         }
         const float tot = group_sums<LPR / 2>(part, lane);
-        if (mine) *y = from_float<T>(tot + dsk * xr[myrow]);
+        if (mine) *y = from_float<T>(tot + dsk * x(myrow));
     }
 };
 
@@ -252,7 +252,7 @@ step_fused_kernel(const float *state_in, float *state_out, const T *__restrict__
     T *yr = y + (tok * s.H + h) * P + p0 + rows.myrow;
 #pragma unroll 1
     for (int t = 0; t < L; ++t)
-        rows.token(s_b + t * N, s_c + t * N, s_x + t * ROWS, s_dt[t], s_a[t], dsk, yr + (int64_t)t * s.H * P);
+        rows.token(s_b + t * N, s_c + t * N, [=](int p) { return s_x[t * ROWS + p]; }, s_dt[t], s_a[t], dsk, yr + (int64_t)t * s.H * P);
     rows.store(state_out + base);
 }
 
@@ -325,10 +325,34 @@ step_mixed_kernel(const float *state_in, float *state_out, const T *__restrict__
         const int n = min(TG, L - t0);
 #pragma unroll 1
         for (int t = 0; t < n; ++t)
-            rows.token(s_bc + t * 2 * N, s_bc + t * 2 * N + N, s_x + t * ROWS, s_dt[t], s_a[t], dsk,
+            rows.token(s_bc + t * 2 * N, s_bc + t * 2 * N + N, [&](int p) { return s_x[t * ROWS + p]; }, s_dt[t], s_a[t], dsk,
                        yr + (int64_t)(t0 + t) * s.H * P);
         lds_barrier();
     }
+    rows.store(state_out + base);
+}
+
+// One token whose rows come mixed: nothing to keep in LDS.
+template <typename T, int N, int R>
+__global__ void __launch_bounds__(STEP_THREADS, 8)
+step_mixed_one_kernel(const float *state_in, float *state_out, const T *__restrict__ x, const T *__restrict__ dt,
+                      const float *__restrict__ A, const float *__restrict__ D, const float *__restrict__ bc,
+                      T *__restrict__ y, Shape s, int slices)
+{
+    const int P = s.P;
+    const int sl = blockIdx.x % slices;
+    const int h = (blockIdx.x / slices) % s.H;
+    const int b = blockIdx.x / (slices * s.H);
+    const int g = (h * s.G) / s.H;
+    const int p0 = sl * StepRows<N, R>::ROWS;
+    const int64_t bh = (int64_t)b * s.H + h, base = (bh * P + p0) * N;
+    const float dtv = to_float(dt[bh]), decay = expf(dtv * A[h]), dsk = D ? D[h] : 0.f;
+    const float *row = bc + ((int64_t)b * s.G + g) * 2 * N;
+    const T *xr = x + bh * P + p0;
+    const int last = P - 1 - p0;
+    StepRows<N, R> rows(threadIdx.x, p0, P);
+    rows.load(state_in + base);
+    rows.token(row, row + N, [=](int p) { return to_float(xr[min(p, last)]); }, dtv, decay, dsk, y + bh * P + p0 + rows.myrow);
     rows.store(state_out + base);
 }
 
@@ -375,7 +399,8 @@ static void launch_rows(const Shape &s, const float *state_in, float *state_out,
     const int slices = (s.P + ROWS - 1) / ROWS;
     const dim3 grid((unsigned)(s.B * s.H * slices));
     if (bc) {
-        auto kernel = s.L > 4 ? step_mixed_kernel<T, N, R, 16> : step_mixed_kernel<T, N, (R > 4 ? 4 : R), 4>;   // R <= 4 there
+        constexpr int R4 = R > 4 ? 4 : R;                    // at most, up to four tokens (launch_update)
+        auto kernel = s.L > 4 ? step_mixed_kernel<T, N, R, 16> : s.L > 1 ? step_mixed_kernel<T, N, R4, 4> : step_mixed_one_kernel<T, N, R4>;
         hipLaunchKernelGGL(kernel, grid, dim3(STEP_THREADS), 0, st, state_in, state_out, (const T *)x, (const T *)dt, A, D,
                            bc, (T *)y, s, slices);
         return;
