@@ -623,15 +623,20 @@ chain_f32_kernel(const T *__restrict__ x, const T *__restrict__ dt, const float 
 
 // Segments a sequence is walked in.  A chain keeps a quarter of a compute unit's two resident workgroups busy
 // for its whole segment, so short of about 1.5 workgroups per compute unit the chip idles; the extra
-// launch (state part of all segments but the last, 2/5 of the work) pays from four steps per segment on.  Up to 64
-// segments: 16384 tokens of one head, P = N = 16, 206 us in 8, 115 in 16, 72 in 32, 56 in 64; of eight heads,
+// launch (state part of all segments but the last, 2/5 of the work) pays from four steps per segment on.  Short of 192
+// chains most of the chip idles either way and the serial steps are all there is: two steps per segment, from six
+// steps on (four heads, P = N = 16, 700 tokens: one segment 53.4 us, four 30.5; 1024 tokens, eight heads, P = 64,
+// N = 128: four 47.1, eight 37.5; three to five steps: 28.3 -> 31.5, 32.4 -> 32.9, 36.1 -> 38.6 with 96 chains).
+// Up to 64 segments: 16384 tokens of one head, P = N = 16, 206 us in 8, 115 in 16, 72 in 32, 56 in 64; of eight heads,
 // P = 64, N = 128, 239, 138 and 126 in 8, 16 and 32 (512 chains).
 int chain_f32_segments(int64_t B, int64_t L, int64_t H, int64_t P)
 {
     const int64_t steps = (L + CF_STEP - 1) / CF_STEP, chains = B * H * ((P + 31) / 32);
     if (chains == 0) return 1;
     int nseg = 1;
-    while (nseg < CHAIN_F32_MAX_SEGMENTS && chains * nseg < 384 && steps >= 8 * (int64_t)nseg) nseg *= 2;
+    while (nseg < CHAIN_F32_MAX_SEGMENTS && ((chains * nseg < 192 && steps > 5 && steps > 2 * (int64_t)nseg) ||
+                                             (chains * nseg < 384 && steps >= 8 * (int64_t)nseg)))
+        nseg *= 2;
     // Some compute units then hold one chain more than others and set the time: twice as many chains of half the
     // length where that takes a fifth off the fullest unit (96 chains of 32 steps: 4 segments 113 us, 8 102;
     // 128 chains, where it takes nothing off: 113 and 125).

@@ -49,9 +49,9 @@ def check(y, hf, p, k, h0, io):
     (1, 65, 3, 33, 126, 3, 17, 2, "f32"),
     (1, 511, 2, 64, 128, 1, 8, 2, "f32"),
     (1, 513, 2, 40, 129, 1, 8, 2, "f32"),      # two state tiles per wave
-    (1, 577, 4, 32, 256, 2, 8, 2, "f32"),      # ten steps in two segments
-    (1, 1100, 2, 64, 64, 1, 5, 5, "f32"),      # 18 steps in four segments, the last one short
-    (1, 2100, 2, 16, 48, 1, 8, 2, "f32"),      # 33 steps in eight: five each, the last one empty
+    (1, 577, 4, 32, 256, 2, 8, 2, "f32"),      # ten steps in five segments
+    (1, 1100, 2, 64, 64, 1, 5, 5, "f32"),      # 18 steps in nine segments
+    (1, 2100, 2, 16, 48, 1, 8, 2, "f32"),      # 33 steps in 32: two each, the last fifteen empty, one short
     (1, 16623, 1, 16, 16, 1, 8, 2, "f32"),     # 260 steps in 64: five each, the last twelve empty
     (2, 8200, 2, 33, 20, 1, 4, 2, "f32"),      # 129 steps in 32, a slice of one channel
     (2, 2050, 48, 8, 12, 2, 4, 2, "f32"),      # 96 chains in eight segments, more steps than mix in four parts
@@ -99,7 +99,7 @@ def test_final_state_over_the_initial_one():
 
 
 @pytest.mark.parametrize("cfg", [
-    (1, 2100, 2, 16, 48, 1, 8, 2, "f32"),      # five steps a segment, the eighth empty
+    (1, 2100, 2, 16, 48, 1, 8, 2, "f32"),      # two steps a segment, nearly half of them empty
     (2, 700, 4, 64, 128, 1, 8, 2, "f32"),
     (1, 577, 4, 33, 240, 2, 8, 2, "f32"),      # a slice of one channel, two state tiles per wave
     (1, 1100, 1, 24, 18, 1, 8, 2, "bf16"),
@@ -124,7 +124,7 @@ def test_a_state_in_place_gives_the_same_bits(cfg):
 def test_values_that_are_not_finite_stay_causal(which, L, j):
     """Uninitialised padding behind a sequence, say: tokens in front of it, other channels (x), other heads (dt)
     and other sequences keep their values; its own token does not hide it."""
-    cfg = (2, L, 4, 40, 48, 1, 8, 2, "f32")                         # 600 tokens: two segments of five steps
+    cfg = (2, L, 4, 40, 48, 1, 8, 2, "f32")                         # 600 tokens: five segments of two steps
     B, _, H, P = cfg[:4]
     p, h0 = inputs(*cfg)
     d = to_device(p, "f32")
