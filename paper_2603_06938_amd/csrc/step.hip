@@ -21,38 +21,6 @@ static __device__ __align__(256) float scratch[SWIMBA_STATIC_SCRATCH_BYTES / siz
 constexpr int STEP_THREADS = 256;
 typedef float __attribute__((ext_vector_type(4))) f32x4_t;
 
-// ---- routing + mixing: block = (b, g), mixed (B; C) rows of N fp32 each ------------------
-template <typename T>
-__global__ void __launch_bounds__(128)
-step_mix_kernel(const T *__restrict__ Be, const T *__restrict__ Ce, const T *__restrict__ logits,
-                float *__restrict__ bc, int32_t *__restrict__ idx_out, Shape s)
-{
-    __shared__ float s_w[SWIMBA_MAX_TOPK];
-    __shared__ int32_t s_idx[SWIMBA_MAX_TOPK];
-    const int b = blockIdx.x / s.G, g = blockIdx.x % s.G;
-    const int tid = threadIdx.x;
-    // the logits go through LDS first: one memory latency instead of one per pass of the router
-    __shared__ float s_log[SWIMBA_MAX_EXPERTS];
-    for (int e = tid; e < s.E; e += 128) s_log[e] = to_float(logits[(int64_t)b * s.E + e]);
-    __syncthreads();
-    if (tid == 0) route_token([&](int e) { return s_log[e]; }, s.E, s.K, s_idx, s_w);
-    __syncthreads();
-    if (idx_out && g == 0 && tid < s.K) idx_out[(int64_t)b * s.K + tid] = s_idx[tid];
-    const T *Bb = Be + ((int64_t)b * s.E * s.G + g) * s.N;
-    const T *Cb = Ce + ((int64_t)b * s.E * s.G + g) * s.N;
-    float *out = bc + (int64_t)blockIdx.x * 2 * s.N;
-    for (int n = tid; n < s.N; n += 128) {
-        float bm = 0.f, cm = 0.f;
-        for (int r = 0; r < s.K; ++r) {
-            const int64_t o = (int64_t)s_idx[r] * s.G * s.N + n;
-            bm += s_w[r] * to_float(Bb[o]);
-            cm += s_w[r] * to_float(Cb[o]);
-        }
-        out[n] = bm;
-        out[s.N + n] = cm;
-    }
-}
-
 // ---- one launch: routing, mixing and update -----------------------------------------------
 // Exchange of a butterfly step at distance D: returns the partner's value.  The partner of lane i is i ^ D,
 // except for D = 4, where it is i ^ 7 (row_half_mirror); together with the steps at 2 and 1 that reaches
@@ -125,6 +93,68 @@ __device__ __forceinline__ void route_row16(float v, int lane, int E, int K, int
             idx[r] = best;
             w[r] = route_exp(bv - m) * invZ;
         }
+    }
+}
+
+// ---- routing + mixing of a token: bc[g] = its mixed rows (B; C) of N fp32 each -------------
+// Pieces of V columns of one row, four where N allows it, else one.  Block = (token, 128 U pieces), U per lane: one
+// fills the chip at few tokens and groups; four requested together where blocks are plenty, for the routing in front
+// of them is a chain that every block of a token repeats (64 x 32 tokens, 64 groups: 185 us for the call with one,
+// 171 with four).
+constexpr int STEP_MIX_THREADS = 128;
+template <typename T, int V, int U>
+__global__ void __launch_bounds__(STEP_MIX_THREADS)
+step_mix_kernel(const T *__restrict__ Be, const T *__restrict__ Ce, const T *__restrict__ logits,
+                float *__restrict__ bc, int32_t *__restrict__ idx_out, Shape s, int parts)
+{
+    __shared__ float s_w[SWIMBA_MAX_TOPK];
+    __shared__ int32_t s_idx[SWIMBA_MAX_TOPK];
+    __shared__ float s_log[SWIMBA_MAX_EXPERTS];
+    const int part = blockIdx.x % parts;
+    const int64_t tok = blockIdx.x / parts;
+    const int tid = threadIdx.x;
+    if (s.E <= STEP_FUSED_EXPERTS) {
+        // as in the update that routes by itself (the four rows of lanes hold the same logits)
+        if (tid < 64) {
+            const int e = tid & 15;
+            route_row16(e < s.E ? to_float(logits[tok * s.E + e]) : -INFINITY, tid, s.E, s.K, s_idx, s_w);
+        }
+    } else {
+        // the logits go through LDS first: one memory latency instead of one per pass of the router
+        for (int e = tid; e < s.E; e += STEP_MIX_THREADS) s_log[e] = to_float(logits[tok * s.E + e]);
+        __syncthreads();
+        if (tid == 0) route_token([&](int e) { return s_log[e]; }, s.E, s.K, s_idx, s_w);
+    }
+    __syncthreads();
+    if (idx_out && part == 0 && tid < s.K) idx_out[tok * s.K + tid] = s_idx[tid];
+    const int row = s.N / V, pieces = s.G * 2 * row;                          // (g, B or C, piece of the row)
+    struct alignas(sizeof(T) * V) Piece { T q[V]; };
+    const T *src[U];
+    int to[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int i = min((part * U + u) * STEP_MIX_THREADS + tid, pieces - 1);
+        const int n = i % row * V, c = i / row % 2, g = i / (2 * row);
+        src[u] = (c ? Ce : Be) + (tok * s.E * s.G + g) * s.N + n;
+        to[u] = (g * 2 + c) * s.N + n;
+    }
+    float m[U][V] = {};
+    for (int r = 0; r < s.K; ++r) {
+        const int64_t o = (int64_t)s_idx[r] * s.G * s.N;
+        Piece v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) __builtin_memcpy(&v[u], __builtin_assume_aligned(src[u] + o, sizeof v[u]), sizeof v[u]);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int q = 0; q < V; ++q) m[u][q] += s_w[r] * to_float(v[u].q[q]);
+    }
+    float *out = bc + tok * s.G * 2 * s.N;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        if ((part * U + u) * STEP_MIX_THREADS + tid >= pieces) continue;
+        if constexpr (V == 4) *reinterpret_cast<f32x4_t *>(out + to[u]) = f32x4_t{m[u][0], m[u][1], m[u][2], m[u][3]};
+        else out[to[u]] = m[u][0];
     }
 }
 
@@ -455,11 +485,14 @@ static swimba_status launch_step_multi_t(const Shape &s, const float *state_in, 
     const bool route_in_update = s.E <= STEP_FUSED_EXPERTS && s.L <= STEP_FUSED_TOKENS;
     const bool rows = (s.N & (s.N - 1)) == 0 && s.N >= 16 && s.N <= 256 && blocks * s.P < (1ll << 31);
     if (!rows || !route_in_update) {
-        Shape tok = s;             // the mix kernel sees B*L independent tokens
-        tok.B = s.B * s.L;
-        tok.L = 1;
-        hipLaunchKernelGGL(step_mix_kernel<T>, dim3((unsigned)(tok.B * s.G)), dim3(128), 0, st, (const T *)Be,
-                           (const T *)Ce, (const T *)logits, bc, idx, tok);
+        const int V = s.N % 4 == 0 ? 4 : 1, pieces = s.G * 2 * (s.N / V);
+        const int64_t tokens = (int64_t)s.B * s.L;
+        auto parts = [&](int u) { return (pieces + u * STEP_MIX_THREADS - 1) / (u * STEP_MIX_THREADS); };
+        const int U = parts(4) < parts(1) && tokens * parts(4) >= 16 * device_cus() ? 4 : 1;
+        auto mix = V == 4 ? U == 4 ? step_mix_kernel<T, 4, 4> : step_mix_kernel<T, 4, 1>
+                          : U == 4 ? step_mix_kernel<T, 1, 4> : step_mix_kernel<T, 1, 1>;
+        hipLaunchKernelGGL(mix, dim3((unsigned)(tokens * parts(U))), dim3(STEP_MIX_THREADS), 0, st, (const T *)Be,
+                           (const T *)Ce, (const T *)logits, bc, idx, s, parts(U));
         SWIMBA_CHECK_LAUNCH();
     }
     if (rows) {

@@ -34,6 +34,8 @@ pytestmark = pytest.mark.gpu
     (8, 18, 24, 64, 128, 1, 20, 2, "f32"),
     (64, 17, 16, 64, 128, 1, 4, 1, "bf16"),
     (40, 16, 16, 33, 256, 1, 18, 1, "f32"),
+    (64, 64, 8, 2, 64, 8, 2, 1, "f32"),        # four pieces of the mixed rows per lane, two of them past the end
+    (64, 64, 4, 2, 33, 4, 3, 2, "bf16"),       # the same a column at a time
 ], ids=lambda c: "B%dL%dH%dP%dN%dG%dE%dk%d%s" % c)
 def test_step_sizes_match_oracle(cfg):
     B, L, H, P, N, G, E, k, io = cfg
