@@ -72,20 +72,19 @@ __device__ __forceinline__ float4 load4(const bf16 *p)
 }
 
 // Operand arrays, per (batch, step, group), N padded to NT tiles of 32 columns.  IT, QN and GB are 2, 8 and 12, and
-// less where a whole sequence is shorter than a step (chain_ops): a sequence of 16 tokens takes 8 KB a group, not 28.
+// less for sequences of at most 32 tokens, which the chain walks by one tile row: 16 tokens take 8 KB a group, not 28.
 //   cop (IT, NT, 4, 64, 4) [I][nt][a][lane][b] = C[32 I + lane%32][32 nt + 8a + 4(lane/32) + b]
 //   bop (NT, QN, 64, 4)    [nt][q][lane][b]    = B[8q + 4(lane/32) + b][32 nt + lane%32]
 //   gop (GB, 64, 4)        [blk][lane][b]      = (j <= i) C[i] . B[j], blk < 4: i = lane%32, q = blk, else i = 32 + lane%32,
 //                          q = blk - 4; j = 8q + 4(lane/32) + b
-// Of a step that is not full only what its tokens need is written, and the chain reads nothing else: the tile rows of C
-// and of G and the blocks of eight B rows with a token in them.
+// Of a step that is not full the rows of C and G without a token are not written: they meet no other row.
 struct ChainOps {
     int IT, QN, GB;
 };
 __host__ __device__ inline ChainOps chain_ops(int L)
 {
     const int q = (L + 7) / 8;
-    return L > 32 ? ChainOps{2, q < 8 ? q : 8, CF_GBLK} : ChainOps{1, q, q};
+    return L > 32 ? ChainOps{2, 8, CF_GBLK} : ChainOps{1, q, q};
 }
 
 // PARTS = 4: four workgroups share a step, each with 16 of its tokens as rows of C and of G; it mixes the B rows
@@ -113,7 +112,8 @@ mix_ops_kernel(const T *__restrict__ Be, const T *__restrict__ Ce, const T *__re
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int valid = min(CF_STEP, s.L - c * CF_STEP);
-    if (r0 >= valid) return;
+    const bool one_row = s.L <= 32;                      // of tiles (chain_ops)
+    if (one_row && r0 >= valid) return;
     const int64_t tok0 = (int64_t)b * s.L + (int64_t)c * CF_STEP;
     const bool sel = (w_sel != nullptr);
     const ChainOps ops = chain_ops(s.L);
@@ -151,7 +151,7 @@ mix_ops_kernel(const T *__restrict__ Be, const T *__restrict__ Ce, const T *__re
     const int rowsE = sel ? K : s.E;
     const int64_t estride = (int64_t)s.G * s.N, tokstride = rowsE * estride;
     const bool vec = (s.N % 4 == 0);
-    const int rowsC = min(valid - r0, R), rowsB = min(valid, r0 + R);
+    const int rowsC = max(0, min(valid - r0, R)), rowsB = rowsC > 0 ? min(valid, r0 + R) : 0;
     const int QPR = NP / 4, units = (rowsC + rowsB) * QPR;
     for (int g = g_begin; g < g_begin + gpb; ++g) {
     // ---- mixed rows: a lane takes quads of 4 columns of one stream, QF at a time; C rows [r0, r0 + R), then the B
@@ -216,7 +216,7 @@ mix_ops_kernel(const T *__restrict__ Be, const T *__restrict__ Ce, const T *__re
         for (int t = t_begin + wave; t < t_end; t += CF_MIX_THREADS / 64) {
             // tile rows 0, 1 have columns J = 0, 1; rows 2, 3 columns 0..3
             const int I = t < 4 ? t >> 1 : 2 + ((t - 4) >> 2), J = t < 4 ? t & 1 : (t - 4) & 3;
-            if (16 * I >= valid || 16 * J >= valid) continue;
+            if (16 * I >= valid || (one_row && 16 * J >= valid)) continue;
             cf_f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
             if (J <= I) {
                 const float *br = s_B + (16 * J + l16) * RS + 4 * kq, *cr = s_C + (16 * I + l16) * RS + 4 * kq;
@@ -242,7 +242,7 @@ mix_ops_kernel(const T *__restrict__ Be, const T *__restrict__ Ce, const T *__re
         co[(((row >> 5) * NT + nt) * 4 + a) * 64 + kg * 32 + (row & 31)] =
             *reinterpret_cast<const float4 *>(s_C + row * RS + 32 * nt + 8 * a + 4 * kg);
     }
-    const int QS = (rowsC + 7) / 8;                      // blocks of eight B rows in this workgroup
+    const int QS = one_row ? (rowsC + 7) / 8 : R / 8;    // blocks of eight B rows in this workgroup
     for (int u = tid; u < NT * QS * 64; u += CF_MIX_THREADS) {
         const int ln = u & 63, q = r0 / 8 + (u >> 6) % QS, nt = (u >> 6) / QS, row = 8 * q + 4 * (ln >> 5);
         const float *src = s_B + row * RS + 32 * nt + (ln & 31);
@@ -378,24 +378,21 @@ chain_f32_kernel(const T *__restrict__ x, const T *__restrict__ dt, const float 
     // its own (brn) and is requested a whole step ahead.
     float4 cr[NTW][ROWT][4], br[NTW][QT], brn[NTW][QT], gr[ROWT == 2 ? 3 : 1];
     const int64_t bg0 = ((int64_t)b * s.nc) * s.G + g;
-    const ChainOps ops = chain_ops(s.L);
-    // Tile rows and blocks without a token are not there: the last ones that are come in their place, for results
-    // that are not stored and products with zeros of x.
-    auto last_token = [&](int c) __attribute__((always_inline)) { return min(CF_STEP, s.L - c * CF_STEP) - 1; };
+    // of one tile row only the blocks with a token are there: the last of them comes for those behind it, to meet zeros
+    const ChainOps ops = ROWT == 2 ? ChainOps{2, 8, CF_GBLK} : chain_ops(s.L);
+    const int ql = ROWT == 2 ? 7 : ops.QN - 1;
     auto load_c = [&](int c) __attribute__((always_inline)) {
         const float4 *src = reinterpret_cast<const float4 *>(cop) + (bg0 + (int64_t)c * s.G) * (ops.IT * NT * 4 * 64) + lane;
-        const int Il = last_token(c) >> 5;
 #pragma unroll
         for (int k = 0; k < NTW; ++k)
 #pragma unroll
             for (int I = 0; I < ROWT; ++I)
 #pragma unroll
                 for (int a = 0; a < 4; ++a)
-                    cr[k][I][a] = src[((min(I, Il) * NT + min(wave * NTW + k, NT - 1)) * 4 + a) * 64];
+                    cr[k][I][a] = src[((I * NT + min(wave * NTW + k, NT - 1)) * 4 + a) * 64];
     };
     auto load_b = [&](int c, float4 (&br)[NTW][QT]) __attribute__((always_inline)) {
         const float4 *src = reinterpret_cast<const float4 *>(bop) + (bg0 + (int64_t)c * s.G) * (NT * ops.QN * 64) + lane;
-        const int ql = last_token(c) >> 3;
 #pragma unroll
         for (int k = 0; k < NTW; ++k)
 #pragma unroll
@@ -403,10 +400,9 @@ chain_f32_kernel(const T *__restrict__ x, const T *__restrict__ dt, const float 
     };
     auto load_g = [&](int c) __attribute__((always_inline)) {
         const float4 *src = reinterpret_cast<const float4 *>(gop) + (bg0 + (int64_t)c * s.G) * (ops.GB * 64) + lane;
-        const int ql = last_token(c) >> 3;
-        gr[0] = src[min(wave, ql) * 64];
+        gr[0] = src[(ROWT == 2 ? wave : min(wave, ql)) * 64];
 #pragma unroll
-        for (int t = 1; t < (ROWT == 2 ? 3 : 1); ++t) gr[t] = src[(ql > 3 ? 4 + min(2 * wave + t - 1, ql) : 0) * 64];
+        for (int t = 1; t < (ROWT == 2 ? 3 : 1); ++t) gr[t] = src[(3 + 2 * wave + t) * 64];
     };
     // x^T tile and tables of step c (in the registers) into buffer buf
     auto stage = [&](int c, int buf) __attribute__((always_inline)) {
