@@ -89,9 +89,10 @@ __host__ __device__ inline ChainOps chain_ops(int L)
 
 // PARTS = 4: four workgroups share a step, each with 16 of its tokens as rows of C and of G; it mixes the B rows
 // that these meet, so B is read 2.5 times, by compute units that would have none of the steps.
-// gpb groups per workgroup: its tokens are routed once for all of them.
-template <typename T, int PARTS>
-__global__ void __launch_bounds__(CF_MIX_THREADS, PARTS == 1 ? 4 : 2)
+// gpb groups per workgroup: its tokens are routed once for all of them.  QF: quads of a lane in flight, four where two
+// workgroups share a compute unit, eight where one has it to itself.
+template <typename T, int PARTS, int QF>
+__global__ void __launch_bounds__(CF_MIX_THREADS, QF == 4 ? 4 : 2)
 mix_ops_kernel(const T *__restrict__ Be, const T *__restrict__ Ce, const T *__restrict__ logits,
                int32_t *__restrict__ idx_out, float *__restrict__ w_out, const float *__restrict__ w_sel,
                float *__restrict__ cop, float *__restrict__ bop, float *__restrict__ gop, Shape s, int NT, int gpb)
@@ -103,8 +104,6 @@ mix_ops_kernel(const T *__restrict__ Be, const T *__restrict__ Ce, const T *__re
     float *s_B = s_w + CF_STEP * K;                                          // [64][RS]
     float *s_C = s_B + CF_STEP * RS;                                         // [64][RS]
     constexpr int R = CF_STEP / PARTS;                   // rows of C and G in this workgroup
-    // quads of a lane in flight: with a step per workgroup two of these share a compute unit
-    constexpr int QF = PARTS == 1 ? 4 : 8;
     const int part = blockIdx.x % PARTS, r0 = part * R, item = blockIdx.x / PARTS, gblocks = s.G / gpb;
     const int g_begin = (item % gblocks) * gpb;
     const int c = (item / gblocks) % s.nc;
@@ -270,6 +269,7 @@ chain_f32_kernel(const T *__restrict__ x, const T *__restrict__ dt, const float 
     static_assert(OUT || ROWT == 2, "segments are of whole steps");
     __shared__ __align__(16) float s_x[2][32 * CF_XS];           // x^T of a step: [channel][token]
     __shared__ __align__(16) float s_cs[2][CF_STEP], s_dt[2][CF_STEP], s_c[2][CF_STEP];
+    __shared__ int s_odd;                                        // an x or dt is not finite
     __shared__ __align__(16) float s_y[OUT ? 4 : 1][OUT ? 32 * ROWT * CF_YS : 1];   // partial Y per wave: [token][channel]
 
     // (batch, segment, head, slice), neighbours (heads of one group) on one XCD: they read the same operands
@@ -532,6 +532,8 @@ chain_f32_kernel(const T *__restrict__ x, const T *__restrict__ dt, const float 
         }
         stage(cn, buf ^ 1);
         if (OUT) {
+            if constexpr (!decltype(one_by_one)::value)
+                if (__ballot(!(odd == 0.f))) s_odd = 1;
             lds_barrier();
             const int valid = min(CF_STEP, s.L - c * CF_STEP);
             if (xj < valid && p0 + xp < P) {
@@ -578,13 +580,17 @@ chain_f32_kernel(const T *__restrict__ x, const T *__restrict__ dt, const float 
             }
         }
     };
+    if (OUT && tid == 0) s_odd = 0;
     walk(std::false_type{});
     // A masked entry of M (j > i) times an x or dt that is not finite is NaN, in tokens that such a value must not
     // reach.  The segment is then walked again with the products of M taken one by one, only those with j <= i.  (Testing
     // inside a step instead, with a branch there or with finite stand-ins for such values, keeps the products of M from
     // overlapping with the readout: 104.4 us on the 130M-shaped layer, 102.8 this way, 101.5 with no test at all.)
     if constexpr (OUT)
-        if (__syncthreads_or(!(odd == 0.f))) walk(std::true_type{});
+        if (__builtin_amdgcn_readfirstlane(s_odd)) {
+            __syncthreads();                             // every wave has read it
+            walk(std::true_type{});
+        }
     if (!OUT) {
         float4 *dst = hseg_frag(seg);
 #pragma unroll
@@ -624,20 +630,21 @@ chain_f32_kernel(const T *__restrict__ x, const T *__restrict__ dt, const float 
 // steps on (four heads, P = N = 16, 700 tokens: one segment 53.4 us, four 30.5; 1024 tokens, eight heads, P = 64,
 // N = 128: four 47.1, eight 37.5; three to five steps: 28.3 -> 31.5, 32.4 -> 32.9, 36.1 -> 38.6 with 96 chains).
 // Up to 64 segments: 16384 tokens of one head, P = N = 16, 206 us in 8, 115 in 16, 72 in 32, 56 in 64; of eight heads,
-// P = 64, N = 128, 239, 138 and 126 in 8, 16 and 32 (512 chains).
+// P = 64, N = 128, 239 in 8, 138 in 16 (256 chains).  From 192 chains on eight at most: where a unit holds one chain
+// (N > 128) 448 take two rounds (14 x 4347 tokens, two heads, N = 256: 180 us in 8, 209 in 16).
 int chain_f32_segments(int64_t B, int64_t L, int64_t H, int64_t P)
 {
     const int64_t steps = (L + CF_STEP - 1) / CF_STEP, chains = B * H * ((P + 31) / 32);
     if (chains == 0) return 1;
     int nseg = 1;
     while (nseg < CHAIN_F32_MAX_SEGMENTS && ((chains * nseg < 192 && steps > 5 && steps > 2 * (int64_t)nseg) ||
-                                             (chains * nseg < 384 && steps >= 8 * (int64_t)nseg)))
+                                             (nseg < 8 && chains * nseg < 384 && steps >= 8 * (int64_t)nseg)))
         nseg *= 2;
     // Some compute units then hold one chain more than others and set the time: twice as many chains of half the
     // length where that takes a fifth off the fullest unit (96 chains of 32 steps: 4 segments 113 us, 8 102;
     // 128 chains, where it takes nothing off: 113 and 125).
     const int64_t cus = 256, full = (chains * nseg + cus - 1) / cus, full2 = (2 * chains * nseg + cus - 1) / cus;
-    if (nseg > 1 && nseg < CHAIN_F32_MAX_SEGMENTS && steps >= 8 * (int64_t)nseg && 10 * full2 <= 16 * full) nseg *= 2;
+    if (nseg > 1 && nseg < 8 && steps >= 8 * (int64_t)nseg && 10 * full2 <= 16 * full) nseg *= 2;
     return nseg;
 }
 
@@ -695,9 +702,11 @@ static swimba_status launch_f32_t(const Shape &s, const void *x, const void *dt,
     const uint64_t bit = 1ull << (dev & 63);
     if (!(attr_set.load(std::memory_order_acquire) & bit)) {
         constexpr size_t most = (size_t)CF_STEP * SWIMBA_MAX_TOPK * 8 + (size_t)2 * CF_STEP * (SWIMBA_MAX_DSTATE + 4) * sizeof(float);
-        e = hipFuncSetAttribute((const void *)mix_ops_kernel<T, 1>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)most);
+        e = hipFuncSetAttribute((const void *)mix_ops_kernel<T, 1, 4>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)most);
         if (e == hipSuccess)
-            e = hipFuncSetAttribute((const void *)mix_ops_kernel<T, 4>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)most);
+            e = hipFuncSetAttribute((const void *)mix_ops_kernel<T, 1, 8>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)most);
+        if (e == hipSuccess)
+            e = hipFuncSetAttribute((const void *)mix_ops_kernel<T, 4, 8>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)most);
         if (e != hipSuccess) { set_last_hip_error((int)e); return SWIMBA_ERR_HIP; }
         attr_set.fetch_or(bit, std::memory_order_release);
     }
@@ -707,7 +716,7 @@ static swimba_status launch_f32_t(const Shape &s, const void *x, const void *dt,
     // another's unit: 96 steps 157.9 for 153.2, 256 steps 282 for 255.
     const int ncu = device_cus();
     if (items <= ncu / 4)
-        hipLaunchKernelGGL((mix_ops_kernel<T, 4>), dim3((unsigned)items * 4), dim3(CF_MIX_THREADS), shm, st, (const T *)Be,
+        hipLaunchKernelGGL((mix_ops_kernel<T, 4, 8>), dim3((unsigned)items * 4), dim3(CF_MIX_THREADS), shm, st, (const T *)Be,
                            (const T *)Ce, (const T *)logits, idx, w, w_sel, cop, bop, gop, s, NT, 1);
     else {
         // Groups share a workgroup and its routing as long as two workgroups per compute unit remain, what a unit holds
@@ -715,7 +724,9 @@ static swimba_status launch_f32_t(const Shape &s, const void *x, const void *dt,
         int gpb = 1;
         for (int n = 2; n <= s.G; ++n)
             if (s.G % n == 0 && items / n >= 2 * ncu) gpb = n;
-        hipLaunchKernelGGL((mix_ops_kernel<T, 1>), dim3((unsigned)(items / gpb)), dim3(CF_MIX_THREADS), shm, st, (const T *)Be,
+        // more than half a unit's LDS (states beyond 128): no second workgroup beside it
+        auto mix = 2 * shm > 160 * 1024 ? mix_ops_kernel<T, 1, 8> : mix_ops_kernel<T, 1, 4>;
+        hipLaunchKernelGGL(mix, dim3((unsigned)(items / gpb)), dim3(CF_MIX_THREADS), shm, st, (const T *)Be,
                            (const T *)Ce, (const T *)logits, idx, w, w_sel, cop, bop, gop, s, NT, gpb);
     }
     SWIMBA_CHECK_LAUNCH();
