@@ -719,11 +719,19 @@ static swimba_status launch_f32_t(const Shape &s, const void *x, const void *dt,
         hipLaunchKernelGGL((mix_ops_kernel<T, 4, 8>), dim3((unsigned)items * 4), dim3(CF_MIX_THREADS), shm, st, (const T *)Be,
                            (const T *)Ce, (const T *)logits, idx, w, w_sel, cop, bop, gop, s, NT, 1);
     else {
-        // Groups share a workgroup and its routing as long as two workgroups per compute unit remain, what a unit holds
-        // at once (700 x 9 tokens, 4 groups, 64 experts: 82 us so, 95 with four a unit, 136 with a group each).
+        // Groups share a workgroup and its routing (about one group's time, three beyond 16 experts) where that takes
+        // time off the rounds of two workgroups per compute unit: 700 x 9 tokens, 4 groups, 64 experts, 136 us with a group
+        // each, 95 with two, 81 with four; 89 x 146 tokens, 8 groups, N = 256, where four would leave 22 workgroups for
+        // a second round, 273 with four, 246 with two.
         int gpb = 1;
-        for (int n = 2; n <= s.G; ++n)
-            if (s.G % n == 0 && items / n >= 2 * ncu) gpb = n;
+        int64_t least = 0;
+        for (int n = 1; n <= s.G; ++n) {
+            const int64_t time = (items / n + 2 * ncu - 1) / (2 * ncu) * ((s.E > 16 && !w_sel ? 3 : 1) + n);
+            if (s.G % n == 0 && (n == 1 || time < least)) {
+                gpb = n;
+                least = time;
+            }
+        }
         // more than half a unit's LDS (states beyond 128): no second workgroup beside it
         auto mix = 2 * shm > 160 * 1024 ? mix_ops_kernel<T, 1, 8> : mix_ops_kernel<T, 1, 4>;
         hipLaunchKernelGGL(mix, dim3((unsigned)(items / gpb)), dim3(CF_MIX_THREADS), shm, st, (const T *)Be,
