@@ -34,3 +34,52 @@ def test_refused_sizes_raise_their_status(k, status):
     with pytest.raises(sw.SwimbaError) as e:
         sw.swimba_mixer_fwd_proj(torch.zeros(1, 2, 8, device="cuda:0"), W, W, x, dt, A, None, lg, k, 64, want_topk=True)
     assert e.value.status == status
+
+
+def forward_args(io=torch.float32):
+    t = lambda *shape, dtype=io: torch.randn(*shape, device="cuda:0").abs().to(dtype)
+    f32 = torch.float32
+    return dict(x=t(2, 3, 4, 8), dt=t(2, 3, 4), A=-t(4, dtype=f32), D=t(4, dtype=f32), B_experts=t(2, 3, 5, 2, 8),
+                C_experts=t(2, 3, 5, 2, 8), router_logits=t(2, 3, 5), top_k=2, chunk=64, h0=t(2, 4, 8, 8, dtype=f32),
+                y=t(2, 3, 4, 8), h_final=t(2, 4, 8, 8, dtype=f32), topk_idx=torch.zeros(2, 3, 2, dtype=torch.int32, device="cuda:0"),
+                topk_w=t(2, 3, 2, dtype=f32))
+
+
+def step_args():
+    a = {k: v for k, v in forward_args().items() if k not in ("chunk", "topk_w", "h0", "h_final")}
+    return dict(a, state=torch.zeros(2, 4, 8, 8, device="cuda:0"), state_out=torch.zeros(2, 4, 8, 8, device="cuda:0"))
+
+
+CALLS = {"swimba_mixer_fwd": forward_args, "swimba_step_multi": step_args}
+
+
+@pytest.mark.parametrize("call,name", [(c, n) for c, a in (("swimba_mixer_fwd", "x dt A D B_experts C_experts router_logits h0 y "
+                                        "h_final topk_idx topk_w"), ("swimba_step_multi", "state state_out x dt A D B_experts C_experts "
+                                        "router_logits y topk_idx")) for n in a.split()])
+def test_every_argument_is_checked(call, name):
+    """A tensor of another type, shape, layout or device is named and refused."""
+    args = CALLS[call]()
+    good = args[name]
+    wide = torch.empty(good.shape + (2,), dtype=good.dtype, device=good.device)[..., 0]
+    for bad, kind in ((good.to(torch.float64), TypeError), (good[:-1].contiguous(), ValueError),
+                      (good.cpu(), ValueError), (wide, ValueError), (3, TypeError)):
+        # sizes are read from x and B_experts: one of those of another shape is told by a tensor that does not match it
+        match = None if name in ("x", "B_experts") else name
+        with pytest.raises(kind, match=match):
+            getattr(sw, call)(**{**args, name: bad})
+
+
+def test_given_outputs_are_the_ones_that_come_back():
+    a = forward_args()
+    out = sw.swimba_mixer_fwd(**a)
+    fresh = sw.swimba_mixer_fwd(**{k: v for k, v in a.items() if k not in ("y", "h_final", "topk_idx", "topk_w")}, want_topk=True)
+    for n in ("y", "h_final", "topk_idx", "topk_w"):
+        assert getattr(out, n) is a[n] and torch.equal(getattr(out, n), getattr(fresh, n))
+    none = sw.swimba_mixer_fwd(**{k: v for k, v in a.items() if k not in ("h_final", "topk_idx", "topk_w")}, want_h_final=False)
+    assert none.y is a["y"] and none.h_final is None and none.topk_idx is None and none.topk_w is None
+    s = step_args()
+    out = sw.swimba_step_multi(**s)
+    assert out.y is s["y"] and out.state is s["state_out"] and out.topk_idx is s["topk_idx"]
+    assert not s["state"].any()
+    out = sw.swimba_step_multi(**dict(s, state_out=None, topk_idx=None))
+    assert out.state is s["state"] and out.topk_idx is None and torch.equal(s["state"], s["state_out"])
