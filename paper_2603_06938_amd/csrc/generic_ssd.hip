@@ -1,7 +1,7 @@
-// fp32 SSD chunk kernels for any (P, N, Q, io type) within the library limits.
-// These are the kernels of the fp32 workloads and of bf16 shapes the MFMA
-// kernels do not cover.  The expert mixing is done while the chunk's B/C rows
-// are staged into LDS; mixed streams never go to HBM.
+// fp32 SSD chunk kernels for any (P, N, Q, io type) within the library limits, on plain arithmetic: the fp32 stage
+// entries, the separated contrast and the forward with one input stream per expert outside the bf16 kernels' sizes.
+// (The fp32 forward itself is chain_f32.hip.)  The expert mixing is done while the chunk's B/C rows are staged into
+// LDS; mixed streams never go to HBM.
 #include "common.hpp"
 
 namespace swimba {
