@@ -23,8 +23,10 @@
 // segment of the output launch starts from the sum of those in front of it (the recurrence is linear
 // in the state).
 //
-// Bound: the f32 matrix pipe (157 TFLOP/s); 64-cycle MFMAs, one operand register per MFMA, so LDS and
-// L2 are far from their limits.
+// Bound: no single unit.  On the 130M-shaped layer (two sequences of 2048 tokens: operands 12 us, contributions 30, output
+// 66, 101 for the call) the f32 matrix pipe, 64 cycles an MFMA, is busy 44 % of the output launch and 39 % of the other
+// by the counters; the rest is the waits between the dependent phases of a step and its two barriers, with two
+// workgroups on a compute unit.
 #include "common.hpp"
 #include "mfma_util.hpp"
 
@@ -153,103 +155,103 @@ mix_ops_kernel(const T *__restrict__ Be, const T *__restrict__ Ce, const T *__re
     const int rowsC = max(0, min(valid - r0, R)), rowsB = rowsC > 0 ? min(valid, r0 + R) : 0;
     const int QPR = NP / 4, units = (rowsC + rowsB) * QPR;
     for (int g = g_begin; g < g_begin + gpb; ++g) {
-    // ---- mixed rows: a lane takes quads of 4 columns of one stream, QF at a time; C rows [r0, r0 + R), then the B
-    // ---- rows up to the last of them ----
-    const T *Bg = Be + (tok0 * rowsE * s.G + g) * s.N;
-    const T *Cg = Ce + (tok0 * rowsE * s.G + g) * s.N;
-    for (int u0 = 0; u0 < units; u0 += QF * CF_MIX_THREADS) {
-        float4 am[QF];
+        // ---- mixed rows: a lane takes quads of 4 columns of one stream, QF at a time; C rows [r0, r0 + R), then the B
+        // ---- rows up to the last of them ----
+        const T *Bg = Be + (tok0 * rowsE * s.G + g) * s.N;
+        const T *Cg = Ce + (tok0 * rowsE * s.G + g) * s.N;
+        for (int u0 = 0; u0 < units; u0 += QF * CF_MIX_THREADS) {
+            float4 am[QF];
 #pragma unroll
-        for (int m = 0; m < QF; ++m) am[m] = make_float4(0.f, 0.f, 0.f, 0.f);
-        for (int r = 0; r < K; ++r) {
-            float4 v[QF];
-            float ww[QF];
+            for (int m = 0; m < QF; ++m) am[m] = make_float4(0.f, 0.f, 0.f, 0.f);
+            for (int r = 0; r < K; ++r) {
+                float4 v[QF];
+                float ww[QF];
 #pragma unroll
-            for (int m = 0; m < QF; ++m) {
-                if (u0 + m * CF_MIX_THREADS >= units) continue;          // uniform
-                const int u = min(u0 + m * CF_MIX_THREADS + tid, units - 1);
-                const int rr = u / QPR, n = (u % QPR) * 4, j = rr < rowsC ? r0 + rr : rr - rowsC;
-                const T *src = (rr < rowsC ? Cg : Bg) + j * tokstride + s_idx[j * K + r] * estride;
-                ww[m] = s_w[j * K + r];
-                if (vec) {
-                    v[m] = load4(src + min(n, s.N - 4));
-                } else {
-                    float t[4];
+                for (int m = 0; m < QF; ++m) {
+                    if (u0 + m * CF_MIX_THREADS >= units) continue;          // uniform
+                    const int u = min(u0 + m * CF_MIX_THREADS + tid, units - 1);
+                    const int rr = u / QPR, n = (u % QPR) * 4, j = rr < rowsC ? r0 + rr : rr - rowsC;
+                    const T *src = (rr < rowsC ? Cg : Bg) + j * tokstride + s_idx[j * K + r] * estride;
+                    ww[m] = s_w[j * K + r];
+                    if (vec) {
+                        v[m] = load4(src + min(n, s.N - 4));
+                    } else {
+                        float t[4];
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) t[q] = to_float(src[min(n + q, s.N - 1)]);
-                    v[m] = make_float4(t[0], t[1], t[2], t[3]);
+                        for (int q = 0; q < 4; ++q) t[q] = to_float(src[min(n + q, s.N - 1)]);
+                        v[m] = make_float4(t[0], t[1], t[2], t[3]);
+                    }
+                }
+#pragma unroll
+                for (int m = 0; m < QF; ++m) {
+                    if (u0 + m * CF_MIX_THREADS >= units) continue;
+                    am[m].x += ww[m] * v[m].x; am[m].y += ww[m] * v[m].y; am[m].z += ww[m] * v[m].z; am[m].w += ww[m] * v[m].w;
                 }
             }
 #pragma unroll
             for (int m = 0; m < QF; ++m) {
-                if (u0 + m * CF_MIX_THREADS >= units) continue;
-                am[m].x += ww[m] * v[m].x; am[m].y += ww[m] * v[m].y; am[m].z += ww[m] * v[m].z; am[m].w += ww[m] * v[m].w;
+                const int u = u0 + m * CF_MIX_THREADS + tid;
+                if (u < units) {
+                    const int rr = u / QPR, n = (u % QPR) * 4;
+                    float *f = reinterpret_cast<float *>(&am[m]);
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        if (n + q >= s.N) f[q] = 0.f;                   // padding columns
+                    *reinterpret_cast<float4 *>((rr < rowsC ? s_C + (r0 + rr) * RS : s_B + (rr - rowsC) * RS) + n) = am[m];
+                }
             }
         }
-#pragma unroll
-        for (int m = 0; m < QF; ++m) {
-            const int u = u0 + m * CF_MIX_THREADS + tid;
-            if (u < units) {
-                const int rr = u / QPR, n = (u % QPR) * 4;
-                float *f = reinterpret_cast<float *>(&am[m]);
+        __syncthreads();
+
+        const int64_t bcg = ((int64_t)b * s.nc + c) * s.G + g;
+        float4 *co = reinterpret_cast<float4 *>(cop) + bcg * (ops.IT * NT * 4 * 64);
+        float4 *bo = reinterpret_cast<float4 *>(bop) + bcg * (NT * ops.QN * 64);
+        float4 *go = reinterpret_cast<float4 *>(gop) + bcg * (ops.GB * 64);
+        // ---- G^T[j][i] = B[j] . C[i] in 16 x 16 tiles (v_mfma_f32_16x16x4_f32): lane (i = lane%16, kq = lane/16) ends
+        // ---- with four consecutive j of one i, which is a float4 of gop.  Tiles right of the diagonal are zero.  Rows past
+        // ---- the end hold what LDS held: their entries are masked (j > i) or belong to no token. ----
+        {
+            const int l16 = lane & 15, kq = lane >> 4;
+            const int t_begin = PARTS == 1 ? 0 : part < 2 ? 2 * part : 4 * part - 4;
+            const int t_end = PARTS == 1 ? 12 : part < 2 ? t_begin + 2 : t_begin + 4;
+            for (int t = t_begin + wave; t < t_end; t += CF_MIX_THREADS / 64) {
+                // tile rows 0, 1 have columns J = 0, 1; rows 2, 3 columns 0..3
+                const int I = t < 4 ? t >> 1 : 2 + ((t - 4) >> 2), J = t < 4 ? t & 1 : (t - 4) & 3;
+                if (16 * I >= valid || (one_row && 16 * J >= valid)) continue;
+                cf_f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+                if (J <= I) {
+                    const float *br = s_B + (16 * J + l16) * RS + 4 * kq, *cr = s_C + (16 * I + l16) * RS + 4 * kq;
+                    for (int k = 0; k < NP; k += 16) {
+                        const float4 av = *reinterpret_cast<const float4 *>(br + k);
+                        const float4 bv = *reinterpret_cast<const float4 *>(cr + k);
+                        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av.x, bv.x, acc, 0, 0, 0);
+                        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av.y, bv.y, acc, 0, 0, 0);
+                        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av.z, bv.z, acc, 0, 0, 0);
+                        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av.w, bv.w, acc, 0, 0, 0);
+                    }
+                }
+                const int i = 16 * I + l16, j0 = 16 * J + 4 * kq;
 #pragma unroll
                 for (int q = 0; q < 4; ++q)
-                    if (n + q >= s.N) f[q] = 0.f;                   // padding columns
-                *reinterpret_cast<float4 *>((rr < rowsC ? s_C + (r0 + rr) * RS : s_B + (rr - rowsC) * RS) + n) = am[m];
+                    if (j0 + q > i) acc[q] = 0.f;
+                const int blk = (i >> 5) * 4 + (j0 >> 3);
+                if (blk < ops.GB) go[blk * 64 + ((j0 >> 2) & 1) * 32 + (i & 31)] = make_float4(acc[0], acc[1], acc[2], acc[3]);
             }
         }
-    }
-    __syncthreads();
-
-    const int64_t bcg = ((int64_t)b * s.nc + c) * s.G + g;
-    float4 *co = reinterpret_cast<float4 *>(cop) + bcg * (ops.IT * NT * 4 * 64);
-    float4 *bo = reinterpret_cast<float4 *>(bop) + bcg * (NT * ops.QN * 64);
-    float4 *go = reinterpret_cast<float4 *>(gop) + bcg * (ops.GB * 64);
-    // ---- G^T[j][i] = B[j] . C[i] in 16 x 16 tiles (v_mfma_f32_16x16x4_f32): lane (i = lane%16, kq = lane/16) ends
-    // ---- with four consecutive j of one i, which is a float4 of gop.  Tiles right of the diagonal are zero.  Rows past
-    // ---- the end hold what LDS held: their entries are masked (j > i) or belong to no token. ----
-    {
-        const int l16 = lane & 15, kq = lane >> 4;
-        const int t_begin = PARTS == 1 ? 0 : part < 2 ? 2 * part : 4 * part - 4;
-        const int t_end = PARTS == 1 ? 12 : part < 2 ? t_begin + 2 : t_begin + 4;
-        for (int t = t_begin + wave; t < t_end; t += CF_MIX_THREADS / 64) {
-            // tile rows 0, 1 have columns J = 0, 1; rows 2, 3 columns 0..3
-            const int I = t < 4 ? t >> 1 : 2 + ((t - 4) >> 2), J = t < 4 ? t & 1 : (t - 4) & 3;
-            if (16 * I >= valid || (one_row && 16 * J >= valid)) continue;
-            cf_f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
-            if (J <= I) {
-                const float *br = s_B + (16 * J + l16) * RS + 4 * kq, *cr = s_C + (16 * I + l16) * RS + 4 * kq;
-                for (int k = 0; k < NP; k += 16) {
-                    const float4 av = *reinterpret_cast<const float4 *>(br + k);
-                    const float4 bv = *reinterpret_cast<const float4 *>(cr + k);
-                    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av.x, bv.x, acc, 0, 0, 0);
-                    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av.y, bv.y, acc, 0, 0, 0);
-                    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av.z, bv.z, acc, 0, 0, 0);
-                    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av.w, bv.w, acc, 0, 0, 0);
-                }
-            }
-            const int i = 16 * I + l16, j0 = 16 * J + 4 * kq;
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-                if (j0 + q > i) acc[q] = 0.f;
-            const int blk = (i >> 5) * 4 + (j0 >> 3);
-            if (blk < ops.GB) go[blk * 64 + ((j0 >> 2) & 1) * 32 + (i & 31)] = make_float4(acc[0], acc[1], acc[2], acc[3]);
+        for (int u = tid; u < rowsC * NT * 8; u += CF_MIX_THREADS) {
+            const int row = r0 + u % rowsC, v = u / rowsC, kg = v & 1, a = (v >> 1) & 3, nt = v >> 3;
+            co[(((row >> 5) * NT + nt) * 4 + a) * 64 + kg * 32 + (row & 31)] =
+                *reinterpret_cast<const float4 *>(s_C + row * RS + 32 * nt + 8 * a + 4 * kg);
         }
-    }
-    for (int u = tid; u < rowsC * NT * 8; u += CF_MIX_THREADS) {
-        const int row = r0 + u % rowsC, v = u / rowsC, kg = v & 1, a = (v >> 1) & 3, nt = v >> 3;
-        co[(((row >> 5) * NT + nt) * 4 + a) * 64 + kg * 32 + (row & 31)] =
-            *reinterpret_cast<const float4 *>(s_C + row * RS + 32 * nt + 8 * a + 4 * kg);
-    }
-    const int QS = one_row ? (rowsC + 7) / 8 : R / 8;    // blocks of eight B rows in this workgroup
-    for (int u = tid; u < NT * QS * 64; u += CF_MIX_THREADS) {
-        const int ln = u & 63, q = r0 / 8 + (u >> 6) % QS, nt = (u >> 6) / QS, row = 8 * q + 4 * (ln >> 5);
-        const float *src = s_B + row * RS + 32 * nt + (ln & 31);
-        // rows past the end are multiplied by zeros of x: they have to be finite
-        bo[(nt * ops.QN + q) * 64 + ln] = make_float4(row < valid ? src[0] : 0.f, row + 1 < valid ? src[RS] : 0.f,
-                                                      row + 2 < valid ? src[2 * RS] : 0.f, row + 3 < valid ? src[3 * RS] : 0.f);
-    }
-    __syncthreads();                                     // the next group's rows
+        const int QS = one_row ? (rowsC + 7) / 8 : R / 8;    // blocks of eight B rows in this workgroup
+        for (int u = tid; u < NT * QS * 64; u += CF_MIX_THREADS) {
+            const int ln = u & 63, q = r0 / 8 + (u >> 6) % QS, nt = (u >> 6) / QS, row = 8 * q + 4 * (ln >> 5);
+            const float *src = s_B + row * RS + 32 * nt + (ln & 31);
+            // rows past the end are multiplied by zeros of x: they have to be finite
+            bo[(nt * ops.QN + q) * 64 + ln] = make_float4(row < valid ? src[0] : 0.f, row + 1 < valid ? src[RS] : 0.f,
+                                                          row + 2 < valid ? src[2 * RS] : 0.f, row + 3 < valid ? src[3 * RS] : 0.f);
+        }
+        __syncthreads();                                     // the next group's rows
     }
 }
 
@@ -585,7 +587,7 @@ chain_f32_kernel(const T *__restrict__ x, const T *__restrict__ dt, const float 
     // A masked entry of M (j > i) times an x or dt that is not finite is NaN, in tokens that such a value must not
     // reach.  The segment is then walked again with the products of M taken one by one, only those with j <= i.  (Testing
     // inside a step instead, with a branch there or with finite stand-ins for such values, keeps the products of M from
-    // overlapping with the readout: 104.4 us on the 130M-shaped layer, 102.8 this way, 101.5 with no test at all.)
+    // overlapping with the readout: 104.4 us on the 130M-shaped layer where this takes 101.4.)
     if constexpr (OUT)
         if (__builtin_amdgcn_readfirstlane(s_odd)) {
             __syncthreads();                             // every wave has read it
