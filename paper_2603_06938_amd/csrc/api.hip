@@ -199,6 +199,22 @@ static bool use_chunk_mix(const swimba_dims *d, bool selected)
     return mix_chunk_covers(s, selected) && (int64_t)s.B * s.nc * s.G >= 2 * (int64_t)device_cus();
 }
 
+// The bf16 forward as one walk over 64-token steps (chain_bf16.hip), two launches; its scratch lies over cmix .. cb and
+// states_lp.  A chain's steps are serial, 0.7 us each (two workgroups to a compute unit) to 1.5 (all units busy): ahead of the
+// kernels above everywhere up to 16 steps (8 to 1024 chains, 64 to 1024 tokens: 0.5 to 0.98 of their time; 8 chains of 1024
+// tokens 22.5 / 23.0 us), from 96 chains on up to 128 (96 chains of 8192 tokens 142 / 157) and where the chains fill three
+// fifths of their rounds at any length (256 of 4096 tokens 122 / 147); 128 chains of 256 steps 401 / 392, 48 of 32 steps
+// 34.0 / 34.9, of 64 56.3 / 52.6; 24 of 32 33.3 / 28.8.  Short of that the kernels that also parallelise over chunks or cut
+// the sequence stay ahead.
+static bool use_chain_bf16(const swimba_dims *d)
+{
+    if (!use_mfma_path(d)) return false;
+    const int64_t chains = (int64_t)d->batch * d->nheads, steps = ((int64_t)d->seqlen + 63) / 64, ncu = device_cus();
+    const int64_t rounds = (chains + ncu - 1) / ncu;
+    return steps <= 16 || (steps <= 32 && 32 * chains >= 5 * ncu) || (steps <= 128 && 8 * chains >= 3 * ncu) ||
+           10 * chains >= 6 * rounds * ncu;
+}
+
 struct Ws {
     int32_t *idx;
     float *w;
@@ -570,6 +586,10 @@ swimba_status swimba_mixer_fwd(const swimba_dims *dims, const void *x, const voi
             return launch_chain_f32(s, dims->io_dtype, x, dt, A, D, B_experts, C_experts, router_logits, nullptr, h0, y,
                                     h_final, topk_idx ? topk_idx : ws.idx, topk_w ? topk_w : ws.w, ws.cop, ws.bop, ws.gop,
                                     ws.hseg, ws.aseg, ws.hinit, stream);
+        if (use_chain_bf16(dims))
+            return launch_chain_bf16(s, x, dt, A, D, B_experts, C_experts, router_logits, nullptr, h0, y, h_final,
+                                     topk_idx ? topk_idx : ws.idx, topk_w ? topk_w : ws.w, ws.cmix, (float *)ws.states_lp,
+                                     stream);
         // On the bf16 MFMA path the mix kernel routes the tokens itself and the chunk-state
         // kernel computes the cumsum itself: two launches fewer.
         const bool chunk_mix = use_chunk_mix(dims, false);
@@ -1060,6 +1080,9 @@ static swimba_status mixer_selected_core(const swimba_dims *dims, const void *x,
     const bool mf = use_mfma_path(dims);
     swimba_status st;
     if (T > 0) {
+        if (mf && use_chain_bf16(dims))
+            return launch_chain_bf16(s, x, dt, A, D, B_sel, C_sel, nullptr, w_sel, h0, y, h_final, nullptr, nullptr, ws.cmix,
+                                     (float *)ws.states_lp, stream);
         if (mf) {
             const bool chunk_mix = use_chunk_mix(dims, true);
             st = chunk_mix ? launch_mix_chunk_mfma(s, B_sel, C_sel, nullptr, nullptr, nullptr, ws.cmix, ws.bmix_t8,

@@ -1,0 +1,711 @@
+// SSD forward for bf16 io on v_mfma_f32_32x32x16_bf16 as one walk over 64-token steps per (batch, head)
+// (paper, background section on SSD: matrix work inside chunks, a linear recurrence between chunks; Theorem 1: the
+// mixed streams feed one plain SSM).  The result does not depend on the chunk length.
+//   mix_steps_kernel   (batch, step, groups): routes 64 tokens, mixes their B and C rows and writes them, and the masked
+//                      products G = C B^T, as the operand registers the chain reads; and, in workgroups of its own, the
+//                      decay tables of every (batch, head, step).  Shared by the heads of a group.
+//   chain_bf16_kernel  (batch, head, 64 or 32 channels): the state never leaves the accumulators.  With a reference R of the
+//                      step (ChainTables) x~_j = f_j x_j, H' = the state at R:
+//                        Y[i][p]  = e_i (sum_n C[i][n] H'[n][p] + sum_j G[i][j] x~_j[p]) + D x_i[p]
+//                        H'      <- 2^(R_next - ..) (H' + sum_j B[j][n] x~_j[p])
+//                      so the three contractions take x~ alone, G as it was written, and no operand is scaled per head.
+// Compute waves (32 channels x half of the state columns) hold their part of the state in the accumulators, which packed to
+// bf16 are the A operand of the readout as they are; 19 MFMAs each per step (N = 128).  The halves' partial Y meet in LDS.  I/O
+// waves load x three steps ahead, write x~ into LDS two steps ahead, and finish and store Y one step behind; one LDS-only
+// barrier a step.  ds_read_b64_tr_b16 transposes x~ (and, in the mix kernel, B) on the way out of LDS.
+//
+// Against the staged kernels and the per-head pass over whole chunks (two to five launches, G scaled element by element per
+// head, x and chunk states more than once through memory): 130M-shaped layer 76.7 -> 57.7 us, 370M-shaped layer
+// 147.3 -> 121.9, five sequences of 1237 tokens x 32 heads 52.6 -> 35.7, 150 tokens x 24 heads 21.6 -> 12.5.
+// Bound: waits.  A step of the 370M-shaped layer takes 1.55 us with every compute unit busy; its matrix work is 0.28 us, its
+// LDS traffic about 0.6, what goes through the vector L1 (38 KB of operands, read by both channel tiles, 16 KB of x and y)
+// 0.65, x and y at the rate of a copy in this pattern 1.0; taking x and y away leaves 1.0 us, the operands 1.15.
+#include "common.hpp"
+#include "mfma_util.hpp"
+
+#include <atomic>
+#include <type_traits>
+
+namespace swimba {
+
+constexpr int CB_STEP = 64;            // tokens per step
+constexpr int CB_MIX_THREADS = 512;
+constexpr float CB_RANGE = 120.f;      // log2 of the largest product of two factors of a step (ChainTables)
+constexpr int CB_RING = 6;             // x tiles in an i/o wave's registers (a multiple of the 3 in LDS); 9 spill time: 130M 64.6 us
+
+typedef __attribute__((ext_vector_type(4))) short cb_s16x4_t;
+typedef __attribute__((address_space(3))) cb_s16x4_t cb_lds_s16x4_t;
+
+// 16 lanes read a 4 x 16 block of 16-bit elements, lane s four columns of row s / 4; lane s gets column s, rows 0..3
+__device__ __forceinline__ uint2 lds_read_tr(const unsigned char *p)
+{
+    return __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((cb_lds_s16x4_t *)(p)));
+}
+
+__device__ __forceinline__ float lane_value(float v, int l)
+{
+    return __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(v), l));
+}
+
+// Operand images, one item per (batch, step, group), NT tiles of 32 state columns:
+//   C (2, 2 NT, 64, 8) [I][s][lane][e]   = C[32 I + lane%32][16 s + 8(e/4) + 4(lane/32) + e%4]
+//   B (NT, 4, 64, 8)   [nt][ks][lane][e] = B[16 ks + 8(e/4) + 4(lane/32) + e%4][32 nt + lane%32]
+//   G (6, 64, 8)       [f][lane][e]      = (j <= i) C[i] . B[j];  f < 2: i = lane%32, j = 16 f + ..; else i = 32 + lane%32,
+//                                          j = 16 (f - 2) + 8(e/4) + 4(lane/32) + e%4
+__host__ __device__ constexpr int cb_item_frags(int NT) { return 8 * NT + 6; }
+
+// Per (batch, head, step), written by the mix launch (cs: inclusive sum of log2 e dt A from the step's first token):
+//   fe  (B, H, nsteps, 64, 2)  factor of x, dt_j 2^(R - cs_j), and of y, 2^(cs_i - R)
+//   ref (B, H, nsteps, 4)      mode and references (pack_ref); 2^(fraction of cs_last); 2^(R1 - R0) or, of a direct step, 2^cs_last
+//   cd  (B, H, nsteps, 64, 2)  cs_j and dt_j, of direct steps alone
+// With a reference R in the middle of the step's range, 2^(cs_i - cs_j) dt_j is a factor of token j times a factor of token i,
+// both far from the ends of the exponent range: no element of the masked products needs a factor of its own, and the state is
+// updated and read at R, too.  R is a whole number, so another one changes no bit of a result: the bits of a token do not
+// depend on the tokens behind it.
+//   mode 0  one reference for the step, whose cs span at most CB_RANGE
+//   mode 1  one for each half of 32 tokens, each of which spans at most that: the state and the second half's Y change over
+//           in the middle of the step (about one head in fifty with dt log-uniform in [1e-3, 1e-1] and -A in [1, 16])
+//   mode 2  direct: the others, and values that are not finite.  x takes dt_j 2^(cs_last - cs_j), for the state alone.
+// CB_RANGE: two neighbouring steps change the state's reference by up to as much, which has to be a normal factor.
+struct ChainTables {
+    float *fe, *ref, *cd;
+};
+__device__ __forceinline__ int pack_ref(int mode, int R0, int rem) { return mode | (R0 + 128) << 2 | (rem + 128) << 10; }
+__device__ __forceinline__ int ref_mode(int p) { return p & 3; }
+__device__ __forceinline__ int ref_r0(int p) { return ((p >> 2) & 255) - 128; }
+__device__ __forceinline__ int ref_rem(int p) { return ((p >> 10) & 255) - 128; }   // whole part of cs_last, less the last reference
+
+__device__ __forceinline__ void chain_table(const ChainTables &t, int64_t bhs, float d, float Ah, int lane)
+{
+    const float v = d * Ah;
+    const float cs = wave_scan(v);
+    const float mid = lane_value(cs, 31), last = lane_value(cs, 63);
+    // least and greatest of 0, cs_0 .. cs_31 and of cs_31 .. cs_63
+    float lo0 = fminf(0.f, mid), hi0 = fmaxf(0.f, mid), lo1 = fminf(mid, last), hi1 = fmaxf(mid, last);
+    if (__ballot(!(v <= 0.f)) != 0 && __ballot(!(v >= 0.f)) != 0) {      // it turns
+        float lo = cs, hi = cs;
+#pragma unroll
+        for (int o = 16; o; o >>= 1) { lo = fminf(lo, __shfl_xor(lo, o)); hi = fmaxf(hi, __shfl_xor(hi, o)); }
+        lo0 = fminf(lo0, lane_value(lo, 0)); hi0 = fmaxf(hi0, lane_value(hi, 0));
+        lo1 = fminf(lo1, lane_value(lo, 32)); hi1 = fmaxf(hi1, lane_value(hi, 32));
+    }
+    const float lo = fminf(lo0, lo1), hi = fmaxf(hi0, hi1);
+    const bool finite = __ballot(!(fabsf(v) <= 3e38f)) == 0;
+    const int mode = finite && hi - lo <= CB_RANGE ? 0 : finite && hi0 - lo0 <= CB_RANGE && hi1 - lo1 <= CB_RANGE ? 1 : 2;
+    const float R0 = mode == 0 ? rintf(0.5f * (lo + hi)) : rintf(0.5f * (lo0 + hi0));
+    const float R1 = mode == 0 ? R0 : rintf(0.5f * (lo1 + hi1));
+    const float whole = rintf(cs), part = cs - whole, last_whole = rintf(last);
+    const float R = lane < 32 ? R0 : R1;
+    float2 fe = make_float2(d * fast_exp2(last - cs), 1.f);
+    float4 ref = make_float4(0.f, 1.f, fast_exp2(last), 0.f);
+    int pack = pack_ref(2, 0, 0);
+    if (mode != 2) {
+        fe.x = ldexpf(d * fast_exp2(-part), (int)(R - whole));
+        fe.y = ldexpf(fast_exp2(part), (int)(whole - R));
+        ref.y = fast_exp2(last - last_whole);
+        ref.z = ldexpf(1.f, (int)(R1 - R0));
+        // mode 1: R0, R1 and cs_last can be far from the step's start, but not from each other's tile
+        pack = pack_ref(mode, (int)R0, (int)(last_whole - R1));
+    }
+    ref.x = __int_as_float(pack);
+    reinterpret_cast<float2 *>(t.fe)[bhs * CB_STEP + lane] = fe;
+    if (mode == 2) reinterpret_cast<float2 *>(t.cd)[bhs * CB_STEP + lane] = make_float2(cs, d);
+    if (lane == 0) reinterpret_cast<float4 *>(t.ref)[bhs] = ref;
+}
+
+template <int NT>
+__global__ void __launch_bounds__(CB_MIX_THREADS, 4)
+mix_steps_kernel(const bf16 *__restrict__ Be, const bf16 *__restrict__ Ce, const bf16 *__restrict__ logits,
+                 int32_t *__restrict__ idx_out, float *__restrict__ w_out, const float *__restrict__ w_sel,
+                 uint16_t *__restrict__ ops, const bf16 *__restrict__ dt, const float *__restrict__ A, ChainTables tb, Shape s,
+                 int nsteps, int gpb, int items)
+{
+    constexpr int RS = 64 * NT + 16;                     // row stride of the mixed rows (bytes)
+    constexpr int PPR = 4 * NT;                          // 16-byte pieces of a row
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    unsigned char *s_rows[2] = {smem_raw, smem_raw + CB_STEP * RS};              // B, C
+    int32_t *s_idx = reinterpret_cast<int32_t *>(smem_raw + 2 * CB_STEP * RS);   // [64][K]
+    float *s_w = reinterpret_cast<float *>(s_idx + CB_STEP * s.K);               // [64][K]
+    float *s_l = s_w + CB_STEP * s.K;                                            // [64][E|1]
+    const int K = s.K, tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if ((int)blockIdx.x >= items) {
+        // tables: a wave takes eight heads of a step
+        const int octets = (s.H + 7) / 8;
+        const int unit = ((int)blockIdx.x - items) * (CB_MIX_THREADS / 64) + wave;
+        const int h0 = 8 * (unit % octets), c = (unit / octets) % nsteps, b = unit / (octets * nsteps);
+        if (b >= s.B) return;
+        const int t = c * CB_STEP + lane;
+        const bf16 *src = dt + ((int64_t)b * s.L + min(t, s.L - 1)) * s.H;
+        uint16_t d[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) d[k] = src[min(h0 + k, s.H - 1)].bits;
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+            if (h0 + k < s.H)
+                chain_table(tb, ((int64_t)b * s.H + h0 + k) * nsteps + c, t < s.L ? bf_lo(d[k]) : 0.f, A[h0 + k] * LOG2E, lane);
+        return;
+    }
+    const int gblocks = s.G / gpb;
+    const int item = blockIdx.x;
+    const int g_begin = (item % gblocks) * gpb;
+    const int c = (item / gblocks) % nsteps;
+    const int b = item / (gblocks * nsteps);
+    const int valid = min(CB_STEP, s.L - c * CB_STEP);
+    const int64_t tok0 = (int64_t)b * s.L + (int64_t)c * CB_STEP;
+    const bool sel = (w_sel != nullptr);
+
+    if (!sel) {
+        const int ES = s.E | 1;
+        for (int i = tid; i < valid * s.E; i += CB_MIX_THREADS) s_l[i / s.E * ES + i % s.E] = to_float(logits[tok0 * s.E + i]);
+        __syncthreads();
+    }
+    if (tid < CB_STEP) {
+        int32_t *ix = s_idx + tid * K;
+        float *wx = s_w + tid * K;
+        if (tid >= valid) {
+            for (int r = 0; r < K; ++r) { ix[r] = 0; wx[r] = 0.f; }
+        } else if (sel) {
+            for (int r = 0; r < K; ++r) { ix[r] = r; wx[r] = w_sel[(tok0 + tid) * K + r]; }
+        } else {
+            const float *row = s_l + tid * (s.E | 1);
+            route_token([&](int e) { return row[e]; }, s.E, K, ix, wx);
+            if (g_begin == 0)
+                for (int r = 0; r < K; ++r) { idx_out[(tok0 + tid) * K + r] = ix[r]; w_out[(tok0 + tid) * K + r] = wx[r]; }
+        }
+    }
+    __syncthreads();
+
+    const int rowsE = sel ? K : s.E;
+    const int64_t estride = (int64_t)s.G * s.N, tokstride = rowsE * estride;
+    const int l32 = lane & 31, hi = lane >> 5, s16 = lane & 15, half = (lane >> 4) & 1;
+    for (int g = g_begin; g < g_begin + gpb; ++g) {
+        // ---- mixed rows: units of 8 columns, NT a thread; B rows first, then C rows ----
+        {
+            float acc[NT][8];
+#pragma unroll
+            for (int m = 0; m < NT; ++m)
+#pragma unroll
+                for (int q = 0; q < 8; ++q) acc[m][q] = 0.f;
+            auto source = [&](int m, int r, float &w) __attribute__((always_inline)) {
+                const int u = m * CB_MIX_THREADS + tid, row = (u / PPR) % CB_STEP, pc = u % PPR;
+                const uint16_t *base = reinterpret_cast<const uint16_t *>(u >= CB_STEP * PPR ? Ce : Be);
+                const int j = min(row, valid - 1);
+                w = s_w[row * K + r];
+                return reinterpret_cast<const uint4 *>(base + (tok0 + j) * tokstride + s_idx[row * K + r] * estride +
+                                                       (int64_t)g * s.N + min(8 * pc, s.N - 8));
+            };
+            int r = 0;
+            for (; r + 1 < K; r += 2) {
+                uint4 v0[NT], v1[NT];
+                float w0[NT], w1[NT];
+#pragma unroll
+                for (int m = 0; m < NT; ++m) {
+                    v0[m] = *source(m, r, w0[m]);
+                    v1[m] = *source(m, r + 1, w1[m]);
+                }
+#pragma unroll
+                for (int m = 0; m < NT; ++m) {
+                    fma_bf16x8(acc[m], v0[m], w0[m]);
+                    fma_bf16x8(acc[m], v1[m], w1[m]);
+                }
+            }
+            if (r < K) {
+                uint4 v0[NT];
+                float w0[NT];
+#pragma unroll
+                for (int m = 0; m < NT; ++m) v0[m] = *source(m, r, w0[m]);
+#pragma unroll
+                for (int m = 0; m < NT; ++m) fma_bf16x8(acc[m], v0[m], w0[m]);
+            }
+#pragma unroll
+            for (int m = 0; m < NT; ++m) {
+                const int u = m * CB_MIX_THREADS + tid, row = (u / PPR) % CB_STEP, pc = u % PPR;
+                uint4 v = pack8(acc[m]);
+                if (row >= valid || 8 * pc >= s.N) v = make_uint4(0, 0, 0, 0);
+                *reinterpret_cast<uint4 *>(smem_raw + (u >= CB_STEP * PPR ? CB_STEP * RS : 0) + row * RS + 16 * pc) = v;
+            }
+        }
+        __syncthreads();
+        uint4 *dst = reinterpret_cast<uint4 *>(ops) + (((int64_t)b * nsteps + c) * s.G + g) * (cb_item_frags(NT) * 64) + lane;
+        if (wave < 3) {                                  // G^T tiles (I, J) = (0, 0), (1, 0), (1, 1)
+            const int I = wave > 0, J = wave == 2;
+            const unsigned char *br = s_rows[0] + (32 * J + l32) * RS + 16 * hi, *cr = s_rows[1] + (32 * I + l32) * RS + 16 * hi;
+            f32x16_t acc = {0};
+#pragma unroll
+            for (int k = 0; k < 2 * NT; ++k)
+                acc = mfma32(*reinterpret_cast<const uint4 *>(br + 32 * k), *reinterpret_cast<const uint4 *>(cr + 32 * k), acc);
+            float m[16];
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int j = 8 * (v >> 2) + 4 * hi + (v & 3);
+                m[v] = (wave == 1 || j <= l32) ? acc[v] : 0.f;
+            }
+            dst[(8 * NT + 2 * wave) * 64] = pack8(m);
+            dst[(8 * NT + 2 * wave + 1) * 64] = pack8(m + 8);
+        }
+        for (int f = CB_MIX_THREADS / 64 - 1 - wave; f < 8 * NT; f += CB_MIX_THREADS / 64) {
+            if (f < 4 * NT) {                            // C
+                const unsigned char *cr = s_rows[1] + (32 * (f / (2 * NT)) + l32) * RS + 32 * (f % (2 * NT)) + 8 * hi;
+                const uint2 a = *reinterpret_cast<const uint2 *>(cr), e = *reinterpret_cast<const uint2 *>(cr + 16);
+                dst[f * 64] = make_uint4(a.x, a.y, e.x, e.y);
+            } else {                                     // B, tokens innermost
+                const int fb = f - 4 * NT;
+                const unsigned char *br = s_rows[0] + (16 * (fb & 3) + 4 * hi + (s16 >> 2)) * RS + 64 * (fb >> 2) + 32 * half + 8 * (s16 & 3);
+                const uint2 a = lds_read_tr(br), e = lds_read_tr(br + 8 * RS);
+                dst[f * 64] = make_uint4(a.x, a.y, e.x, e.y);
+            }
+        }
+        if (g + 1 < g_begin + gpb) __syncthreads();      // the next group's rows
+    }
+}
+
+template <int NT, int PT>
+__global__ void __launch_bounds__(256 * PT, 2)
+chain_bf16_kernel(const uint16_t *__restrict__ x, const float *__restrict__ D, const uint16_t *__restrict__ ops, ChainTables tb,
+                  const float *h0, float *h_final, uint16_t *__restrict__ y, Shape s, int nsteps, int nslice, int nseg,
+                  int steps_per_seg, int total, int nblocks)
+{
+    constexpr int NTS = NT > 1 ? NT / 2 : 1;             // state tiles per compute wave
+    constexpr int NW = 2 * PT;                           // compute waves; as many i/o waves
+    constexpr int XROW = 64 * PT;                        // bytes of an x row
+    constexpr int XB = CB_STEP * XROW, YB = 2 * XB;      // bytes of an x tile, of a partial Y tile
+    constexpr int PPR = 4 * PT;                          // 16-byte pieces of an x row
+    constexpr int YM = 8 * PT - 1;                       // 16-byte pieces of a Y row, less one
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    unsigned char *s_x = smem_raw;                       // [3] x rows times f, bf16
+    unsigned char *s_y = s_x + 3 * XB;                   // [2][2] partial Y by halves of the state columns, fp32
+    float4 *s_ref = reinterpret_cast<float4 *>(s_y + 4 * YB);       // [4] references of a step
+
+    const int lid = xcd_logical_id(blockIdx.x, nblocks);
+    if (lid >= total) return;
+    const int sl = lid % nslice;
+    const int h = (lid / nslice) % s.H;
+    const int seg = (lid / (nslice * s.H)) % nseg;
+    const int b = lid / (nslice * s.H * nseg);
+    const int g = (h * s.G) / s.H;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l32 = lane & 31, hi = lane >> 5;
+    const int c_begin = seg * steps_per_seg, c_end = min(nsteps, c_begin + steps_per_seg);
+    const int t_end = min(s.L, c_end * CB_STEP);         // of the segment
+    const int p0 = 32 * PT * sl, P = s.P;
+    const int64_t tokb = (int64_t)b * s.L, trow = (int64_t)s.H * P;
+    const int64_t bhs = ((int64_t)b * s.H + h) * nsteps;
+
+    // ================= compute waves: 32 channels x half of the state columns =================
+    auto compute_wave = [&](auto nh_) __attribute__((always_inline)) {
+        constexpr int nh = decltype(nh_)::value;
+        constexpr bool on = nh * NTS < NT;               // one tile: the second half has none
+        constexpr int nt0 = on ? nh * NTS : 0;
+        const int ph = wave % PT, p = p0 + 32 * ph + l32;
+        const uint4 *item0 = reinterpret_cast<const uint4 *>(ops) + ((int64_t)b * nsteps * s.G + g) * (cb_item_frags(NT) * 64) + lane;
+        const int64_t item_step = (int64_t)s.G * (cb_item_frags(NT) * 64);
+        auto item = [&](int c) __attribute__((always_inline)) { return item0 + min(c, c_end - 1) * item_step; };
+        // operand of k-step ks from the x rows: channels 32 ph + lane%32, tokens 16 ks + 4 hi + 0..3 and + 8
+        const int s16 = lane & 15, r4 = s16 >> 2;
+        const int x_fr = (4 * hi + r4) * XROW + (((ph * 2 + ((lane >> 4) & 1)) ^ (PT == 2 ? r4 : (r4 >> 1))) << 5) + 8 * (s16 & 3);
+        uint4 xf[4];
+        auto read_x = [&](const unsigned char *base, int from, int to) __attribute__((always_inline)) {
+#pragma unroll
+            for (int ks = from; ks < to; ++ks) {
+                const unsigned char *q = base + x_fr + ks * 16 * XROW;
+                const uint2 a = lds_read_tr(q), e = lds_read_tr(q + 8 * XROW);
+                xf[ks] = make_uint4(a.x, a.y, e.x, e.y);
+            }
+        };
+        uint4 cf[2][2 * NTS], bfr[NTS][4], gf[3];
+        auto load_c = [&](int c) __attribute__((always_inline)) {
+            const uint4 *src = item(c);
+#pragma unroll
+            for (int k = 0; k < 2 * NTS; ++k)
+#pragma unroll
+                for (int it = 0; it < 2; ++it) cf[it][k] = src[(it * 2 * NT + 2 * nt0 + k) * 64];
+        };
+        auto load_g = [&](int c) __attribute__((always_inline)) {
+            const uint4 *src = item(c);
+#pragma unroll
+            for (int k = 0; k < 3; ++k) gf[k] = src[(8 * NT + 3 * nh + k) * 64];
+        };
+        auto load_b = [&](int c) __attribute__((always_inline)) {
+            const uint4 *src = item(c);
+#pragma unroll
+            for (int k = 0; k < NTS; ++k)
+#pragma unroll
+                for (int ks = 0; ks < 4; ++ks) bfr[k][ks] = src[(4 * NT + (nt0 + k) * 4 + ks) * 64];
+        };
+        load_c(c_begin);
+        load_g(c_begin);
+        load_b(c_begin);
+        f32x16_t st[NTS];
+        const int64_t hoff = (((int64_t)b * s.H + h) * P + min(p, P - 1)) * s.N;
+#pragma unroll
+        for (int k = 0; k < NTS; ++k)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int n = 32 * (nt0 + k) + 8 * q + 4 * hi;
+                float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+                if (h0 && p < P && n < s.N) v = *reinterpret_cast<const float4 *>(h0 + hoff + n);
+                st[k][4 * q] = v.x; st[k][4 * q + 1] = v.y; st[k][4 * q + 2] = v.z; st[k][4 * q + 3] = v.w;
+            }
+        f32x16_t yt[2];
+        // the state to the reference of a step, and its share of that step's Y (two tiles of 32 tokens)
+        auto readout = [&](float sc) __attribute__((always_inline)) {
+#pragma unroll
+            for (int it = 0; it < 2; ++it)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) yt[it][v] = 0.f;
+#pragma unroll
+            for (int k = 0; k < NTS; ++k) {
+                float m[16];
+#pragma unroll
+                for (int v = 0; v < 16; ++v) m[v] = (st[k][v] *= sc);
+                const uint4 hf[2] = {pack8(m), pack8(m + 8)};
+                if (on) {
+#pragma unroll
+                    for (int q = 0; q < 2; ++q)
+#pragma unroll
+                        for (int it = 0; it < 2; ++it) yt[it] = mfma32(hf[q], cf[it][2 * k + q], yt[it]);
+                }
+            }
+        };
+        lds_barrier();                                   // x and references of the first two steps
+        float4 rc = s_ref[0];
+        int pc = __builtin_amdgcn_readfirstlane(__float_as_int(rc.x));
+        readout(ldexpf(1.f, ref_r0(pc)));
+        load_c(c_begin + 1);
+        read_x(s_x, 0, 4);
+        unsigned char *y_wr = s_y + nh * YB + l32 * (128 * PT);
+        int slot = 0;                                    // of x
+        for (int c = c_begin; c < c_end; ++c) {
+            lds_barrier();
+            const float4 rn = s_ref[(c + 1 - c_begin) & 3];
+            const int mode = ref_mode(pc);
+            if (__builtin_expect(mode == 2, 0)) {
+                // a direct step: its masked products one decay at a time, on x as it is
+                const float2 *cd = reinterpret_cast<const float2 *>(tb.cd) + (bhs + c) * CB_STEP;
+                const float ci[2] = {cd[l32].x, cd[32 + l32].x};
+#pragma unroll
+                for (int it = 0; it < 2; ++it) {
+                    const float ei = fast_exp2(ci[it]);
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) yt[it][v] *= ei;
+                }
+#pragma unroll
+                for (int k = 0; k < NTS; ++k)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) st[k][v] *= rc.z;
+#pragma unroll
+                for (int k = 0; k < 3; ++k) {
+                    const int f = 3 * nh + k, it = f >= 2, ks = it ? f - 2 : f;
+                    float m[8];
+                    unpack8(m, gf[k]);
+                    uint32_t xv[8];
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        const int j = 16 * ks + 8 * (e >> 2) + 4 * hi + (e & 3), t = c * CB_STEP + j;
+                        const float2 q = cd[j];
+                        const float w = m[e] * (q.y * fast_exp2(ci[it] - q.x));
+                        m[e] = j <= 32 * it + l32 ? w : 0.f;
+                        xv[e] = x[(tokb + min(t, t_end - 1)) * trow + (int64_t)h * P + min(p, P - 1)];
+                        if (t >= t_end || p >= P) xv[e] = 0;
+                    }
+                    yt[it] = mfma32(make_uint4(xv[0] | xv[1] << 16, xv[2] | xv[3] << 16, xv[4] | xv[5] << 16, xv[6] | xv[7] << 16), pack8(m), yt[it]);
+                    gf[k] = make_uint4(0, 0, 0, 0);
+                }
+#pragma unroll
+                for (int ks = 0; ks < 4; ++ks) xf[ks] = make_uint4(0, 0, 0, 0);
+            }
+            auto masked_products = [&](int half) __attribute__((always_inline)) {
+#pragma unroll
+                for (int k = 0; k < 3; ++k) {
+                    const int f = 3 * nh + k, it = f >= 2, ks = it ? f - 2 : f;
+                    if (ks / 2 == half) yt[it] = mfma32(xf[ks], gf[k], yt[it]);
+                }
+            };
+            const uint4 *next = item(c + 1);
+            auto load_b1 = [&](int k, int ks) __attribute__((always_inline)) { bfr[k][ks] = next[(4 * NT + (nt0 + k) * 4 + ks) * 64]; };
+            auto write_y = [&](int it, int q) __attribute__((always_inline)) {
+                *reinterpret_cast<float4 *>(y_wr + (c & 1) * 2 * YB + it * 32 * 128 * PT + (((4 * ph + q + 4 * PT * hi) ^ (l32 & YM)) << 4)) =
+                    make_float4(yt[it][4 * q], yt[it][4 * q + 1], yt[it][4 * q + 2], yt[it][4 * q + 3]);
+            };
+            masked_products(0);
+            if (__builtin_expect(mode == 2, 0)) read_x(s_x + slot * XB, 0, 2);
+            // Memory instructions go out one behind each MFMA: a wave that issues them in a row waits for the CU's address
+            // unit and LDS each time, with its matrix core idle.
+#pragma unroll
+            for (int k = 0; k < NTS; ++k)
+#pragma unroll
+                for (int ks = 0; ks < 2; ++ks) {
+                    st[k] = mfma32(bfr[k][ks], xf[ks], st[k]);
+                    load_b1(k, ks);
+                    write_y(0, (2 * k + ks) & 3);
+                }
+            if (NTS == 1) { write_y(0, 2); write_y(0, 3); }
+#pragma unroll
+            for (int i = 0; i < 2 * NTS; ++i) {
+                __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x20, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
+            }
+            if (__builtin_expect(mode == 1, 0)) {
+                // from the reference of the first 32 tokens to that of the others
+#pragma unroll
+                for (int v = 0; v < 16; ++v) yt[1][v] *= rc.z;
+#pragma unroll
+                for (int k = 0; k < NTS; ++k)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) st[k][v] *= rc.z;
+            }
+            masked_products(1);
+            if (__builtin_expect(mode == 2, 0)) read_x(s_x + slot * XB, 2, 4);
+            const int pn = __builtin_amdgcn_readfirstlane(__float_as_int(rn.x));
+            const float sc = ldexpf(rc.y, ref_rem(pc) + (c + 1 < c_end ? ref_r0(pn) : 0));
+            load_g(c + 1);
+            __builtin_amdgcn_sched_barrier(0xf);
+#pragma unroll
+            for (int k = 0; k < NTS; ++k)
+#pragma unroll
+                for (int ks = 2; ks < 4; ++ks) {
+                    st[k] = mfma32(bfr[k][ks], xf[ks], st[k]);
+                    load_b1(k, ks);
+                    write_y(1, (2 * k + ks) & 3);
+                }
+            if (NTS == 1) { write_y(1, 0); write_y(1, 1); }
+            slot = slot == 2 ? 0 : slot + 1;
+            read_x(s_x + slot * XB, 0, 4);
+#pragma unroll
+            for (int i = 0; i < 2 * NTS; ++i) {
+                __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x20, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
+            }
+            __builtin_amdgcn_sched_group_barrier(0x100, 8, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            // the state at the reference of the next step, and its share of that step's Y
+            const uint4 *after = item(c + 2);
+#pragma unroll
+            for (int it = 0; it < 2; ++it)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) yt[it][v] = 0.f;
+#pragma unroll
+            for (int k = 0; k < NTS; ++k) {
+                float m[16];
+#pragma unroll
+                for (int v = 0; v < 16; ++v) m[v] = (st[k][v] *= sc);
+                const uint4 hf[2] = {pack8(m), pack8(m + 8)};
+                if (on) {
+#pragma unroll
+                    for (int q = 0; q < 2; ++q)
+#pragma unroll
+                        for (int it = 0; it < 2; ++it) {
+                            yt[it] = mfma32(hf[q], cf[it][2 * k + q], yt[it]);
+                            cf[it][2 * k + q] = after[(it * 2 * NT + 2 * (nt0 + k) + q) * 64];
+                        }
+                }
+            }
+            rc = rn;
+            pc = pn;
+        }
+        lds_barrier();
+        if (h_final && seg == nseg - 1 && p < P && on) {
+#pragma unroll
+            for (int k = 0; k < NTS; ++k)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int n = 32 * (nt0 + k) + 8 * q + 4 * hi;
+                    if (n < s.N)
+                        *reinterpret_cast<float4 *>(h_final + hoff + n) =
+                            make_float4(st[k][4 * q], st[k][4 * q + 1], st[k][4 * q + 2], st[k][4 * q + 3]);
+                }
+        }
+    };
+
+    if (wave < PT) {
+        compute_wave(std::integral_constant<int, 0>{});
+    } else if (wave < NW) {
+        compute_wave(std::integral_constant<int, 1>{});
+    } else {
+        // ================= i/o waves: two pieces of 8 channels of one token a thread =================
+        const int io = tid - NW * 64, iow = wave - NW;
+        const int xpc = io % PPR, xp = p0 + 8 * xpc, xj0 = io / PPR;      // tokens xj0 and xj0 + 32
+        const bool xin = xp < P;
+        const int64_t xbase = tokb * trow + (int64_t)h * P;               // uniform
+        int64_t xoff[2];
+#pragma unroll
+        for (int m = 0; m < 2; ++m) xoff[m] = (xj0 + 32 * m) * trow + (xin ? xp : 0);
+        const float dsk = D ? D[h] : 0.f;
+        const bool skip = D != nullptr;
+        const float2 *fe0 = reinterpret_cast<const float2 *>(tb.fe) + bhs * CB_STEP;
+        auto load_x = [&](int c, uint4 (&v)[2], float2 (&fe)[2]) __attribute__((always_inline)) {
+            c = min(c, c_end - 1);
+            const uint16_t *q = x + xbase + (int64_t)c * CB_STEP * trow;
+            const int last = t_end - 1 - c * CB_STEP;
+            int64_t o[2] = {xoff[0], xoff[1]};
+            if (last < CB_STEP - 1) {                    // a step that is not full
+#pragma unroll
+                for (int m = 0; m < 2; ++m) o[m] -= max(xj0 + 32 * m - last, 0) * trow;
+            }
+#pragma unroll
+            for (int m = 0; m < 2; ++m) {
+                v[m] = *reinterpret_cast<const uint4 *>(q + o[m]);
+                fe[m] = fe0[(int64_t)c * CB_STEP + xj0 + 32 * m];
+            }
+        };
+        const int sw = PT == 2 ? (xj0 & 3) : ((xj0 >> 1) & 1);
+        const int x_at = xj0 * XROW + (((xpc >> 1) ^ sw) << 5) + ((xpc & 1) << 4);
+        // x of step c (v) times its factor into LDS
+        auto stage_x = [&](int c, int at, const uint4 (&v)[2], const float2 (&fe)[2]) __attribute__((always_inline)) {
+#pragma unroll
+            for (int m = 0; m < 2; ++m) {
+                // channels past P and tokens past the end hold something else's x
+                const uint32_t k = (xin && c * CB_STEP + xj0 + 32 * m < t_end) ? ~0u : 0u;
+                float a[8];
+                unpack8(a, make_uint4(v[m].x & k, v[m].y & k, v[m].z & k, v[m].w & k));
+#pragma unroll
+                for (int q = 0; q < 8; ++q) a[q] *= fe[m].x;
+                *reinterpret_cast<uint4 *>(s_x + at * XB + x_at + m * 32 * XROW) = pack8(a);
+            }
+        };
+        const int ya0 = xj0 * (128 * PT) + ((xpc ^ (xj0 & YM)) << 4), ya1 = xj0 * (128 * PT) + (((xpc + 4 * PT) ^ (xj0 & YM)) << 4);
+        // stages step c + 2 (xn) and finishes step c - 1 (xo)
+        auto pass = [&](int c, int at, const uint4 (&xn)[2], const float2 (&fn)[2], const uint4 (&xo)[2], const float2 (&fo)[2]) __attribute__((always_inline)) {
+            const unsigned char *q = s_y + ((c - 1) & 1) * 2 * YB;
+            float4 v[2][4];
+#pragma unroll
+            for (int m = 0; m < 2; ++m) {
+                v[m][0] = *reinterpret_cast<const float4 *>(q + ya0 + m * 32 * 128 * PT);
+                v[m][1] = *reinterpret_cast<const float4 *>(q + YB + ya0 + m * 32 * 128 * PT);
+                v[m][2] = *reinterpret_cast<const float4 *>(q + ya1 + m * 32 * 128 * PT);
+                v[m][3] = *reinterpret_cast<const float4 *>(q + YB + ya1 + m * 32 * 128 * PT);
+            }
+            stage_x(c + 2, at, xn, fn);
+            uint16_t *yq = y + xbase + (int64_t)(c - 1) * CB_STEP * trow;
+            float r[2][8];
+#pragma unroll
+            for (int m = 0; m < 2; ++m)
+#pragma unroll
+                for (int k = 0; k < 2; ++k) {
+                    r[m][4 * k + 0] = (v[m][2 * k].x + v[m][2 * k + 1].x) * fo[m].y;
+                    r[m][4 * k + 1] = (v[m][2 * k].y + v[m][2 * k + 1].y) * fo[m].y;
+                    r[m][4 * k + 2] = (v[m][2 * k].z + v[m][2 * k + 1].z) * fo[m].y;
+                    r[m][4 * k + 3] = (v[m][2 * k].w + v[m][2 * k + 1].w) * fo[m].y;
+                }
+            if (skip) {
+#pragma unroll
+                for (int m = 0; m < 2; ++m) {
+                    float a[8];
+                    unpack8(a, xo[m]);
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) r[m][k] += dsk * a[k];
+                }
+            }
+#pragma unroll
+            for (int m = 0; m < 2; ++m)
+                if (xin && c > c_begin && (c - 1) * CB_STEP + xj0 + 32 * m < t_end) store_nt(yq + xoff[m], pack8(r[m]));
+        };
+        // x of step k in xr[(k - c_begin) % CB_RING]: loaded CB_RING - 4 steps before it is staged, kept until its y goes out
+        uint4 xr[CB_RING][2];
+        float2 fr[CB_RING][2];
+        const float4 *ref0 = reinterpret_cast<const float4 *>(tb.ref) + bhs + (lane & 0);
+        float4 rf[CB_RING];
+        auto load_ref = [&](int c) __attribute__((always_inline)) { return ref0[min(c, c_end - 1)]; };
+#pragma unroll
+        for (int u = 0; u < CB_RING - 1; ++u) load_x(c_begin + u, xr[u], fr[u]);
+        if (iow == 0) {
+#pragma unroll
+            for (int u = 0; u < CB_RING - 1; ++u) rf[u] = load_ref(c_begin + u);
+            if (lane == 0) { s_ref[0] = rf[0]; s_ref[1] = rf[1]; }
+        }
+        stage_x(c_begin, 0, xr[0], fr[0]);
+        stage_x(c_begin + 1, 1, xr[1], fr[1]);
+        lds_barrier();                                   // x of the first two steps
+        auto walk = [&](auto refs_) __attribute__((always_inline)) {
+            constexpr bool refs = decltype(refs_)::value;
+            for (int c0 = c_begin;; c0 += CB_RING) {
+#pragma unroll
+                for (int u = 0; u < CB_RING; ++u) {
+                    const int c = c0 + u;
+                    lds_barrier();
+                    pass(c, (u + 2) % 3, xr[(u + 2) % CB_RING], fr[(u + 2) % CB_RING], xr[(u + CB_RING - 1) % CB_RING], fr[(u + CB_RING - 1) % CB_RING]);
+                    if (c >= c_end) return;
+                    if (refs) {
+                        if (lane == 0) s_ref[(c + 2 - c_begin) & 3] = rf[(u + 2) % CB_RING];
+                        rf[(u + CB_RING - 1) % CB_RING] = load_ref(c + CB_RING - 1);
+                    }
+                    load_x(c + CB_RING - 1, xr[(u + CB_RING - 1) % CB_RING], fr[(u + CB_RING - 1) % CB_RING]);
+                }
+            }
+        };
+        if (iow == 0) walk(std::true_type{});
+        else walk(std::false_type{});
+    }
+}
+
+// scratch: operand images and tables
+size_t chain_bf16_ops_bytes(const Shape &s)
+{
+    const int NT = s.N > 64 ? 4 : s.N > 32 ? 2 : 1;
+    return (size_t)s.B * ((s.L + CB_STEP - 1) / CB_STEP) * s.G * cb_item_frags(NT) * 1024;
+}
+size_t chain_bf16_table_bytes(const Shape &s)
+{
+    return (size_t)s.B * s.H * ((s.L + CB_STEP - 1) / CB_STEP) * (4 * CB_STEP + 4) * sizeof(float);
+}
+
+template <int NT>
+static swimba_status launch_chain_t(const Shape &s, const void *x, const void *dt, const float *A, const float *D,
+                                    const void *Be, const void *Ce, const void *logits, const float *w_sel, const float *h0,
+                                    void *y, float *h_final, int32_t *idx, float *w, void *ops, float *tables, hipStream_t st)
+{
+    const int nsteps = (s.L + CB_STEP - 1) / CB_STEP, ncu = device_cus();
+    auto mix_shm = [](int K, int E) { return (size_t)2 * CB_STEP * (64 * NT + 16) + (size_t)CB_STEP * K * 8 + (E ? (size_t)CB_STEP * (E | 1) * 4 : 0); };
+    auto chain_shm = [](int PT) { return (size_t)11 * CB_STEP * 64 * PT + 64; };
+    // more than 64 KB of dynamic LDS has to be allowed once per device
+    static std::atomic<uint64_t> attr_set{0};            // one bit per device ordinal
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) { set_last_hip_error((int)e); return SWIMBA_ERR_HIP; }
+    const uint64_t bit = 1ull << (dev & 63);
+    if (!(attr_set.load(std::memory_order_acquire) & bit)) {
+        e = hipFuncSetAttribute((const void *)mix_steps_kernel<NT>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)mix_shm(SWIMBA_MAX_TOPK, SWIMBA_MAX_EXPERTS));
+        if (e == hipSuccess) e = hipFuncSetAttribute((const void *)chain_bf16_kernel<NT, 1>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)chain_shm(1));
+        if (e == hipSuccess) e = hipFuncSetAttribute((const void *)chain_bf16_kernel<NT, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)chain_shm(2));
+        if (e != hipSuccess) { set_last_hip_error((int)e); return SWIMBA_ERR_HIP; }
+        attr_set.fetch_or(bit, std::memory_order_release);
+    }
+    // A workgroup routes its tokens once for as many groups as leave two workgroups to a compute unit.
+    int gpb = 1;
+    for (int n = 2; n <= s.G; ++n)
+        if (s.G % n == 0 && (int64_t)s.B * nsteps * s.G / n >= 2 * (int64_t)ncu) gpb = n;
+    const int items = (int)((int64_t)s.B * nsteps * s.G / gpb);
+    const int64_t bhs = (int64_t)s.B * s.H * nsteps;
+    const ChainTables tb = {tables, tables + bhs * 2 * CB_STEP, tables + bhs * (2 * CB_STEP + 4)};
+    const int tblocks = (int)(((int64_t)s.B * nsteps * ((s.H + 7) / 8) + 7) / 8);
+    hipLaunchKernelGGL(mix_steps_kernel<NT>, dim3(items + tblocks), dim3(CB_MIX_THREADS), mix_shm(s.K, w_sel ? 0 : s.E), st,
+                       (const bf16 *)Be, (const bf16 *)Ce, (const bf16 *)logits, idx, w, w_sel, (uint16_t *)ops,
+                       (const bf16 *)dt, A, tb, s, nsteps, gpb, items);
+    SWIMBA_CHECK_LAUNCH();
+    // Both channel tiles of a head in one workgroup (one to a compute unit) where the heads fill at least three fifths of
+    // their rounds; else a workgroup per tile, two to a unit.
+    const int64_t chains = (int64_t)s.B * s.H, rounds = (chains + ncu - 1) / ncu;
+    const int PT = s.P > 32 && 10 * chains >= 6 * rounds * ncu ? 2 : 1;
+    const int nslice = (s.P + 32 * PT - 1) / (32 * PT);
+    const int total = s.B * s.H * nslice, nblocks = xcd_padded(total);
+    hipLaunchKernelGGL((PT == 2 ? chain_bf16_kernel<NT, 2> : chain_bf16_kernel<NT, 1>), dim3(nblocks), dim3(256 * PT), chain_shm(PT),
+                       st, (const uint16_t *)x, D, (const uint16_t *)ops, tb, h0, h_final, (uint16_t *)y, s, nsteps, nslice, 1,
+                       nsteps, total, nblocks);
+    SWIMBA_CHECK_LAUNCH();
+    return SWIMBA_OK;
+}
+
+swimba_status launch_chain_bf16(const Shape &s, const void *x, const void *dt, const float *A, const float *D, const void *Be,
+                                const void *Ce, const void *logits, const float *w_sel, const float *h0, void *y,
+                                float *h_final, int32_t *idx, float *w, void *ops, float *tables, hipStream_t st)
+{
+    auto launch = s.N > 64 ? launch_chain_t<4> : s.N > 32 ? launch_chain_t<2> : launch_chain_t<1>;
+    return launch(s, x, dt, A, D, Be, Ce, logits, w_sel, h0, y, h_final, idx, w, ops, tables, st);
+}
+
+}  // namespace swimba

@@ -48,23 +48,6 @@ __device__ __forceinline__ f32x16_t mfma_f32(float a, float b, f32x16_t c)
     return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
 }
 
-// Inclusive sum over the 64 lanes in register moves (DPP): four shifted additions inside rows of 16, then the last
-// lane of a row onto the next one and of the lower half onto the upper.  No LDS pass: one wave scans while the
-// others wait at the step's barrier, and six shuffles would cost it six LDS latencies.
-__device__ __forceinline__ float wave_scan(float v)
-{
-#define CF_SCAN(ctrl, rows)                                                                                              \
-    v += __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), ctrl, rows, 0xf, false))
-    CF_SCAN(0x111, 0xf);   // row_shr:1
-    CF_SCAN(0x112, 0xf);   // row_shr:2
-    CF_SCAN(0x114, 0xf);   // row_shr:4
-    CF_SCAN(0x118, 0xf);   // row_shr:8
-    CF_SCAN(0x142, 0xa);   // row_bcast:15 into rows 1 and 3
-    CF_SCAN(0x143, 0xc);   // row_bcast:31 into rows 2 and 3
-#undef CF_SCAN
-    return v;
-}
-
 // four consecutive elements as fp32
 __device__ __forceinline__ float4 load4(const float *p) { return *reinterpret_cast<const float4 *>(p); }
 __device__ __forceinline__ float4 load4(const bf16 *p)

@@ -86,6 +86,23 @@ __device__ __forceinline__ float fast_exp2(float v) { return __builtin_amdgcn_ex
 
 constexpr float LOG2E = 1.4426950408889634f;
 
+// Inclusive sum over the 64 lanes in register moves (DPP): four shifted additions inside rows of 16, then the last
+// lane of a row onto the next one and of the lower half onto the upper.  No LDS pass: one wave scans while the
+// others wait at the step's barrier, and six shuffles would cost it six LDS latencies.
+__device__ __forceinline__ float wave_scan(float v)
+{
+#define WAVE_SCAN_STEP(ctrl, rows)                                                                                              \
+    v += __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), ctrl, rows, 0xf, false))
+    WAVE_SCAN_STEP(0x111, 0xf);   // row_shr:1
+    WAVE_SCAN_STEP(0x112, 0xf);   // row_shr:2
+    WAVE_SCAN_STEP(0x114, 0xf);   // row_shr:4
+    WAVE_SCAN_STEP(0x118, 0xf);   // row_shr:8
+    WAVE_SCAN_STEP(0x142, 0xa);   // row_bcast:15 into rows 1 and 3
+    WAVE_SCAN_STEP(0x143, 0xc);   // row_bcast:31 into rows 2 and 3
+#undef WAVE_SCAN_STEP
+    return v;
+}
+
 // =========================================================================================
 // cb tile of one wave: pair p = I(I+1)/2 + J, J <= I, of one (batch, chunk, group):
 //   cb (B, nc, G, NP, 2, 64, 8) bf16: the accumulator registers v = 8t..8t+7 of lane l

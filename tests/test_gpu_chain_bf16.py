@@ -1,0 +1,126 @@
+"""The walk over 64-token steps behind the bf16 forwards: edges of steps and tiles, padded sizes, routing options, the three
+ways a step's decays are split over its tokens (one reference, one per half, direct), and that none of them is seen by the
+tokens in front."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import swimba_oracle as orc
+from paper_2603_06938_amd import binding as sw
+from paper_2603_06938_amd import synth
+from gpu_util import TOL, abs_inputs, comp_tol, componentwise_excess, host, rel_errors, to_device
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # B, L, H, P, N, G, E, k, h0, D, factor on dt
+    (1, 1, 1, 64, 128, 1, 2, 1, False, True, 1.0),
+    (2, 31, 2, 32, 32, 1, 4, 2, True, True, 1.0),
+    (2, 63, 4, 64, 128, 2, 8, 2, True, False, 1.0),
+    (1, 64, 2, 64, 64, 1, 8, 2, False, True, 1.0),
+    (3, 65, 3, 40, 72, 1, 5, 3, True, True, 1.0),
+    (2, 96, 2, 8, 8, 2, 4, 2, True, True, 1.0),
+    (1, 129, 8, 64, 16, 8, 16, 2, False, True, 1.0),
+    (2, 200, 4, 56, 40, 1, 64, 4, True, True, 1.0),
+    (1, 577, 2, 64, 128, 1, 8, 2, True, True, 1.0),
+    (2, 448, 160, 64, 128, 4, 4, 2, True, True, 1.0),     # 320 chains: a workgroup per channel tile, several groups each
+    (1, 300, 160, 48, 104, 1, 4, 1, True, True, 1.0),     # 160 chains: both channel tiles in one workgroup
+    (2, 333, 4, 64, 128, 2, 5, 2, True, True, 4.0),       # a reference per half for the fast heads
+    (2, 333, 4, 64, 128, 2, 5, 2, True, True, 40.0),      # mostly direct
+    (1, 190, 160, 64, 128, 2, 5, 2, True, True, 10.0),    # all three
+    (2, 333, 4, 64, 48, 2, 5, 2, True, True, 1e-3),
+]
+
+
+def inputs(case, seed):
+    B, L, H, P, N, G, E, k, with_h0, with_D, dt_scale = case
+    w = synth.Workload("chain", B, L, H, P, N, G, E, k, 64, "bf16", 9)
+    p = synth.make_inputs(w, seed=seed)
+    # scaled step sizes, rounded to bf16 here so that both sides see the same values
+    p["dt"] = torch.from_numpy(p["dt"] * np.float32(dt_scale)).to(torch.bfloat16).to(torch.float32).numpy()
+    rng = np.random.default_rng(seed)
+    p["D"] = rng.standard_normal(H).astype(np.float32)
+    h0 = (0.1 * rng.standard_normal((B, H, P, N))).astype(np.float32) if with_h0 else None
+    return p, h0
+
+
+def forward(p, k, h0, with_D, chunk=64):
+    d = to_device(p, "bf16")
+    return sw.swimba_mixer_fwd(d["x"], d["dt"], d["A"], d["D"] if with_D else None, d["B_experts"], d["C_experts"],
+                               d["router_logits"], k, chunk, None if h0 is None else torch.from_numpy(h0).to("cuda:0"),
+                               want_topk=True)
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "B%dL%dH%dP%dN%dG%dE%dk%d_h0%d_D%d_dt%g" % c)
+def test_chain_matches_oracle(case):
+    B, L, H, P, N, G, E, k, with_h0, with_D, dt_scale = case
+    p, h0 = inputs(case, 100 + CASES.index(case))
+    D = p["D"] if with_D else None
+    out = forward(p, k, h0, with_D)
+    torch.cuda.synchronize()
+    ref = orc.mixer_fwd(p["x"], p["dt"], p["A"], D, p["B_experts"], p["C_experts"], p["router_logits"], k, h0=h0)
+    np.testing.assert_array_equal(out.topk_idx.cpu().numpy(), ref["topk_idx"])
+    np.testing.assert_allclose(host(out.topk_w), ref["topk_w"], rtol=1e-5, atol=1e-30)
+    q = abs_inputs(p)
+    aref = orc.mixer_fwd(q["x"], q["dt"], q["A"], None if D is None else np.abs(D), q["B_experts"], q["C_experts"],
+                         q["router_logits"], k, h0=None if h0 is None else np.abs(h0))
+    # every term passes at most five roundings to bf16: B, x times its factor, the state, C (or C B^T), the stored y
+    ey = componentwise_excess(host(out.y), ref["y"], aref["y"])
+    eh = componentwise_excess(host(out.h_final), ref["h_final"], aref["h_final"])
+    assert ey <= comp_tol("bf16") and eh <= comp_tol("bf16"), (ey, eh)
+    if L >= 16:
+        l2, linf = rel_errors(host(out.y), ref["y"], (0, 2))
+        assert l2 <= TOL["bf16"] and linf <= TOL["bf16"], (l2, linf)
+    # the chunk length of the call is not the chain's: the same bits
+    other = forward(p, k, h0, with_D, 256)
+    assert torch.equal(other.y, out.y) and torch.equal(other.h_final, out.h_final)
+
+
+def test_decays_that_turn_and_growing_states():
+    """dt of both signs (cs falls and rises inside a step) and of the negative one alone (the state grows)"""
+    p, h0 = inputs((2, 200, 4, 64, 128, 1, 4, 2, True, True, 1.0), 7)
+    rng = np.random.default_rng(8)
+    turned = np.where(rng.random(p["dt"].shape) < 0.3, -0.25, 1.0).astype(np.float32)
+    for f in (turned, np.float32(-0.03)):
+        r = dict(p, dt=torch.from_numpy(p["dt"] * f).to(torch.bfloat16).to(torch.float32).numpy())
+        out = forward(r, 2, h0, True)
+        ref = orc.mixer_fwd(r["x"], r["dt"], r["A"], r["D"], r["B_experts"], r["C_experts"], r["router_logits"], 2, h0=h0)
+        l2, linf = rel_errors(host(out.y), ref["y"], (0, 2))
+        hl2, hlinf = rel_errors(host(out.h_final), ref["h_final"], (0, 1))
+        assert max(l2, linf, hl2, hlinf) <= TOL["bf16"], (l2, linf, hl2, hlinf)
+
+
+@pytest.mark.parametrize("s", [5, 31, 32, 40, 50, 64, 100])
+def test_a_reference_changes_no_bit_in_front(s):
+    """Larger step sizes from token s on take a step from one reference to two: tokens in front keep their bits."""
+    p, h0 = inputs((1, 128, 24, 64, 128, 1, 4, 2, True, True, 1.0), 3)
+    p["A"][::2] = -16.0
+    bf = lambda v: torch.from_numpy(v.astype(np.float32)).to(torch.bfloat16).to(torch.float32).numpy()
+    t = np.arange(128) % 64
+    rng = np.random.default_rng(4)
+    p["dt"] = bf(np.where(t < 32, 0.08, 0.04)[None, :, None] * (1 + 0.05 * rng.random((1, 128, 24))))
+    dt = p["dt"].copy()
+    dt[:, s:] = bf(0.145 * (1 + 0.05 * rng.random((1, 128 - s, 24))))
+    step = 0 if s < 64 else 64
+    span = lambda d, lo, hi: d[0, step + lo:step + hi, ::2].sum(0) * 16 * 1.4427
+    assert span(p["dt"], 0, 64).max() < 118 and span(dt, 0, 64).min() > 122
+    assert span(dt, 0, 32).max() < 118 and span(dt, 32, 64).max() < 118
+    base = forward(p, 2, h0, True).y
+    got = forward(dict(p, dt=dt), 2, h0, True).y
+    assert torch.equal(got[:, :s], base[:, :s]) and not torch.equal(got[:, s:], base[:, s:])
+
+
+@pytest.mark.parametrize("value", [float("nan"), float("inf")])
+def test_values_that_are_not_finite_reach_no_earlier_tile(value):
+    """A dt or x that is not finite leaves the tokens of the 32-token tiles in front of its own alone."""
+    p, h0 = inputs((1, 192, 4, 64, 128, 1, 4, 2, True, True, 1.0), 5)
+    base = forward(p, 2, h0, True).y
+    for name in ("dt", "x"):
+        q = dict(p)
+        q[name] = p[name].copy()
+        q[name][0, 100, 1] = value
+        got = forward(q, 2, h0, True)
+        assert torch.isfinite(got.y[:, :64]).all() and torch.equal(got.y[:, :64], base[:, :64])
+        assert torch.isfinite(got.y[:, :96, 1]).all()
+        assert torch.equal(got.y[:, :, [0, 2, 3]], base[:, :, [0, 2, 3]])
+        assert not torch.isfinite(got.y[:, 100:, 1]).all()
