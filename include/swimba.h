@@ -201,7 +201,7 @@ swimba_status swimba_stage_pass(const swimba_dims *dims, const void *x, const vo
 
 /* How the stage calls evaluate these dims best on the current device.  swimba_mixer_fwd (and the
  * _selected/_proj forms) run the kernels named here for few (batch, head) pairs with long sequences; everywhere
- * else in bf16 they walk 64-token steps in two launches of their own, which no stage call splits.
+ * else in bf16 they walk 64-token steps in two or three launches of their own, which no stage call splits.
  * SWIMBA_PATH_GENERIC (fp32-capable kernels, any shape), SWIMBA_PATH_STAGED
  * (bf16 MFMA: mix, chunk_state, state_scan, output; SWIMBA_PATH_STAGED_SHORT for at most 8 chunks,
  * see below), or a single pass over the chunks with the

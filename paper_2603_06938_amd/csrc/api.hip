@@ -199,20 +199,20 @@ static bool use_chunk_mix(const swimba_dims *d, bool selected)
     return mix_chunk_covers(s, selected) && (int64_t)s.B * s.nc * s.G >= 2 * (int64_t)device_cus();
 }
 
-// The bf16 forward as one walk over 64-token steps (chain_bf16.hip), two launches; its scratch lies over cmix .. cb and
-// states_lp.  A chain's steps are serial, 0.7 us each (two workgroups to a compute unit) to 1.5 (all units busy): ahead of the
-// kernels above everywhere up to 16 steps (8 to 1024 chains, 64 to 1024 tokens: 0.5 to 0.98 of their time; 8 chains of 1024
-// tokens 22.5 / 23.0 us), from 96 chains on up to 128 (96 chains of 8192 tokens 142 / 157) and where the chains fill three
-// fifths of their rounds at any length (256 of 4096 tokens 122 / 147); 128 chains of 256 steps 401 / 392, 48 of 32 steps
-// 34.0 / 34.9, of 64 56.3 / 52.6; 24 of 32 33.3 / 28.8.  Short of that the kernels that also parallelise over chunks or cut
-// the sequence stay ahead.
+// The bf16 forward as one walk over 64-token steps (chain_bf16.hip), two launches, or three where it cuts the sequence; its
+// scratch lies over cmix .. cb, states_lp, hmid and cs.  A chain's steps are serial, 0.7 us each (two workgroups to a compute unit)
+// to 1.6 (all units busy): ahead of the kernels above everywhere up to 16 steps (8 to 1024 chains, 64 to 1024 tokens: 0.5 to
+// 0.98 of their time; 8 chains of 1024 tokens 22.5 / 23.0 us), from 40 chains on up to 24 and from 64 on up to 32 (48 chains of 32
+// steps, 4 groups: 37.8 / 35.9), from 96 chains on up to 128 (96 chains of 6000 tokens 89 / 110) and where the chains fill
+// three fifths of their rounds at any length (256 of 4096 tokens 122 / 147), or where segments do (chain_bf16_segments).
+// Short of that the kernels that also parallelise over chunks stay ahead.
 static bool use_chain_bf16(const swimba_dims *d)
 {
     if (!use_mfma_path(d)) return false;
     const int64_t chains = (int64_t)d->batch * d->nheads, steps = ((int64_t)d->seqlen + 63) / 64, ncu = device_cus();
     const int64_t rounds = (chains + ncu - 1) / ncu;
-    return steps <= 16 || (steps <= 32 && 32 * chains >= 5 * ncu) || (steps <= 128 && 8 * chains >= 3 * ncu) ||
-           10 * chains >= 6 * rounds * ncu;
+    return steps <= 16 || (steps <= 24 && 32 * chains >= 5 * ncu) || (steps <= 32 && 4 * chains >= ncu) ||
+           (steps <= 128 && 8 * chains >= 3 * ncu) || 10 * chains >= 6 * rounds * ncu || chain_bf16_segments(chains, steps, ncu) > 1;
 }
 
 struct Ws {
@@ -223,6 +223,7 @@ struct Ws {
     void *states_lp, *cmix, *bmix_t8, *bmix_frag, *cb;
     float *cs2, *fdec, *cdec, *hmid;
     float *cop, *bop, *gop, *hseg, *aseg, *hinit;   // fp32 chain
+    ChainScratch chain;                             // bf16 chain
 };
 
 static swimba_status carve(const swimba_dims *d, void *workspace, size_t bytes, Ws *ws)
@@ -248,6 +249,11 @@ static swimba_status carve(const swimba_dims *d, void *workspace, size_t bytes, 
     ws->fdec = mf ? (float *)(p + lo.fdec) : nullptr;
     ws->cdec = mf ? (float *)(p + lo.cdec) : nullptr;
     ws->hmid = mf ? (float *)(p + lo.hmid) : nullptr;
+    if (mf) {
+        const size_t tables = align_up(chain_bf16_table_bytes(make_shape(d)), 256);
+        ws->chain = {ws->cmix, ws->states_lp, (float *)(p + lo.states_lp + tables), ws->hmid, lo.cmix - lo.states_lp - tables,
+                     lo.total - lo.hmid, ws->cs};
+    }
     ws->cop = mf ? nullptr : (float *)(p + cf.cop);
     ws->bop = mf ? nullptr : (float *)(p + cf.bop);
     ws->gop = mf ? nullptr : (float *)(p + cf.gop);
@@ -588,8 +594,8 @@ swimba_status swimba_mixer_fwd(const swimba_dims *dims, const void *x, const voi
                                     ws.hseg, ws.aseg, ws.hinit, stream);
         if (use_chain_bf16(dims))
             return launch_chain_bf16(s, x, dt, A, D, B_experts, C_experts, router_logits, nullptr, h0, y, h_final,
-                                     topk_idx ? topk_idx : ws.idx, topk_w ? topk_w : ws.w, ws.cmix, (float *)ws.states_lp,
-                                     stream);
+                                     topk_idx ? topk_idx : ws.idx, topk_w ? topk_w : ws.w, ws.chain,
+                                     head64_segments(dims) > 1, stream);
         // On the bf16 MFMA path the mix kernel routes the tokens itself and the chunk-state
         // kernel computes the cumsum itself: two launches fewer.
         const bool chunk_mix = use_chunk_mix(dims, false);
@@ -1081,8 +1087,8 @@ static swimba_status mixer_selected_core(const swimba_dims *dims, const void *x,
     swimba_status st;
     if (T > 0) {
         if (mf && use_chain_bf16(dims))
-            return launch_chain_bf16(s, x, dt, A, D, B_sel, C_sel, nullptr, w_sel, h0, y, h_final, nullptr, nullptr, ws.cmix,
-                                     (float *)ws.states_lp, stream);
+            return launch_chain_bf16(s, x, dt, A, D, B_sel, C_sel, nullptr, w_sel, h0, y, h_final, nullptr, nullptr, ws.chain,
+                                     head64_segments(dims) > 1, stream);
         if (mf) {
             const bool chunk_mix = use_chunk_mix(dims, true);
             st = chunk_mix ? launch_mix_chunk_mfma(s, B_sel, C_sel, nullptr, nullptr, nullptr, ws.cmix, ws.bmix_t8,

@@ -13,6 +13,8 @@
 // bf16 are the A operand of the readout as they are; 19 MFMAs each per step (N = 128).  The halves' partial Y meet in LDS.  I/O
 // waves load x three steps ahead, write x~ into LDS two steps ahead, and finish and store Y one step behind; one LDS-only
 // barrier a step.  ds_read_b64_tr_b16 transposes x~ (and, in the mix kernel, B) on the way out of LDS.
+// Too few chains to fill the chip: a sequence is walked as segments, whose initial states come from a launch in front of the
+// chain (ChainPieces, chain_bf16_segments).
 //
 // Against the staged kernels and the per-head pass over whole chunks (two to five launches, G scaled element by element per
 // head, x and chunk states more than once through memory): 130M-shaped layer 76.7 -> 57.7 us, 370M-shaped layer
@@ -23,6 +25,7 @@
 #include "common.hpp"
 #include "mfma_util.hpp"
 
+#include <algorithm>
 #include <atomic>
 #include <type_traits>
 
@@ -56,7 +59,8 @@ __host__ __device__ constexpr int cb_item_frags(int NT) { return 8 * NT + 6; }
 
 // Per (batch, head, step), written by the mix launch (cs: inclusive sum of log2 e dt A from the step's first token):
 //   fe  (B, H, nsteps, 64, 2)  factor of x, dt_j 2^(R - cs_j), and of y, 2^(cs_i - R)
-//   ref (B, H, nsteps, 4)      mode and references (pack_ref); 2^(fraction of cs_last); 2^(R1 - R0) or, of a direct step, 2^cs_last
+//   ref (B, H, nsteps, 4)      mode and references (pack_ref); 2^(fraction of cs_last); 2^(R1 - R0) or, of a direct step, 2^cs_last;
+//                              cs_last
 //   cd  (B, H, nsteps, 64, 2)  cs_j and dt_j, of direct steps alone
 // With a reference R in the middle of the step's range, 2^(cs_i - cs_j) dt_j is a factor of token j times a factor of token i,
 // both far from the ends of the exponent range: no element of the masked products needs a factor of its own, and the state is
@@ -97,7 +101,7 @@ __device__ __forceinline__ void chain_table(const ChainTables &t, int64_t bhs, f
     const float whole = rintf(cs), part = cs - whole, last_whole = rintf(last);
     const float R = lane < 32 ? R0 : R1;
     float2 fe = make_float2(d * fast_exp2(last - cs), 1.f);
-    float4 ref = make_float4(0.f, 1.f, fast_exp2(last), 0.f);
+    float4 ref = make_float4(0.f, 1.f, fast_exp2(last), last);
     int pack = pack_ref(2, 0, 0);
     if (mode != 2) {
         fe.x = ldexpf(d * fast_exp2(-part), (int)(R - whole));
@@ -260,11 +264,36 @@ mix_steps_kernel(const bf16 *__restrict__ Be, const bf16 *__restrict__ Ce, const
     }
 }
 
-template <int NT, int PT>
+// 2^e, also where it is no normal number, times v
+__device__ __forceinline__ float scale_exp2(float v, float frac, int whole) { return ldexpf(v * frac, whole); }
+__device__ __forceinline__ void split_exp2(float e, float &frac, int &whole)
+{
+    const float c = e != e ? e : fminf(fmaxf(e, -1000.f), 1000.f), w = rintf(c);
+    frac = fast_exp2(c - w);
+    whole = (int)w;
+}
+
+// A sequence walked as segments.  A first launch (OUT = false: the state part alone) walks pieces of the segments in front of
+// the last from a zero state, pieces to a segment, and writes what each leaves behind; a segment of the output launch starts from
+// their sum, each decayed to its first token (the recurrence is linear in the state).
+//   piece(q) (B, H, P tiles, NT, 4, 64, 4) fp32 accumulator registers; the first n_a pieces lie in a, the others in b
+//   sum (B, H, npiece, 2)  log2 of a piece's decay; 1 where the piece is written.  With skip set one whose factor up to the
+//                          segment's end is under 2^-150, which no fp32 sum sees, is not walked.
+struct ChainPieces {
+    float *a, *b, *sum, *h0_copy;
+    int npiece, n_a, per_seg, steps, skip;
+};
+__device__ __forceinline__ float4 *piece_frag(const ChainPieces &pc, int64_t bh, int64_t nbh, int q, int ptiles, int ptile, int NT)
+{
+    float *base = q < pc.n_a ? pc.a + (q * nbh + bh) * (int64_t)(ptiles * NT * 1024) : pc.b + ((q - pc.n_a) * nbh + bh) * (int64_t)(ptiles * NT * 1024);
+    return reinterpret_cast<float4 *>(base + ptile * NT * 1024);
+}
+
+template <int NT, int PT, bool OUT>
 __global__ void __launch_bounds__(256 * PT, 2)
 chain_bf16_kernel(const uint16_t *__restrict__ x, const float *__restrict__ D, const uint16_t *__restrict__ ops, ChainTables tb,
                   const float *h0, float *h_final, uint16_t *__restrict__ y, Shape s, int nsteps, int nslice, int nseg,
-                  int steps_per_seg, int total, int nblocks)
+                  int steps_per_seg, int hblock, ChainPieces pieces, int total, int nblocks)
 {
     constexpr int NTS = NT > 1 ? NT / 2 : 1;             // state tiles per compute wave
     constexpr int NW = 2 * PT;                           // compute waves; as many i/o waves
@@ -275,13 +304,15 @@ chain_bf16_kernel(const uint16_t *__restrict__ x, const float *__restrict__ D, c
     extern __shared__ __align__(16) unsigned char smem_raw[];
     unsigned char *s_x = smem_raw;                       // [3] x rows times f, bf16
     unsigned char *s_y = s_x + 3 * XB;                   // [2][2] partial Y by halves of the state columns, fp32
-    float4 *s_ref = reinterpret_cast<float4 *>(s_y + 4 * YB);       // [4] references of a step
+    float4 *s_ref = reinterpret_cast<float4 *>(s_y + (OUT ? 4 * YB : 0));       // [4] references of a step
 
     const int lid = xcd_logical_id(blockIdx.x, nblocks);
     if (lid >= total) return;
-    const int sl = lid % nslice;
-    const int h = (lid / nslice) % s.H;
-    const int seg = (lid / (nslice * s.H)) % nseg;
+    // consecutive ids, which share an XCD: the slices, heads and segments of a sequence, innermost first; of pieces hblock heads,
+    // then the pieces, then the other heads, so that every XCD gets near and far ones of those that are not walked
+    const int sl = lid % nslice, hl = lid / nslice % hblock;
+    const int seg = lid / (nslice * hblock) % nseg;
+    const int h = lid / (nslice * hblock * nseg) % (s.H / hblock) * hblock + hl;
     const int b = lid / (nslice * s.H * nseg);
     const int g = (h * s.G) / s.H;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -292,6 +323,26 @@ chain_bf16_kernel(const uint16_t *__restrict__ x, const float *__restrict__ D, c
     const int p0 = 32 * PT * sl, P = s.P;
     const int64_t tokb = (int64_t)b * s.L, trow = (int64_t)s.H * P;
     const int64_t bhs = ((int64_t)b * s.H + h) * nsteps;
+    const int64_t bh = (int64_t)b * s.H + h, nbh = (int64_t)s.B * s.H;
+    const int ptiles = (P + 31) / 32;
+
+    if (!OUT) {
+        if (seg == 0 && pieces.h0_copy)                  // of this workgroup's channels
+            for (int i = tid; i < min(32 * PT, P - p0) * s.N / 4; i += 256 * PT)
+                reinterpret_cast<float4 *>(pieces.h0_copy + (bh * P + p0) * s.N)[i] = reinterpret_cast<const float4 *>(h0 + (bh * P + p0) * s.N)[i];
+        // decay of this piece, and from its end to the end of its segment
+        const float4 *ref = reinterpret_cast<const float4 *>(tb.ref) + bhs;
+        const int s_end = (seg / pieces.per_seg + 1) * pieces.per_seg * pieces.steps;
+        float own = 0.f, after = 0.f;
+        for (int c = c_begin + lane; c < c_end; c += 64) own += ref[c].w;
+        if (pieces.skip)
+            for (int c = c_end + lane; c < s_end; c += 64) after += ref[c].w;
+        own = lane_value(wave_scan(own), 63);
+        after = lane_value(wave_scan(after), 63);
+        const bool dead = pieces.skip && after < -150.f;
+        if (sl == 0 && tid == 0) reinterpret_cast<float2 *>(pieces.sum)[bh * pieces.npiece + seg] = make_float2(own, dead ? 0.f : 1.f);
+        if (dead) return;
+    }
 
     // ================= compute waves: 32 channels x half of the state columns =================
     auto compute_wave = [&](auto nh_) __attribute__((always_inline)) {
@@ -334,8 +385,10 @@ chain_bf16_kernel(const uint16_t *__restrict__ x, const float *__restrict__ D, c
 #pragma unroll
                 for (int ks = 0; ks < 4; ++ks) bfr[k][ks] = src[(4 * NT + (nt0 + k) * 4 + ks) * 64];
         };
-        load_c(c_begin);
-        load_g(c_begin);
+        if (OUT) {
+            load_c(c_begin);
+            load_g(c_begin);
+        }
         load_b(c_begin);
         f32x16_t st[NTS];
         const int64_t hoff = (((int64_t)b * s.H + h) * P + min(p, P - 1)) * s.N;
@@ -345,9 +398,60 @@ chain_bf16_kernel(const uint16_t *__restrict__ x, const float *__restrict__ D, c
             for (int q = 0; q < 4; ++q) {
                 const int n = 32 * (nt0 + k) + 8 * q + 4 * hi;
                 float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-                if (h0 && p < P && n < s.N) v = *reinterpret_cast<const float4 *>(h0 + hoff + n);
+                if (OUT && h0 && p < P && n < s.N) v = *reinterpret_cast<const float4 *>(h0 + hoff + n);
                 st[k][4 * q] = v.x; st[k][4 * q + 1] = v.y; st[k][4 * q + 2] = v.z; st[k][4 * q + 3] = v.w;
             }
+        if (OUT && seg > 0) {
+            // lane l: the piece l pieces in front of the segment's first step, and its factor
+            const int np = seg * pieces.per_seg;
+            float2 sum = make_float2(0.f, 0.f);
+            if (lane < np) sum = reinterpret_cast<const float2 *>(pieces.sum)[bh * pieces.npiece + np - 1 - lane];
+            const float upto = wave_scan(sum.x);
+            float e = __shfl_up(upto, 1);
+            if (lane == 0) e = 0.f;
+            uint64_t todo = __ballot(sum.y != 0.f && !(pieces.skip && e < -150.f));
+            float frac;
+            int whole;
+            split_exp2(lane_value(upto, 63), frac, whole);
+#pragma unroll
+            for (int k = 0; k < NTS; ++k)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) st[k][v] = scale_exp2(st[k][v], frac, whole);
+            auto add = [&](int i, const float4 (&v)[NTS][4]) __attribute__((always_inline)) {
+                split_exp2(lane_value(e, i), frac, whole);
+#pragma unroll
+                for (int k = 0; k < NTS; ++k)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        st[k][4 * q + 0] += scale_exp2(v[k][q].x, frac, whole);
+                        st[k][4 * q + 1] += scale_exp2(v[k][q].y, frac, whole);
+                        st[k][4 * q + 2] += scale_exp2(v[k][q].z, frac, whole);
+                        st[k][4 * q + 3] += scale_exp2(v[k][q].w, frac, whole);
+                    }
+            };
+            auto fetch = [&](int i, float4 (&v)[NTS][4]) __attribute__((always_inline)) {
+                const float4 *src = piece_frag(pieces, bh, nbh, np - 1 - i, ptiles, min(sl * PT + ph, ptiles - 1), NT) + nt0 * 256 + lane;
+#pragma unroll
+                for (int k = 0; k < NTS; ++k)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) v[k][q] = src[(k * 4 + q) * 64];
+            };
+            while (on && todo) {                         // two pieces in flight
+                float4 v0[NTS][4], v1[NTS][4];
+                const int i0 = 63 - __builtin_clzll(todo);
+                todo &= ~(1ull << i0);
+                fetch(i0, v0);
+                if (todo) {
+                    const int i1 = 63 - __builtin_clzll(todo);
+                    todo &= ~(1ull << i1);
+                    fetch(i1, v1);
+                    add(i0, v0);
+                    add(i1, v1);
+                } else {
+                    add(i0, v0);
+                }
+            }
+        }
         f32x16_t yt[2];
         // the state to the reference of a step, and its share of that step's Y (two tiles of 32 tokens)
         auto readout = [&](float sc) __attribute__((always_inline)) {
@@ -372,8 +476,10 @@ chain_bf16_kernel(const uint16_t *__restrict__ x, const float *__restrict__ D, c
         lds_barrier();                                   // x and references of the first two steps
         float4 rc = s_ref[0];
         int pc = __builtin_amdgcn_readfirstlane(__float_as_int(rc.x));
-        readout(ldexpf(1.f, ref_r0(pc)));
-        load_c(c_begin + 1);
+        if (OUT) {
+            readout(ldexpf(1.f, ref_r0(pc)));
+            load_c(c_begin + 1);
+        }
         read_x(s_x, 0, 4);
         unsigned char *y_wr = s_y + nh * YB + l32 * (128 * PT);
         int slot = 0;                                    // of x
@@ -383,6 +489,12 @@ chain_bf16_kernel(const uint16_t *__restrict__ x, const float *__restrict__ D, c
             const int mode = ref_mode(pc);
             if (__builtin_expect(mode == 2, 0)) {
                 // a direct step: its masked products one decay at a time, on x as it is
+#pragma unroll
+                for (int k = 0; k < NTS; ++k)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) st[k][v] *= rc.z;
+            }
+            if (OUT && __builtin_expect(mode == 2, 0)) {
                 const float2 *cd = reinterpret_cast<const float2 *>(tb.cd) + (bhs + c) * CB_STEP;
                 const float ci[2] = {cd[l32].x, cd[32 + l32].x};
 #pragma unroll
@@ -391,10 +503,6 @@ chain_bf16_kernel(const uint16_t *__restrict__ x, const float *__restrict__ D, c
 #pragma unroll
                     for (int v = 0; v < 16; ++v) yt[it][v] *= ei;
                 }
-#pragma unroll
-                for (int k = 0; k < NTS; ++k)
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) st[k][v] *= rc.z;
 #pragma unroll
                 for (int k = 0; k < 3; ++k) {
                     const int f = 3 * nh + k, it = f >= 2, ks = it ? f - 2 : f;
@@ -429,8 +537,10 @@ chain_bf16_kernel(const uint16_t *__restrict__ x, const float *__restrict__ D, c
                 *reinterpret_cast<float4 *>(y_wr + (c & 1) * 2 * YB + it * 32 * 128 * PT + (((4 * ph + q + 4 * PT * hi) ^ (l32 & YM)) << 4)) =
                     make_float4(yt[it][4 * q], yt[it][4 * q + 1], yt[it][4 * q + 2], yt[it][4 * q + 3]);
             };
-            masked_products(0);
-            if (__builtin_expect(mode == 2, 0)) read_x(s_x + slot * XB, 0, 2);
+            if (OUT) {
+                masked_products(0);
+                if (__builtin_expect(mode == 2, 0)) read_x(s_x + slot * XB, 0, 2);
+            }
             // Memory instructions go out one behind each MFMA: a wave that issues them in a row waits for the CU's address
             // unit and LDS each time, with its matrix core idle.
 #pragma unroll
@@ -439,29 +549,33 @@ chain_bf16_kernel(const uint16_t *__restrict__ x, const float *__restrict__ D, c
                 for (int ks = 0; ks < 2; ++ks) {
                     st[k] = mfma32(bfr[k][ks], xf[ks], st[k]);
                     load_b1(k, ks);
-                    write_y(0, (2 * k + ks) & 3);
+                    if (OUT) write_y(0, (2 * k + ks) & 3);
                 }
-            if (NTS == 1) { write_y(0, 2); write_y(0, 3); }
+            if (OUT && NTS == 1) { write_y(0, 2); write_y(0, 3); }
 #pragma unroll
             for (int i = 0; i < 2 * NTS; ++i) {
                 __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
                 __builtin_amdgcn_sched_group_barrier(0x20, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
+                if (OUT) __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
             }
             if (__builtin_expect(mode == 1, 0)) {
                 // from the reference of the first 32 tokens to that of the others
+                if (OUT) {
 #pragma unroll
-                for (int v = 0; v < 16; ++v) yt[1][v] *= rc.z;
+                    for (int v = 0; v < 16; ++v) yt[1][v] *= rc.z;
+                }
 #pragma unroll
                 for (int k = 0; k < NTS; ++k)
 #pragma unroll
                     for (int v = 0; v < 16; ++v) st[k][v] *= rc.z;
             }
-            masked_products(1);
-            if (__builtin_expect(mode == 2, 0)) read_x(s_x + slot * XB, 2, 4);
+            if (OUT) {
+                masked_products(1);
+                if (__builtin_expect(mode == 2, 0)) read_x(s_x + slot * XB, 2, 4);
+            }
             const int pn = __builtin_amdgcn_readfirstlane(__float_as_int(rn.x));
             const float sc = ldexpf(rc.y, ref_rem(pc) + (c + 1 < c_end ? ref_r0(pn) : 0));
-            load_g(c + 1);
+            if (OUT) load_g(c + 1);
             __builtin_amdgcn_sched_barrier(0xf);
 #pragma unroll
             for (int k = 0; k < NTS; ++k)
@@ -469,16 +583,16 @@ chain_bf16_kernel(const uint16_t *__restrict__ x, const float *__restrict__ D, c
                 for (int ks = 2; ks < 4; ++ks) {
                     st[k] = mfma32(bfr[k][ks], xf[ks], st[k]);
                     load_b1(k, ks);
-                    write_y(1, (2 * k + ks) & 3);
+                    if (OUT) write_y(1, (2 * k + ks) & 3);
                 }
-            if (NTS == 1) { write_y(1, 0); write_y(1, 1); }
+            if (OUT && NTS == 1) { write_y(1, 0); write_y(1, 1); }
             slot = slot == 2 ? 0 : slot + 1;
             read_x(s_x + slot * XB, 0, 4);
 #pragma unroll
             for (int i = 0; i < 2 * NTS; ++i) {
                 __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
                 __builtin_amdgcn_sched_group_barrier(0x20, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
+                if (OUT) __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
             }
             __builtin_amdgcn_sched_group_barrier(0x100, 8, 0);
             __builtin_amdgcn_sched_barrier(0);
@@ -494,7 +608,7 @@ chain_bf16_kernel(const uint16_t *__restrict__ x, const float *__restrict__ D, c
 #pragma unroll
                 for (int v = 0; v < 16; ++v) m[v] = (st[k][v] *= sc);
                 const uint4 hf[2] = {pack8(m), pack8(m + 8)};
-                if (on) {
+                if (OUT && on) {
 #pragma unroll
                     for (int q = 0; q < 2; ++q)
 #pragma unroll
@@ -508,7 +622,15 @@ chain_bf16_kernel(const uint16_t *__restrict__ x, const float *__restrict__ D, c
             pc = pn;
         }
         lds_barrier();
-        if (h_final && seg == nseg - 1 && p < P && on) {
+        if (!OUT && on && sl * PT + ph < ptiles) {
+            float4 *dst = piece_frag(pieces, bh, nbh, seg, ptiles, sl * PT + ph, NT) + nt0 * 256 + lane;
+#pragma unroll
+            for (int k = 0; k < NTS; ++k)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    dst[(k * 4 + q) * 64] = make_float4(st[k][4 * q], st[k][4 * q + 1], st[k][4 * q + 2], st[k][4 * q + 3]);
+        }
+        if (OUT && h_final && seg == nseg - 1 && p < P && on) {
 #pragma unroll
             for (int k = 0; k < NTS; ++k)
 #pragma unroll
@@ -570,6 +692,10 @@ chain_bf16_kernel(const uint16_t *__restrict__ x, const float *__restrict__ D, c
         const int ya0 = xj0 * (128 * PT) + ((xpc ^ (xj0 & YM)) << 4), ya1 = xj0 * (128 * PT) + (((xpc + 4 * PT) ^ (xj0 & YM)) << 4);
         // stages step c + 2 (xn) and finishes step c - 1 (xo)
         auto pass = [&](int c, int at, const uint4 (&xn)[2], const float2 (&fn)[2], const uint4 (&xo)[2], const float2 (&fo)[2]) __attribute__((always_inline)) {
+            if (!OUT) {
+                stage_x(c + 2, at, xn, fn);
+                return;
+            }
             const unsigned char *q = s_y + ((c - 1) & 1) * 2 * YB;
             float4 v[2][4];
 #pragma unroll
@@ -653,14 +779,31 @@ size_t chain_bf16_table_bytes(const Shape &s)
     return (size_t)s.B * s.H * ((s.L + CB_STEP - 1) / CB_STEP) * (4 * CB_STEP + 4) * sizeof(float);
 }
 
+// Segments of a sequence, before the scratch is asked how many pieces it holds.  A compute unit takes 1.6 us for a step of a
+// head when all are busy, and a chain alone 0.75 a step, so short of a quarter as many chains as units the chip idles: as many
+// segments as fill it, of at least 12 steps each, or 8 where it stays half empty (24 chains of 256 steps: 1 segment 191 us, 5
+// 82, 10 70; 64 of 64: 58, 4 segments 48).  With less work than nine steps a unit the kernels that parallelise over chunks are
+// ahead (48 chains of 40 steps: 38.1 / 34.9, 32 of 64: 39.1 / 36.8; 48 of 56: 45.9 / 49.3, 8 of 217: 40 / 92).  From a quarter
+// as many chains on the extra launch pays from 128 steps on (128 of 256 steps: 396 / 345, 96 of 128: 148 / 139, 96 of 64:
+// 62 / 66), and two rounds of more segments where they are fuller by a sixth than one (96 chains of 256 steps: 2 segments
+// 262, 5 259).  Chains that fill three fifths of a round stay whole.
+int chain_bf16_segments(int64_t chains, int64_t steps, int64_t ncu)
+{
+    if (steps <= 32 || chains == 0 || 10 * chains >= 6 * ncu || (chains * steps < 9 * ncu && steps < 160)) return 1;
+    const int64_t one = ncu / chains, two = 2 * ncu / chains;
+    if (4 * chains <= ncu) return (int)std::min<int64_t>({one, 16, chains * (steps / 8) <= ncu / 2 ? steps / 8 : steps / 12});
+    if (steps < (one > 1 ? 128 : 96)) return 1;
+    return (int)(6 * two >= 14 * one && steps >= 24 * two ? two : one);
+}
+
 template <int NT>
 static swimba_status launch_chain_t(const Shape &s, const void *x, const void *dt, const float *A, const float *D,
                                     const void *Be, const void *Ce, const void *logits, const float *w_sel, const float *h0,
-                                    void *y, float *h_final, int32_t *idx, float *w, void *ops, float *tables, hipStream_t st)
+                                    void *y, float *h_final, int32_t *idx, float *w, const ChainScratch &scr, bool skip, hipStream_t st)
 {
     const int nsteps = (s.L + CB_STEP - 1) / CB_STEP, ncu = device_cus();
     auto mix_shm = [](int K, int E) { return (size_t)2 * CB_STEP * (64 * NT + 16) + (size_t)CB_STEP * K * 8 + (E ? (size_t)CB_STEP * (E | 1) * 4 : 0); };
-    auto chain_shm = [](int PT) { return (size_t)11 * CB_STEP * 64 * PT + 64; };
+    auto chain_shm = [](int PT, bool out) { return (size_t)(out ? 11 : 3) * CB_STEP * 64 * PT + 64; };
     // more than 64 KB of dynamic LDS has to be allowed once per device
     static std::atomic<uint64_t> attr_set{0};            // one bit per device ordinal
     int dev = 0;
@@ -670,8 +813,8 @@ static swimba_status launch_chain_t(const Shape &s, const void *x, const void *d
     if (!(attr_set.load(std::memory_order_acquire) & bit)) {
         e = hipFuncSetAttribute((const void *)mix_steps_kernel<NT>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 (int)mix_shm(SWIMBA_MAX_TOPK, SWIMBA_MAX_EXPERTS));
-        if (e == hipSuccess) e = hipFuncSetAttribute((const void *)chain_bf16_kernel<NT, 1>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)chain_shm(1));
-        if (e == hipSuccess) e = hipFuncSetAttribute((const void *)chain_bf16_kernel<NT, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)chain_shm(2));
+        if (e == hipSuccess) e = hipFuncSetAttribute((const void *)chain_bf16_kernel<NT, 1, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)chain_shm(1, true));
+        if (e == hipSuccess) e = hipFuncSetAttribute((const void *)chain_bf16_kernel<NT, 2, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)chain_shm(2, true));
         if (e != hipSuccess) { set_last_hip_error((int)e); return SWIMBA_ERR_HIP; }
         attr_set.fetch_or(bit, std::memory_order_release);
     }
@@ -681,31 +824,61 @@ static swimba_status launch_chain_t(const Shape &s, const void *x, const void *d
         if (s.G % n == 0 && (int64_t)s.B * nsteps * s.G / n >= 2 * (int64_t)ncu) gpb = n;
     const int items = (int)((int64_t)s.B * nsteps * s.G / gpb);
     const int64_t bhs = (int64_t)s.B * s.H * nsteps;
+    float *tables = (float *)scr.tables;
     const ChainTables tb = {tables, tables + bhs * 2 * CB_STEP, tables + bhs * (2 * CB_STEP + 4)};
     const int tblocks = (int)(((int64_t)s.B * nsteps * ((s.H + 7) / 8) + 7) / 8);
     hipLaunchKernelGGL(mix_steps_kernel<NT>, dim3(items + tblocks), dim3(CB_MIX_THREADS), mix_shm(s.K, w_sel ? 0 : s.E), st,
-                       (const bf16 *)Be, (const bf16 *)Ce, (const bf16 *)logits, idx, w, w_sel, (uint16_t *)ops,
+                       (const bf16 *)Be, (const bf16 *)Ce, (const bf16 *)logits, idx, w, w_sel, (uint16_t *)scr.ops,
                        (const bf16 *)dt, A, tb, s, nsteps, gpb, items);
     SWIMBA_CHECK_LAUNCH();
+    // pieces that the scratch holds, one place kept for a copy of h0
+    const size_t unit = (size_t)s.B * s.H * ((s.P + 31) / 32) * NT * 4096;
+    ChainPieces pieces = {scr.a, scr.b, scr.sum, nullptr, 0, (int)std::min(scr.a_bytes / unit, (size_t)64), 1, nsteps, skip};
+    const int cap = (int)std::min(pieces.n_a + scr.b_bytes / unit, (size_t)65) - 1;
+    // A piece is about 32 steps at most: enough pieces to fill the chip where a segment is long.
+    int nseg = chain_bf16_segments((int64_t)s.B * s.H, nsteps, ncu), steps_per_seg = nsteps;
+    for (; nseg > 1; --nseg) {
+        pieces.per_seg = std::max(1, (nsteps / nseg + 16) / 32);
+        pieces.steps = (nsteps + nseg * pieces.per_seg - 1) / (nseg * pieces.per_seg);
+        steps_per_seg = pieces.steps * pieces.per_seg;
+        if ((nsteps + steps_per_seg - 1) / steps_per_seg <= nseg) nseg = (nsteps + steps_per_seg - 1) / steps_per_seg;
+        if ((nseg - 1) * pieces.per_seg <= cap) break;
+    }
+    if (nseg == 1) steps_per_seg = nsteps;
+    pieces.npiece = (nseg - 1) * pieces.per_seg;
+    int hblock = std::min(s.H, 8);
+    while (s.H % hblock) --hblock;
     // Both channel tiles of a head in one workgroup (one to a compute unit) where the heads fill at least three fifths of
     // their rounds; else a workgroup per tile, two to a unit.
-    const int64_t chains = (int64_t)s.B * s.H, rounds = (chains + ncu - 1) / ncu;
-    const int PT = s.P > 32 && 10 * chains >= 6 * rounds * ncu ? 2 : 1;
-    const int nslice = (s.P + 32 * PT - 1) / (32 * PT);
-    const int total = s.B * s.H * nslice, nblocks = xcd_padded(total);
-    hipLaunchKernelGGL((PT == 2 ? chain_bf16_kernel<NT, 2> : chain_bf16_kernel<NT, 1>), dim3(nblocks), dim3(256 * PT), chain_shm(PT),
-                       st, (const uint16_t *)x, D, (const uint16_t *)ops, tb, h0, h_final, (uint16_t *)y, s, nsteps, nslice, 1,
-                       nsteps, total, nblocks);
+    auto launch = [&](auto out_, int count, int steps) {
+        constexpr bool OUT = decltype(out_)::value;
+        const int64_t chains = (int64_t)s.B * s.H * count, rounds = (chains + ncu - 1) / ncu;
+        const int PT = s.P > 32 && 10 * chains >= 6 * rounds * ncu ? 2 : 1;
+        const int nslice = (s.P + 32 * PT - 1) / (32 * PT);
+        const int total = (int)chains * nslice, nblocks = xcd_padded(total);
+        hipLaunchKernelGGL((PT == 2 ? chain_bf16_kernel<NT, 2, OUT> : chain_bf16_kernel<NT, 1, OUT>), dim3(nblocks), dim3(256 * PT),
+                           chain_shm(PT, OUT), st, (const uint16_t *)x, D, (const uint16_t *)scr.ops, tb, h0, h_final,
+                           (uint16_t *)y, s, nsteps, nslice, count, steps, OUT ? s.H : hblock, pieces, total, nblocks);
+    };
+    if (nseg > 1) {
+        // with the final state written over the initial one the first segment can start after the last one has ended
+        if (h0 && h0 == h_final)
+            pieces.h0_copy = pieces.npiece < pieces.n_a ? scr.a + pieces.npiece * (unit / 4) : scr.b + (pieces.npiece - pieces.n_a) * (unit / 4);
+        launch(std::false_type{}, pieces.npiece, pieces.steps);
+        SWIMBA_CHECK_LAUNCH();
+        if (pieces.h0_copy) h0 = pieces.h0_copy;
+    }
+    launch(std::true_type{}, nseg, steps_per_seg);
     SWIMBA_CHECK_LAUNCH();
     return SWIMBA_OK;
 }
 
 swimba_status launch_chain_bf16(const Shape &s, const void *x, const void *dt, const float *A, const float *D, const void *Be,
                                 const void *Ce, const void *logits, const float *w_sel, const float *h0, void *y,
-                                float *h_final, int32_t *idx, float *w, void *ops, float *tables, hipStream_t st)
+                                float *h_final, int32_t *idx, float *w, const ChainScratch &scr, bool skip, hipStream_t st)
 {
     auto launch = s.N > 64 ? launch_chain_t<4> : s.N > 32 ? launch_chain_t<2> : launch_chain_t<1>;
-    return launch(s, x, dt, A, D, Be, Ce, logits, w_sel, h0, y, h_final, idx, w, ops, tables, st);
+    return launch(s, x, dt, A, D, Be, Ce, logits, w_sel, h0, y, h_final, idx, w, scr, skip, st);
 }
 
 }  // namespace swimba

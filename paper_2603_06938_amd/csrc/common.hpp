@@ -95,11 +95,17 @@ swimba_status launch_chain_f32(const Shape &s, int io_dtype, const void *x, cons
                                const float *h0, void *y, float *h_final, int32_t *idx, float *w, float *cop, float *bop,
                                float *gop, float *hseg, float *aseg, float *hinit, hipStream_t st);
 // bf16 io at the sizes of use_mfma_path as one walk over 64-token steps (chain_bf16.hip)
-size_t chain_bf16_ops_bytes(const Shape &s);
+struct ChainScratch {
+    void *ops, *tables;                  // operand images, decay tables
+    float *a, *b;                        // what pieces of a sequence leave behind, as many as they hold
+    size_t a_bytes, b_bytes;
+    float *sum;                          // (B, H, pieces, 2)
+};
 size_t chain_bf16_table_bytes(const Shape &s);
+int chain_bf16_segments(int64_t chains, int64_t steps, int64_t ncu);   // before the limit of the scratch
 swimba_status launch_chain_bf16(const Shape &s, const void *x, const void *dt, const float *A, const float *D, const void *Be,
                                 const void *Ce, const void *logits, const float *w_sel, const float *h0, void *y,
-                                float *h_final, int32_t *idx, float *w, void *ops, float *tables, hipStream_t st);
+                                float *h_final, int32_t *idx, float *w, const ChainScratch &scr, bool skip, hipStream_t st);
 // routed expert in-projection (expert_proj.hip)
 swimba_status launch_expert_proj(int64_t tokens, int E, int K, int GN, int Dm, int io_dtype, const void *u,
                                  const void *WB, const void *WC, const void *logits, void *Be, void *Ce,

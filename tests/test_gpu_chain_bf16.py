@@ -76,6 +76,61 @@ def test_chain_matches_oracle(case):
     assert torch.equal(other.y, out.y) and torch.equal(other.h_final, out.h_final)
 
 
+SEGMENTED = [
+    # sequences cut into segments: few chains, long sequences (B, L, H, P, N, G, E, k, h0, D, factor on dt, chunk)
+    (1, 10300, 2, 40, 72, 1, 5, 3, True, True, 1.0, 256),       # 161 steps, as many segments as the scratch holds
+    (1, 10240, 3, 32, 16, 1, 4, 1, False, True, 0.05, 64),      # slow decays: every piece reaches the end
+    (1, 2400, 64, 64, 128, 2, 8, 2, True, False, 1.0, 256),     # 38 steps in 3
+    (1, 3072, 64, 64, 128, 1, 4, 2, True, True, 4.0, 64),       # whole chunks: pieces that no sum sees are not walked
+    (1, 3072, 64, 64, 64, 8, 4, 2, True, True, 0.3, 64),
+    (2, 8200, 48, 64, 128, 1, 4, 2, True, True, 1.0, 256),      # 96 chains: two rounds of segments
+    (4, 6200, 36, 8, 40, 4, 4, 2, False, True, 10.0, 128),      # 144 chains; direct steps
+]
+
+
+@pytest.mark.parametrize("case", SEGMENTED, ids=lambda c: "B%dL%dH%dP%dN%dG%dE%dk%d_h0%d_D%d_dt%g_Q%d" % c)
+def test_segments_match_oracle(case):
+    B, L, H, P, N, G, E, k, with_h0, with_D, dt_scale, chunk = case
+    p, h0 = inputs(case[:-1], 300 + SEGMENTED.index(case))
+    D = p["D"] if with_D else None
+    out = forward(p, k, h0, with_D, chunk)
+    torch.cuda.synchronize()
+    ref = orc.mixer_fwd(p["x"], p["dt"], p["A"], D, p["B_experts"], p["C_experts"], p["router_logits"], k, h0=h0)
+    q = abs_inputs(p)
+    aref = orc.mixer_fwd(q["x"], q["dt"], q["A"], None if D is None else np.abs(D), q["B_experts"], q["C_experts"],
+                         q["router_logits"], k, h0=None if h0 is None else np.abs(h0))
+    # the roundings of the whole walk; the states that pieces leave behind are fp32
+    ey = componentwise_excess(host(out.y), ref["y"], aref["y"])
+    eh = componentwise_excess(host(out.h_final), ref["h_final"], aref["h_final"])
+    assert ey <= comp_tol("bf16") and eh <= comp_tol("bf16"), (ey, eh)
+    l2, linf = rel_errors(host(out.y), ref["y"], (0, 2))
+    assert l2 <= TOL["bf16"] and linf <= TOL["bf16"], (l2, linf)
+
+
+def test_segments_final_state_over_the_initial_one():
+    """In place the segments read a copy of h0: the bits of the same call out of place, every time."""
+    p, h0 = inputs((1, 3100, 64, 64, 128, 1, 4, 2, True, True, 0.2), 11)
+    want = forward(p, 2, h0, True, 256)
+    d = to_device(p, "bf16")
+    for _ in range(3):
+        h = torch.from_numpy(h0).to("cuda:0")
+        got = sw.swimba_mixer_fwd(d["x"], d["dt"], d["A"], d["D"], d["B_experts"], d["C_experts"], d["router_logits"], 2, 256, h,
+                                  h_final=h)
+        assert torch.equal(got.y, want.y) and torch.equal(h, want.h_final)
+
+
+def test_segments_values_that_are_not_finite():
+    """An x that is not finite reaches the tokens behind it through every later segment, and none in front."""
+    p, h0 = inputs((1, 10300, 4, 64, 128, 1, 4, 2, True, True, 1.0), 12)
+    base = forward(p, 2, h0, True, 256).y
+    q = dict(p, x=p["x"].copy())
+    q["x"][0, 3000, 1] = float("inf")
+    got = forward(q, 2, h0, True, 256)
+    assert torch.equal(got.y[:, :2944], base[:, :2944])
+    assert torch.equal(got.y[:, :, [0, 2, 3]], base[:, :, [0, 2, 3]])
+    assert not torch.isfinite(got.y[:, 3000:, 1]).any(dim=-1).any() and not torch.isfinite(got.h_final[:, 1]).any()
+
+
 def test_decays_that_turn_and_growing_states():
     """dt of both signs (cs falls and rises inside a step) and of the negative one alone (the state grows)"""
     p, h0 = inputs((2, 200, 4, 64, 128, 1, 4, 2, True, True, 1.0), 7)
