@@ -20,6 +20,9 @@
 // output columns of one token (two 16-byte stores).
 #include "common.hpp"
 
+#include <atomic>
+#include <type_traits>
+
 namespace swimba {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 pj_bf16x8_t;
@@ -89,24 +92,26 @@ __device__ __forceinline__ uint32_t pj_pack(float lo, float hi)
 // columns 64 (w & 3) .. + 63 of the block and one of two row groups.  The `nslots` workgroups
 // that fit on the chip at once (one per compute unit) are divided among the experts in
 // proportion to their list lengths (known on the device only), and a workgroup walks its share
-// in passes of up to 192 entries (6 row tiles of 32, at most 3 per row group): the whole launch
-// is one round of co-resident workgroups, whatever the routing.  (With fixed 64-entry tiles and
-// two workgroups per compute unit the 130M-shaped layer had 517 workgroups for 512 places, and
-// the second round of five cost 12 us; every workgroup also streamed the weights for 64 entries
-// only.)  Measured on that layer (29 us): everything but the k-steps 8.5 us, MFMAs alone + 10 us,
-// operand reads from LDS alone + 14 us (about 60 bytes per clock and compute unit, no bank
-// conflicts), both + 22 us: the operand reads are the limit.  One wave per SIMD with 4 x 3 tiles
-// (7 reads per 12 MFMAs instead of 5 per 6) measured slower (34 us): nothing hides its waits.
-// The contraction runs in stages of 64 features.  A stage of both operands (256 weight rows,
-// 192 token rows, 128 bytes each) is read with fully coalesced 16-byte loads (8 lanes per
-// row), parked in registers while the previous stage is multiplied, and then passed through
-// LDS, from where the lanes read their operand registers.
+// in passes of up to 256 entries (2 to 4 row tiles of 32 per row group, one code path each): the
+// whole launch is one round of co-resident workgroups, whatever the routing.  The contraction
+// runs in stages of 64 features: both operands (256 weight rows, 64 per row tile of a group of
+// token rows, 128 bytes each) are read with fully coalesced 16-byte loads (8 lanes per row),
+// parked in registers while earlier stages are multiplied, and passed through one of two LDS
+// buffers, from where the lanes read their operand registers: one barrier a stage.
+// Against one code path of three row tiles per group, one LDS buffer and shares spread over the
+// XCDs: 8192 tokens x 1792 columns (130M-shaped layer with input streams) 86 -> 75 us, the whole
+// call 171 -> 164, of which the shares' place on the XCDs is 5; 16384 tokens x 256 columns 31 -> 30.
+// What is left there (us, 75 / 30): without the MFMAs and operand reads 45 / 19, without the writes
+// of a stage into LDS 50 / 20, without the stores of the results 60 / 25; the loads are hidden.
+// LDS is busy a quarter of the time, so its waits and the stages' order count, not its rate: the
+// barrier moved between the k-steps of a stage measured the same (75.6 / 31), results through LDS
+// to store whole lines worse (79 / 34).
 constexpr int PJ_THREADS = 512;
 constexpr int PJ_KT = 64;             // features per stage
 constexpr int PJ_STR = PJ_KT + 8;     // LDS row stride (elements): rows stay 16-byte aligned
-constexpr int PJ_UD = 2;              // stages the loads run ahead (even)
-constexpr int PJ_RT = 3;              // row tiles (of 32 list entries) per wave and pass
-constexpr int PJ_ROWS = 2 * 32 * PJ_RT;   // list entries per workgroup and pass
+constexpr int PJ_MAX_RT = 4;          // row tiles (of 32 list entries) per wave and pass
+constexpr int PJ_BUF = (PJ_COLS + 64 * PJ_MAX_RT) * PJ_STR;   // elements of an LDS buffer
+constexpr size_t PJ_SHM = 2 * PJ_BUF * sizeof(uint16_t);
 
 // workgroups expert e gets out of nslots, given its list length
 __device__ __forceinline__ int proj_share(int cnt, int nslots, int64_t total)
@@ -117,17 +122,18 @@ __device__ __forceinline__ int proj_share(int cnt, int nslots, int64_t total)
 __global__ void __launch_bounds__(PJ_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
 proj_mfma_kernel(const uint16_t *__restrict__ u, ProjBlocks pb, const int32_t *__restrict__ counts,
                  const int32_t *__restrict__ lists, int64_t tokens, int E, int K, int Dm, int nslots,
-                 int compact)
+                 int colblocks, int compact)
 {
-    __shared__ __align__(16) uint16_t sW[PJ_COLS * PJ_STR];
-    __shared__ __align__(16) uint16_t sU[PJ_ROWS * PJ_STR];
+    extern __shared__ __align__(16) uint16_t s_buf[];        // [2] weight rows, then token rows
     __shared__ int32_t s_share[SWIMBA_MAX_EXPERTS];
-    __shared__ int32_t s_sel[2];
+    __shared__ int32_t s_sel[3];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int64_t total = tokens * K;
 
     // ---- which expert, which part of its list: prefix sum of the shares (E <= 256 = 4 per lane) ----
+    // Workgroups of one XCD (ids equal mod 8) take neighbouring shares with all their column blocks, so
+    // that its L2 holds the weights of about one expert and the token rows are read into it once.
     if (tid < SWIMBA_MAX_EXPERTS) s_share[tid] = tid < E ? proj_share(counts[tid], nslots, total) : 0;
     if (tid == 0) s_sel[0] = -1;
     __syncthreads();
@@ -141,11 +147,13 @@ proj_mfma_kernel(const uint16_t *__restrict__ u, ProjBlocks pb, const int32_t *_
             const int t = __shfl_up(incl, d);
             if (lane >= d) incl += t;
         }
-        int r = (int)blockIdx.x - (incl - sum);
-        if (r >= 0 && r < sum) {
+        const int used = __builtin_amdgcn_readlane(incl, 63) * colblocks, per = (used + 7) / 8;
+        const int j = (int)blockIdx.x >> 3, lid = ((int)blockIdx.x & 7) * per + j;
+        int r = lid / colblocks - (incl - sum);
+        if (j < per && lid < used && r >= 0 && r < sum) {
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                if (r >= 0 && r < v[q]) { s_sel[0] = 4 * lane + q; s_sel[1] = r; }
+                if (r >= 0 && r < v[q]) { s_sel[0] = 4 * lane + q; s_sel[1] = r; s_sel[2] = lid % colblocks; }
                 r -= v[q];          // negative from the match on: no later q matches
             }
         }
@@ -160,10 +168,10 @@ proj_mfma_kernel(const uint16_t *__restrict__ u, ProjBlocks pb, const int32_t *_
     const int t_begin = (int)((int64_t)part * n32 / nparts), t_end = (int)((int64_t)(part + 1) * n32 / nparts);
     const int nt = t_end - t_begin;
     if (nt <= 0) return;
-    const int npass = (nt + 2 * PJ_RT - 1) / (2 * PJ_RT);
+    const int npass = (nt + 2 * PJ_MAX_RT - 1) / (2 * PJ_MAX_RT);
 
     const int cw = wave & 3, rg = wave >> 2;                 // column group, row group of the wave
-    const int colblk = blockIdx.y * PJ_COLS;                 // first column of the workgroup in [B | C | X]
+    const int colblk = __builtin_amdgcn_readfirstlane(s_sel[2]) * PJ_COLS;   // first column of the workgroup in [B | C | X]
     const int col0 = colblk + cw * 64;
     const bool active = col0 < pb.tot;                       // wave-uniform; idle waves still stage
     const int l32 = lane & 31, kg = lane >> 5;
@@ -187,135 +195,132 @@ proj_mfma_kernel(const uint16_t *__restrict__ u, ProjBlocks pb, const int32_t *_
     // permutation is applied when the rows are staged (column x goes to LDS row wrow), so the
     // lanes of a wave read consecutive LDS rows: no bank conflicts.
     const int wrow = 8 * ((r32 >> 2) & 3) + 4 * ((r32 >> 4) & 1) + (r32 & 3) + 32 * rg;
-    const uint16_t *aop[2];
-#pragma unroll
-    for (int q = 0; q < 2; ++q) aop[q] = sW + (cw * 64 + 32 * q + l32) * PJ_STR + 8 * kg;
+    const int wr_at = wrow * PJ_STR + piece * 8, ur_at = (PJ_COLS + row0) * PJ_STR + piece * 8;
+    const int a_at = (cw * 64 + l32) * PJ_STR + 8 * kg;
     int cc;                                                  // column inside the row of the wave's block
     const int ob = proj_block_of(pb, min(col0, pb.tot - 64), cc);
     uint16_t *out = (uint16_t *)pb.out[ob];
     const int ncol = pb.n[ob];                               // row length of that output
 
-    for (int pass = 0; pass < npass; ++pass) {
-        const int p_begin = t_begin + (int)((int64_t)pass * nt / npass);
-        const int p_end = t_begin + (int)((int64_t)(pass + 1) * nt / npass);
-        const int ptiles = p_end - p_begin;                              // 1..6 row tiles
+    // entries [32 p_begin, 32 p_end) of the list, at most 2 RT tiles.  SETS: stages parked in registers.
+    auto run_pass = [&](auto rt_, auto sets_, int p_begin, int p_end) __attribute__((always_inline)) {
+        constexpr int RT = decltype(rt_)::value, SETS = decltype(sets_)::value;
+        const int ptiles = p_end - p_begin;
         const int half = (ptiles + 1) / 2;
         const int tbase = rg ? half : 0;                                 // first tile of this wave's row group
-        const int nrt = rg ? ptiles - half : half;                       // its tiles: 0..3, wave-uniform
+        const int nrt = rg ? ptiles - half : half;                       // its tiles, wave-uniform
         const int nvalid = min(32 * p_end, cnt) - 32 * p_begin;          // entries of this pass
         const int32_t *lst = lists + (int64_t)e * tokens + 32 * p_begin;
-        const uint16_t *usrc[PJ_RT];
+        const uint16_t *usrc[RT];
 #pragma unroll
-        for (int i = 0; i < PJ_RT; ++i) usrc[i] = u + (int64_t)(lst[min(row0 + 64 * i, nvalid - 1)] / K) * Dm;
-        const uint16_t *bop = sU + (32 * tbase + l32) * PJ_STR + 8 * kg;
-        // Register sets: the weight rows (L2 hits) and the token rows (scattered 128-byte reads
-        // that mostly come from HBM) of stage i + 2 are requested while stage i is multiplied.
+        for (int i = 0; i < RT; ++i) usrc[i] = u + (int64_t)(lst[min(row0 + 64 * i, nvalid - 1)] / K) * Dm;
+        const int b_at = (PJ_COLS + 32 * tbase + l32) * PJ_STR + 8 * kg;
         // All loads are clamped and unconditional, so that the waits on them stay exact counts;
         // the issues past the last stage re-read it and are not used.
-        uint4 wreg[2][4], ureg[PJ_UD][PJ_RT];
-        auto load_w = [&](uint4 (&wr)[4], int k0) __attribute__((always_inline)) {
+        uint4 wreg[SETS][4], ureg[SETS][RT];
+        auto load = [&](uint4 (&wr)[4], uint4 (&ur)[RT], int k0) __attribute__((always_inline)) {
             const int kk = min(min(k0, k_last) + piece * 8, Dm - 8);   // a short last stage stays inside the row
 #pragma unroll
             for (int i = 0; i < 4; ++i) wr[i] = *reinterpret_cast<const uint4 *>(wbase[i] + (wlane + kk));
-        };
-        auto load_u = [&](uint4 (&ur)[PJ_RT], int k0) __attribute__((always_inline)) {
-            const int kk = min(min(k0, k_last) + piece * 8, Dm - 8);
 #pragma unroll
-            for (int i = 0; i < PJ_RT; ++i) ur[i] = *reinterpret_cast<const uint4 *>(usrc[i] + kk);
+            for (int i = 0; i < RT; ++i) ur[i] = *reinterpret_cast<const uint4 *>(usrc[i] + kk);
         };
-        pj_f32x16_t acc[2][PJ_RT];
+        // registers -> LDS; pieces past the end of a short last stage as zeros: every stage is 4 k-steps
+        auto put = [&](uint16_t *buf, const uint4 (&wr)[4], const uint4 (&ur)[RT], int k0) __attribute__((always_inline)) {
+            const uint32_t m = k0 + piece * 8 < Dm ? ~0u : 0u;
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                *reinterpret_cast<uint4 *>(buf + wr_at + 64 * i * PJ_STR) = make_uint4(wr[i].x & m, wr[i].y & m, wr[i].z & m, wr[i].w & m);
+#pragma unroll
+            for (int i = 0; i < RT; ++i)
+                *reinterpret_cast<uint4 *>(buf + ur_at + 64 * i * PJ_STR) = make_uint4(ur[i].x & m, ur[i].y & m, ur[i].z & m, ur[i].w & m);
+        };
+        pj_f32x16_t acc[2][RT];
 #pragma unroll
         for (int ct = 0; ct < 2; ++ct)
 #pragma unroll
-            for (int rt = 0; rt < PJ_RT; ++rt) acc[ct][rt] = pj_f32x16_t{0};
-
-        // the 4 k-steps of a stage; the operands of k-step s + 1 are read from LDS before the
-        // MFMAs of k-step s are issued (two operand sets rotated by name)
-        auto read_ops = [&](uint4 (&a)[2], uint4 (&b)[PJ_RT], int s4) __attribute__((always_inline)) {
+            for (int rt = 0; rt < RT; ++rt) acc[ct][rt] = pj_f32x16_t{0};
+        auto read_ops = [&](const uint16_t *buf, uint4 (&a)[2], uint4 (&b)[RT], int s4) __attribute__((always_inline)) {
 #pragma unroll
-            for (int q = 0; q < 2; ++q) a[q] = *reinterpret_cast<const uint4 *>(aop[q] + 16 * s4);
+            for (int q = 0; q < 2; ++q) a[q] = *reinterpret_cast<const uint4 *>(buf + a_at + 32 * q * PJ_STR + 16 * s4);
 #pragma unroll
-            for (int rt = 0; rt < PJ_RT; ++rt)
-                b[rt] = *reinterpret_cast<const uint4 *>(bop + 32 * rt * PJ_STR + 16 * s4);
+            for (int rt = 0; rt < RT; ++rt)
+                b[rt] = *reinterpret_cast<const uint4 *>(buf + b_at + 32 * rt * PJ_STR + 16 * s4);
         };
-        auto mfmas = [&](const uint4 (&a)[2], const uint4 (&b)[PJ_RT]) __attribute__((always_inline)) {
+        auto mfmas = [&](const uint4 (&a)[2], const uint4 (&b)[RT]) __attribute__((always_inline)) {
 #pragma unroll
-            for (int rt = 0; rt < PJ_RT; ++rt)
+            for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
                 for (int ct = 0; ct < 2; ++ct)
                     acc[ct][rt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
                         __builtin_bit_cast(pj_bf16x8_t, a[ct]), __builtin_bit_cast(pj_bf16x8_t, b[rt]),
                         acc[ct][rt], 0, 0, 0);
         };
-        auto multiply = [&]() __attribute__((always_inline)) {
-            uint4 a0[2], b0[PJ_RT], a1[2], b1[PJ_RT];
-            read_ops(a0, b0, 0);
-            read_ops(a1, b1, 1);
+        // One stage: multiply buf; the next one's rows go into other, behind the first MFMAs, and its registers are
+        // refilled.  The operands of k-step s + 1 are read from LDS before the MFMAs of k-step s are issued (two sets
+        // rotated by name).  All RT row tiles are multiplied whether the wave has that many or not (the rows are staged
+        // clamped, the epilogue skips them): a branch per row tile would make every pair of MFMAs wait for its own read.
+        auto stage = [&](const uint16_t *buf, uint16_t *other, uint4 (&wr)[4], uint4 (&ur)[RT], int k0) __attribute__((always_inline)) {
+            lds_barrier();                       // buf is written; every wave is done with other
+            uint4 a0[2], b0[RT], a1[2], b1[RT];
+            read_ops(buf, a0, b0, 0);
+            read_ops(buf, a1, b1, 1);
             __builtin_amdgcn_sched_barrier(0);
             mfmas(a0, b0);
             __builtin_amdgcn_sched_barrier(0);
-            read_ops(a0, b0, 2);
+            read_ops(buf, a0, b0, 2);
+            __builtin_amdgcn_sched_barrier(0);
+            put(other, wr, ur, k0 + PJ_KT);
+            load(wr, ur, k0 + (1 + SETS) * PJ_KT);
             __builtin_amdgcn_sched_barrier(0);
             mfmas(a1, b1);
             __builtin_amdgcn_sched_barrier(0);
-            read_ops(a1, b1, 3);
+            read_ops(buf, a1, b1, 3);
             __builtin_amdgcn_sched_barrier(0);
             mfmas(a0, b0);
             mfmas(a1, b1);
-        };
-        // one stage: registers -> LDS, refill the registers two stages ahead, multiply from LDS
-        auto stage = [&](uint4 (&wr)[4], uint4 (&ur)[PJ_RT], int k0) __attribute__((always_inline)) {
-            lds_barrier();                                       // every wave is done with the previous stage
-            // pieces past the end of a short last stage are staged as zeros: every stage is 4 k-steps
-            const bool inside = k0 + piece * 8 < Dm;
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                *reinterpret_cast<uint4 *>(sW + (wrow + 64 * i) * PJ_STR + piece * 8) =
-                    inside ? wr[i] : make_uint4(0, 0, 0, 0);
-#pragma unroll
-            for (int i = 0; i < PJ_RT; ++i)
-                *reinterpret_cast<uint4 *>(sU + (row0 + 64 * i) * PJ_STR + piece * 8) =
-                    inside ? ur[i] : make_uint4(0, 0, 0, 0);
-            lds_barrier();
-            load_w(wr, k0 + 2 * PJ_KT);
-            load_u(ur, k0 + PJ_UD * PJ_KT);
-            // All three row tiles are multiplied whether the wave has that many or not (the rows are
-            // staged clamped, the epilogue skips them): a branch per row tile inside the k-steps made
-            // every pair of MFMAs wait for its own LDS read, and one code path per tile count spills.
-            if (active) multiply();
         };
         // prologue in the order the loop consumes (scheduling barriers keep the issue order)
-#pragma unroll
-        for (int d = 0; d < PJ_UD; ++d) {
-            load_w(wreg[d], d * PJ_KT);
-            load_u(ureg[d], d * PJ_KT);
-            __builtin_amdgcn_sched_barrier(0);
+        load(wreg[0], ureg[0], 0);
+        __builtin_amdgcn_sched_barrier(0);
+        if (SETS == 2) load(wreg[SETS - 1], ureg[SETS - 1], PJ_KT);
+        __builtin_amdgcn_sched_barrier(0);
+        lds_barrier();                           // every wave is done with the pass in front
+        put(s_buf, wreg[0], ureg[0], 0);
+        load(wreg[0], ureg[0], SETS * PJ_KT);
+        // pairs of stages (an odd count runs an all-zero one): no branch between the buffers and register sets
+        for (int k0 = 0; k0 < Dm; k0 += 2 * PJ_KT) {
+            stage(s_buf, s_buf + PJ_BUF, wreg[SETS - 1], ureg[SETS - 1], k0);
+            stage(s_buf + PJ_BUF, s_buf, wreg[0], ureg[0], k0 + PJ_KT);
         }
-        // straight-line groups of PJ_UD stages (a stage count that is not a multiple runs all-zero
-        // stages): no branch between the register sets
-        for (int k0 = 0; k0 < Dm; k0 += PJ_UD * PJ_KT) {
+        if (!active) return;
 #pragma unroll
-            for (int d = 0; d < PJ_UD; ++d) stage(wreg[d], ureg[d], k0 + d * PJ_KT);
-        }
-        if (active) {
+        for (int rt = 0; rt < RT; ++rt) {
+            const int prow = 32 * (tbase + rt) + l32;                         // entry inside the pass
+            if (rt < nrt && prow < nvalid) {
+                const int64_t ent = lst[prow];                                // t*K + r
+                const int64_t row = compact ? ent : (ent / K) * E + e;
 #pragma unroll
-            for (int rt = 0; rt < PJ_RT; ++rt) {
-                const int prow = 32 * (tbase + rt) + l32;                         // entry inside the pass
-                if (rt < nrt && prow < nvalid) {
-                    const int64_t ent = lst[prow];                                // t*K + r
-                    const int64_t row = compact ? ent : (ent / K) * E + e;
-#pragma unroll
-                    for (int ct = 0; ct < 2; ++ct) {
-                        uint16_t *dst = out + row * ncol + cc + 32 * ct + 16 * kg;
-                        const pj_f32x16_t v = acc[ct][rt];
-                        *reinterpret_cast<uint4 *>(dst) =
-                            make_uint4(pj_pack(v[0], v[1]), pj_pack(v[2], v[3]), pj_pack(v[4], v[5]), pj_pack(v[6], v[7]));
-                        *reinterpret_cast<uint4 *>(dst + 8) = make_uint4(pj_pack(v[8], v[9]), pj_pack(v[10], v[11]),
-                                                                         pj_pack(v[12], v[13]), pj_pack(v[14], v[15]));
-                    }
+                for (int ct = 0; ct < 2; ++ct) {
+                    uint16_t *dst = out + row * ncol + cc + 32 * ct + 16 * kg;
+                    const pj_f32x16_t v = acc[ct][rt];
+                    *reinterpret_cast<uint4 *>(dst) =
+                        make_uint4(pj_pack(v[0], v[1]), pj_pack(v[2], v[3]), pj_pack(v[4], v[5]), pj_pack(v[6], v[7]));
+                    *reinterpret_cast<uint4 *>(dst + 8) = make_uint4(pj_pack(v[8], v[9]), pj_pack(v[10], v[11]),
+                                                                     pj_pack(v[12], v[13]), pj_pack(v[14], v[15]));
                 }
             }
         }
+    };
+    for (int pass = 0; pass < npass; ++pass) {
+        const int p_begin = t_begin + (int)((int64_t)pass * nt / npass);
+        const int p_end = t_begin + (int)((int64_t)(pass + 1) * nt / npass);
+        if (p_end - p_begin <= 4)
+            run_pass(std::integral_constant<int, 2>{}, std::integral_constant<int, 2>{}, p_begin, p_end);
+        else if (p_end - p_begin <= 6)
+            run_pass(std::integral_constant<int, 3>{}, std::integral_constant<int, 2>{}, p_begin, p_end);
+        else
+            run_pass(std::integral_constant<int, 4>{}, std::integral_constant<int, 1>{}, p_begin, p_end);
     }
 }
 
@@ -388,9 +393,18 @@ swimba_status launch_expert_proj(int64_t tokens, int E, int K, int GN, int Dm, i
     if (he != hipSuccess) { set_last_hip_error((int)he); return SWIMBA_ERR_HIP; }
     const int colblocks = (pb.tot + PJ_COLS - 1) / PJ_COLS;
     const int nslots = max(1, ncu / colblocks);
-    const dim3 grid((unsigned)(nslots + E), (unsigned)colblocks);   // the shares sum to at most nslots + E
-    hipLaunchKernelGGL(proj_mfma_kernel, grid, dim3(PJ_THREADS), 0, st, (const uint16_t *)u, pb, counts, lists,
-                       tokens, E, K, Dm, nslots, compact);
+    // more than 64 KB of dynamic LDS has to be allowed once per device
+    static std::atomic<uint64_t> attr_set{0};                // one bit per device ordinal
+    const uint64_t bit = 1ull << (devid & 63);
+    if (!(attr_set.load(std::memory_order_acquire) & bit)) {
+        he = hipFuncSetAttribute((const void *)proj_mfma_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)PJ_SHM);
+        if (he != hipSuccess) { set_last_hip_error((int)he); return SWIMBA_ERR_HIP; }
+        attr_set.fetch_or(bit, std::memory_order_release);
+    }
+    // the shares sum to at most nslots + E
+    const unsigned grid = (unsigned)(((int64_t)(nslots + E) * colblocks + 7) / 8 * 8);
+    hipLaunchKernelGGL(proj_mfma_kernel, dim3(grid), dim3(PJ_THREADS), PJ_SHM, st, (const uint16_t *)u, pb, counts, lists,
+                       tokens, E, K, Dm, nslots, colblocks, compact);
     SWIMBA_CHECK_LAUNCH();
     return SWIMBA_OK;
 }

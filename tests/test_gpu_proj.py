@@ -118,3 +118,34 @@ def test_expert_proj_empty_and_errors():
         sw.swimba_expert_proj(torch.zeros((1, 4, 16), device=d), torch.zeros((3, 1, 4, 16), device=d),
                               torch.zeros((3, 1, 4, 16), device=d), torch.zeros((1, 4, 3), device=d), 2,
                               workspace=torch.empty(256, dtype=torch.uint8, device=d))
+
+
+@pytest.mark.parametrize("T,Dm,E,k,skew", [
+    (257, 64, 8, 2, 0.0),          # one row tile a share and less
+    (16384, 16, 4, 2, 0.0),        # four row tiles a share, one short stage
+    (16385, 144, 8, 2, 0.0),       # and five; an odd number of stages
+    (20000, 64, 4, 2, 0.0),        # shares of five to six row tiles
+    (28000, 80, 4, 2, 0.0),        # of seven to eight
+    (40000, 64, 16, 2, 3.0),       # of more than one pass, experts with few entries or none
+    (70000, 32, 5, 1, 8.0),        # half a stage, most entries with one expert
+])
+def test_expert_proj_shares_and_passes(T, Dm, E, k, skew):
+    """Every selected row of the grouped product, where the shares, their passes or the stages have their edges."""
+    gen = torch.Generator(device="cuda:0").manual_seed(T)
+    rnd = lambda *s: torch.randn(s, generator=gen, device="cuda:0")
+    u = rnd(1, T, Dm).bfloat16()
+    WB, WC = [(rnd(E, 1, 64, Dm) * Dm ** -0.5).bfloat16() for _ in range(2)]
+    logits = (rnd(1, T, E) - skew * torch.arange(E, device="cuda:0")).bfloat16()
+    got = sw.swimba_expert_proj_selected(u, WB, WC, logits, k)
+    idx = got.topk_idx.long()
+    # the router's rule: logits descending, ties by the lower index
+    order = torch.sort(logits.float(), dim=-1, descending=True, stable=True).indices[..., :k]
+    assert torch.equal(idx, order)
+    for out, W in ((got.B_experts, WB), (got.C_experts, WC)):
+        want = torch.empty(T, k, 64, device="cuda:0")
+        for e in range(E):
+            rows = (idx[0] == e).nonzero(as_tuple=True)
+            want[rows] = u[0, rows[0]].float() @ W[e, 0].float().T
+        # half a unit in the last place of the bf16 result; fp32 sums in another order
+        tol = 2.0 ** -8 * want.abs() + 1e-5 * Dm ** 0.5
+        assert bool(((out[0, :, :, 0].float() - want).abs() <= tol).all())
