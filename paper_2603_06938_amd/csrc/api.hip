@@ -210,6 +210,7 @@ static bool use_chain_bf16(const swimba_dims *d)
 {
     if (!use_mfma_path(d)) return false;
     const int64_t chains = (int64_t)d->batch * d->nheads, steps = ((int64_t)d->seqlen + 63) / 64, ncu = device_cus();
+    if (ncu == 0) return false;      // no device: the other kernels' launches report it
     const int64_t rounds = (chains + ncu - 1) / ncu;
     return steps <= 16 || (steps <= 24 && 32 * chains >= 5 * ncu) || (steps <= 32 && 4 * chains >= ncu) ||
            (steps <= 128 && 8 * chains >= 3 * ncu) || 10 * chains >= 6 * rounds * ncu || chain_bf16_segments(chains, steps, ncu) > 1;

@@ -699,7 +699,7 @@ static swimba_status launch_f32_t(const Shape &s, const void *x, const void *dt,
     // Up to a quarter as many steps as compute units (64 here) four workgroups share one, each on a unit of its own:
     // 4 steps 32.3 us for 35.4, 64 steps of the 130M-shaped layer 101.9 for 105.8.  Beyond, a part would wait for
     // another's unit: 96 steps 157.9 for 153.2, 256 steps 282 for 255.
-    const int ncu = device_cus();
+    const int ncu = std::max(device_cus(), 1);   // without a device the launch below reports it
     if (items <= ncu / 4)
         hipLaunchKernelGGL((mix_ops_kernel<T, 4, 8>), dim3((unsigned)items * 4), dim3(CF_MIX_THREADS), shm, st, (const T *)Be,
                            (const T *)Ce, (const T *)logits, idx, w, w_sel, cop, bop, gop, s, NT, 1);

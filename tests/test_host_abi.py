@@ -196,6 +196,23 @@ def test_later_entry_points_validate_on_the_host():
     assert lib.swimba_step_multi(ctypes.byref(dims(seqlen=4)), *p[:9], p[9] + 8, p[10], ws, big, None) == 7
 
 
+@pytest.mark.parametrize("io_dtype,seqlen", [(0, 64), (0, 16384), (1, 512), (1, 1600), (1, 4096), (1, 16384)])
+def test_forwards_without_a_device_return_a_status(io_dtype, seqlen):
+    """The rules that divide by the device's compute units see none: SWIMBA_ERR_HIP, and the process lives.  Pointer values
+    only: nothing can be launched."""
+    import torch
+    if torch.cuda.device_count() > 0:
+        pytest.skip("the calls would launch on made-up pointers")
+    lib = sw._load()
+    d = dims(headdim=64, dstate=128, chunk=256, io_dtype=io_dtype, seqlen=seqlen)
+    p = [0x1000000 * (i + 1) for i in range(13)]
+    ws = 0x40000000
+    assert lib.swimba_mixer_fwd(ctypes.byref(d), *p[:12], ws, 1 << 40, None) == 6
+    assert lib.swimba_mixer_fwd_selected(ctypes.byref(d), *p[:10], ws, 1 << 40, None) == 6
+    assert lib.swimba_mixer_fwd_proj(ctypes.byref(d), 64, *p[:13], ws, 1 << 40, None) == 6
+    assert lib.swimba_last_hip_error() != 0
+
+
 def test_header_is_plain_c_and_links_against_the_library(tmp_path):
     """include/swimba.h compiles as C99 with gcc (no C++ in the boundary), and a C program that
     only uses host-side calls links against libswimba.so and runs without a GPU."""
