@@ -57,22 +57,29 @@ __device__ __forceinline__ float lane_value(float v, int l)
 //                                          j = 16 (f - 2) + 8(e/4) + 4(lane/32) + e%4
 __host__ __device__ constexpr int cb_item_frags(int NT) { return 8 * NT + 6; }
 
-// Per (batch, head, step), written by the mix launch (cs: inclusive sum of log2 e dt A from the step's first token):
-//   fe  (B, H, nsteps, 64, 2)  factor of x, dt_j 2^(R - cs_j), and of y, 2^(cs_i - R)
-//   ref (B, H, nsteps, 4)      mode and references (pack_ref); 2^(fraction of cs_last); 2^(R1 - R0) or, of a direct step, 2^cs_last;
-//                              cs_last
-//   cd  (B, H, nsteps, 64, 2)  cs_j and dt_j, of direct steps alone
+// Per (batch, head, step), written by the mix launch (cs: inclusive sum of log2 e dt A from the step's first token, whole and
+// part its nearest whole number and the rest):
+//   fe  (B, H, nsteps, 64, 2)  factor of x, dt_j 2^(R - cs_j), and of y, 2^(cs_i - R); of a direct step dt_j and cs_j
+//   ref (B, H, nsteps, 4)      mode and references (pack_ref); 2^(part of cs_last); 2^(R1 - R0) or, of a direct step,
+//                              2^(whole of cs_last); cs_last
 // With a reference R in the middle of the step's range, 2^(cs_i - cs_j) dt_j is a factor of token j times a factor of token i,
 // both far from the ends of the exponent range: no element of the masked products needs a factor of its own, and the state is
-// updated and read at R, too.  R is a whole number, so another one changes no bit of a result: the bits of a token do not
-// depend on the tokens behind it.
-//   mode 0  one reference for the step, whose cs span at most CB_RANGE
-//   mode 1  one for each half of 32 tokens, each of which spans at most that: the state and the second half's Y change over
-//           in the middle of the step (about one head in fifty with dt log-uniform in [1e-3, 1e-1] and -A in [1, 16])
-//   mode 2  direct: the others, and values that are not finite.  x takes dt_j 2^(cs_last - cs_j), for the state alone.
-// CB_RANGE: two neighbouring steps change the state's reference by up to as much, which has to be a normal factor.
+// updated and read at R, too.
+//   mode 0  one reference for the step, whose cs falls by at most CB_RANGE
+//   mode 1  one for each half of 32 tokens, each of which falls by at most that: the state and the second half's Y change over
+//           in the middle of the step
+//   mode 2  direct: the others, steps where cs rises, and values that are not finite.  Token j takes dt_j 2^(-part_j), the
+//           masked products 2^(whole_i - whole_j) element by element, and the state another copy of x times
+//           2^(whole_last - whole_j).
+// The parts go where they go in every mode, and the rest are whole powers of two: the modes round alike, and the bits of a
+// token do not depend on the tokens behind it, which choose the mode.
+// A direct step takes 0.2 to 0.35 us longer: all steps direct, 130M-shaped layer 55 -> 62 us, 370M-shaped layer 115 -> 121,
+// five sequences of 1237 tokens x 32 heads 37 -> 44 (x and cs gathered from memory by the compute waves: 155, 325, 96; the
+// staged kernels and the per-head pass, which know no modes: 71, 147, 50).
+// A step size or decay that is not finite makes the tokens from its own on and the state behind them NaN, those in front take
+// the direct step without it.  A token's cs falls by 300 at most, which leaves nothing of any fp32 value.
 struct ChainTables {
-    float *fe, *ref, *cd;
+    float *fe, *ref;
 };
 __device__ __forceinline__ int pack_ref(int mode, int R0, int rem) { return mode | (R0 + 128) << 2 | (rem + 128) << 10; }
 __device__ __forceinline__ int ref_mode(int p) { return p & 3; }
@@ -81,39 +88,31 @@ __device__ __forceinline__ int ref_rem(int p) { return ((p >> 10) & 255) - 128; 
 
 __device__ __forceinline__ void chain_table(const ChainTables &t, int64_t bhs, float d, float Ah, int lane)
 {
-    const float v = d * Ah;
+    const float raw = d * Ah;
+    const uint64_t bad = __ballot(!(fabsf(d) <= 3e38f) || !(raw <= 3e38f));
+    const float v = fminf(fmaxf(raw, -300.f), 300.f);
     const float cs = wave_scan(v);
     const float mid = lane_value(cs, 31), last = lane_value(cs, 63);
-    // least and greatest of 0, cs_0 .. cs_31 and of cs_31 .. cs_63
-    float lo0 = fminf(0.f, mid), hi0 = fmaxf(0.f, mid), lo1 = fminf(mid, last), hi1 = fmaxf(mid, last);
-    if (__ballot(!(v <= 0.f)) != 0 && __ballot(!(v >= 0.f)) != 0) {      // it turns
-        float lo = cs, hi = cs;
-#pragma unroll
-        for (int o = 16; o; o >>= 1) { lo = fminf(lo, __shfl_xor(lo, o)); hi = fmaxf(hi, __shfl_xor(hi, o)); }
-        lo0 = fminf(lo0, lane_value(lo, 0)); hi0 = fmaxf(hi0, lane_value(hi, 0));
-        lo1 = fminf(lo1, lane_value(lo, 32)); hi1 = fmaxf(hi1, lane_value(hi, 32));
-    }
-    const float lo = fminf(lo0, lo1), hi = fmaxf(hi0, hi1);
-    const bool finite = __ballot(!(fabsf(v) <= 3e38f)) == 0;
-    const int mode = finite && hi - lo <= CB_RANGE ? 0 : finite && hi0 - lo0 <= CB_RANGE && hi1 - lo1 <= CB_RANGE ? 1 : 2;
-    const float R0 = mode == 0 ? rintf(0.5f * (lo + hi)) : rintf(0.5f * (lo0 + hi0));
-    const float R1 = mode == 0 ? R0 : rintf(0.5f * (lo1 + hi1));
-    const float whole = rintf(cs), part = cs - whole, last_whole = rintf(last);
-    const float R = lane < 32 ? R0 : R1;
-    float2 fe = make_float2(d * fast_exp2(last - cs), 1.f);
-    float4 ref = make_float4(0.f, 1.f, fast_exp2(last), last);
+    const bool falls = bad == 0 && __ballot(v > 0.f) == 0;
+    const int mode = falls && -last <= CB_RANGE ? 0 : falls && -mid <= CB_RANGE && mid - last <= CB_RANGE ? 1 : 2;
+    const float last_whole = rintf(last);
+    float2 fe = make_float2(d, cs);
+    float4 ref = make_float4(0.f, fast_exp2(last - last_whole), ldexpf(1.f, (int)last_whole), last);
     int pack = pack_ref(2, 0, 0);
     if (mode != 2) {
+        const float R0 = rintf(0.5f * (mode == 0 ? last : mid)), R1 = mode == 0 ? R0 : rintf(0.5f * (mid + last));
+        const float whole = rintf(cs), part = cs - whole, R = lane < 32 ? R0 : R1;
         fe.x = ldexpf(d * fast_exp2(-part), (int)(R - whole));
         fe.y = ldexpf(fast_exp2(part), (int)(whole - R));
-        ref.y = fast_exp2(last - last_whole);
         ref.z = ldexpf(1.f, (int)(R1 - R0));
         // mode 1: R0, R1 and cs_last can be far from the step's start, but not from each other's tile
         pack = pack_ref(mode, (int)R0, (int)(last_whole - R1));
+    } else if (bad != 0) {
+        if (lane >= __builtin_ctzll(bad)) fe = make_float2(0.f, NAN);
+        ref.y = ref.w = NAN;
     }
     ref.x = __int_as_float(pack);
     reinterpret_cast<float2 *>(t.fe)[bhs * CB_STEP + lane] = fe;
-    if (mode == 2) reinterpret_cast<float2 *>(t.cd)[bhs * CB_STEP + lane] = make_float2(cs, d);
     if (lane == 0) reinterpret_cast<float4 *>(t.ref)[bhs] = ref;
 }
 
@@ -303,8 +302,10 @@ chain_bf16_kernel(const uint16_t *__restrict__ x, const float *__restrict__ D, c
     constexpr int YM = 8 * PT - 1;                       // 16-byte pieces of a Y row, less one
     extern __shared__ __align__(16) unsigned char smem_raw[];
     unsigned char *s_x = smem_raw;                       // [3] x rows times f, bf16
-    unsigned char *s_y = s_x + 3 * XB;                   // [2][2] partial Y by halves of the state columns, fp32
+    unsigned char *s_xs = s_x + (OUT ? 3 * XB : 0);      // [3] of direct steps: x as the state takes it
+    unsigned char *s_y = s_xs + 3 * XB;                  // [2][2] partial Y by halves of the state columns, fp32
     float4 *s_ref = reinterpret_cast<float4 *>(s_y + (OUT ? 4 * YB : 0));       // [4] references of a step
+    int *s_whole = reinterpret_cast<int *>(s_ref + 4);   // [4][64] of direct steps: whole parts of cs
 
     const int lid = xcd_logical_id(blockIdx.x, nblocks);
     if (lid >= total) return;
@@ -488,41 +489,30 @@ chain_bf16_kernel(const uint16_t *__restrict__ x, const float *__restrict__ D, c
             const float4 rn = s_ref[(c + 1 - c_begin) & 3];
             const int mode = ref_mode(pc);
             if (__builtin_expect(mode == 2, 0)) {
-                // a direct step: its masked products one decay at a time, on x as it is
+                // the state to the step's end
 #pragma unroll
                 for (int k = 0; k < NTS; ++k)
 #pragma unroll
                     for (int v = 0; v < 16; ++v) st[k][v] *= rc.z;
-            }
-            if (OUT && __builtin_expect(mode == 2, 0)) {
-                const float2 *cd = reinterpret_cast<const float2 *>(tb.cd) + (bhs + c) * CB_STEP;
-                const float ci[2] = {cd[l32].x, cd[32 + l32].x};
+                if (OUT) {
+                    const int *whole = s_whole + ((c - c_begin) & 3) * CB_STEP;
+                    const int wi[2] = {whole[l32], whole[32 + l32]};
 #pragma unroll
-                for (int it = 0; it < 2; ++it) {
-                    const float ei = fast_exp2(ci[it]);
+                    for (int it = 0; it < 2; ++it)
 #pragma unroll
-                    for (int v = 0; v < 16; ++v) yt[it][v] *= ei;
-                }
+                        for (int v = 0; v < 16; ++v) yt[it][v] = ldexpf(yt[it][v], wi[it]);
 #pragma unroll
-                for (int k = 0; k < 3; ++k) {
-                    const int f = 3 * nh + k, it = f >= 2, ks = it ? f - 2 : f;
-                    float m[8];
-                    unpack8(m, gf[k]);
-                    uint32_t xv[8];
+                    for (int k = 0; k < 3; ++k) {
+                        const int f = 3 * nh + k, it = f >= 2, ks = it ? f - 2 : f;
+                        const int4 w0 = *reinterpret_cast<const int4 *>(whole + 16 * ks + 4 * hi), w1 = *reinterpret_cast<const int4 *>(whole + 16 * ks + 8 + 4 * hi);
+                        const int wj[8] = {w0.x, w0.y, w0.z, w0.w, w1.x, w1.y, w1.z, w1.w};
+                        float m[8];
+                        unpack8(m, gf[k]);
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        const int j = 16 * ks + 8 * (e >> 2) + 4 * hi + (e & 3), t = c * CB_STEP + j;
-                        const float2 q = cd[j];
-                        const float w = m[e] * (q.y * fast_exp2(ci[it] - q.x));
-                        m[e] = j <= 32 * it + l32 ? w : 0.f;
-                        xv[e] = x[(tokb + min(t, t_end - 1)) * trow + (int64_t)h * P + min(p, P - 1)];
-                        if (t >= t_end || p >= P) xv[e] = 0;
+                        for (int e = 0; e < 8; ++e) m[e] = ldexpf(m[e], wi[it] - wj[e]);
+                        gf[k] = pack8(m);
                     }
-                    yt[it] = mfma32(make_uint4(xv[0] | xv[1] << 16, xv[2] | xv[3] << 16, xv[4] | xv[5] << 16, xv[6] | xv[7] << 16), pack8(m), yt[it]);
-                    gf[k] = make_uint4(0, 0, 0, 0);
                 }
-#pragma unroll
-                for (int ks = 0; ks < 4; ++ks) xf[ks] = make_uint4(0, 0, 0, 0);
             }
             auto masked_products = [&](int half) __attribute__((always_inline)) {
 #pragma unroll
@@ -539,7 +529,7 @@ chain_bf16_kernel(const uint16_t *__restrict__ x, const float *__restrict__ D, c
             };
             if (OUT) {
                 masked_products(0);
-                if (__builtin_expect(mode == 2, 0)) read_x(s_x + slot * XB, 0, 2);
+                if (__builtin_expect(mode == 2, 0)) read_x(s_xs + slot * XB, 0, 2);
             }
             // Memory instructions go out one behind each MFMA: a wave that issues them in a row waits for the CU's address
             // unit and LDS each time, with its matrix core idle.
@@ -571,7 +561,7 @@ chain_bf16_kernel(const uint16_t *__restrict__ x, const float *__restrict__ D, c
             }
             if (OUT) {
                 masked_products(1);
-                if (__builtin_expect(mode == 2, 0)) read_x(s_x + slot * XB, 2, 4);
+                if (__builtin_expect(mode == 2, 0)) read_x(s_xs + slot * XB, 2, 4);
             }
             const int pn = __builtin_amdgcn_readfirstlane(__float_as_int(rn.x));
             const float sc = ldexpf(rc.y, ref_rem(pc) + (c + 1 < c_end ? ref_r0(pn) : 0));
@@ -676,24 +666,39 @@ chain_bf16_kernel(const uint16_t *__restrict__ x, const float *__restrict__ D, c
         };
         const int sw = PT == 2 ? (xj0 & 3) : ((xj0 >> 1) & 1);
         const int x_at = xj0 * XROW + (((xpc >> 1) ^ sw) << 5) + ((xpc & 1) << 4);
-        // x of step c (v) times its factor into LDS
-        auto stage_x = [&](int c, int at, const uint4 (&v)[2], const float2 (&fe)[2]) __attribute__((always_inline)) {
+        // x of step c (v) times its factor into LDS; of a direct step two copies, and fe turns into the factors
+        auto stage_x = [&](int c, int at, const uint4 (&v)[2], float2 (&fe)[2], const float4 &ref) __attribute__((always_inline)) {
+            const bool direct = ref_mode(__builtin_amdgcn_readfirstlane(__float_as_int(ref.x))) == 2;
 #pragma unroll
             for (int m = 0; m < 2; ++m) {
                 // channels past P and tokens past the end hold something else's x
                 const uint32_t k = (xin && c * CB_STEP + xj0 + 32 * m < t_end) ? ~0u : 0u;
                 float a[8];
                 unpack8(a, make_uint4(v[m].x & k, v[m].y & k, v[m].z & k, v[m].w & k));
+                if (__builtin_expect(direct, 0)) {
+                    const float cs = fe[m].y, whole = rintf(cs), part = cs - whole;
+                    const int w = (int)whole;            // 0 of NaN
+                    fe[m].x = cs == cs ? fe[m].x * fast_exp2(-part) : 0.f;
+                    fe[m].y = fast_exp2(part);
+                    const float fs = ldexpf(fe[m].x, (int)rintf(ref.w) - w);
+                    float q[8];
 #pragma unroll
-                for (int q = 0; q < 8; ++q) a[q] *= fe[m].x;
-                *reinterpret_cast<uint4 *>(s_x + at * XB + x_at + m * 32 * XROW) = pack8(a);
+                    for (int e = 0; e < 8; ++e) q[e] = a[e] * fs;
+                    *reinterpret_cast<uint4 *>(s_xs + at * XB + x_at + m * 32 * XROW) = pack8(q);
+                    if (OUT && xpc == 0) s_whole[((c - c_begin) & 3) * CB_STEP + xj0 + 32 * m] = w;
+                }
+                if (OUT || !direct) {
+#pragma unroll
+                    for (int q = 0; q < 8; ++q) a[q] *= fe[m].x;
+                    *reinterpret_cast<uint4 *>(s_x + at * XB + x_at + m * 32 * XROW) = pack8(a);
+                }
             }
         };
         const int ya0 = xj0 * (128 * PT) + ((xpc ^ (xj0 & YM)) << 4), ya1 = xj0 * (128 * PT) + (((xpc + 4 * PT) ^ (xj0 & YM)) << 4);
         // stages step c + 2 (xn) and finishes step c - 1 (xo)
-        auto pass = [&](int c, int at, const uint4 (&xn)[2], const float2 (&fn)[2], const uint4 (&xo)[2], const float2 (&fo)[2]) __attribute__((always_inline)) {
+        auto pass = [&](int c, int at, const uint4 (&xn)[2], float2 (&fn)[2], const float4 &rn, const uint4 (&xo)[2], const float2 (&fo)[2]) __attribute__((always_inline)) {
             if (!OUT) {
-                stage_x(c + 2, at, xn, fn);
+                stage_x(c + 2, at, xn, fn, rn);
                 return;
             }
             const unsigned char *q = s_y + ((c - 1) & 1) * 2 * YB;
@@ -705,7 +710,7 @@ chain_bf16_kernel(const uint16_t *__restrict__ x, const float *__restrict__ D, c
                 v[m][2] = *reinterpret_cast<const float4 *>(q + ya1 + m * 32 * 128 * PT);
                 v[m][3] = *reinterpret_cast<const float4 *>(q + YB + ya1 + m * 32 * 128 * PT);
             }
-            stage_x(c + 2, at, xn, fn);
+            stage_x(c + 2, at, xn, fn, rn);
             uint16_t *yq = y + xbase + (int64_t)(c - 1) * CB_STEP * trow;
             float r[2][8];
 #pragma unroll
@@ -737,34 +742,27 @@ chain_bf16_kernel(const uint16_t *__restrict__ x, const float *__restrict__ D, c
         float4 rf[CB_RING];
         auto load_ref = [&](int c) __attribute__((always_inline)) { return ref0[min(c, c_end - 1)]; };
 #pragma unroll
-        for (int u = 0; u < CB_RING - 1; ++u) load_x(c_begin + u, xr[u], fr[u]);
-        if (iow == 0) {
-#pragma unroll
-            for (int u = 0; u < CB_RING - 1; ++u) rf[u] = load_ref(c_begin + u);
-            if (lane == 0) { s_ref[0] = rf[0]; s_ref[1] = rf[1]; }
+        for (int u = 0; u < CB_RING - 1; ++u) {
+            load_x(c_begin + u, xr[u], fr[u]);
+            rf[u] = load_ref(c_begin + u);
         }
-        stage_x(c_begin, 0, xr[0], fr[0]);
-        stage_x(c_begin + 1, 1, xr[1], fr[1]);
+        if (iow == 0 && lane == 0) { s_ref[0] = rf[0]; s_ref[1] = rf[1]; }
+        stage_x(c_begin, 0, xr[0], fr[0], rf[0]);
+        stage_x(c_begin + 1, 1, xr[1], fr[1], rf[1]);
         lds_barrier();                                   // x of the first two steps
-        auto walk = [&](auto refs_) __attribute__((always_inline)) {
-            constexpr bool refs = decltype(refs_)::value;
-            for (int c0 = c_begin;; c0 += CB_RING) {
+        for (int c0 = c_begin;; c0 += CB_RING) {
 #pragma unroll
-                for (int u = 0; u < CB_RING; ++u) {
-                    const int c = c0 + u;
-                    lds_barrier();
-                    pass(c, (u + 2) % 3, xr[(u + 2) % CB_RING], fr[(u + 2) % CB_RING], xr[(u + CB_RING - 1) % CB_RING], fr[(u + CB_RING - 1) % CB_RING]);
-                    if (c >= c_end) return;
-                    if (refs) {
-                        if (lane == 0) s_ref[(c + 2 - c_begin) & 3] = rf[(u + 2) % CB_RING];
-                        rf[(u + CB_RING - 1) % CB_RING] = load_ref(c + CB_RING - 1);
-                    }
-                    load_x(c + CB_RING - 1, xr[(u + CB_RING - 1) % CB_RING], fr[(u + CB_RING - 1) % CB_RING]);
-                }
+            for (int u = 0; u < CB_RING; ++u) {
+                const int c = c0 + u;
+                lds_barrier();
+                pass(c, (u + 2) % 3, xr[(u + 2) % CB_RING], fr[(u + 2) % CB_RING], rf[(u + 2) % CB_RING], xr[(u + CB_RING - 1) % CB_RING],
+                     fr[(u + CB_RING - 1) % CB_RING]);
+                if (c >= c_end) return;
+                if (iow == 0 && lane == 0) s_ref[(c + 2 - c_begin) & 3] = rf[(u + 2) % CB_RING];
+                rf[(u + CB_RING - 1) % CB_RING] = load_ref(c + CB_RING - 1);
+                load_x(c + CB_RING - 1, xr[(u + CB_RING - 1) % CB_RING], fr[(u + CB_RING - 1) % CB_RING]);
             }
-        };
-        if (iow == 0) walk(std::true_type{});
-        else walk(std::false_type{});
+        }
     }
 }
 
@@ -776,7 +774,7 @@ size_t chain_bf16_ops_bytes(const Shape &s)
 }
 size_t chain_bf16_table_bytes(const Shape &s)
 {
-    return (size_t)s.B * s.H * ((s.L + CB_STEP - 1) / CB_STEP) * (4 * CB_STEP + 4) * sizeof(float);
+    return (size_t)s.B * s.H * ((s.L + CB_STEP - 1) / CB_STEP) * (2 * CB_STEP + 4) * sizeof(float);
 }
 
 // Segments of a sequence, before the scratch is asked how many pieces it holds.  A compute unit takes 1.6 us for a step of a
@@ -803,7 +801,7 @@ static swimba_status launch_chain_t(const Shape &s, const void *x, const void *d
 {
     const int nsteps = (s.L + CB_STEP - 1) / CB_STEP, ncu = device_cus();
     auto mix_shm = [](int K, int E) { return (size_t)2 * CB_STEP * (64 * NT + 16) + (size_t)CB_STEP * K * 8 + (E ? (size_t)CB_STEP * (E | 1) * 4 : 0); };
-    auto chain_shm = [](int PT, bool out) { return (size_t)(out ? 11 : 3) * CB_STEP * 64 * PT + 64; };
+    auto chain_shm = [](int PT, bool out) { return (size_t)(out ? 14 : 3) * CB_STEP * 64 * PT + 64 + (out ? 16 * CB_STEP : 0); };
     // more than 64 KB of dynamic LDS has to be allowed once per device
     static std::atomic<uint64_t> attr_set{0};            // one bit per device ordinal
     int dev = 0;
@@ -825,7 +823,7 @@ static swimba_status launch_chain_t(const Shape &s, const void *x, const void *d
     const int items = (int)((int64_t)s.B * nsteps * s.G / gpb);
     const int64_t bhs = (int64_t)s.B * s.H * nsteps;
     float *tables = (float *)scr.tables;
-    const ChainTables tb = {tables, tables + bhs * 2 * CB_STEP, tables + bhs * (2 * CB_STEP + 4)};
+    const ChainTables tb = {tables, tables + bhs * 2 * CB_STEP};
     const int tblocks = (int)(((int64_t)s.B * nsteps * ((s.H + 7) / 8) + 7) / 8);
     hipLaunchKernelGGL(mix_steps_kernel<NT>, dim3(items + tblocks), dim3(CB_MIX_THREADS), mix_shm(s.K, w_sel ? 0 : s.E), st,
                        (const bf16 *)Be, (const bf16 *)Ce, (const bf16 *)logits, idx, w, w_sel, (uint16_t *)scr.ops,

@@ -165,6 +165,37 @@ def test_a_reference_changes_no_bit_in_front(s):
     assert torch.equal(got[:, :s], base[:, :s]) and not torch.equal(got[:, s:], base[:, s:])
 
 
+@pytest.mark.parametrize("s", [1, 20, 31, 32, 33, 50, 63, 64, 100])
+@pytest.mark.parametrize("shape", [(24, 64, 128), (3, 40, 72), (160, 64, 16)], ids=["H24", "H3P40N72", "H160N16"])
+def test_a_direct_step_changes_no_bit_in_front(s, shape):
+    """Step sizes from token s on that take its step from one reference, or one per half, to direct, to a rising cs, or to a
+    value that is not finite: tokens in front keep their bits, and so do all others where the mode alone changes."""
+    H, P, N = shape
+    p, h0 = inputs((1, 150, H, P, N, 1, 4, 2, True, True, 1.0), 13)
+    p["A"][::2] = -16.0                                   # of these heads some steps have a reference per half
+    base = forward(p, 2, h0, True).y
+    for value in (8.0, -0.01, float("inf"), float("nan")):
+        dt = p["dt"].copy()
+        dt[:, s:s + 1] = value                            # one token: its step is direct, those behind it are not
+        got = forward(dict(p, dt=dt), 2, h0, True).y
+        assert torch.equal(got[:, :s], base[:, :s]), value
+        if not np.isfinite(value):
+            assert torch.isnan(got[:, s:]).all()
+
+
+def test_direct_steps_round_as_the_others_do():
+    """A token that no one sees (x = 0, decay 1, first of its step's tail) but whose rising cs makes the step direct: the
+    same bits everywhere."""
+    p, h0 = inputs((2, 192, 24, 64, 128, 1, 4, 2, True, True, 1.0), 14)
+    p["A"][:] = -np.abs(p["A"])
+    q = dict(p, dt=p["dt"].copy(), x=p["x"].copy())
+    p["dt"][:, 127] = 0.0
+    q["dt"][:, 127] = -2.0 ** -60                         # cs and 2^(part of cs) stay what they are, but it rises
+    p["x"][:, 127] = q["x"][:, 127] = 0.0
+    base, got = forward(p, 2, h0, True), forward(q, 2, h0, True)
+    assert torch.equal(got.y, base.y) and torch.equal(got.h_final, base.h_final)
+
+
 @pytest.mark.parametrize("value", [float("nan"), float("inf")])
 def test_values_that_are_not_finite_reach_no_earlier_tile(value):
     """A dt or x that is not finite leaves the tokens of the 32-token tiles in front of its own alone."""
