@@ -33,11 +33,30 @@ namespace swimba {
 
 constexpr int CB_STEP = 64;            // tokens per step
 constexpr int CB_MIX_THREADS = 512;
-constexpr float CB_RANGE = 120.f;      // log2 of the largest product of two factors of a step (ChainTables)
+constexpr float CB_RANGE = 120.f;      // most that cs falls under one reference (ChainTables)
 constexpr int CB_RING = 6;             // x tiles in an i/o wave's registers (a multiple of the 3 in LDS); 9 spill time: 130M 64.6 us
 
 typedef __attribute__((ext_vector_type(4))) short cb_s16x4_t;
 typedef __attribute__((address_space(3))) cb_s16x4_t cb_lds_s16x4_t;
+
+typedef __attribute__((ext_vector_type(4))) float cb_f32x4_t;
+typedef __attribute__((ext_vector_type(2))) float cb_f32x2_t;
+typedef __attribute__((address_space(4))) cb_f32x2_t cb_scalar_f32x2_t;          // read through the scalar cache
+
+// Largest of the 64 lanes' values, none of them negative, in lane 63
+__device__ __forceinline__ float wave_max(float v)
+{
+#define WAVE_MAX_STEP(ctrl, rows) \
+    v = fmaxf(v, __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), ctrl, rows, 0xf, false)))
+    WAVE_MAX_STEP(0x111, 0xf);   // row_shr:1
+    WAVE_MAX_STEP(0x112, 0xf);   // row_shr:2
+    WAVE_MAX_STEP(0x114, 0xf);   // row_shr:4
+    WAVE_MAX_STEP(0x118, 0xf);   // row_shr:8
+    WAVE_MAX_STEP(0x142, 0xa);   // row_bcast:15 into rows 1 and 3
+    WAVE_MAX_STEP(0x143, 0xc);   // row_bcast:31 into rows 2 and 3
+#undef WAVE_MAX_STEP
+    return v;
+}
 
 // 16 lanes read a 4 x 16 block of 16-bit elements, lane s four columns of row s / 4; lane s gets column s, rows 0..3
 __device__ __forceinline__ uint2 lds_read_tr(const unsigned char *p)
@@ -60,8 +79,9 @@ __host__ __device__ constexpr int cb_item_frags(int NT) { return 8 * NT + 6; }
 // Per (batch, head, step), written by the mix launch (cs: inclusive sum of log2 e dt A from the step's first token, whole and
 // part its nearest whole number and the rest):
 //   fe  (B, H, nsteps, 64, 2)  factor of x, dt_j 2^(R - cs_j), and of y, 2^(cs_i - R); of a direct step dt_j and cs_j
-//   ref (B, H, nsteps, 4)      mode and references (pack_ref); 2^(part of cs_last); 2^(R1 - R0) or, of a direct step,
-//                              2^(whole of cs_last); cs_last
+//   ref (B, H, nsteps, 2)      mode and references (pack_ref); 2^(part of cs_last)
+//   sum (B, H, nsteps)         cs_last
+//   mag (B, nsteps, G, 2)      bounds for x times its factor (mag_bounds)
 // With a reference R in the middle of the step's range, 2^(cs_i - cs_j) dt_j is a factor of token j times a factor of token i,
 // both far from the ends of the exponent range: no element of the masked products needs a factor of its own, and the state is
 // updated and read at R, too.
@@ -73,18 +93,34 @@ __host__ __device__ constexpr int cb_item_frags(int NT) { return 8 * NT + 6; }
 //           2^(whole_last - whole_j).
 // The parts go where they go in every mode, and the rest are whole powers of two: the modes round alike, and the bits of a
 // token do not depend on the tokens behind it, which choose the mode.
-// A direct step takes 0.2 to 0.35 us longer: all steps direct, 130M-shaped layer 55 -> 62 us, 370M-shaped layer 115 -> 121,
-// five sequences of 1237 tokens x 32 heads 37 -> 44 (x and cs gathered from memory by the compute waves: 155, 325, 96; the
-// staged kernels and the per-head pass, which know no modes: 71, 147, 50).
+// A direct step takes 0.1 to 0.3 us longer: all steps direct, 130M-shaped layer 56 -> 58 us, 370M-shaped layer 115 -> 121,
+// five sequences of 1237 tokens x 32 heads 37 -> 41 (x and cs gathered from memory by the compute waves: 155, 325, 96; the
+// staged kernels and the per-head pass, which know no modes: 71, 147, 50).  A smaller CB_RANGE makes more steps direct: 32
+// took 66, 122 and 45 us.
 // A step size or decay that is not finite makes the tokens from its own on and the state behind them NaN, those in front take
 // the direct step without it.  A token's cs falls by 300 at most, which leaves nothing of any fp32 value.
+// Factors of up to 2^60 either way could take a product that is in range by itself out of it.  So the waves that multiply x by
+// its factor look at what comes out: a step with anything above an upper bound, or, where the reference is more than 8 from
+// some token's cs, with eight channels of a token that are all below a lower one, is turned direct before it is used
+// (mag_bounds; turn_direct).  The bounds leave 2^26 to the ends of the exponent range, for sums of up to N products and for
+// elements of B, C and x far under the largest.  The check's 20 instructions in the i/o waves take 45 ns of a step where
+// memory does not set the time: five sequences of 1237 tokens 35.4 -> 36.6 us, 150 tokens x 24 heads 12.9 -> 13.5.
 struct ChainTables {
-    float *fe, *ref;
+    float *fe, *ref, *sum, *mag;
 };
-__device__ __forceinline__ int pack_ref(int mode, int R0, int rem) { return mode | (R0 + 128) << 2 | (rem + 128) << 10; }
+constexpr float CB_NEAR = 16.f;        // most that cs falls in a step that takes no harm from small values
+__device__ __forceinline__ float2 mag_bounds(float b, float c)      // largest |B| and |C|
+{
+    const int eb = __builtin_amdgcn_frexp_expf(b), ebc = eb + __builtin_amdgcn_frexp_expf(c);
+    return make_float2(ldexpf(1.f, max(0, max(-eb, -ebc)) - 100), ldexpf(1.f, 100 - max(0, max(eb, ebc))));
+}
+// mode; R0, whole part of cs_last less the last reference, R1 - R0; of a direct step 0, 0, whole part of cs_last
+__device__ __forceinline__ int pack_ref(int mode, int R0, int rem, int R1) { return mode | (R0 + 128) << 2 | (rem + 128) << 10 | (R1 - R0 + 128) << 18; }
+__device__ __forceinline__ int pack_direct(int last) { return 2 | last << 2; }
 __device__ __forceinline__ int ref_mode(int p) { return p & 3; }
-__device__ __forceinline__ int ref_r0(int p) { return ((p >> 2) & 255) - 128; }
-__device__ __forceinline__ int ref_rem(int p) { return ((p >> 10) & 255) - 128; }   // whole part of cs_last, less the last reference
+__device__ __forceinline__ int ref_r0(int p) { return ref_mode(p) == 2 ? 0 : ((p >> 2) & 255) - 128; }
+__device__ __forceinline__ int ref_rem(int p) { return ref_mode(p) == 2 ? 0 : ((p >> 10) & 255) - 128; }
+__device__ __forceinline__ int ref_shift(int p) { return ref_mode(p) == 2 ? p >> 2 : ((p >> 18) & 255) - 128; }
 
 __device__ __forceinline__ void chain_table(const ChainTables &t, int64_t bhs, float d, float Ah, int lane)
 {
@@ -97,23 +133,24 @@ __device__ __forceinline__ void chain_table(const ChainTables &t, int64_t bhs, f
     const int mode = falls && -last <= CB_RANGE ? 0 : falls && -mid <= CB_RANGE && mid - last <= CB_RANGE ? 1 : 2;
     const float last_whole = rintf(last);
     float2 fe = make_float2(d, cs);
-    float4 ref = make_float4(0.f, fast_exp2(last - last_whole), ldexpf(1.f, (int)last_whole), last);
-    int pack = pack_ref(2, 0, 0);
+    float frac = fast_exp2(last - last_whole), sum = last;
+    int pack = pack_direct((int)last_whole);
     if (mode != 2) {
         const float R0 = rintf(0.5f * (mode == 0 ? last : mid)), R1 = mode == 0 ? R0 : rintf(0.5f * (mid + last));
         const float whole = rintf(cs), part = cs - whole, R = lane < 32 ? R0 : R1;
         fe.x = ldexpf(d * fast_exp2(-part), (int)(R - whole));
         fe.y = ldexpf(fast_exp2(part), (int)(whole - R));
-        ref.z = ldexpf(1.f, (int)(R1 - R0));
         // mode 1: R0, R1 and cs_last can be far from the step's start, but not from each other's tile
-        pack = pack_ref(mode, (int)R0, (int)(last_whole - R1));
+        pack = pack_ref(mode, (int)R0, (int)(last_whole - R1), (int)R1);
     } else if (bad != 0) {
         if (lane >= __builtin_ctzll(bad)) fe = make_float2(0.f, NAN);
-        ref.y = ref.w = NAN;
+        frac = sum = NAN;
     }
-    ref.x = __int_as_float(pack);
     reinterpret_cast<float2 *>(t.fe)[bhs * CB_STEP + lane] = fe;
-    if (lane == 0) reinterpret_cast<float4 *>(t.ref)[bhs] = ref;
+    if (lane == 0) {
+        reinterpret_cast<float2 *>(t.ref)[bhs] = make_float2(__int_as_float(pack), frac);
+        t.sum[bhs] = sum;
+    }
 }
 
 template <int NT>
@@ -126,6 +163,7 @@ mix_steps_kernel(const bf16 *__restrict__ Be, const bf16 *__restrict__ Ce, const
     constexpr int RS = 64 * NT + 16;                     // row stride of the mixed rows (bytes)
     constexpr int PPR = 4 * NT;                          // 16-byte pieces of a row
     extern __shared__ __align__(16) unsigned char smem_raw[];
+    __shared__ float s_mag[CB_MIX_THREADS / 64];         // largest value a wave has mixed
     unsigned char *s_rows[2] = {smem_raw, smem_raw + CB_STEP * RS};              // B, C
     int32_t *s_idx = reinterpret_cast<int32_t *>(smem_raw + 2 * CB_STEP * RS);   // [64][K]
     float *s_w = reinterpret_cast<float *>(s_idx + CB_STEP * s.K);               // [64][K]
@@ -156,7 +194,7 @@ mix_steps_kernel(const bf16 *__restrict__ Be, const bf16 *__restrict__ Ce, const
     const int b = item / (gblocks * nsteps);
     const int valid = min(CB_STEP, s.L - c * CB_STEP);
     const int64_t tok0 = (int64_t)b * s.L + (int64_t)c * CB_STEP;
-    const bool sel = (w_sel != nullptr);
+    const bool sel = (w_sel != nullptr), is_c = wave >= CB_MIX_THREADS / 128;
 
     if (!sel) {
         const int ES = s.E | 1;
@@ -183,7 +221,7 @@ mix_steps_kernel(const bf16 *__restrict__ Be, const bf16 *__restrict__ Ce, const
     const int64_t estride = (int64_t)s.G * s.N, tokstride = rowsE * estride;
     const int l32 = lane & 31, hi = lane >> 5, s16 = lane & 15, half = (lane >> 4) & 1;
     for (int g = g_begin; g < g_begin + gpb; ++g) {
-        // ---- mixed rows: units of 8 columns, NT a thread; B rows first, then C rows ----
+        // ---- mixed rows: units of 8 columns, NT a thread; waves 0..3 B rows, the others C rows ----
         {
             float acc[NT][8];
 #pragma unroll
@@ -191,8 +229,8 @@ mix_steps_kernel(const bf16 *__restrict__ Be, const bf16 *__restrict__ Ce, const
 #pragma unroll
                 for (int q = 0; q < 8; ++q) acc[m][q] = 0.f;
             auto source = [&](int m, int r, float &w) __attribute__((always_inline)) {
-                const int u = m * CB_MIX_THREADS + tid, row = (u / PPR) % CB_STEP, pc = u % PPR;
-                const uint16_t *base = reinterpret_cast<const uint16_t *>(u >= CB_STEP * PPR ? Ce : Be);
+                const int u = m * (CB_MIX_THREADS / 2) + tid % (CB_MIX_THREADS / 2), row = u / PPR, pc = u % PPR;
+                const uint16_t *base = reinterpret_cast<const uint16_t *>(is_c ? Ce : Be);
                 const int j = min(row, valid - 1);
                 w = s_w[row * K + r];
                 return reinterpret_cast<const uint4 *>(base + (tok0 + j) * tokstride + s_idx[row * K + r] * estride +
@@ -221,16 +259,27 @@ mix_steps_kernel(const bf16 *__restrict__ Be, const bf16 *__restrict__ Ce, const
 #pragma unroll
                 for (int m = 0; m < NT; ++m) fma_bf16x8(acc[m], v0[m], w0[m]);
             }
+            float most = 0.f;
 #pragma unroll
             for (int m = 0; m < NT; ++m) {
-                const int u = m * CB_MIX_THREADS + tid, row = (u / PPR) % CB_STEP, pc = u % PPR;
+                const int u = m * (CB_MIX_THREADS / 2) + tid % (CB_MIX_THREADS / 2), row = u / PPR, pc = u % PPR;
                 uint4 v = pack8(acc[m]);
                 if (row >= valid || 8 * pc >= s.N) v = make_uint4(0, 0, 0, 0);
-                *reinterpret_cast<uint4 *>(smem_raw + (u >= CB_STEP * PPR ? CB_STEP * RS : 0) + row * RS + 16 * pc) = v;
+                *reinterpret_cast<uint4 *>(s_rows[is_c] + row * RS + 16 * pc) = v;
+#pragma unroll
+                for (int q = 0; q < 8; ++q) most = fmaxf(most, fabsf(acc[m][q]));
             }
+            most = wave_max(most);
+            if (lane == 63) s_mag[wave] = most;
         }
         __syncthreads();
         uint4 *dst = reinterpret_cast<uint4 *>(ops) + (((int64_t)b * nsteps + c) * s.G + g) * (cb_item_frags(NT) * 64) + lane;
+        if (tid == CB_MIX_THREADS - 1) {                 // of a wave that makes no tile
+            float b_most = 0.f, c_most = 0.f;
+#pragma unroll
+            for (int q = 0; q < CB_MIX_THREADS / 64; ++q) (q < CB_MIX_THREADS / 128 ? b_most : c_most) = fmaxf(q < CB_MIX_THREADS / 128 ? b_most : c_most, s_mag[q]);
+            reinterpret_cast<float2 *>(tb.mag)[((int64_t)b * nsteps + c) * s.G + g] = mag_bounds(b_most, c_most);
+        }
         if (wave < 3) {                                  // G^T tiles (I, J) = (0, 0), (1, 0), (1, 1)
             const int I = wave > 0, J = wave == 2;
             const unsigned char *br = s_rows[0] + (32 * J + l32) * RS + 16 * hi, *cr = s_rows[1] + (32 * I + l32) * RS + 16 * hi;
@@ -304,8 +353,9 @@ chain_bf16_kernel(const uint16_t *__restrict__ x, const float *__restrict__ D, c
     unsigned char *s_x = smem_raw;                       // [3] x rows times f, bf16
     unsigned char *s_xs = s_x + (OUT ? 3 * XB : 0);      // [3] of direct steps: x as the state takes it
     unsigned char *s_y = s_xs + 3 * XB;                  // [2][2] partial Y by halves of the state columns, fp32
-    float4 *s_ref = reinterpret_cast<float4 *>(s_y + (OUT ? 4 * YB : 0));       // [4] references of a step
-    int *s_whole = reinterpret_cast<int *>(s_ref + 4);   // [4][64] of direct steps: whole parts of cs
+    // [3] mode and references, 2^(part of cs_last), and a byte an i/o wave: x times its factor left its bounds
+    int4 *s_ref = reinterpret_cast<int4 *>(s_y + (OUT ? 4 * YB : 0));
+    int *s_whole = reinterpret_cast<int *>(s_ref + 3);   // [3][64] of direct steps: whole parts of cs
 
     const int lid = xcd_logical_id(blockIdx.x, nblocks);
     if (lid >= total) return;
@@ -332,18 +382,59 @@ chain_bf16_kernel(const uint16_t *__restrict__ x, const float *__restrict__ D, c
             for (int i = tid; i < min(32 * PT, P - p0) * s.N / 4; i += 256 * PT)
                 reinterpret_cast<float4 *>(pieces.h0_copy + (bh * P + p0) * s.N)[i] = reinterpret_cast<const float4 *>(h0 + (bh * P + p0) * s.N)[i];
         // decay of this piece, and from its end to the end of its segment
-        const float4 *ref = reinterpret_cast<const float4 *>(tb.ref) + bhs;
+        const float *last = tb.sum + bhs;
         const int s_end = (seg / pieces.per_seg + 1) * pieces.per_seg * pieces.steps;
         float own = 0.f, after = 0.f;
-        for (int c = c_begin + lane; c < c_end; c += 64) own += ref[c].w;
+        for (int c = c_begin + lane; c < c_end; c += 64) own += last[c];
         if (pieces.skip)
-            for (int c = c_end + lane; c < s_end; c += 64) after += ref[c].w;
+            for (int c = c_end + lane; c < s_end; c += 64) after += last[c];
         own = lane_value(wave_scan(own), 63);
         after = lane_value(wave_scan(after), 63);
         const bool dead = pieces.skip && after < -150.f;
         if (sl == 0 && tid == 0) reinterpret_cast<float2 *>(pieces.sum)[bh * pieces.npiece + seg] = make_float2(own, dead ? 0.f : 1.f);
         if (dead) return;
     }
+
+    auto flagged = [&](int w) __attribute__((always_inline)) {
+        return (__builtin_amdgcn_readfirstlane(w) & (PT == 2 ? ~0 : 0xffff)) != 0;
+    };
+    // two pieces of 8 channels of one token a thread of either role: tokens xj0 and xj0 + 32
+    const int io = tid & (NW * 64 - 1), xpc = io % PPR, xp = p0 + 8 * xpc, xj0 = io / PPR;
+    const bool xin = xp < P;
+    const int64_t xbase = tokb * trow + (int64_t)h * P;                  // uniform
+    const int x_at = xj0 * XROW + (((xpc >> 1) ^ (PT == 2 ? (xj0 & 3) : ((xj0 >> 1) & 1))) << 5) + ((xpc & 1) << 4);
+    const float2 *fe0 = reinterpret_cast<const float2 *>(tb.fe) + bhs * CB_STEP;
+    // x of a direct step: f holds dt and the part of cs, w is the whole of cs
+    auto stage_direct = [&](int at, int m, const float (&a)[8], float f, int w, int last) __attribute__((always_inline)) {
+        const float fs = ldexpf(f, last - w);
+        float q[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) q[e] = a[e] * fs;
+        *reinterpret_cast<uint4 *>(s_xs + at * XB + x_at + m * 32 * XROW) = pack8(q);
+        if (!OUT) return;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) q[e] = a[e] * f;
+        *reinterpret_cast<uint4 *>(s_x + at * XB + x_at + m * 32 * XROW) = pack8(q);
+        if (xpc == 0) s_whole[at * CB_STEP + xj0 + 32 * m] = w;
+    };
+    // what a factor of y moves to that of x in a step turned direct: any whole number near its exponent
+    auto exponent = [](float v) __attribute__((always_inline)) { return (int)rintf(__builtin_amdgcn_logf(v)); };
+    // Step c, whose x has been staged in slot at, turned direct by the compute waves: one copy of this code, where the i/o
+    // waves' steps are unrolled.
+    auto turn_direct = [&](int c, int at, int &pack) __attribute__((always_inline)) {
+        const int R0 = ref_r0(pack), R1 = R0 + ref_shift(pack), last = R1 + ref_rem(pack);
+#pragma unroll 1
+        for (int m = 0; m < 2; ++m) {
+            const int tok = c * CB_STEP + xj0 + 32 * m;
+            float a[8];
+            unpack8(a, xin && tok < t_end ? *reinterpret_cast<const uint4 *>(x + xbase + tok * trow + xp) : make_uint4(0, 0, 0, 0));
+            const float2 fe = fe0[tok];
+            const int e = exponent(fe.y);
+            stage_direct(at, m, a, ldexpf(fe.x, e), (m ? R1 : R0) + e, last);
+        }
+        pack = pack_direct(last);
+        lds_barrier();
+    };
 
     // ================= compute waves: 32 channels x half of the state columns =================
     auto compute_wave = [&](auto nh_) __attribute__((always_inline)) {
@@ -475,27 +566,30 @@ chain_bf16_kernel(const uint16_t *__restrict__ x, const float *__restrict__ D, c
             }
         };
         lds_barrier();                                   // x and references of the first two steps
-        float4 rc = s_ref[0];
-        int pc = __builtin_amdgcn_readfirstlane(__float_as_int(rc.x));
+        int4 rc = s_ref[0];
+        int pc = __builtin_amdgcn_readfirstlane(rc.x);
+        if (__builtin_expect(flagged(rc.w), 0)) turn_direct(c_begin, 0, pc);
         if (OUT) {
             readout(ldexpf(1.f, ref_r0(pc)));
             load_c(c_begin + 1);
         }
         read_x(s_x, 0, 4);
         unsigned char *y_wr = s_y + nh * YB + l32 * (128 * PT);
-        int slot = 0;                                    // of x
+        int slot = 0;                                    // of x, references and whole parts
         for (int c = c_begin; c < c_end; ++c) {
             lds_barrier();
-            const float4 rn = s_ref[(c + 1 - c_begin) & 3];
+            const int next_slot = slot == 2 ? 0 : slot + 1;
+            const int4 rn = s_ref[next_slot];
             const int mode = ref_mode(pc);
             if (__builtin_expect(mode == 2, 0)) {
                 // the state to the step's end
+                const float to_end = ldexpf(1.f, ref_shift(pc));
 #pragma unroll
                 for (int k = 0; k < NTS; ++k)
 #pragma unroll
-                    for (int v = 0; v < 16; ++v) st[k][v] *= rc.z;
+                    for (int v = 0; v < 16; ++v) st[k][v] *= to_end;
                 if (OUT) {
-                    const int *whole = s_whole + ((c - c_begin) & 3) * CB_STEP;
+                    const int *whole = s_whole + slot * CB_STEP;
                     const int wi[2] = {whole[l32], whole[32 + l32]};
 #pragma unroll
                     for (int it = 0; it < 2; ++it)
@@ -524,7 +618,7 @@ chain_bf16_kernel(const uint16_t *__restrict__ x, const float *__restrict__ D, c
             const uint4 *next = item(c + 1);
             auto load_b1 = [&](int k, int ks) __attribute__((always_inline)) { bfr[k][ks] = next[(4 * NT + (nt0 + k) * 4 + ks) * 64]; };
             auto write_y = [&](int it, int q) __attribute__((always_inline)) {
-                *reinterpret_cast<float4 *>(y_wr + (c & 1) * 2 * YB + it * 32 * 128 * PT + (((4 * ph + q + 4 * PT * hi) ^ (l32 & YM)) << 4)) =
+                *reinterpret_cast<float4 *>(y_wr + ((c - c_begin) & 1) * 2 * YB + it * 32 * 128 * PT + (((4 * ph + q + 4 * PT * hi) ^ (l32 & YM)) << 4)) =
                     make_float4(yt[it][4 * q], yt[it][4 * q + 1], yt[it][4 * q + 2], yt[it][4 * q + 3]);
             };
             if (OUT) {
@@ -550,21 +644,26 @@ chain_bf16_kernel(const uint16_t *__restrict__ x, const float *__restrict__ D, c
             }
             if (__builtin_expect(mode == 1, 0)) {
                 // from the reference of the first 32 tokens to that of the others
+                const float over = ldexpf(1.f, ref_shift(pc));
                 if (OUT) {
 #pragma unroll
-                    for (int v = 0; v < 16; ++v) yt[1][v] *= rc.z;
+                    for (int v = 0; v < 16; ++v) yt[1][v] *= over;
                 }
 #pragma unroll
                 for (int k = 0; k < NTS; ++k)
 #pragma unroll
-                    for (int v = 0; v < 16; ++v) st[k][v] *= rc.z;
+                    for (int v = 0; v < 16; ++v) st[k][v] *= over;
             }
             if (OUT) {
                 masked_products(1);
-                if (__builtin_expect(mode == 2, 0)) read_x(s_xs + slot * XB, 2, 4);
             }
-            const int pn = __builtin_amdgcn_readfirstlane(__float_as_int(rn.x));
-            const float sc = ldexpf(rc.y, ref_rem(pc) + (c + 1 < c_end ? ref_r0(pn) : 0));
+            int pn = __builtin_amdgcn_readfirstlane(rn.x);
+            const bool turn = flagged(rn.w);
+            if (__builtin_expect(turn || (OUT && mode == 2), 0)) {
+                if (OUT && mode == 2) read_x(s_xs + slot * XB, 2, 4);
+                if (turn) turn_direct(c + 1, next_slot, pn);
+            }
+            const float sc = ldexpf(__int_as_float(rc.y), ref_rem(pc) + (c + 1 < c_end ? ref_r0(pn) : 0));
             if (OUT) load_g(c + 1);
             __builtin_amdgcn_sched_barrier(0xf);
 #pragma unroll
@@ -576,7 +675,7 @@ chain_bf16_kernel(const uint16_t *__restrict__ x, const float *__restrict__ D, c
                     if (OUT) write_y(1, (2 * k + ks) & 3);
                 }
             if (OUT && NTS == 1) { write_y(1, 0); write_y(1, 1); }
-            slot = slot == 2 ? 0 : slot + 1;
+            slot = next_slot;
             read_x(s_x + slot * XB, 0, 4);
 #pragma unroll
             for (int i = 0; i < 2 * NTS; ++i) {
@@ -639,20 +738,18 @@ chain_bf16_kernel(const uint16_t *__restrict__ x, const float *__restrict__ D, c
         compute_wave(std::integral_constant<int, 1>{});
     } else {
         // ================= i/o waves: two pieces of 8 channels of one token a thread =================
-        const int io = tid - NW * 64, iow = wave - NW;
-        const int xpc = io % PPR, xp = p0 + 8 * xpc, xj0 = io / PPR;      // tokens xj0 and xj0 + 32
-        const bool xin = xp < P;
-        const int64_t xbase = tokb * trow + (int64_t)h * P;               // uniform
+        const int iow = wave - NW;
         int64_t xoff[2];
 #pragma unroll
         for (int m = 0; m < 2; ++m) xoff[m] = (xj0 + 32 * m) * trow + (xin ? xp : 0);
         const float dsk = D ? D[h] : 0.f;
         const bool skip = D != nullptr;
-        const float2 *fe0 = reinterpret_cast<const float2 *>(tb.fe) + bhs * CB_STEP;
-        auto load_x = [&](int c, uint4 (&v)[2], float2 (&fe)[2]) __attribute__((always_inline)) {
-            c = min(c, c_end - 1);
-            const uint16_t *q = x + xbase + (int64_t)c * CB_STEP * trow;
-            const int last = t_end - 1 - c * CB_STEP;
+        // the next step's x and factors; past the end the last one's again
+        int xc = c_begin;
+        const uint16_t *xq = x + xbase + (int64_t)c_begin * CB_STEP * trow;
+        const float2 *fq = fe0 + (int64_t)c_begin * CB_STEP + xj0;
+        auto load_x = [&](uint4 (&v)[2], float2 (&fe)[2]) __attribute__((always_inline)) {
+            const int last = t_end - 1 - xc * CB_STEP;
             int64_t o[2] = {xoff[0], xoff[1]};
             if (last < CB_STEP - 1) {                    // a step that is not full
 #pragma unroll
@@ -660,48 +757,65 @@ chain_bf16_kernel(const uint16_t *__restrict__ x, const float *__restrict__ D, c
             }
 #pragma unroll
             for (int m = 0; m < 2; ++m) {
-                v[m] = *reinterpret_cast<const uint4 *>(q + o[m]);
-                fe[m] = fe0[(int64_t)c * CB_STEP + xj0 + 32 * m];
+                v[m] = *reinterpret_cast<const uint4 *>(xq + o[m]);
+                fe[m] = fq[32 * m];
             }
+            const bool more = xc < c_end - 1;
+            xc += more;
+            xq += more ? CB_STEP * trow : 0;
+            fq += more ? CB_STEP : 0;
         };
-        const int sw = PT == 2 ? (xj0 & 3) : ((xj0 >> 1) & 1);
-        const int x_at = xj0 * XROW + (((xpc >> 1) ^ sw) << 5) + ((xpc & 1) << 4);
-        // x of step c (v) times its factor into LDS; of a direct step two copies, and fe turns into the factors
-        auto stage_x = [&](int c, int at, const uint4 (&v)[2], float2 (&fe)[2], const float4 &ref) __attribute__((always_inline)) {
-            const bool direct = ref_mode(__builtin_amdgcn_readfirstlane(__float_as_int(ref.x))) == 2;
+        // x of step c (v) times its factor into LDS; of a direct step two copies, and fe turns into the factors.  Channels past
+        // P hold something else's x, for rows of Y and columns of the state that go nowhere.
+        auto stage_x = [&](int c, int at, uint4 (&v)[2], float2 (&fe)[2], const cb_f32x4_t &ref) __attribute__((always_inline)) {
+            const int p = __float_as_int(ref[0]), left = t_end - c * CB_STEP;
+            if (__builtin_expect(left < CB_STEP, 0)) {   // tokens past the end hold another one's x
 #pragma unroll
-            for (int m = 0; m < 2; ++m) {
-                // channels past P and tokens past the end hold something else's x
-                const uint32_t k = (xin && c * CB_STEP + xj0 + 32 * m < t_end) ? ~0u : 0u;
-                float a[8];
-                unpack8(a, make_uint4(v[m].x & k, v[m].y & k, v[m].z & k, v[m].w & k));
-                if (__builtin_expect(direct, 0)) {
+                for (int m = 0; m < 2; ++m)
+                    if (xj0 + 32 * m >= left) v[m] = make_uint4(0, 0, 0, 0);
+            }
+            uint64_t in = ~0ull;
+            if (__builtin_expect(ref_mode(p) == 2, 0)) {
+#pragma unroll
+                for (int m = 0; m < 2; ++m) {
                     const float cs = fe[m].y, whole = rintf(cs), part = cs - whole;
-                    const int w = (int)whole;            // 0 of NaN
                     fe[m].x = cs == cs ? fe[m].x * fast_exp2(-part) : 0.f;
                     fe[m].y = fast_exp2(part);
-                    const float fs = ldexpf(fe[m].x, (int)rintf(ref.w) - w);
-                    float q[8];
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) q[e] = a[e] * fs;
-                    *reinterpret_cast<uint4 *>(s_xs + at * XB + x_at + m * 32 * XROW) = pack8(q);
-                    if (OUT && xpc == 0) s_whole[((c - c_begin) & 3) * CB_STEP + xj0 + 32 * m] = w;
+                    float a[8];
+                    unpack8(a, v[m]);
+                    stage_direct(at, m, a, fe[m].x, (int)whole, ref_shift(p));           // 0 of NaN
                 }
-                if (OUT || !direct) {
+            } else {
+                float most[2] = {0.f, 0.f};
+#pragma unroll
+                for (int m = 0; m < 2; ++m) {
+                    float a[8];
+                    unpack8(a, v[m]);
 #pragma unroll
                     for (int q = 0; q < 8; ++q) a[q] *= fe[m].x;
+#pragma unroll
+                    for (int q = 0; q < 8; ++q) most[m] = fmaxf(most[m], fabsf(a[q]));
                     *reinterpret_cast<uint4 *>(s_x + at * XB + x_at + m * 32 * XROW) = pack8(a);
                 }
+                if (__builtin_expect(left < CB_STEP, 0)) {
+#pragma unroll
+                    for (int m = 0; m < 2; ++m)
+                        if (xj0 + 32 * m >= left) most[m] = ref[2];
+                }
+                const bool wide = ref_mode(p) == 1 || ref_r0(p) < -(int)CB_NEAR / 2;
+                in = __ballot(fminf(most[0], most[1]) >= (wide ? ref[2] : -1.f) && fmaxf(most[0], most[1]) <= ref[3]);
             }
+            reinterpret_cast<unsigned char *>(&s_ref[at].w)[iow] = left > 0 && in != ~0ull;
         };
         const int ya0 = xj0 * (128 * PT) + ((xpc ^ (xj0 & YM)) << 4), ya1 = xj0 * (128 * PT) + (((xpc + 4 * PT) ^ (xj0 & YM)) << 4);
+        uint16_t *yq = y + xbase + (int64_t)c_begin * CB_STEP * trow;
         // stages step c + 2 (xn) and finishes step c - 1 (xo)
-        auto pass = [&](int c, int at, const uint4 (&xn)[2], float2 (&fn)[2], const float4 &rn, const uint4 (&xo)[2], const float2 (&fo)[2]) __attribute__((always_inline)) {
+        auto pass = [&](int c, int at, uint4 (&xn)[2], float2 (&fn)[2], const cb_f32x4_t &rn, const uint4 (&xo)[2], const float2 (&fo)[2], int ybuf) __attribute__((always_inline)) {
             if (!OUT) {
                 stage_x(c + 2, at, xn, fn, rn);
                 return;
             }
-            const unsigned char *q = s_y + ((c - 1) & 1) * 2 * YB;
+            const unsigned char *q = s_y + ybuf * 2 * YB;
             float4 v[2][4];
 #pragma unroll
             for (int m = 0; m < 2; ++m) {
@@ -711,7 +825,6 @@ chain_bf16_kernel(const uint16_t *__restrict__ x, const float *__restrict__ D, c
                 v[m][3] = *reinterpret_cast<const float4 *>(q + YB + ya1 + m * 32 * 128 * PT);
             }
             stage_x(c + 2, at, xn, fn, rn);
-            uint16_t *yq = y + xbase + (int64_t)(c - 1) * CB_STEP * trow;
             float r[2][8];
 #pragma unroll
             for (int m = 0; m < 2; ++m)
@@ -731,36 +844,62 @@ chain_bf16_kernel(const uint16_t *__restrict__ x, const float *__restrict__ D, c
                     for (int k = 0; k < 8; ++k) r[m][k] += dsk * a[k];
                 }
             }
+            if (c > c_begin) {
+                const int left = t_end - (c - 1) * CB_STEP;
+                if (left >= CB_STEP) {
+                    if (xin) {
+                        store_nt(yq + xoff[0], pack8(r[0]));
+                        store_nt(yq + xoff[1], pack8(r[1]));
+                    }
+                } else {
 #pragma unroll
-            for (int m = 0; m < 2; ++m)
-                if (xin && c > c_begin && (c - 1) * CB_STEP + xj0 + 32 * m < t_end) store_nt(yq + xoff[m], pack8(r[m]));
+                    for (int m = 0; m < 2; ++m)
+                        if (xin && xj0 + 32 * m < left) store_nt(yq + xoff[m], pack8(r[m]));
+                }
+                yq += CB_STEP * trow;
+            }
         };
         // x of step k in xr[(k - c_begin) % CB_RING]: loaded CB_RING - 4 steps before it is staged, kept until its y goes out
         uint4 xr[CB_RING][2];
         float2 fr[CB_RING][2];
-        const float4 *ref0 = reinterpret_cast<const float4 *>(tb.ref) + bhs + (lane & 0);
-        float4 rf[CB_RING];
-        auto load_ref = [&](int c) __attribute__((always_inline)) { return ref0[min(c, c_end - 1)]; };
+        // what all lanes take of a step comes through the scalar cache, three steps ahead
+        const cb_scalar_f32x2_t *refs = (const cb_scalar_f32x2_t *)tb.ref + bhs, *mags = (const cb_scalar_f32x2_t *)tb.mag + (int64_t)b * nsteps * s.G + g;
+        auto load_ref = [&](int c) __attribute__((always_inline)) -> cb_f32x4_t {
+            c = min(c, c_end - 1);
+            const cb_f32x2_t r = refs[c], m = mags[(int64_t)c * s.G];
+            return cb_f32x4_t{r.x, r.y, m.x, m.y};
+        };
+        auto put_ref = [&](int at, const cb_f32x4_t &r) __attribute__((always_inline)) {
+            if (iow == 0) *reinterpret_cast<float2 *>(s_ref + at) = make_float2(r[0], r[1]);
+        };
+        const cb_f32x4_t first = load_ref(c_begin), second = load_ref(c_begin + 1);
+        cb_f32x4_t after = load_ref(c_begin + 2);
 #pragma unroll
-        for (int u = 0; u < CB_RING - 1; ++u) {
-            load_x(c_begin + u, xr[u], fr[u]);
-            rf[u] = load_ref(c_begin + u);
-        }
-        if (iow == 0 && lane == 0) { s_ref[0] = rf[0]; s_ref[1] = rf[1]; }
-        stage_x(c_begin, 0, xr[0], fr[0], rf[0]);
-        stage_x(c_begin + 1, 1, xr[1], fr[1], rf[1]);
+        for (int u = 0; u < CB_RING - 1; ++u) load_x(xr[u], fr[u]);
+        put_ref(0, first);
+        put_ref(1, second);
+        stage_x(c_begin, 0, xr[0], fr[0], first);
+        stage_x(c_begin + 1, 1, xr[1], fr[1], second);
         lds_barrier();                                   // x of the first two steps
+        // a step that the compute waves turn direct: its factor of y, and the barrier in turn_direct
+        auto turned = [&](float2 (&fe)[2]) __attribute__((always_inline)) {
+#pragma unroll
+            for (int m = 0; m < 2; ++m) fe[m].y = ldexpf(fe[m].y, -exponent(fe[m].y));
+            lds_barrier();
+        };
+        if (__builtin_expect(flagged(s_ref[0].w), 0)) turned(fr[0]);
         for (int c0 = c_begin;; c0 += CB_RING) {
 #pragma unroll
             for (int u = 0; u < CB_RING; ++u) {
-                const int c = c0 + u;
+                const int c = c0 + u, n1 = (u + 1) % CB_RING, n2 = (u + 2) % CB_RING, o = (u + CB_RING - 1) % CB_RING;
                 lds_barrier();
-                pass(c, (u + 2) % 3, xr[(u + 2) % CB_RING], fr[(u + 2) % CB_RING], rf[(u + 2) % CB_RING], xr[(u + CB_RING - 1) % CB_RING],
-                     fr[(u + CB_RING - 1) % CB_RING]);
+                const int next = s_ref[(u + 1) % 3].w;
+                pass(c, (u + 2) % 3, xr[n2], fr[n2], after, xr[o], fr[o], (u + 1) & 1);
                 if (c >= c_end) return;
-                if (iow == 0 && lane == 0) s_ref[(c + 2 - c_begin) & 3] = rf[(u + 2) % CB_RING];
-                rf[(u + CB_RING - 1) % CB_RING] = load_ref(c + CB_RING - 1);
-                load_x(c + CB_RING - 1, xr[(u + CB_RING - 1) % CB_RING], fr[(u + CB_RING - 1) % CB_RING]);
+                put_ref((u + 2) % 3, after);
+                after = load_ref(c + 3);
+                load_x(xr[o], fr[o]);
+                if (__builtin_expect(flagged(next), 0)) turned(fr[n1]);
             }
         }
     }
@@ -774,7 +913,7 @@ size_t chain_bf16_ops_bytes(const Shape &s)
 }
 size_t chain_bf16_table_bytes(const Shape &s)
 {
-    return (size_t)s.B * s.H * ((s.L + CB_STEP - 1) / CB_STEP) * (2 * CB_STEP + 4) * sizeof(float);
+    return (size_t)s.B * ((s.L + CB_STEP - 1) / CB_STEP) * (s.H * (size_t)(2 * CB_STEP + 4) + 2 * s.G) * sizeof(float);
 }
 
 // Segments of a sequence, before the scratch is asked how many pieces it holds.  A compute unit takes 1.6 us for a step of a
@@ -801,7 +940,7 @@ static swimba_status launch_chain_t(const Shape &s, const void *x, const void *d
 {
     const int nsteps = (s.L + CB_STEP - 1) / CB_STEP, ncu = device_cus();
     auto mix_shm = [](int K, int E) { return (size_t)2 * CB_STEP * (64 * NT + 16) + (size_t)CB_STEP * K * 8 + (E ? (size_t)CB_STEP * (E | 1) * 4 : 0); };
-    auto chain_shm = [](int PT, bool out) { return (size_t)(out ? 14 : 3) * CB_STEP * 64 * PT + 64 + (out ? 16 * CB_STEP : 0); };
+    auto chain_shm = [](int PT, bool out) { return (size_t)(out ? 14 : 3) * CB_STEP * 64 * PT + 48 + (out ? 12 * CB_STEP : 0); };
     // more than 64 KB of dynamic LDS has to be allowed once per device
     static std::atomic<uint64_t> attr_set{0};            // one bit per device ordinal
     int dev = 0;
@@ -823,7 +962,7 @@ static swimba_status launch_chain_t(const Shape &s, const void *x, const void *d
     const int items = (int)((int64_t)s.B * nsteps * s.G / gpb);
     const int64_t bhs = (int64_t)s.B * s.H * nsteps;
     float *tables = (float *)scr.tables;
-    const ChainTables tb = {tables, tables + bhs * 2 * CB_STEP};
+    const ChainTables tb = {tables, tables + bhs * 2 * CB_STEP, tables + bhs * (2 * CB_STEP + 2), tables + (bhs * (2 * CB_STEP + 3) + 1) / 2 * 2};
     const int tblocks = (int)(((int64_t)s.B * nsteps * ((s.H + 7) / 8) + 7) / 8);
     hipLaunchKernelGGL(mix_steps_kernel<NT>, dim3(items + tblocks), dim3(CB_MIX_THREADS), mix_shm(s.K, w_sel ? 0 : s.E), st,
                        (const bf16 *)Be, (const bf16 *)Ce, (const bf16 *)logits, idx, w, w_sel, (uint16_t *)scr.ops,

@@ -196,6 +196,52 @@ def test_direct_steps_round_as_the_others_do():
     assert torch.equal(got.y, base.y) and torch.equal(got.h_final, base.h_final)
 
 
+# powers of two on (x and h0, B, C) and tokens: the scaled problem is the scaled base problem, but for the inputs' own least
+# values where they come near the end of the range
+MAGNITUDES = [(100, 0, 0, 330), (115, 0, 0, 330), (0, 70, -70, 200), (60, 40, -90, 200), (90, 0, 0, 10300),
+              (-100, 0, 0, 330), (0, -90, 60, 200), (-50, -40, 80, 200), (-90, 0, 0, 10300)]
+
+
+@pytest.mark.parametrize("sx,sb,sc,L", MAGNITUDES)
+def test_magnitudes(sx, sb, sc, L):
+    """Inputs far from 1 whose results are in range, at decays from slow to one that no step can hold: what the same inputs
+    near 1 give."""
+    H = 8
+    p, h0 = inputs((1, L, H, 64, 128, 1, 4, 2, True, False, 1.0), 15)
+    p["A"][:] = -16.0
+    dts = np.array([1e-3, 0.01, 0.03, 0.045, 0.09, 0.16, 0.5, 3.0], np.float32)
+    p["dt"] = torch.from_numpy(np.broadcast_to(dts, (1, L, H)).copy()).to(torch.bfloat16).to(torch.float32).numpy()
+    base = forward(p, 2, h0, False)
+    f = lambda e: np.float32(2.0 ** e)
+    q = dict(p, x=p["x"] * f(sx), B_experts=p["B_experts"] * f(sb), C_experts=p["C_experts"] * f(sc))
+    got = forward(q, 2, h0 * f(sx) * f(sb), False)
+    y = host(got.y) / 2.0 ** (sx + sb + sc)
+    h = host(got.h_final) / 2.0 ** (sx + sb)
+    if min(sx, sb) >= 0 and L < 2048:
+        assert np.array_equal(y, host(base.y)) and np.array_equal(h, host(base.h_final))
+    # values of x and B under 2^-126 are 2^-26 of the others at most
+    assert rel_errors(y, host(base.y), (0, 2))[0] < 1e-5 and rel_errors(h, host(base.h_final), (0, 1))[0] < 1e-5
+
+
+@pytest.mark.parametrize("scale", [1e30, 5e37, 1e-30, 0.0])
+@pytest.mark.parametrize("s", [0, 5, 40, 63, 64, 130])
+def test_one_tokens_magnitude_changes_no_bit_in_front(scale, s):
+    """A token whose x no factor fits takes its step to direct: the tokens in front keep their bits, those behind it are right."""
+    p, h0 = inputs((1, 150, 24, 64, 128, 1, 4, 2, True, True, 1.0), 16)
+    p["A"][::2] = -16.0
+    p["dt"] = np.abs(p["dt"]) + np.float32(0.03125)       # most steps span 2^60 and more
+    p["dt"] = torch.from_numpy(p["dt"]).to(torch.bfloat16).to(torch.float32).numpy()
+    base = forward(p, 2, h0, True)
+    q = dict(p, x=p["x"].copy())
+    q["x"][:, s] = torch.from_numpy(np.clip(q["x"][:, s], -1, 1) * np.float32(scale)).to(torch.bfloat16).to(torch.float32).numpy()
+    got = forward(q, 2, h0, True)
+    assert torch.equal(got.y[:, :s], base.y[:, :s]) and torch.isfinite(got.y).all()
+    ref = orc.mixer_fwd(q["x"], q["dt"], q["A"], q["D"], q["B_experts"], q["C_experts"], q["router_logits"], 2, h0=h0)
+    a = abs_inputs(q)
+    aref = orc.mixer_fwd(a["x"], a["dt"], a["A"], a["D"], a["B_experts"], a["C_experts"], a["router_logits"], 2, h0=np.abs(h0))
+    assert componentwise_excess(host(got.y), ref["y"], aref["y"]) <= comp_tol("bf16")
+
+
 @pytest.mark.parametrize("value", [float("nan"), float("inf")])
 def test_values_that_are_not_finite_reach_no_earlier_tile(value):
     """A dt or x that is not finite leaves the tokens of the 32-token tiles in front of its own alone."""
