@@ -251,9 +251,12 @@ static swimba_status carve(const swimba_dims *d, void *workspace, size_t bytes, 
     ws->cdec = mf ? (float *)(p + lo.cdec) : nullptr;
     ws->hmid = mf ? (float *)(p + lo.hmid) : nullptr;
     if (mf) {
+        // what pieces leave behind: as much room as with the largest chunk, which has the fewest chunk states, so that the
+        // chunk length does not change the segments and with them a result
         const size_t tables = align_up(chain_bf16_table_bytes(make_shape(d)), 256);
-        ws->chain = {ws->cmix, ws->states_lp, (float *)(p + lo.states_lp + tables), ws->hmid, lo.cmix - lo.states_lp - tables,
-                     lo.total - lo.hmid, ws->cs};
+        const size_t states = (size_t)d->batch * (((size_t)d->seqlen + 255) / 256) * d->nheads * 64 * 128 * sizeof(uint16_t);
+        const size_t hmid = (size_t)d->batch * (PASS_SPLIT_MAX_SEGMENTS - 1) * d->nheads * d->headdim * d->dstate * sizeof(float);
+        ws->chain = {ws->cmix, ws->states_lp, (float *)(p + lo.states_lp + tables), ws->hmid, states - tables, hmid, ws->cs};
     }
     ws->cop = mf ? nullptr : (float *)(p + cf.cop);
     ws->bop = mf ? nullptr : (float *)(p + cf.bop);

@@ -1,6 +1,6 @@
 // SSD forward for bf16 io on v_mfma_f32_32x32x16_bf16 as one walk over 64-token steps per (batch, head)
 // (paper, background section on SSD: matrix work inside chunks, a linear recurrence between chunks; Theorem 1: the
-// mixed streams feed one plain SSM).  The result does not depend on the chunk length.
+// mixed streams feed one plain SSM).  The chunk length changes no bit of a finite result; ChainPieces has the other case.
 //   mix_steps_kernel   (batch, step, groups): routes 64 tokens, mixes their B and C rows and writes them, and the masked
 //                      products G = C B^T, as the operand registers the chain reads; and, in workgroups of its own, the
 //                      decay tables of every (batch, head, step).  Shared by the heads of a group.
@@ -326,7 +326,9 @@ __device__ __forceinline__ void split_exp2(float e, float &frac, int &whole)
 // their sum, each decayed to its first token (the recurrence is linear in the state).
 //   piece(q) (B, H, P tiles, NT, 4, 64, 4) fp32 accumulator registers; the first n_a pieces lie in a, the others in b
 //   sum (B, H, npiece, 2)  log2 of a piece's decay; 1 where the piece is written.  With skip set one whose factor up to the
-//                          segment's end is under 2^-150, which no fp32 sum sees, is not walked.
+//                          segment's end is under 2^-150, a factor of zero in fp32, is not walked.  It is set where the split
+//                          pass over whole chunks left the same out, so there an x that is not finite can end with its
+//                          segment, as it did; elsewhere it reaches all that follows.
 struct ChainPieces {
     float *a, *b, *sum, *h0_copy;
     int npiece, n_a, per_seg, steps, skip;

@@ -107,6 +107,17 @@ def test_segments_match_oracle(case):
     assert l2 <= TOL["bf16"] and linf <= TOL["bf16"], (l2, linf)
 
 
+@pytest.mark.parametrize("case", [(1, 10240, 2, 40, 72, 1, 4, 2, True, True, 0.01), (1, 10496, 3, 64, 128, 1, 4, 2, True, True, 0.01)],
+                         ids=["H2P40N72", "H3"])
+def test_the_chunk_length_changes_no_bit_of_segments(case):
+    """Scratch limits the segments of these; it is larger for smaller chunks."""
+    p, h0 = inputs(case, 17)
+    want = forward(p, 2, h0, True, 256)
+    for chunk in (64, 128):
+        got = forward(p, 2, h0, True, chunk)
+        assert torch.equal(got.y, want.y) and torch.equal(got.h_final, want.h_final)
+
+
 def test_segments_final_state_over_the_initial_one():
     """In place the segments read a copy of h0: the bits of the same call out of place, every time."""
     p, h0 = inputs((1, 3100, 64, 64, 128, 1, 4, 2, True, True, 0.2), 11)
