@@ -1,8 +1,7 @@
 #!/usr/bin/env python3
 """Benchmark of the Swimba token-mixer hot path on one MI355X.
 
-A step = one swimba_mixer_fwd call (router + mixing, cumsum + chunk states, state scan,
-output) over one batch of synthetic input resident in HBM.  The headline workload is the
+A step = one swimba_mixer_fwd call (router + mixing, the SSM's forward) over one batch of synthetic input resident in HBM.  The headline workload is the
 largest single-GPU one (long sequence, 8 B/C groups, 16 experts); the two Mamba-2-shaped layers
 and the decode step ride along as extra keys of the same JSON line.  Prints ONE JSON line:
 whole-path tokens/s by host clock over exactly K steps, median / min per-step times from HIP
@@ -81,6 +80,21 @@ def work_model(w, live=1.0, nseg=2):
                    "irreducible": T * (2 * H * P * 2 + H * 2), "flops": 2.0 * T * Q * P * H + 2.0 * T * N * P * H},
     }
     kernels["pass64"] = kernels["pass"]
+    # ---- the walk over 64-token steps ----
+    # router + mixing per step: writes top-k, the C, B and C.B^T operands of a step (6 KB of 16 x 32 tiles of C.B^T; the
+    # states padded to 32, 64 or 128) and, from dt, the decay tables of every head
+    nsteps = w.batch * ((w.seqlen + 63) // 64)
+    op_bytes = nsteps * G * (8 * (4 if N > 64 else 2 if N > 32 else 1) + 6) * 1024
+    tab_bytes = nsteps * (H * (64 * 8 + 12) + G * 8)
+    kernels["chain_mix"] = {"moved": T * (E * 2 + k * 8 + 2 * k * G * N * 2 + H * 2) + op_bytes + tab_bytes,
+                            "irreducible": T * (E * 2 + 2 * k * G * N * 2 + H * 2), "flops": 2.0 * T * 64 * N * G}
+    # x, the operands (once per XCD, from its L2, for the heads of a group) and the tables to y and the final state; cut into
+    # segments, the parts in front of the last one are walked for their state alone first (`live` of them, by 64-token steps)
+    first = (nseg - 1) / nseg * live
+    kernels["chain_walk"] = {"moved": T * 2 * H * P * 2 + op_bytes + tab_bytes + w.batch * H * P * N * 4
+                                      + first * (T * H * P * 2 + T * G * N * 2 + tab_bytes),
+                             "irreducible": T * 2 * H * P * 2 + w.batch * H * P * N * 4,
+                             "flops": T * H * (2.0 * 64 * P + 4.0 * N * P) + first * 2.0 * T * N * P * H}
     # split pass: the chunk states in front of the segment boundaries ((nseg - 1) / nseg of the chunks), of which
     # only the fraction `live` still counts at the boundary behind it (it depends on dt and A; the bench measures
     # it on its inputs), and the boundary states.  Nothing of it is irreducible: x and dt are read a second time.
@@ -98,10 +112,6 @@ def work_model(w, live=1.0, nseg=2):
                                "irreducible": kernels["output"]["irreducible"] + w.batch * H * P * N * 4,
                                "flops": kernels["output"]["flops"]}
     return call, kernels
-
-
-def nchunks_of(w):
-    return (w.seqlen + w.chunk - 1) // w.chunk
 
 
 def main() -> int:
@@ -125,7 +135,7 @@ def main() -> int:
                     help="mixed against separated forward for E in {1,2,4,8,16} on the headline shape")
     ap.add_argument("--stage", default=None,
                     help="run only this stage in the timed loop (for profilers): "
-                         "fwd|mix|mix_chunk|tables|prep|pass|chunk_state|state_scan|output|step|copy")
+                         "fwd|chain_mix|chain_walk|mix|mix_chunk|tables|prep|pass|chunk_state|state_scan|output|step|copy")
     ap.add_argument("--graph", action="store_true",
                     help="launch every timed forward call from a HIP graph captured once per input set instead of "
                          "eagerly (measured: no gain on the long-sequence workload, 7 % on the 370M-shaped one)")
@@ -211,9 +221,14 @@ def main() -> int:
                 self.sets.append(d)
             dims = self.dims
             mix = lambda d: sw.swimba_stage_mix(dims, d["B_experts"], d["C_experts"], d["router_logits"], d["ws"])
-            # the two evaluations of the forward on the MFMA path: one pass over the chunks with the
-            # state in registers, or chunk states through memory; swimba_mixer_fwd picks by shape
+            # the evaluations of the forward on the MFMA path: the walk over 64-token steps, one pass over the chunks
+            # with the state in registers, or chunk states through memory; swimba_mixer_fwd picks by shape
             self.paths = {
+                sw.PATH_CHAIN_BF16: {
+                    "chain_mix": lambda d: sw.swimba_stage_chain_mix(dims, d["dt"], d["A"], d["B_experts"], d["C_experts"],
+                                                                     d["router_logits"], d["ws"]),
+                    "chain_walk": lambda d: sw.swimba_stage_chain_walk(dims, d["x"], d["D"], None, d["y"], d["h_final"], d["ws"]),
+                },
                 sw.PATH_SINGLE_PASS: {
                     "mix": mix,
                     "prep": lambda d: sw.swimba_stage_prep(dims, d["dt"], d["A"], d["ws"]),
@@ -270,19 +285,22 @@ def main() -> int:
             # the pass with one workgroup per (batch, head) instead of per 32-channel slice
             self.extra = {"pass64": lambda d: sw.swimba_stage_pass64(dims, d["x"], d["dt"], d["D"], None, d["y"],
                                                                      d["h_final"], d["ws"])}
-            self.path = sw.swimba_prefill_path(dims)
-            self.nseg = sw.swimba_pass_segments(dims)
+            self.path = sw.swimba_forward_path(dims)
+            self.nseg = sw.swimba_forward_segments(dims)
             self.live = 1.0
             if self.nseg > 1:
                 # fraction of the (chunk, head) pairs in front of a segment boundary whose chunk state reaches
-                # it with a factor of at least 2^-150 (what the split pass computes and reads)
+                # it with a factor of at least 2^-150 (what is computed and read for the boundary); of the walk by
+                # 64-token steps
                 d0 = self.sets[0]
-                nper = nchunks_of(w) // self.nseg
-                tot = (d0["dt"].float() * d0["A"].float()).reshape(w.batch, self.nseg, nper, w.chunk, w.nheads).sum(3)
+                Q = 64 if self.path == sw.PATH_CHAIN_BF16 else w.chunk
+                nper = w.seqlen // Q // self.nseg
+                cut = nper * Q * self.nseg
+                tot = (d0["dt"].float() * d0["A"].float())[:, :cut].reshape(w.batch, self.nseg, nper, Q, w.nheads).sum(3)
                 tot = tot[:, :-1] * 1.4426950408889634
                 suf = torch.flip(torch.cumsum(torch.flip(tot, (2,)), 2), (2,)) - tot
                 self.live = float((suf >= -150.0).float().mean().item())
-            self.path_name = {sw.PATH_SINGLE_PASS: "single_pass", sw.PATH_STAGED: "staged",
+            self.path_name = {sw.PATH_CHAIN_BF16: "walk_over_64_token_steps", sw.PATH_SINGLE_PASS: "single_pass", sw.PATH_STAGED: "staged",
                               sw.PATH_SINGLE_PASS_CHUNK_MIX: "single_pass_chunk_mix",
                               sw.PATH_SINGLE_PASS_HEAD: "single_pass_head", sw.PATH_STAGED_SHORT: "staged_short",
                               sw.PATH_SINGLE_PASS_HEAD_CHUNK_MIX: "single_pass_head_chunk_mix",
@@ -617,7 +635,7 @@ def main() -> int:
 
     p_head = head.p
     head_desc, head_nsets, head_path = head.describe(), head.nsets, head.path_name
-    head_split = {"segments_per_sequence": head.nseg, "chunk_states_live_at_boundary": round(head.live, 4)} if head.nseg > 1 else {}
+    head_split = {"segments_per_sequence": head.nseg, "states_live_at_boundary": round(head.live, 4)} if head.nseg > 1 else {}
     head.close()
     del head
 
@@ -758,7 +776,7 @@ def main() -> int:
             "irreducible_bytes": call["irreducible_bytes"], "dense_flops": call["flops"],
             "dominant_kernel": dict(kernels[dom], name=dom)}
     # the targets the kernels are held to, and whether this run met them
-    contr = {n: kernels[n]["mfma_frac"] for n in ("pass", "pass64", "chunk_state", "output", "chunk_state_tiles",
+    contr = {n: kernels[n]["mfma_frac"] for n in ("chain_walk", "pass", "pass64", "chunk_state", "output", "chunk_state_tiles",
                                                   "output_carry") if n in kernels}
     targets = {
         "contractions_mfma_frac": {"target": 0.5, "value": contr, "met": all(v >= 0.5 for v in contr.values()),
@@ -766,7 +784,7 @@ def main() -> int:
                                            "ridge 312): at the HBM floor the contractions would sit at %.2f of MFMA peak"
                                            % (round(call["flops"] / call["irreducible_bytes"]),
                                               call["flops"] / call["irreducible_bytes"] / 312.5)},
-        "mixing_hbm_frac": {"target": 0.6, "value": (kernels.get("mix") or kernels.get("mix_chunk") or {}).get("hbm_frac")},
+        "mixing_hbm_frac": {"target": 0.6, "value": (kernels.get("chain_mix") or kernels.get("mix") or kernels.get("mix_chunk") or {}).get("hbm_frac")},
         "scan_hbm_frac": ({"target": 0.6, "value": kernels["state_scan"]["hbm_frac_with_intermediates"],
                            "note": "on the chunk states it reads and writes (intermediates of the staged path)"}
                           if "state_scan" in kernels else

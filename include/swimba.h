@@ -75,8 +75,9 @@ typedef struct {
 } swimba_dims;
 
 /* Byte offsets of the scratch arrays inside the workspace (for tests and
- * profiling of single stages; a plain caller only needs `total`).  The fp32 forwards keep scratch of
- * their own from `cs` on; only topk_idx and topk_w can be read after them. */
+ * profiling of single stages; a plain caller only needs `total`).  The forwards that walk 64-token steps
+ * (swimba_forward_path) keep scratch of their own from `cs` on; only topk_idx and topk_w can be read after
+ * them, where the caller gave no arrays of its own for these. */
 typedef struct {
     size_t topk_idx;  /* (B,L,k) int32 : active experts, router order              */
     size_t topk_w;    /* (B,L,k) fp32  : their un-renormalised softmax weights      */
@@ -155,11 +156,18 @@ swimba_status swimba_router_topk(int64_t tokens, int32_t nexperts, int32_t top_k
  * contractions run on bf16 MFMA
  * with fp32 accumulation (mixed streams, decay-weighted x, the C.B^T block, on the diagonal
  * tiles also after the decay mask, and the state carried into a chunk are rounded to bf16
- * as operands; the recurrence between chunks itself runs in fp32 registers);
+ * as operands; the recurrence between chunks itself runs in fp32 registers).  Where swimba_forward_path
+ * gives SWIMBA_PATH_CHAIN_BF16 the contractions run over steps of 64 tokens whatever Q: x is rounded
+ * after its step size and the part of its decay that is no whole power of two, C.B^T before any
+ * decay, and the state at every step; whole powers of two go onto operands and sums without a rounding,
+ * so of finite inputs no bit of a token's y depends on the values behind it, and their magnitude does
+ * not matter as long as operands and results are in range;
  * other bf16 shapes use the fp32 kernels.
  * In fp32 arithmetic an input that is not finite reaches no token in front of its own, no other
  * sequence and, in x (one channel) or dt (one head), nothing beside its channel or head.  The bf16
- * MFMA kernels multiply tiles of 32 tokens and make no such promise.
+ * MFMA kernels multiply tiles of 32 tokens and make no such promise: an x that is not finite reaches the
+ * tokens of its tile, and where a sequence is cut into segments its effect can end with its segment
+ * if everything in that segment decays to zero by its end.
  */
 swimba_status swimba_mixer_fwd(const swimba_dims *dims, const void *x, const void *dt,
                                const float *A, const float *D, const void *B_experts,
@@ -170,9 +178,9 @@ swimba_status swimba_mixer_fwd(const swimba_dims *dims, const void *x, const voi
 /*
  * The stages of swimba_mixer_fwd, one call each, on the same workspace (for
  * per-kernel measurement and stage-level tests).  Running router, cumsum, mix,
- * chunk_state, state_scan, output in this order computes what swimba_mixer_fwd computes
- * (on the bf16 MFMA path swimba_mixer_fwd itself runs mix, prep, pass: the single-pass
- * evaluation below, same operands and roundings, another summation order).
+ * chunk_state, state_scan, output in this order computes what swimba_mixer_fwd computes, to
+ * the rounding of the operands (swimba_forward_path says which kernels that call itself runs;
+ * on SWIMBA_PATH_CHAIN_BF16 the calls chain_mix, chain_walk are its launches).
  *   router      : logits -> ws.topk_idx, ws.topk_w     (no-op on the bf16 MFMA path: mix routes)
  *   cumsum      : dt, A  -> ws.cs   (per-chunk cumsum of dt*A; no-op on the bf16 MFMA path:
  *                 chunk_state computes it)
@@ -199,9 +207,8 @@ swimba_status swimba_stage_pass(const swimba_dims *dims, const void *x, const vo
                                 const float *h0, void *y, float *h_final, void *workspace,
                                 size_t workspace_bytes, void *hip_stream);
 
-/* How the stage calls evaluate these dims best on the current device.  swimba_mixer_fwd (and the
- * _selected/_proj forms) run the kernels named here for few (batch, head) pairs with long sequences; everywhere
- * else in bf16 they walk 64-token steps in two or three launches of their own, which no stage call splits.
+/* Which evaluation over whole chunks fits these dims best on the current device, of those the stage calls below offer.
+ * What swimba_mixer_fwd itself runs is swimba_forward_path.
  * SWIMBA_PATH_GENERIC (fp32-capable kernels, any shape), SWIMBA_PATH_STAGED
  * (bf16 MFMA: mix, chunk_state, state_scan, output; SWIMBA_PATH_STAGED_SHORT for at most 8 chunks,
  * see below), or a single pass over the chunks with the
@@ -228,13 +235,34 @@ swimba_status swimba_stage_pass(const swimba_dims *dims, const void *x, const vo
 #define SWIMBA_PATH_SINGLE_PASS_HEAD_SPLIT 7      /* mix, prep, boundary_states, pass64 on segments */
 #define SWIMBA_PATH_SINGLE_PASS_HEAD_SPLIT_CHUNK_MIX 8   /* mix_chunk, tables, boundary_states, pass64 on segments */
 int swimba_prefill_path(const swimba_dims *dims);
-/* Segments per sequence of the per-head single pass the forward takes for these dims on the current
- * device (1: whole sequences, also on every other path).  Minus the swimba_status for invalid dims. */
+/* Segments per sequence of the per-head single pass where swimba_prefill_path names its split form (1: whole
+ * sequences, also on every other path).  Minus the swimba_status for invalid dims. */
 int swimba_pass_segments(const swimba_dims *dims);
 
+/* What swimba_mixer_fwd runs for these dims on the current device: SWIMBA_PATH_CHAIN_F32 (fp32 arithmetic; a walk over
+ * 64-token steps), SWIMBA_PATH_CHAIN_BF16 (the walk on bf16 MFMA: chain_mix, chain_walk), or, in bf16 with few
+ * (batch, head) pairs and more than 16 steps of 64 tokens, SWIMBA_PATH_STAGED_SHORT, SWIMBA_PATH_STAGED or the split
+ * per-head pass, as swimba_prefill_path names them.  The _selected and _proj forms follow the same rule.
+ * swimba_forward_segments: segments per sequence that a walk or the split pass cuts (1: none).  Minus the
+ * swimba_status for invalid dims.  Host only; launch nothing. */
+#define SWIMBA_PATH_CHAIN_BF16 9
+#define SWIMBA_PATH_CHAIN_F32 10
+int swimba_forward_path(const swimba_dims *dims);
+int swimba_forward_segments(const swimba_dims *dims);
+
+/* The launches behind SWIMBA_PATH_CHAIN_BF16, for any bf16 MFMA dims (SWIMBA_ERR_UNSUPPORTED otherwise), on scratch of
+ * their own that lies over that of the other stages: run in this order they give swimba_mixer_fwd's bits.
+ *   chain_mix  : logits, B/C_experts, dt, A -> ws.topk_idx, ws.topk_w, mixed operands and decay tables of every 64-token step
+ *   chain_walk : x, D, h0 -> y, h_final; one launch, or two where a sequence is cut into segments */
+swimba_status swimba_stage_chain_mix(const swimba_dims *dims, const void *dt, const float *A, const void *B_experts,
+                                     const void *C_experts, const void *router_logits, void *workspace, size_t workspace_bytes,
+                                     void *hip_stream);
+swimba_status swimba_stage_chain_walk(const swimba_dims *dims, const void *x, const float *D, const float *h0, void *y,
+                                      float *h_final, void *workspace, size_t workspace_bytes, void *hip_stream);
+
 /* Single pass with the router, the mixing and the tiles of Bmix.Cmix^T done per whole chunk in one
- * persistent kernel (SWIMBA_PATH_SINGLE_PASS_CHUNK_MIX: mix_chunk, tables, pass).  Taken by the forward
- * on single-pass shapes with at most 16 experts, top_k <= 2 and at least two (batch, chunk, group)
+ * persistent kernel (SWIMBA_PATH_SINGLE_PASS_CHUNK_MIX: mix_chunk, tables, pass).  Named
+ * for single-pass shapes with at most 16 experts, top_k <= 2 and at least two (batch, chunk, group)
  * triples per compute unit; same results as mix + prep, bit for bit.
  *   mix_chunk : B/C_experts, logits -> ws.topk_*, ws.cmix, ws.bmix_t8, ws.cb   (ws.bmix_frag is not written)
  *   tables    : dt, A -> ws.cs2, ws.fdec, ws.cdec                              (prep without the tiles)

@@ -79,6 +79,14 @@ def _load():
         lib.swimba_stage_prep.argtypes = [dp, vp, vp, vp, sz, vp]
         lib.swimba_prefill_path.restype = ctypes.c_int
         lib.swimba_prefill_path.argtypes = [dp]
+        lib.swimba_forward_path.restype = ctypes.c_int
+        lib.swimba_forward_path.argtypes = [dp]
+        lib.swimba_forward_segments.restype = ctypes.c_int
+        lib.swimba_forward_segments.argtypes = [dp]
+        lib.swimba_stage_chain_mix.restype = i32
+        lib.swimba_stage_chain_mix.argtypes = [dp, vp, vp, vp, vp, vp, vp, sz, vp]
+        lib.swimba_stage_chain_walk.restype = i32
+        lib.swimba_stage_chain_walk.argtypes = [dp, vp, vp, vp, vp, vp, vp, sz, vp]
         lib.swimba_stage_mix_chunk.restype = i32
         lib.swimba_stage_mix_chunk.argtypes = [dp, vp, vp, vp, vp, sz, vp]
         lib.swimba_stage_tables.restype = i32
@@ -555,14 +563,45 @@ def swimba_stage_output(dims, x, dt, D, B_experts, C_experts, y, workspace):
 PATH_GENERIC, PATH_STAGED, PATH_SINGLE_PASS, PATH_SINGLE_PASS_CHUNK_MIX, PATH_SINGLE_PASS_HEAD = 0, 1, 2, 3, 4
 PATH_SINGLE_PASS_HEAD_CHUNK_MIX, PATH_STAGED_SHORT = 5, 6
 PATH_SINGLE_PASS_HEAD_SPLIT, PATH_SINGLE_PASS_HEAD_SPLIT_CHUNK_MIX = 7, 8
+PATH_CHAIN_BF16, PATH_CHAIN_F32 = 9, 10
+
+
+def _query(name, dims) -> int:
+    r = getattr(_load(), name)(ctypes.byref(dims))
+    if r < 0:
+        _check(-r, name)
+    return r
 
 
 def swimba_prefill_path(dims) -> int:
-    """Kernels the forward runs for these dims on the current device (PATH_* values)."""
-    r = _load().swimba_prefill_path(ctypes.byref(dims))
-    if r < 0:
-        _check(-r, "swimba_prefill_path")
-    return r
+    """Which evaluation over whole chunks fits these dims best on the current device (PATH_* values)."""
+    return _query("swimba_prefill_path", dims)
+
+
+def swimba_forward_path(dims) -> int:
+    """Kernels swimba_mixer_fwd runs for these dims on the current device (PATH_* values)."""
+    return _query("swimba_forward_path", dims)
+
+
+def swimba_forward_segments(dims) -> int:
+    """Segments per sequence that swimba_mixer_fwd cuts for these dims (1: none)."""
+    return _query("swimba_forward_segments", dims)
+
+
+def swimba_stage_chain_mix(dims, dt, A, B_experts, C_experts, router_logits, workspace):
+    _check(_load().swimba_stage_chain_mix(ctypes.byref(dims), _ptr(dt, "dt"), _ptr(A, "A", torch.float32),
+                                          _ptr(B_experts, "B_experts"), _ptr(C_experts, "C_experts"),
+                                          _ptr(router_logits, "router_logits"),
+                                          _ptr(workspace, "workspace", torch.uint8), workspace.numel(), _stream()),
+           "swimba_stage_chain_mix")
+
+
+def swimba_stage_chain_walk(dims, x, D, h0, y, h_final, workspace):
+    _check(_load().swimba_stage_chain_walk(ctypes.byref(dims), _ptr(x, "x"), _ptr(D, "D", torch.float32),
+                                           _ptr(h0, "h0", torch.float32), _ptr(y, "y"),
+                                           _ptr(h_final, "h_final", torch.float32),
+                                           _ptr(workspace, "workspace", torch.uint8), workspace.numel(), _stream()),
+           "swimba_stage_chain_walk")
 
 
 def swimba_stage_mix_chunk(dims, B_experts, C_experts, router_logits, workspace):
@@ -616,11 +655,8 @@ def swimba_stage_pass64(dims, x, dt, D, h0, y, h_final, workspace):
 
 
 def swimba_pass_segments(dims) -> int:
-    """Segments per sequence of the per-head single pass the forward takes for these dims (1: none)."""
-    r = _load().swimba_pass_segments(ctypes.byref(dims))
-    if r < 0:
-        _check(-r, "swimba_pass_segments")
-    return r
+    """Segments per sequence of the per-head single pass where swimba_prefill_path names its split form (1: none)."""
+    return _query("swimba_pass_segments", dims)
 
 
 def swimba_stage_boundary_states(dims, x, dt, A, h0, nseg, workspace):

@@ -227,6 +227,15 @@ struct Ws {
     ChainScratch chain;                             // bf16 chain
 };
 
+// What pieces of a sequence leave behind: as much room as with the largest chunk, which has the fewest chunk states, so that
+// the chunk length does not change the segments and with them a result.
+static void chain_room(const swimba_dims *d, ChainScratch *scr)
+{
+    const size_t tables = align_up(chain_bf16_table_bytes(make_shape(d)), 256);
+    scr->a_bytes = (size_t)d->batch * (((size_t)d->seqlen + 255) / 256) * d->nheads * 64 * 128 * sizeof(uint16_t) - tables;
+    scr->b_bytes = (size_t)d->batch * (PASS_SPLIT_MAX_SEGMENTS - 1) * d->nheads * d->headdim * d->dstate * sizeof(float);
+}
+
 static swimba_status carve(const swimba_dims *d, void *workspace, size_t bytes, Ws *ws)
 {
     swimba_status st = check_mixer(d);
@@ -251,12 +260,9 @@ static swimba_status carve(const swimba_dims *d, void *workspace, size_t bytes, 
     ws->cdec = mf ? (float *)(p + lo.cdec) : nullptr;
     ws->hmid = mf ? (float *)(p + lo.hmid) : nullptr;
     if (mf) {
-        // what pieces leave behind: as much room as with the largest chunk, which has the fewest chunk states, so that the
-        // chunk length does not change the segments and with them a result
         const size_t tables = align_up(chain_bf16_table_bytes(make_shape(d)), 256);
-        const size_t states = (size_t)d->batch * (((size_t)d->seqlen + 255) / 256) * d->nheads * 64 * 128 * sizeof(uint16_t);
-        const size_t hmid = (size_t)d->batch * (PASS_SPLIT_MAX_SEGMENTS - 1) * d->nheads * d->headdim * d->dstate * sizeof(float);
-        ws->chain = {ws->cmix, ws->states_lp, (float *)(p + lo.states_lp + tables), ws->hmid, states - tables, hmid, ws->cs};
+        ws->chain = {ws->cmix, ws->states_lp, (float *)(p + lo.states_lp + tables), ws->hmid, 0, 0, ws->cs};
+        chain_room(d, &ws->chain);
     }
     ws->cop = mf ? nullptr : (float *)(p + cf.cop);
     ws->bop = mf ? nullptr : (float *)(p + cf.bop);
@@ -434,6 +440,54 @@ int swimba_pass_segments(const swimba_dims *dims)
     swimba_status st = check_mixer(dims);
     if (st != SWIMBA_OK) return -(int)st;
     return pass_kind(dims) == PASS_HEAD64 ? head64_segments(dims) : 1;
+}
+
+int swimba_forward_path(const swimba_dims *dims)
+{
+    swimba_status st = check_mixer(dims);
+    if (st != SWIMBA_OK) return -(int)st;
+    if (!use_mfma_path(dims)) return SWIMBA_PATH_CHAIN_F32;
+    return use_chain_bf16(dims) ? SWIMBA_PATH_CHAIN_BF16 : swimba_prefill_path(dims);
+}
+
+int swimba_forward_segments(const swimba_dims *dims)
+{
+    const int path = swimba_forward_path(dims);
+    if (path < 0) return path;
+    if (path == SWIMBA_PATH_CHAIN_F32) return chain_f32_segments(dims->batch, dims->seqlen, dims->nheads, dims->headdim);
+    if (path != SWIMBA_PATH_CHAIN_BF16) return swimba_pass_segments(dims);
+    if ((int64_t)dims->batch * dims->seqlen == 0) return 1;
+    ChainScratch scr = {};
+    chain_room(dims, &scr);
+    return chain_bf16_planned_segments(make_shape(dims), scr, device_cus());
+}
+
+swimba_status swimba_stage_chain_mix(const swimba_dims *dims, const void *dt, const float *A, const void *B_experts,
+                                     const void *C_experts, const void *router_logits, void *workspace, size_t workspace_bytes,
+                                     void *hip_stream)
+{
+    Ws ws;
+    swimba_status st = carve(dims, workspace, workspace_bytes, &ws);
+    if (st != SWIMBA_OK) return st;
+    if (!use_mfma_path(dims)) return SWIMBA_ERR_UNSUPPORTED;
+    if ((int64_t)dims->batch * dims->seqlen == 0) return SWIMBA_OK;
+    if (!dt || !A || !B_experts || !C_experts || !router_logits) return SWIMBA_ERR_NULL;
+    if (check_align(dims->io_dtype, {B_experts, C_experts}, {dt, router_logits}, {A}) != SWIMBA_OK) return SWIMBA_ERR_ALIGNMENT;
+    return launch_chain_mix_bf16(make_shape(dims), dt, A, B_experts, C_experts, router_logits, nullptr, ws.idx, ws.w, ws.chain,
+                                 (hipStream_t)hip_stream);
+}
+
+swimba_status swimba_stage_chain_walk(const swimba_dims *dims, const void *x, const float *D, const float *h0, void *y, float *h_final,
+                                      void *workspace, size_t workspace_bytes, void *hip_stream)
+{
+    Ws ws;
+    swimba_status st = carve(dims, workspace, workspace_bytes, &ws);
+    if (st != SWIMBA_OK) return st;
+    if (!use_mfma_path(dims)) return SWIMBA_ERR_UNSUPPORTED;
+    if ((int64_t)dims->batch * dims->seqlen == 0) return SWIMBA_OK;
+    if (!x || !y) return SWIMBA_ERR_NULL;
+    if (check_align(dims->io_dtype, {x, y, h0, h_final}, {}, {D}) != SWIMBA_OK) return SWIMBA_ERR_ALIGNMENT;
+    return launch_chain_walk_bf16(make_shape(dims), x, D, h0, y, h_final, ws.chain, head64_segments(dims) > 1, (hipStream_t)hip_stream);
 }
 
 swimba_status swimba_stage_mix_chunk(const swimba_dims *dims, const void *B_experts, const void *C_experts,

@@ -27,7 +27,9 @@
 
 #include <algorithm>
 #include <atomic>
+#include <initializer_list>
 #include <type_traits>
+#include <utility>
 
 namespace swimba {
 
@@ -907,12 +909,6 @@ chain_bf16_kernel(const uint16_t *__restrict__ x, const float *__restrict__ D, c
     }
 }
 
-// scratch: operand images and tables
-size_t chain_bf16_ops_bytes(const Shape &s)
-{
-    const int NT = s.N > 64 ? 4 : s.N > 32 ? 2 : 1;
-    return (size_t)s.B * ((s.L + CB_STEP - 1) / CB_STEP) * s.G * cb_item_frags(NT) * 1024;
-}
 size_t chain_bf16_table_bytes(const Shape &s)
 {
     return (size_t)s.B * ((s.L + CB_STEP - 1) / CB_STEP) * (s.H * (size_t)(2 * CB_STEP + 4) + 2 * s.G) * sizeof(float);
@@ -935,43 +931,19 @@ int chain_bf16_segments(int64_t chains, int64_t steps, int64_t ncu)
     return (int)(6 * two >= 14 * one && steps >= 24 * two ? two : one);
 }
 
-template <int NT>
-static swimba_status launch_chain_t(const Shape &s, const void *x, const void *dt, const float *A, const float *D,
-                                    const void *Be, const void *Ce, const void *logits, const float *w_sel, const float *h0,
-                                    void *y, float *h_final, int32_t *idx, float *w, const ChainScratch &scr, bool skip, hipStream_t st)
+static int chain_tiles(const Shape &s) { return s.N > 64 ? 4 : s.N > 32 ? 2 : 1; }
+// bytes of what one piece of a sequence leaves behind, of all (batch, head)
+static size_t chain_piece_bytes(const Shape &s) { return (size_t)s.B * s.H * ((s.P + 31) / 32) * chain_tiles(s) * 4096; }
+
+struct ChainPlan {
+    int nsteps, nseg, steps_per_seg;
+    ChainPieces pieces;
+};
+static ChainPlan chain_plan(const Shape &s, const ChainScratch &scr, bool skip, int ncu)
 {
-    const int nsteps = (s.L + CB_STEP - 1) / CB_STEP, ncu = device_cus();
-    auto mix_shm = [](int K, int E) { return (size_t)2 * CB_STEP * (64 * NT + 16) + (size_t)CB_STEP * K * 8 + (E ? (size_t)CB_STEP * (E | 1) * 4 : 0); };
-    auto chain_shm = [](int PT, bool out) { return (size_t)(out ? 14 : 3) * CB_STEP * 64 * PT + 48 + (out ? 12 * CB_STEP : 0); };
-    // more than 64 KB of dynamic LDS has to be allowed once per device
-    static std::atomic<uint64_t> attr_set{0};            // one bit per device ordinal
-    int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e != hipSuccess) { set_last_hip_error((int)e); return SWIMBA_ERR_HIP; }
-    const uint64_t bit = 1ull << (dev & 63);
-    if (!(attr_set.load(std::memory_order_acquire) & bit)) {
-        e = hipFuncSetAttribute((const void *)mix_steps_kernel<NT>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)mix_shm(SWIMBA_MAX_TOPK, SWIMBA_MAX_EXPERTS));
-        if (e == hipSuccess) e = hipFuncSetAttribute((const void *)chain_bf16_kernel<NT, 1, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)chain_shm(1, true));
-        if (e == hipSuccess) e = hipFuncSetAttribute((const void *)chain_bf16_kernel<NT, 2, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)chain_shm(2, true));
-        if (e != hipSuccess) { set_last_hip_error((int)e); return SWIMBA_ERR_HIP; }
-        attr_set.fetch_or(bit, std::memory_order_release);
-    }
-    // A workgroup routes its tokens once for as many groups as leave two workgroups to a compute unit.
-    int gpb = 1;
-    for (int n = 2; n <= s.G; ++n)
-        if (s.G % n == 0 && (int64_t)s.B * nsteps * s.G / n >= 2 * (int64_t)ncu) gpb = n;
-    const int items = (int)((int64_t)s.B * nsteps * s.G / gpb);
-    const int64_t bhs = (int64_t)s.B * s.H * nsteps;
-    float *tables = (float *)scr.tables;
-    const ChainTables tb = {tables, tables + bhs * 2 * CB_STEP, tables + bhs * (2 * CB_STEP + 2), tables + (bhs * (2 * CB_STEP + 3) + 1) / 2 * 2};
-    const int tblocks = (int)(((int64_t)s.B * nsteps * ((s.H + 7) / 8) + 7) / 8);
-    hipLaunchKernelGGL(mix_steps_kernel<NT>, dim3(items + tblocks), dim3(CB_MIX_THREADS), mix_shm(s.K, w_sel ? 0 : s.E), st,
-                       (const bf16 *)Be, (const bf16 *)Ce, (const bf16 *)logits, idx, w, w_sel, (uint16_t *)scr.ops,
-                       (const bf16 *)dt, A, tb, s, nsteps, gpb, items);
-    SWIMBA_CHECK_LAUNCH();
+    const int nsteps = (s.L + CB_STEP - 1) / CB_STEP;
     // pieces that the scratch holds, one place kept for a copy of h0
-    const size_t unit = (size_t)s.B * s.H * ((s.P + 31) / 32) * NT * 4096;
+    const size_t unit = chain_piece_bytes(s);
     ChainPieces pieces = {scr.a, scr.b, scr.sum, nullptr, 0, (int)std::min(scr.a_bytes / unit, (size_t)64), 1, nsteps, skip};
     const int cap = (int)std::min(pieces.n_a + scr.b_bytes / unit, (size_t)65) - 1;
     // A piece is about 32 steps at most: enough pieces to fill the chip where a segment is long.
@@ -985,6 +957,66 @@ static swimba_status launch_chain_t(const Shape &s, const void *x, const void *d
     }
     if (nseg == 1) steps_per_seg = nsteps;
     pieces.npiece = (nseg - 1) * pieces.per_seg;
+    return {nsteps, nseg, steps_per_seg, pieces};
+}
+int chain_bf16_planned_segments(const Shape &s, const ChainScratch &scr, int ncu) { return chain_plan(s, scr, false, ncu).nseg; }
+
+static ChainTables chain_tables(const Shape &s, const ChainScratch &scr)
+{
+    const int64_t bhs = (int64_t)s.B * s.H * ((s.L + CB_STEP - 1) / CB_STEP);
+    float *t = (float *)scr.tables;
+    return {t, t + bhs * 2 * CB_STEP, t + bhs * (2 * CB_STEP + 2), t + (bhs * (2 * CB_STEP + 3) + 1) / 2 * 2};
+}
+
+// more than 64 KB of dynamic LDS has to be allowed once per device and kernel; done holds one bit per device ordinal
+static swimba_status allow_lds(std::atomic<uint64_t> &done, std::initializer_list<std::pair<const void *, size_t>> kernels)
+{
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    const uint64_t bit = 1ull << (dev & 63);
+    if (e == hipSuccess && (done.load(std::memory_order_acquire) & bit)) return SWIMBA_OK;
+    for (const auto &k : kernels)
+        if (e == hipSuccess) e = hipFuncSetAttribute(k.first, hipFuncAttributeMaxDynamicSharedMemorySize, (int)k.second);
+    if (e != hipSuccess) { set_last_hip_error((int)e); return SWIMBA_ERR_HIP; }
+    done.fetch_or(bit, std::memory_order_release);
+    return SWIMBA_OK;
+}
+
+template <int NT>
+static swimba_status launch_mix_t(const Shape &s, const void *dt, const float *A, const void *Be, const void *Ce, const void *logits,
+                                  const float *w_sel, int32_t *idx, float *w, const ChainScratch &scr, hipStream_t st)
+{
+    const int nsteps = (s.L + CB_STEP - 1) / CB_STEP, ncu = device_cus();
+    auto mix_shm = [](int K, int E) { return (size_t)2 * CB_STEP * (64 * NT + 16) + (size_t)CB_STEP * K * 8 + (E ? (size_t)CB_STEP * (E | 1) * 4 : 0); };
+    static std::atomic<uint64_t> done{0};
+    const swimba_status ok = allow_lds(done, {{(const void *)mix_steps_kernel<NT>, mix_shm(SWIMBA_MAX_TOPK, SWIMBA_MAX_EXPERTS)}});
+    if (ok != SWIMBA_OK) return ok;
+    // A workgroup routes its tokens once for as many groups as leave two workgroups to a compute unit.
+    int gpb = 1;
+    for (int n = 2; n <= s.G; ++n)
+        if (s.G % n == 0 && (int64_t)s.B * nsteps * s.G / n >= 2 * (int64_t)ncu) gpb = n;
+    const int items = (int)((int64_t)s.B * nsteps * s.G / gpb);
+    const int tblocks = (int)(((int64_t)s.B * nsteps * ((s.H + 7) / 8) + 7) / 8);
+    hipLaunchKernelGGL(mix_steps_kernel<NT>, dim3(items + tblocks), dim3(CB_MIX_THREADS), mix_shm(s.K, w_sel ? 0 : s.E), st,
+                       (const bf16 *)Be, (const bf16 *)Ce, (const bf16 *)logits, idx, w, w_sel, (uint16_t *)scr.ops,
+                       (const bf16 *)dt, A, chain_tables(s, scr), s, nsteps, gpb, items);
+    SWIMBA_CHECK_LAUNCH();
+    return SWIMBA_OK;
+}
+
+template <int NT>
+static swimba_status launch_walk_t(const Shape &s, const void *x, const float *D, const float *h0, void *y, float *h_final,
+                                   const ChainScratch &scr, bool skip, hipStream_t st)
+{
+    const int ncu = std::max(device_cus(), 1);
+    auto chain_shm = [](int PT, bool out) { return (size_t)(out ? 14 : 3) * CB_STEP * 64 * PT + 48 + (out ? 12 * CB_STEP : 0); };
+    static std::atomic<uint64_t> done{0};
+    const swimba_status ok = allow_lds(done, {{(const void *)chain_bf16_kernel<NT, 1, true>, chain_shm(1, true)},
+                                              {(const void *)chain_bf16_kernel<NT, 2, true>, chain_shm(2, true)}});
+    if (ok != SWIMBA_OK) return ok;
+    ChainPlan plan = chain_plan(s, scr, skip, ncu);
+    ChainPieces &pieces = plan.pieces;
+    const size_t unit = chain_piece_bytes(s);
     int hblock = std::min(s.H, 8);
     while (s.H % hblock) --hblock;
     // Both channel tiles of a head in one workgroup (one to a compute unit) where the heads fill at least three fifths of
@@ -996,10 +1028,10 @@ static swimba_status launch_chain_t(const Shape &s, const void *x, const void *d
         const int nslice = (s.P + 32 * PT - 1) / (32 * PT);
         const int total = (int)chains * nslice, nblocks = xcd_padded(total);
         hipLaunchKernelGGL((PT == 2 ? chain_bf16_kernel<NT, 2, OUT> : chain_bf16_kernel<NT, 1, OUT>), dim3(nblocks), dim3(256 * PT),
-                           chain_shm(PT, OUT), st, (const uint16_t *)x, D, (const uint16_t *)scr.ops, tb, h0, h_final,
-                           (uint16_t *)y, s, nsteps, nslice, count, steps, OUT ? s.H : hblock, pieces, total, nblocks);
+                           chain_shm(PT, OUT), st, (const uint16_t *)x, D, (const uint16_t *)scr.ops, chain_tables(s, scr), h0, h_final,
+                           (uint16_t *)y, s, plan.nsteps, nslice, count, steps, OUT ? s.H : hblock, pieces, total, nblocks);
     };
-    if (nseg > 1) {
+    if (plan.nseg > 1) {
         // with the final state written over the initial one the first segment can start after the last one has ended
         if (h0 && h0 == h_final)
             pieces.h0_copy = pieces.npiece < pieces.n_a ? scr.a + pieces.npiece * (unit / 4) : scr.b + (pieces.npiece - pieces.n_a) * (unit / 4);
@@ -1007,17 +1039,29 @@ static swimba_status launch_chain_t(const Shape &s, const void *x, const void *d
         SWIMBA_CHECK_LAUNCH();
         if (pieces.h0_copy) h0 = pieces.h0_copy;
     }
-    launch(std::true_type{}, nseg, steps_per_seg);
+    launch(std::true_type{}, plan.nseg, plan.steps_per_seg);
     SWIMBA_CHECK_LAUNCH();
     return SWIMBA_OK;
 }
 
+swimba_status launch_chain_mix_bf16(const Shape &s, const void *dt, const float *A, const void *Be, const void *Ce, const void *logits,
+                                    const float *w_sel, int32_t *idx, float *w, const ChainScratch &scr, hipStream_t st)
+{
+    const int NT = chain_tiles(s);
+    return (NT == 4 ? launch_mix_t<4> : NT == 2 ? launch_mix_t<2> : launch_mix_t<1>)(s, dt, A, Be, Ce, logits, w_sel, idx, w, scr, st);
+}
+swimba_status launch_chain_walk_bf16(const Shape &s, const void *x, const float *D, const float *h0, void *y, float *h_final,
+                                     const ChainScratch &scr, bool skip, hipStream_t st)
+{
+    const int NT = chain_tiles(s);
+    return (NT == 4 ? launch_walk_t<4> : NT == 2 ? launch_walk_t<2> : launch_walk_t<1>)(s, x, D, h0, y, h_final, scr, skip, st);
+}
 swimba_status launch_chain_bf16(const Shape &s, const void *x, const void *dt, const float *A, const float *D, const void *Be,
                                 const void *Ce, const void *logits, const float *w_sel, const float *h0, void *y,
                                 float *h_final, int32_t *idx, float *w, const ChainScratch &scr, bool skip, hipStream_t st)
 {
-    auto launch = s.N > 64 ? launch_chain_t<4> : s.N > 32 ? launch_chain_t<2> : launch_chain_t<1>;
-    return launch(s, x, dt, A, D, Be, Ce, logits, w_sel, h0, y, h_final, idx, w, scr, skip, st);
+    const swimba_status ok = launch_chain_mix_bf16(s, dt, A, Be, Ce, logits, w_sel, idx, w, scr, st);
+    return ok == SWIMBA_OK ? launch_chain_walk_bf16(s, x, D, h0, y, h_final, scr, skip, st) : ok;
 }
 
 }  // namespace swimba

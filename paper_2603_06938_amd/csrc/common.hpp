@@ -94,6 +94,7 @@ swimba_status launch_chain_f32(const Shape &s, int io_dtype, const void *x, cons
                                const float *D, const void *Be, const void *Ce, const void *logits, const float *w_sel,
                                const float *h0, void *y, float *h_final, int32_t *idx, float *w, float *cop, float *bop,
                                float *gop, float *hseg, float *aseg, float *hinit, hipStream_t st);
+int chain_f32_segments(int64_t B, int64_t L, int64_t H, int64_t P);
 // bf16 io at the sizes of use_mfma_path as one walk over 64-token steps (chain_bf16.hip)
 struct ChainScratch {
     void *ops, *tables;                  // operand images, decay tables
@@ -103,6 +104,13 @@ struct ChainScratch {
 };
 size_t chain_bf16_table_bytes(const Shape &s);
 int chain_bf16_segments(int64_t chains, int64_t steps, int64_t ncu);   // before the limit of the scratch
+int chain_bf16_planned_segments(const Shape &s, const ChainScratch &scr, int ncu);   // as launched; of scr only the sizes matter
+// its two halves: mixed operands and decay tables, then the walk
+swimba_status launch_chain_mix_bf16(const Shape &s, const void *dt, const float *A, const void *Be, const void *Ce,
+                                    const void *logits, const float *w_sel, int32_t *idx, float *w, const ChainScratch &scr,
+                                    hipStream_t st);
+swimba_status launch_chain_walk_bf16(const Shape &s, const void *x, const float *D, const float *h0, void *y, float *h_final,
+                                     const ChainScratch &scr, bool skip, hipStream_t st);
 swimba_status launch_chain_bf16(const Shape &s, const void *x, const void *dt, const float *A, const float *D, const void *Be,
                                 const void *Ce, const void *logits, const float *w_sel, const float *h0, void *y,
                                 float *h_final, int32_t *idx, float *w, const ChainScratch &scr, bool skip, hipStream_t st);

@@ -118,6 +118,25 @@ def test_the_chunk_length_changes_no_bit_of_segments(case):
         assert torch.equal(got.y, want.y) and torch.equal(got.h_final, want.h_final)
 
 
+@pytest.mark.parametrize("case,chunk,segments", [((2, 200, 4, 56, 40, 1, 64, 4, True, True, 1.0), 64, 1), ((1, 3072, 64, 64, 128, 1, 4, 2, True, True, 1.0), 256, 4)],
+                         ids=["whole", "segments"])
+def test_stage_calls_give_the_forwards_bits(case, chunk, segments):
+    """chain_mix and chain_walk are the launches of swimba_mixer_fwd where swimba_forward_path says so."""
+    p, h0 = inputs(case, 18)
+    k = case[7]
+    d = to_device(p, "bf16")
+    h = torch.from_numpy(h0).to("cuda:0")
+    want = forward(p, k, h0, True, chunk)
+    dims = sw.dims_of(d["x"], d["B_experts"], k, chunk)
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert sw.swimba_forward_path(dims) == sw.PATH_CHAIN_BF16 and sw.swimba_forward_segments(dims) == segments
+    ws = sw.alloc_workspace(dims, "cuda:0")
+    y, hf = torch.empty_like(d["x"]), torch.empty_like(h)
+    sw.swimba_stage_chain_mix(dims, d["dt"], d["A"], d["B_experts"], d["C_experts"], d["router_logits"], ws)
+    sw.swimba_stage_chain_walk(dims, d["x"], d["D"], h, y, hf, ws)
+    assert torch.equal(y, want.y) and torch.equal(hf, want.h_final)
+
+
 def test_segments_final_state_over_the_initial_one():
     """In place the segments read a copy of h0: the bits of the same call out of place, every time."""
     p, h0 = inputs((1, 3100, 64, 64, 128, 1, 4, 2, True, True, 0.2), 11)

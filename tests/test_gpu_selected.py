@@ -120,9 +120,9 @@ def test_mixer_fwd_selected_matches_oracle(cfg):
                          ids=["staged", "split_pass", "pass_per_head"])
 def test_mixer_fwd_selected_equals_mixer_fwd_bitwise(shape):
     """Same kernels behind both entry points: gathering the selected rows on the host and
-    passing the weights the router kernel produced gives the same bits as the dense call, on the
-    staged kernels, on the per-head single pass behind the chunk-level mix kernel and on the split pass
-    behind the per-tile one (the paths these shapes take on a device with 256 compute units)."""
+    passing the weights the router kernel produced gives the same bits as the dense call.  These shapes
+    take the walk over 64-token steps (the evaluations over whole chunks that fit them are asserted with
+    it; where the forwards run those, test_forward_over_whole_chunks_matches_oracle compares the two)."""
     w = synth.Workload("selbit", *shape, "bf16", 5)
     p = synth.make_inputs(w, seed=41)
     d = to_device(p, "bf16")
@@ -131,6 +131,7 @@ def test_mixer_fwd_selected_equals_mixer_fwd_bitwise(shape):
         want = {256: (sw.PATH_STAGED_SHORT,), 64: (sw.PATH_SINGLE_PASS_HEAD_SPLIT, sw.PATH_SINGLE_PASS_HEAD_CHUNK_MIX)}[w.chunk]
         assert sw.swimba_prefill_path(dims) in want
         assert sw.swimba_pass_segments(dims) == (2 if shape[1] == 1536 else 1)
+        assert sw.swimba_forward_path(dims) == sw.PATH_CHAIN_BF16
     dense = sw.swimba_mixer_fwd(d["x"], d["dt"], d["A"], d["D"], d["B_experts"], d["C_experts"],
                                 d["router_logits"], w.top_k, w.chunk, want_topk=True)
     idx = dense.topk_idx.to(torch.int64)[..., None, None].expand(-1, -1, -1, w.ngroups, w.dstate)

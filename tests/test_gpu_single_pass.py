@@ -210,18 +210,41 @@ def test_short_sequence_kernels_equal_the_scan_path(case):
     assert sw.swimba_prefill_path(dims) in (sw.PATH_STAGED_SHORT, sw.PATH_SINGLE_PASS_HEAD, sw.PATH_SINGLE_PASS)
 
 
-def test_long_sequence_on_the_scan_path_matches_oracle():
-    """More than 8 chunks and too few chains for a single pass: mix, chunk state, scan, output from the forward."""
-    w = synth.Workload("sc", 2, 700, 4, 64, 128, 2, 8, 2, 64, "bf16", 6)
+# The forwards over whole chunks: few chains of more than 16 steps of 64 tokens
+FORWARD_OVER_CHUNKS = [
+    # (B, L, H, P, N, G, E, k, Q), the kernels the forward takes on a device with 256 compute units, segments
+    ((2, 1500, 4, 64, 128, 2, 8, 2, 64), sw.PATH_STAGED, 1),                       # mix, chunk state, scan, output
+    ((1, 1100, 4, 48, 72, 1, 5, 3, 256), sw.PATH_STAGED_SHORT, 1),                 # tiles in the chunk-state launch, look-back
+    ((2, 2048, 8, 64, 128, 2, 20, 4, 256), sw.PATH_STAGED_SHORT, 1),               # 8 whole chunks
+    ((1, 6144, 80, 64, 128, 1, 4, 2, 128), sw.PATH_SINGLE_PASS_HEAD_SPLIT, 3),     # a mix per tile in front
+    ((1, 6144, 80, 64, 64, 16, 4, 2, 128), sw.PATH_SINGLE_PASS_HEAD_SPLIT_CHUNK_MIX, 3),
+]
+
+
+@pytest.mark.parametrize("shape,path,nseg", FORWARD_OVER_CHUNKS, ids=["scan", "ragged", "8_chunks", "split", "split_chunk_mix"])
+def test_forward_over_whole_chunks_matches_oracle(shape, path, nseg):
+    """swimba_mixer_fwd where it leaves the walk over 64-token steps, with an initial state and the routing handed out; and
+    the same bits from the selected streams and, continued in place, from the state over itself."""
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("the expected choices are those of a device with 256 compute units")
+    B, L, H, P, N, G, E, k, Q = shape
+    w = synth.Workload("sc", *shape, "bf16", 6)
     p = synth.make_inputs(w, seed=77)
     d = to_device(p, "bf16")
-    dims = sw.dims_of(d["x"], d["B_experts"], 2, 64)
-    assert sw.swimba_prefill_path(dims) == sw.PATH_STAGED
-    h0 = (0.1 * np.random.default_rng(3).standard_normal((2, 4, 64, 128))).astype(np.float32)
-    out = sw.swimba_mixer_fwd(d["x"], d["dt"], d["A"], d["D"], d["B_experts"], d["C_experts"], d["router_logits"], 2, 64,
-                              torch.from_numpy(h0).to("cuda:0"))
+    dims = sw.dims_of(d["x"], d["B_experts"], k, Q)
+    assert sw.swimba_prefill_path(dims) == path and sw.swimba_pass_segments(dims) == nseg
+    assert sw.swimba_forward_path(dims) == path and sw.swimba_forward_segments(dims) == nseg
+    h0 = (0.1 * np.random.default_rng(3).standard_normal((B, H, P, N))).astype(np.float32)
+    h0d = torch.from_numpy(h0).to("cuda:0")
+    out = sw.swimba_mixer_fwd(d["x"], d["dt"], d["A"], d["D"], d["B_experts"], d["C_experts"], d["router_logits"], k, Q, h0d,
+                              want_topk=True)
     torch.cuda.synchronize()
-    ref = orc.mixer_fwd(p["x"], p["dt"], p["A"], p["D"], p["B_experts"], p["C_experts"], p["router_logits"], 2, h0=h0)
+    ref = orc.mixer_fwd(p["x"], p["dt"], p["A"], p["D"], p["B_experts"], p["C_experts"], p["router_logits"], k, h0=h0)
+    np.testing.assert_array_equal(out.topk_idx.cpu().numpy(), ref["topk_idx"])
+    idx = out.topk_idx.to(torch.int64)[..., None, None].expand(-1, -1, -1, G, N)
+    sel = sw.swimba_mixer_fwd_selected(d["x"], d["dt"], d["A"], d["D"], torch.gather(d["B_experts"], 2, idx),
+                                       torch.gather(d["C_experts"], 2, idx), out.topk_w, Q, h0d)
+    assert torch.equal(sel.y, out.y) and torch.equal(sel.h_final, out.h_final)
     l2, linf = rel_errors(host(out.y), ref["y"], (0, 2))
     assert l2 <= TOL["bf16"] and linf <= TOL["bf16"], (l2, linf)
     l2, linf = rel_errors(host(out.h_final), ref["h_final"], (0, 1))
@@ -310,8 +333,8 @@ def test_split_pass_refuses_what_it_does_not_take():
 
 
 def test_forward_paths_of_the_workloads():
-    """Which evaluation the forward picks for the benchmark shapes (a choice made from the shape and the number
-    of compute units; the figures hold for the 256 units of an MI355X)."""
+    """Which evaluation the forward picks for the benchmark shapes, and which of those over whole chunks fits them (choices
+    made from the shape and the number of compute units; the figures hold for the 256 units of an MI355X)."""
     if torch.cuda.get_device_properties(0).multi_processor_count != 256:
         pytest.skip("the expected choices are those of a device with 256 compute units")
     want = {1: (sw.PATH_STAGED_SHORT, 1), 2: (sw.PATH_SINGLE_PASS_HEAD, 1), 3: (sw.PATH_SINGLE_PASS_HEAD_SPLIT_CHUNK_MIX, 2)}
@@ -321,6 +344,8 @@ def test_forward_paths_of_the_workloads():
                             torch.bfloat16)
         assert sw.swimba_prefill_path(dims) == path, idx
         assert sw.swimba_pass_segments(dims) == nseg, idx
+        assert sw.swimba_forward_path(dims) == sw.PATH_CHAIN_BF16, idx
+        assert sw.swimba_forward_segments(dims) == {1: 1, 2: 1, 3: 2}[idx], idx
     # a ragged sequence is not split, 96 chains do not fill two segments' worth of compute units
     for shape in ((2, 16384 - 100, 64, 64, 128, 8, 16, 2, 256), (4, 8192, 24, 64, 128, 1, 8, 2, 256)):
         assert sw.swimba_pass_segments(sw.make_dims(*shape, torch.bfloat16)) == 1, shape

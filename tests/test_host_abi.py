@@ -213,6 +213,24 @@ def test_forwards_without_a_device_return_a_status(io_dtype, seqlen):
     assert lib.swimba_last_hip_error() != 0
 
 
+def test_forward_path_and_chain_stages_on_the_host():
+    """The queries without a device, and what the stage calls of the bf16 walk refuse (pointer values only)."""
+    lib = sw._load()
+    f32, bf = dims(), dims(headdim=64, dstate=128, chunk=64, io_dtype=1)
+    assert sw.swimba_forward_path(f32) == sw.PATH_CHAIN_F32 and sw.swimba_forward_segments(f32) >= 1
+    assert sw.swimba_forward_segments(dims(headdim=64, dstate=128, io_dtype=1, seqlen=0)) == 1
+    assert lib.swimba_forward_path(ctypes.byref(dims(top_k=9))) == -2 and lib.swimba_forward_segments(ctypes.byref(dims(chunk=512))) == -4
+    p, ws, big = [0x10000 * (i + 1) for i in range(6)], 0x4000000, 1 << 40
+    assert lib.swimba_stage_chain_mix(ctypes.byref(f32), *p[:5], ws, big, None) == 4
+    assert lib.swimba_stage_chain_mix(ctypes.byref(bf), *p[:5], None, 0, None) == 5
+    assert lib.swimba_stage_chain_mix(ctypes.byref(bf), *p[:4], None, ws, big, None) == 1
+    assert lib.swimba_stage_chain_mix(ctypes.byref(bf), *p[:2], p[2] + 8, *p[3:5], ws, big, None) == 7
+    assert lib.swimba_stage_chain_walk(ctypes.byref(f32), *p[:5], ws, big, None) == 4
+    assert lib.swimba_stage_chain_walk(ctypes.byref(bf), *p[:5], ws, 16, None) == 5
+    assert lib.swimba_stage_chain_walk(ctypes.byref(bf), None, *p[1:5], ws, big, None) == 1
+    assert lib.swimba_stage_chain_walk(ctypes.byref(bf), *p[:2], p[2] + 4, *p[3:5], ws, big, None) == 7
+
+
 def test_header_is_plain_c_and_links_against_the_library(tmp_path):
     """include/swimba.h compiles as C99 with gcc (no C++ in the boundary), and a C program that
     only uses host-side calls links against libswimba.so and runs without a GPU."""
