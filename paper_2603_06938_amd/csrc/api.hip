@@ -132,10 +132,12 @@ int device_cus()
     return ncu;
 }
 
-// Which evaluation of the SSD part swimba_mixer_fwd takes on the bf16 MFMA path.  A single pass keeps
-// one workgroup (one per compute unit: its LDS) busy for the whole sequence of its chain, so it
-// needs chains that fill the rounds they run in, and enough chunks per chain to pay for the ramp;
-// the staged kernels also parallelise over chunks and win everywhere else.
+// Which evaluation over whole chunks fits a shape of the bf16 MFMA path best.  The forwards walk 64-token steps wherever
+// use_chain_bf16 says so and take only the staged kernels and the split pass of these: whole-sequence head64 (5/8 of the
+// rounds) and slices32 (7/16 as many chains as compute units, at least 16 steps) lie inside that rule for any number of
+// units, and serve the stage calls.  A single pass keeps one workgroup (one per compute unit: its LDS) busy for the whole
+// sequence of its chain, so it needs chains that fill the rounds they run in, and enough chunks per chain to pay for the
+// ramp; of the two, the staged kernels, which also parallelise over chunks, win everywhere else.
 //   head64   a chain per (batch, head), all channels: 7.5 us per chunk with every compute unit busy,
 //            about 6 us with 5/8 of them (the operands come through the same L2s).  Takes the shapes
 //            whose B*H chains fill at least 5/8 of their rounds, from 12 chunks on, and those that fill
@@ -671,22 +673,14 @@ swimba_status swimba_mixer_fwd(const swimba_dims *dims, const void *x, const voi
                 e = hipMemcpyAsync(topk_w, ws.w, n * sizeof(float), hipMemcpyDeviceToDevice, stream);
             if (e != hipSuccess) { set_last_hip_error((int)e); return SWIMBA_ERR_HIP; }
         }
-        const PassKind pk = pass_kind(dims);
-        const bool slices = pk == PASS_SLICES32;
-        if (pk != PASS_STAGED) {
-            // single pass: G^T tiles and cumsum tables, then one walk over the chunks per
-            // (batch, head, 32 channels) or per (batch, head) with the state in registers
+        const int nseg = head64_segments(dims);
+        if (nseg > 1) {
+            // split per-head pass: G^T tiles and cumsum tables, the states at the segment boundaries, then a walk over
+            // the chunks per (batch, segment, head) with the state in registers
             st = launch_prep_mfma(s, dt, A, ws.cmix, ws.bmix_frag, ws.cb, ws.cs2, ws.fdec, ws.cdec, stream, !chunk_mix);
             if (st != SWIMBA_OK) return st;
-            if (slices)
-                return launch_pass_mfma(s, x, dt, D, ws.cmix, ws.bmix_t8, ws.cb, ws.cs2, ws.fdec, ws.cdec, h0, h_final,
-                                        y, stream);
-            const int nseg = head64_segments(dims);
-            if (nseg > 1) {
-                st = launch_boundary_states_mfma(s, nseg, x, dt, A, ws.bmix_t8, ws.cs2, ws.states_lp, h0, ws.hmid,
-                                                 stream);
-                if (st != SWIMBA_OK) return st;
-            }
+            st = launch_boundary_states_mfma(s, nseg, x, dt, A, ws.bmix_t8, ws.cs2, ws.states_lp, h0, ws.hmid, stream);
+            if (st != SWIMBA_OK) return st;
             return launch_pass64_mfma(s, x, dt, D, ws.cmix, ws.bmix_t8, ws.cb, ws.cs2, ws.fdec, ws.cdec, h0, h_final, y,
                                       stream, nseg, ws.hmid);
         }
@@ -1154,21 +1148,14 @@ static swimba_status mixer_selected_core(const swimba_dims *dims, const void *x,
                            : launch_mix_rows_mfma(s, B_sel, C_sel, nullptr, nullptr, nullptr, ws.cmix, ws.bmix_frag,
                                                   ws.bmix_t8, -1, -1, w_sel, stream);
             if (st != SWIMBA_OK) return st;
-            const PassKind pk = pass_kind(dims);
-            const bool slices = pk == PASS_SLICES32;
-            if (pk != PASS_STAGED) {
+            const int nseg = head64_segments(dims);
+            if (nseg > 1) {
                 st = launch_prep_mfma(s, dt, A, ws.cmix, ws.bmix_frag, ws.cb, ws.cs2, ws.fdec, ws.cdec, stream,
                                       !chunk_mix);
                 if (st != SWIMBA_OK) return st;
-                if (slices)
-                    return launch_pass_mfma(s, x, dt, D, ws.cmix, ws.bmix_t8, ws.cb, ws.cs2, ws.fdec, ws.cdec, h0,
-                                            h_final, y, stream);
-                const int nseg = head64_segments(dims);
-                if (nseg > 1) {
-                    st = launch_boundary_states_mfma(s, nseg, x, dt, A, ws.bmix_t8, ws.cs2, ws.states_lp, h0, ws.hmid,
-                                                     stream);
-                    if (st != SWIMBA_OK) return st;
-                }
+                st = launch_boundary_states_mfma(s, nseg, x, dt, A, ws.bmix_t8, ws.cs2, ws.states_lp, h0, ws.hmid,
+                                                 stream);
+                if (st != SWIMBA_OK) return st;
                 return launch_pass64_mfma(s, x, dt, D, ws.cmix, ws.bmix_t8, ws.cb, ws.cs2, ws.fdec, ws.cdec, h0,
                                           h_final, y, stream, nseg, ws.hmid);
             }
