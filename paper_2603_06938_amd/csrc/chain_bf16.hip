@@ -17,11 +17,12 @@
 // chain (ChainPieces, chain_bf16_segments).
 //
 // Against the staged kernels and the per-head pass over whole chunks (two to five launches, G scaled element by element per
-// head, x and chunk states more than once through memory): 130M-shaped layer 76.7 -> 57.7 us, 370M-shaped layer
-// 147.3 -> 121.9, five sequences of 1237 tokens x 32 heads 52.6 -> 35.7, 150 tokens x 24 heads 21.6 -> 12.5.
-// Bound: waits.  A step of the 370M-shaped layer takes 1.55 us with every compute unit busy; its matrix work is 0.28 us, its
+// head, x and chunk states more than once through memory): 130M-shaped layer 76.7 -> 56.4 us, 370M-shaped layer
+// 147.3 -> 115.4, five sequences of 1237 tokens x 32 heads 52.6 -> 35.2, 150 tokens x 24 heads 21.6 -> 13.3.
+// Bound: waits.  A step of the 370M-shaped layer takes 1.5 us with every compute unit busy; its matrix work is 0.28 us, its
 // LDS traffic about 0.6, what goes through the vector L1 (38 KB of operands, read by both channel tiles, 16 KB of x and y)
-// 0.65, x and y at the rate of a copy in this pattern 1.0; taking x and y away leaves 1.0 us, the operands 1.15.
+// 0.65, x and y at the rate of a copy in this pattern 1.0; without x and y it took 1.0 us, without the operands 1.15 (of 1.55
+// then).  Where memory does not set the time every instruction of an i/o wave shows: 20 more in a pass, 45 ns a step.
 #include "common.hpp"
 #include "mfma_util.hpp"
 
@@ -105,8 +106,8 @@ __host__ __device__ constexpr int cb_item_frags(int NT) { return 8 * NT + 6; }
 // its factor look at what comes out: a step with anything above an upper bound, or, where the reference is more than 8 from
 // some token's cs, with eight channels of a token that are all below a lower one, is turned direct before it is used
 // (mag_bounds; turn_direct).  The bounds leave 2^26 to the ends of the exponent range, for sums of up to N products and for
-// elements of B, C and x far under the largest.  The check's 20 instructions in the i/o waves take 45 ns of a step where
-// memory does not set the time: five sequences of 1237 tokens 35.4 -> 36.6 us, 150 tokens x 24 heads 12.9 -> 13.5.
+// elements of B, C and x far under the largest.  The check costs 45 ns of a step where memory does not set the time: five
+// sequences of 1237 tokens 35.4 -> 36.6 us, 150 tokens x 24 heads 12.9 -> 13.3.
 struct ChainTables {
     float *fe, *ref, *sum, *mag;
 };
@@ -569,7 +570,7 @@ chain_bf16_kernel(const uint16_t *__restrict__ x, const float *__restrict__ D, c
                 }
             }
         };
-        lds_barrier();                                   // x and references of the first two steps
+        lds_barrier();                                   // x of the first step, references of the first two
         int4 rc = s_ref[0];
         int pc = __builtin_amdgcn_readfirstlane(rc.x);
         if (__builtin_expect(flagged(rc.w), 0)) turn_direct(c_begin, 0, pc);
@@ -883,8 +884,7 @@ chain_bf16_kernel(const uint16_t *__restrict__ x, const float *__restrict__ D, c
         put_ref(0, first);
         put_ref(1, second);
         stage_x(c_begin, 0, xr[0], fr[0], first);
-        stage_x(c_begin + 1, 1, xr[1], fr[1], second);
-        lds_barrier();                                   // x of the first two steps
+        lds_barrier();                                   // x of the first step
         // a step that the compute waves turn direct: its factor of y, and the barrier in turn_direct
         auto turned = [&](float2 (&fe)[2]) __attribute__((always_inline)) {
 #pragma unroll
@@ -892,6 +892,7 @@ chain_bf16_kernel(const uint16_t *__restrict__ x, const float *__restrict__ D, c
             lds_barrier();
         };
         if (__builtin_expect(flagged(s_ref[0].w), 0)) turned(fr[0]);
+        stage_x(c_begin + 1, 1, xr[1], fr[1], second);   // beside the first readout
         for (int c0 = c_begin;; c0 += CB_RING) {
 #pragma unroll
             for (int u = 0; u < CB_RING; ++u) {
