@@ -203,9 +203,10 @@ static bool use_chunk_mix(const swimba_dims *d, bool selected)
 
 // The bf16 forward as one walk over 64-token steps (chain_bf16.hip), two launches, or three where it cuts the sequence; its
 // scratch lies over cmix .. cb, states_lp, hmid and cs.  A chain's steps are serial, 0.7 us each (two workgroups to a compute unit)
-// to 1.6 (all units busy): ahead of the kernels above everywhere up to 16 steps (8 to 1024 chains, 64 to 1024 tokens: 0.5 to
-// 0.98 of their time; 8 chains of 1024 tokens 22.5 / 23.0 us), from 40 chains on up to 24 and from 64 on up to 32 (48 chains of 32
-// steps, 4 groups: 37.8 / 35.9), from 96 chains on up to 128 (96 chains of 6000 tokens 89 / 110) and where the chains fill
+// to 1.6 (all units busy): ahead of the kernels above up to 16 steps (8 to 1024 chains, 64 to 1024 tokens: 0.5 to 0.98 of their
+// time; 4 and 8 chains of 1024 tokens are level, 22.7 / 22.6 us, 24.3 / 23.5 in 4 groups), from 40 chains on up to 24 (40 chains
+// of 20 steps 26.6 / 28.0, of 24 31.1 / 29.6; 48 of 24 32.9 / 34.7) and from 64 on up to 32 (64 chains 39.1 / 39.4, in 4 groups
+// 40.6 / 40.3; 48 chains 37.8 / 35.9), from 96 chains on up to 128 (96 chains of 6000 tokens 89 / 110) and where the chains fill
 // three fifths of their rounds at any length (256 of 4096 tokens 122 / 147), or where segments do (chain_bf16_segments).
 // Short of that the kernels that also parallelise over chunks stay ahead.
 static bool use_chain_bf16(const swimba_dims *d)

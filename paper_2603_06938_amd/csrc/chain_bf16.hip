@@ -18,7 +18,7 @@
 //
 // Against the staged kernels and the per-head pass over whole chunks (two to five launches, G scaled element by element per
 // head, x and chunk states more than once through memory): 130M-shaped layer 76.7 -> 56.4 us, 370M-shaped layer
-// 147.3 -> 115.4, five sequences of 1237 tokens x 32 heads 52.6 -> 35.2, 150 tokens x 24 heads 21.6 -> 13.3.
+// 147.3 -> 115.4, five sequences of 1237 tokens x 32 heads 52.6 -> 34.6, 150 tokens x 24 heads 21.6 -> 13.3.
 // Bound: waits.  A step of the 370M-shaped layer takes 1.5 us with every compute unit busy; its matrix work is 0.28 us, its
 // LDS traffic about 0.6, what goes through the vector L1 (38 KB of operands, read by both channel tiles, 16 KB of x and y)
 // 0.65, x and y at the rate of a copy in this pattern 1.0; without x and y it took 1.0 us, without the operands 1.15 (of 1.55
@@ -107,7 +107,7 @@ __host__ __device__ constexpr int cb_item_frags(int NT) { return 8 * NT + 6; }
 // some token's cs, with eight channels of a token that are all below a lower one, is turned direct before it is used
 // (mag_bounds; turn_direct).  The bounds leave 2^26 to the ends of the exponent range, for sums of up to N products and for
 // elements of B, C and x far under the largest.  The check costs 45 ns of a step where memory does not set the time: five
-// sequences of 1237 tokens 35.4 -> 36.6 us, 150 tokens x 24 heads 12.9 -> 13.3.
+// sequences of 1237 tokens 35.4 -> 36.6 us (some steps with two references), 150 tokens x 24 heads 12.9 -> 13.3.
 struct ChainTables {
     float *fe, *ref, *sum, *mag;
 };
