@@ -209,9 +209,11 @@ static bool use_chunk_mix(const swimba_dims *d, bool selected)
 // 40.6 / 40.3; 48 chains 37.8 / 35.9), from 96 chains on up to 128 (96 chains of 6000 tokens 89 / 110) and where the chains fill
 // three fifths of their rounds at any length (256 of 4096 tokens 122 / 147), or where segments do (chain_bf16_segments).
 // Short of that the kernels that also parallelise over chunks stay ahead.
+// The walk addresses the 64 rows of a step by 31-bit offsets; past that, a row of 2^24 channels, the staged kernels take over.
+static bool chain_bf16_rows_fit(const swimba_dims *d) { return (int64_t)d->nheads * d->headdim < (1ll << 24); }
 static bool use_chain_bf16(const swimba_dims *d)
 {
-    if (!use_mfma_path(d)) return false;
+    if (!use_mfma_path(d) || !chain_bf16_rows_fit(d)) return false;
     const int64_t chains = (int64_t)d->batch * d->nheads, steps = ((int64_t)d->seqlen + 63) / 64, ncu = device_cus();
     if (ncu == 0) return false;      // no device: the other kernels' launches report it
     const int64_t rounds = (chains + ncu - 1) / ncu;
@@ -486,7 +488,7 @@ swimba_status swimba_stage_chain_walk(const swimba_dims *dims, const void *x, co
     Ws ws;
     swimba_status st = carve(dims, workspace, workspace_bytes, &ws);
     if (st != SWIMBA_OK) return st;
-    if (!use_mfma_path(dims)) return SWIMBA_ERR_UNSUPPORTED;
+    if (!use_mfma_path(dims) || !chain_bf16_rows_fit(dims)) return SWIMBA_ERR_UNSUPPORTED;
     if ((int64_t)dims->batch * dims->seqlen == 0) return SWIMBA_OK;
     if (!x || !y) return SWIMBA_ERR_NULL;
     if (check_align(dims->io_dtype, {x, y, h0, h_final}, {}, {D}) != SWIMBA_OK) return SWIMBA_ERR_ALIGNMENT;

@@ -9,20 +9,22 @@
 //                        Y[i][p]  = e_i (sum_n C[i][n] H'[n][p] + sum_j G[i][j] x~_j[p]) + D x_i[p]
 //                        H'      <- 2^(R_next - ..) (H' + sum_j B[j][n] x~_j[p])
 //                      so the three contractions take x~ alone, G as it was written, and no operand is scaled per head.
-// Compute waves (32 channels x half of the state columns) hold their part of the state in the accumulators, which packed to
-// bf16 are the A operand of the readout as they are; 19 MFMAs each per step (N = 128).  The halves' partial Y meet in LDS.  I/O
-// waves load x three steps ahead, write x~ into LDS two steps ahead, and finish and store Y one step behind; one LDS-only
-// barrier a step.  ds_read_b64_tr_b16 transposes x~ (and, in the mix kernel, B) on the way out of LDS.
+// Two state waves, half of the columns each, keep H' in the accumulators and write it, rounded to bf16, into LDS as the operand
+// registers of the readout; two readout waves, 32 of the 64 tokens each, take it from there a step later with C, G and x~ and
+// leave Y in LDS (N = 128 and 64 channels: 16 and 20 or 24 MFMAs each per step).  So every operand is read by one wave of the
+// workgroup, and two steps ahead.  I/O waves load x three steps ahead, write x~ into LDS two steps ahead, and finish and store Y
+// one step behind; one LDS-only barrier a step.  ds_read_b64_tr_b16 transposes x~ (and, in the mix kernel, B) on the way out of
+// LDS.
 // Too few chains to fill the chip: a sequence is walked as segments, whose initial states come from a launch in front of the
 // chain (ChainPieces, chain_bf16_segments).
 //
-// Against the staged kernels and the per-head pass over whole chunks (two to five launches, G scaled element by element per
-// head, x and chunk states more than once through memory): 130M-shaped layer 76.7 -> 56.4 us, 370M-shaped layer
-// 147.3 -> 115.4, five sequences of 1237 tokens x 32 heads 52.6 -> 34.6, 150 tokens x 24 heads 21.6 -> 13.3.
-// Bound: waits.  A step of the 370M-shaped layer takes 1.5 us with every compute unit busy; its matrix work is 0.28 us, its
-// LDS traffic about 0.6, what goes through the vector L1 (38 KB of operands, read by both channel tiles, 16 KB of x and y)
-// 0.65, x and y at the rate of a copy in this pattern 1.0; without x and y it took 1.0 us, without the operands 1.15 (of 1.55
-// then).  Where memory does not set the time every instruction of an i/o wave shows: 20 more in a pass, 45 ns a step.
+// Against four like waves of 32 channels x half of the columns, which read every operand twice, one step ahead, and met partial
+// sums of Y in LDS: 130M-shaped layer 55.4 -> 50.7 us, 370M-shaped layer 115 -> 103, five sequences of 1237 tokens x 32 heads
+// 34.9 -> 31.1, two of 16384 x 64 335 -> 316; 1 to 3 steps cost 0.2 to 0.4 us more (150 tokens x 24 heads 13.3 -> 13.5).
+// Bound: a step takes 1.0 us wherever its x, y and operands lie in the caches (19 % of it MFMAs, 28 % vector instructions, 35 % of
+// the waves' time waits for LDS and the barrier, all waves alike), 1.35 in the 370M-shaped layer, where x and y stream at
+// 3.2 TB/s.  Worse: Y finished and stored by the readout waves, 32-byte pieces of rows (370M 131 us for the walk's 91); x read
+// again for the finish (97); state and readout in the same four waves (96); one channel tile a workgroup, two to a unit (138).
 #include "common.hpp"
 #include "mfma_util.hpp"
 
@@ -81,7 +83,8 @@ __host__ __device__ constexpr int cb_item_frags(int NT) { return 8 * NT + 6; }
 
 // Per (batch, head, step), written by the mix launch (cs: inclusive sum of log2 e dt A from the step's first token, whole and
 // part its nearest whole number and the rest):
-//   fe  (B, H, nsteps, 64, 2)  factor of x, dt_j 2^(R - cs_j), and of y, 2^(cs_i - R); of a direct step dt_j and cs_j
+//   fe  (B, H, nsteps, 32, 2, 2)  factor of x, dt_j 2^(R - cs_j), and of y, 2^(cs_i - R), tokens j and j + 32 side by side; of a
+//                              direct step dt_j and cs_j
 //   ref (B, H, nsteps, 2)      mode and references (pack_ref); 2^(part of cs_last)
 //   sum (B, H, nsteps)         cs_last
 //   mag (B, nsteps, G, 2)      bounds for x times its factor (mag_bounds)
@@ -149,7 +152,7 @@ __device__ __forceinline__ void chain_table(const ChainTables &t, int64_t bhs, f
         if (lane >= __builtin_ctzll(bad)) fe = make_float2(0.f, NAN);
         frac = sum = NAN;
     }
-    reinterpret_cast<float2 *>(t.fe)[bhs * CB_STEP + lane] = fe;
+    reinterpret_cast<float2 *>(t.fe)[bhs * CB_STEP + 2 * (lane & 31) + (lane >> 5)] = fe;
     if (lane == 0) {
         reinterpret_cast<float2 *>(t.ref)[bhs] = make_float2(__int_as_float(pack), frac);
         t.sum[bhs] = sum;
@@ -342,24 +345,32 @@ __device__ __forceinline__ float4 *piece_frag(const ChainPieces &pc, int64_t bh,
     return reinterpret_cast<float4 *>(base + ptile * NT * 1024);
 }
 
-template <int NT, int PT, bool OUT>
-__global__ void __launch_bounds__(256 * PT, 2)
+// Waves of a workgroup of PT channel tiles that writes Y (CW > 0): CW / 2 of the state, CW / 2 readout, 2 PT i/o; of one that
+// does not (CW = 0), a state wave for each channel tile and half of the columns, 2 PT i/o.
+constexpr int cb_state_waves(int PT, int CW) { return CW ? CW / 2 : 2 * PT; }
+constexpr int cb_threads(int PT, int CW) { return 64 * (cb_state_waves(PT, CW) + CW / 2 + 2 * PT); }
+
+template <int NT, int PT, int CW>
+__global__ void __launch_bounds__(cb_threads(PT, CW), PT == 1 && CW == 4 ? 3 : 2)
 chain_bf16_kernel(const uint16_t *__restrict__ x, const float *__restrict__ D, const uint16_t *__restrict__ ops, ChainTables tb,
                   const float *h0, float *h_final, uint16_t *__restrict__ y, Shape s, int nsteps, int nslice, int nseg,
                   int steps_per_seg, int hblock, ChainPieces pieces, int total, int nblocks)
 {
-    constexpr int NTS = NT > 1 ? NT / 2 : 1;             // state tiles per compute wave
-    constexpr int NW = 2 * PT;                           // compute waves; as many i/o waves
+    constexpr bool OUT = CW > 0;
+    constexpr int SW = cb_state_waves(PT, CW), NW = SW + CW / 2, NIO = 2 * PT;
+    constexpr int DEPTH = CW == 2 ? 1 : 2;               // steps that operands are loaded ahead of their use
     constexpr int XROW = 64 * PT;                        // bytes of an x row
-    constexpr int XB = CB_STEP * XROW, YB = 2 * XB;      // bytes of an x tile, of a partial Y tile
+    constexpr int XB = CB_STEP * XROW, YB = 2 * XB;      // bytes of an x tile, of a Y tile
+    constexpr int HB = PT * NT * 2048;                   // bytes of the state, rounded
     constexpr int PPR = 4 * PT;                          // 16-byte pieces of an x row
     constexpr int YM = 8 * PT - 1;                       // 16-byte pieces of a Y row, less one
     extern __shared__ __align__(16) unsigned char smem_raw[];
     unsigned char *s_x = smem_raw;                       // [3] x rows times f, bf16
     unsigned char *s_xs = s_x + (OUT ? 3 * XB : 0);      // [3] of direct steps: x as the state takes it
-    unsigned char *s_y = s_xs + 3 * XB;                  // [2][2] partial Y by halves of the state columns, fp32
+    unsigned char *s_y = s_xs + 3 * XB;                  // [2] Y, fp32
+    unsigned char *s_h = s_y + (OUT ? 2 * YB : 0);       // [2] the state at a step's reference as operand registers
     // [3] mode and references, 2^(part of cs_last), and a byte an i/o wave: x times its factor left its bounds
-    int4 *s_ref = reinterpret_cast<int4 *>(s_y + (OUT ? 4 * YB : 0));
+    int4 *s_ref = reinterpret_cast<int4 *>(s_h + (OUT ? 2 * HB : 0));
     int *s_whole = reinterpret_cast<int *>(s_ref + 3);   // [3][64] of direct steps: whole parts of cs
 
     const int lid = xcd_logical_id(blockIdx.x, nblocks);
@@ -384,7 +395,7 @@ chain_bf16_kernel(const uint16_t *__restrict__ x, const float *__restrict__ D, c
 
     if (!OUT) {
         if (seg == 0 && pieces.h0_copy)                  // of this workgroup's channels
-            for (int i = tid; i < min(32 * PT, P - p0) * s.N / 4; i += 256 * PT)
+            for (int i = tid; i < min(32 * PT, P - p0) * s.N / 4; i += cb_threads(PT, CW))
                 reinterpret_cast<float4 *>(pieces.h0_copy + (bh * P + p0) * s.N)[i] = reinterpret_cast<const float4 *>(h0 + (bh * P + p0) * s.N)[i];
         // decay of this piece, and from its end to the end of its segment
         const float *last = tb.sum + bhs;
@@ -404,23 +415,25 @@ chain_bf16_kernel(const uint16_t *__restrict__ x, const float *__restrict__ D, c
         return (__builtin_amdgcn_readfirstlane(w) & (PT == 2 ? ~0 : 0xffff)) != 0;
     };
     // two pieces of 8 channels of one token a thread of either role: tokens xj0 and xj0 + 32
-    const int io = tid & (NW * 64 - 1), xpc = io % PPR, xp = p0 + 8 * xpc, xj0 = io / PPR;
+    const int io = (tid - NW * 64) & (NIO * 64 - 1), xpc = io % PPR, xp = p0 + 8 * xpc, xj0 = io / PPR;
     const bool xin = xp < P;
     const int64_t xbase = tokb * trow + (int64_t)h * P;                  // uniform
-    const int x_at = xj0 * XROW + (((xpc >> 1) ^ (PT == 2 ? (xj0 & 3) : ((xj0 >> 1) & 1))) << 5) + ((xpc & 1) << 4);
+    auto x_at = [&](int row, int pc) __attribute__((always_inline)) {    // where a piece of 8 channels of a token lies in its tile
+        return row * XROW + (((pc >> 1) ^ (PT == 2 ? (row & 3) : ((row >> 1) & 1))) << 5) + ((pc & 1) << 4);
+    };
     const float2 *fe0 = reinterpret_cast<const float2 *>(tb.fe) + bhs * CB_STEP;
     // x of a direct step: f holds dt and the part of cs, w is the whole of cs
-    auto stage_direct = [&](int at, int m, const float (&a)[8], float f, int w, int last) __attribute__((always_inline)) {
+    auto stage_direct = [&](int at, int row, int pc, const float (&a)[8], float f, int w, int last) __attribute__((always_inline)) {
         const float fs = ldexpf(f, last - w);
         float q[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) q[e] = a[e] * fs;
-        *reinterpret_cast<uint4 *>(s_xs + at * XB + x_at + m * 32 * XROW) = pack8(q);
+        *reinterpret_cast<uint4 *>(s_xs + at * XB + x_at(row, pc)) = pack8(q);
         if (!OUT) return;
 #pragma unroll
         for (int e = 0; e < 8; ++e) q[e] = a[e] * f;
-        *reinterpret_cast<uint4 *>(s_x + at * XB + x_at + m * 32 * XROW) = pack8(q);
-        if (xpc == 0) s_whole[at * CB_STEP + xj0 + 32 * m] = w;
+        *reinterpret_cast<uint4 *>(s_x + at * XB + x_at(row, pc)) = pack8(q);
+        if (pc == 0) s_whole[at * CB_STEP + row] = w;
     };
     // what a factor of y moves to that of x in a step turned direct: any whole number near its exponent
     auto exponent = [](float v) __attribute__((always_inline)) { return (int)rintf(__builtin_amdgcn_logf(v)); };
@@ -429,75 +442,77 @@ chain_bf16_kernel(const uint16_t *__restrict__ x, const float *__restrict__ D, c
     auto turn_direct = [&](int c, int at, int &pack) __attribute__((always_inline)) {
         const int R0 = ref_r0(pack), R1 = R0 + ref_shift(pack), last = R1 + ref_rem(pack);
 #pragma unroll 1
-        for (int m = 0; m < 2; ++m) {
-            const int tok = c * CB_STEP + xj0 + 32 * m;
+        for (int q = tid; q < CB_STEP * PPR; q += 64 * NW) {
+            const int row = q / PPR, pc = q % PPR, tok = c * CB_STEP + row;
             float a[8];
-            unpack8(a, xin && tok < t_end ? *reinterpret_cast<const uint4 *>(x + xbase + tok * trow + xp) : make_uint4(0, 0, 0, 0));
-            const float2 fe = fe0[tok];
+            unpack8(a, p0 + 8 * pc < P && tok < t_end ? *reinterpret_cast<const uint4 *>(x + xbase + tok * trow + p0 + 8 * pc) : make_uint4(0, 0, 0, 0));
+            const float2 fe = fe0[c * CB_STEP + 2 * (row & 31) + (row >> 5)];
             const int e = exponent(fe.y);
-            stage_direct(at, m, a, ldexpf(fe.x, e), (m ? R1 : R0) + e, last);
+            stage_direct(at, row, pc, a, ldexpf(fe.x, e), (row < 32 ? R0 : R1) + e, last);
         }
         pack = pack_direct(last);
         lds_barrier();
     };
 
-    // ================= compute waves: 32 channels x half of the state columns =================
-    auto compute_wave = [&](auto nh_) __attribute__((always_inline)) {
-        constexpr int nh = decltype(nh_)::value;
-        constexpr bool on = nh * NTS < NT;               // one tile: the second half has none
-        constexpr int nt0 = on ? nh * NTS : 0;
-        const int ph = wave % PT, p = p0 + 32 * ph + l32;
-        const uint4 *item0 = reinterpret_cast<const uint4 *>(ops) + ((int64_t)b * nsteps * s.G + g) * (cb_item_frags(NT) * 64) + lane;
-        const int64_t item_step = (int64_t)s.G * (cb_item_frags(NT) * 64);
-        auto item = [&](int c) __attribute__((always_inline)) { return item0 + min(c, c_end - 1) * item_step; };
-        // operand of k-step ks from the x rows: channels 32 ph + lane%32, tokens 16 ks + 4 hi + 0..3 and + 8
-        const int s16 = lane & 15, r4 = s16 >> 2;
+    // operand of k-step ks from the x rows: channels 32 ph + lane%32, tokens 16 ks + 4 hi + 0..3 and + 8
+    const int s16 = lane & 15, r4 = s16 >> 2;
+    auto read_x = [&](const unsigned char *base, int ph, int ks) __attribute__((always_inline)) {
         const int x_fr = (4 * hi + r4) * XROW + (((ph * 2 + ((lane >> 4) & 1)) ^ (PT == 2 ? r4 : (r4 >> 1))) << 5) + 8 * (s16 & 3);
-        uint4 xf[4];
-        auto read_x = [&](const unsigned char *base, int from, int to) __attribute__((always_inline)) {
+        const unsigned char *q = base + x_fr + ks * 16 * XROW;
+        const uint2 a = lds_read_tr(q), e = lds_read_tr(q + 8 * XROW);
+        return make_uint4(a.x, a.y, e.x, e.y);
+    };
+    // rows of x and y of step c, at the first of which x0 points: nothing is read or written past the segment's end
+    auto rows = [&](const uint16_t *x0, int c) __attribute__((always_inline)) {
+        const int left = __builtin_amdgcn_readfirstlane(max(0, min(CB_STEP, t_end - c * CB_STEP)));
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(x0 + xbase + c * (CB_STEP * trow)), 0, left * (int)trow * 2, 0x27000);
+    };
+    const uint4 *item0 = reinterpret_cast<const uint4 *>(ops) + ((int64_t)b * nsteps * s.G + g) * (cb_item_frags(NT) * 64) + lane;
+    const int64_t item_step = (int64_t)s.G * (cb_item_frags(NT) * 64);
+    auto item = [&](int c) __attribute__((always_inline)) { return item0 + min(c, c_end - 1) * item_step; };
+
+    // ================= state waves: the state's tiles, a part of its columns each =================
+    auto state_wave = [&](int sw) __attribute__((always_inline)) {
+        constexpr int PHW = OUT ? PT : 1;                // channel tiles
+        constexpr int SPLIT = CW == 2 ? 1 : 2;           // waves that share the columns
+        constexpr int NTS = NT > SPLIT ? NT / SPLIT : 1;
+        const int nh = OUT ? sw : sw / PT, ph0 = OUT ? 0 : sw % PT;
+        const bool on = nh * NTS < NT;                   // one tile: the second wave has none
+        const int nt0 = on ? nh * NTS : 0;
+        uint4 bfr[DEPTH][NTS][4], xf[PHW][4];
+        auto load_b = [&](uint4 (&v)[NTS][4], int c) __attribute__((always_inline)) {
+            // in the order of the steps' loads: the waits on them stay exact counts
+            const uint4 *src = item(c) + (4 * NT + nt0 * 4) * 64;
 #pragma unroll
-            for (int ks = from; ks < to; ++ks) {
-                const unsigned char *q = base + x_fr + ks * 16 * XROW;
-                const uint2 a = lds_read_tr(q), e = lds_read_tr(q + 8 * XROW);
-                xf[ks] = make_uint4(a.x, a.y, e.x, e.y);
+            for (int i = 0; i < 4 * NTS; ++i) {
+                const int j = i % (2 * NTS), k = i < 2 * NTS ? j % NTS : j / 2, ks = i < 2 * NTS ? j / NTS : 2 + j % 2;
+                v[k][ks] = src[(k * 4 + ks) * 64];
+                __builtin_amdgcn_sched_barrier(0);
             }
         };
-        uint4 cf[2][2 * NTS], bfr[NTS][4], gf[3];
-        auto load_c = [&](int c) __attribute__((always_inline)) {
-            const uint4 *src = item(c);
-#pragma unroll
-            for (int k = 0; k < 2 * NTS; ++k)
-#pragma unroll
-                for (int it = 0; it < 2; ++it) cf[it][k] = src[(it * 2 * NT + 2 * nt0 + k) * 64];
+        f32x16_t st[PHW][NTS];
+        auto hoff = [&](int ph) __attribute__((always_inline)) {
+            return (((int64_t)b * s.H + h) * P + min(p0 + 32 * (ph0 + ph) + l32, P - 1)) * s.N;
         };
-        auto load_g = [&](int c) __attribute__((always_inline)) {
-            const uint4 *src = item(c);
 #pragma unroll
-            for (int k = 0; k < 3; ++k) gf[k] = src[(8 * NT + 3 * nh + k) * 64];
-        };
-        auto load_b = [&](int c) __attribute__((always_inline)) {
-            const uint4 *src = item(c);
+        for (int ph = 0; ph < PHW; ++ph)
 #pragma unroll
             for (int k = 0; k < NTS; ++k)
 #pragma unroll
-                for (int ks = 0; ks < 4; ++ks) bfr[k][ks] = src[(4 * NT + (nt0 + k) * 4 + ks) * 64];
+                for (int q = 0; q < 4; ++q) {
+                    const int n = 32 * (nt0 + k) + 8 * q + 4 * hi;
+                    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+                    if (OUT && h0 && p0 + 32 * (ph0 + ph) + l32 < P && n < s.N) v = *reinterpret_cast<const float4 *>(h0 + hoff(ph) + n);
+                    st[ph][k][4 * q] = v.x; st[ph][k][4 * q + 1] = v.y; st[ph][k][4 * q + 2] = v.z; st[ph][k][4 * q + 3] = v.w;
+                }
+        auto scale = [&](float f) __attribute__((always_inline)) {
+#pragma unroll
+            for (int ph = 0; ph < PHW; ++ph)
+#pragma unroll
+                for (int k = 0; k < NTS; ++k)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) st[ph][k][v] *= f;
         };
-        if (OUT) {
-            load_c(c_begin);
-            load_g(c_begin);
-        }
-        load_b(c_begin);
-        f32x16_t st[NTS];
-        const int64_t hoff = (((int64_t)b * s.H + h) * P + min(p, P - 1)) * s.N;
-#pragma unroll
-        for (int k = 0; k < NTS; ++k)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int n = 32 * (nt0 + k) + 8 * q + 4 * hi;
-                float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-                if (OUT && h0 && p < P && n < s.N) v = *reinterpret_cast<const float4 *>(h0 + hoff + n);
-                st[k][4 * q] = v.x; st[k][4 * q + 1] = v.y; st[k][4 * q + 2] = v.z; st[k][4 * q + 3] = v.w;
-            }
         if (OUT && seg > 0) {
             // lane l: the piece l pieces in front of the segment's first step, and its factor
             const int np = seg * pieces.per_seg;
@@ -506,301 +521,367 @@ chain_bf16_kernel(const uint16_t *__restrict__ x, const float *__restrict__ D, c
             const float upto = wave_scan(sum.x);
             float e = __shfl_up(upto, 1);
             if (lane == 0) e = 0.f;
-            uint64_t todo = __ballot(sum.y != 0.f && !(pieces.skip && e < -150.f));
+            const uint64_t live = __ballot(sum.y != 0.f && !(pieces.skip && e < -150.f));
             float frac;
             int whole;
             split_exp2(lane_value(upto, 63), frac, whole);
 #pragma unroll
-            for (int k = 0; k < NTS; ++k)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) st[k][v] = scale_exp2(st[k][v], frac, whole);
-            auto add = [&](int i, const float4 (&v)[NTS][4]) __attribute__((always_inline)) {
-                split_exp2(lane_value(e, i), frac, whole);
+            for (int ph = 0; ph < PHW; ++ph)
 #pragma unroll
                 for (int k = 0; k < NTS; ++k)
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        st[k][4 * q + 0] += scale_exp2(v[k][q].x, frac, whole);
-                        st[k][4 * q + 1] += scale_exp2(v[k][q].y, frac, whole);
-                        st[k][4 * q + 2] += scale_exp2(v[k][q].z, frac, whole);
-                        st[k][4 * q + 3] += scale_exp2(v[k][q].w, frac, whole);
+                    for (int v = 0; v < 16; ++v) st[ph][k][v] = scale_exp2(st[ph][k][v], frac, whole);
+#pragma unroll
+            for (int ph = 0; ph < PHW; ++ph) {
+                auto add = [&](int i, const float4 (&v)[NTS][4]) __attribute__((always_inline)) {
+                    split_exp2(lane_value(e, i), frac, whole);
+#pragma unroll
+                    for (int k = 0; k < NTS; ++k)
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            st[ph][k][4 * q + 0] += scale_exp2(v[k][q].x, frac, whole);
+                            st[ph][k][4 * q + 1] += scale_exp2(v[k][q].y, frac, whole);
+                            st[ph][k][4 * q + 2] += scale_exp2(v[k][q].z, frac, whole);
+                            st[ph][k][4 * q + 3] += scale_exp2(v[k][q].w, frac, whole);
+                        }
+                };
+                auto fetch = [&](int i, float4 (&v)[NTS][4]) __attribute__((always_inline)) {
+                    const float4 *src = piece_frag(pieces, bh, nbh, np - 1 - i, ptiles, min(sl * PT + ph0 + ph, ptiles - 1), NT) + nt0 * 256 + lane;
+#pragma unroll
+                    for (int k = 0; k < NTS; ++k)
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) v[k][q] = src[(k * 4 + q) * 64];
+                };
+                for (uint64_t todo = live; todo;) {      // two pieces in flight
+                    float4 v0[NTS][4], v1[NTS][4];
+                    const int i0 = 63 - __builtin_clzll(todo);
+                    todo &= ~(1ull << i0);
+                    fetch(i0, v0);
+                    if (todo) {
+                        const int i1 = 63 - __builtin_clzll(todo);
+                        todo &= ~(1ull << i1);
+                        fetch(i1, v1);
+                        add(i0, v0);
+                        add(i1, v1);
+                    } else {
+                        add(i0, v0);
                     }
-            };
-            auto fetch = [&](int i, float4 (&v)[NTS][4]) __attribute__((always_inline)) {
-                const float4 *src = piece_frag(pieces, bh, nbh, np - 1 - i, ptiles, min(sl * PT + ph, ptiles - 1), NT) + nt0 * 256 + lane;
-#pragma unroll
-                for (int k = 0; k < NTS; ++k)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) v[k][q] = src[(k * 4 + q) * 64];
-            };
-            while (on && todo) {                         // two pieces in flight
-                float4 v0[NTS][4], v1[NTS][4];
-                const int i0 = 63 - __builtin_clzll(todo);
-                todo &= ~(1ull << i0);
-                fetch(i0, v0);
-                if (todo) {
-                    const int i1 = 63 - __builtin_clzll(todo);
-                    todo &= ~(1ull << i1);
-                    fetch(i1, v1);
-                    add(i0, v0);
-                    add(i1, v1);
-                } else {
-                    add(i0, v0);
                 }
             }
         }
-        f32x16_t yt[2];
-        // the state to the reference of a step, and its share of that step's Y (two tiles of 32 tokens)
-        auto readout = [&](float sc) __attribute__((always_inline)) {
 #pragma unroll
-            for (int it = 0; it < 2; ++it)
+        for (int u = 0; u < DEPTH; ++u) load_b(bfr[u], c_begin + u);
+        unsigned char *h_wr = s_h + nt0 * 2048 + lane * 16;
+        // the state at a step's reference, rounded, for the readout
+        auto write_h = [&](int par, int ph, int k) __attribute__((always_inline)) {
+            float m[16];
 #pragma unroll
-                for (int v = 0; v < 16; ++v) yt[it][v] = 0.f;
-#pragma unroll
-            for (int k = 0; k < NTS; ++k) {
-                float m[16];
-#pragma unroll
-                for (int v = 0; v < 16; ++v) m[v] = (st[k][v] *= sc);
-                const uint4 hf[2] = {pack8(m), pack8(m + 8)};
-                if (on) {
-#pragma unroll
-                    for (int q = 0; q < 2; ++q)
-#pragma unroll
-                        for (int it = 0; it < 2; ++it) yt[it] = mfma32(hf[q], cf[it][2 * k + q], yt[it]);
-                }
+            for (int v = 0; v < 16; ++v) m[v] = st[ph][k][v];
+            uint4 *dst = reinterpret_cast<uint4 *>(h_wr + par * HB + (ph * NT + k) * 2048);
+            const uint4 a = pack8(m), e = pack8(m + 8);
+            if (on) {
+                dst[0] = a;
+                dst[64] = e;
             }
         };
         lds_barrier();                                   // x of the first step, references of the first two
         int4 rc = s_ref[0];
         int pc = __builtin_amdgcn_readfirstlane(rc.x);
         if (__builtin_expect(flagged(rc.w), 0)) turn_direct(c_begin, 0, pc);
+        scale(ldexpf(1.f, ref_r0(pc)));
         if (OUT) {
-            readout(ldexpf(1.f, ref_r0(pc)));
-            load_c(c_begin + 1);
+#pragma unroll
+            for (int ph = 0; ph < PHW; ++ph)
+#pragma unroll
+                for (int k = 0; k < NTS; ++k) write_h(0, ph, k);
         }
-        read_x(s_x, 0, 4);
-        unsigned char *y_wr = s_y + nh * YB + l32 * (128 * PT);
+        auto x_base = [&](int pack, int at) __attribute__((always_inline)) { return (ref_mode(pack) == 2 ? s_xs : s_x) + at * XB; };
+        {
+            const unsigned char *base = x_base(pc, 0);
+#pragma unroll
+            for (int ph = 0; ph < PHW; ++ph)
+#pragma unroll
+                for (int ks = 0; ks < 4; ++ks) xf[ph][ks] = read_x(base, ph0 + ph, ks);
+        }
         int slot = 0;                                    // of x, references and whole parts
-        for (int c = c_begin; c < c_end; ++c) {
+        auto step = [&](int c, uint4 (&bf)[NTS][4]) __attribute__((always_inline)) {
             lds_barrier();
             const int next_slot = slot == 2 ? 0 : slot + 1;
             const int4 rn = s_ref[next_slot];
-            const int mode = ref_mode(pc);
-            if (__builtin_expect(mode == 2, 0)) {
-                // the state to the step's end
-                const float to_end = ldexpf(1.f, ref_shift(pc));
+            if (__builtin_expect(ref_mode(pc) == 2, 0)) scale(ldexpf(1.f, ref_shift(pc)));   // to the step's end
+            const uint4 *next = item(c + DEPTH) + (4 * NT + nt0 * 4) * 64;
+            // Memory instructions go out one behind each use of what they replace: a wave that issues them in a row waits
+            // for the CU's address unit and LDS each time, with its matrix core idle.
 #pragma unroll
-                for (int k = 0; k < NTS; ++k)
+            for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
-                    for (int v = 0; v < 16; ++v) st[k][v] *= to_end;
-                if (OUT) {
-                    const int *whole = s_whole + slot * CB_STEP;
-                    const int wi[2] = {whole[l32], whole[32 + l32]};
+                for (int k = 0; k < NTS; ++k) {
 #pragma unroll
-                    for (int it = 0; it < 2; ++it)
-#pragma unroll
-                        for (int v = 0; v < 16; ++v) yt[it][v] = ldexpf(yt[it][v], wi[it]);
-#pragma unroll
-                    for (int k = 0; k < 3; ++k) {
-                        const int f = 3 * nh + k, it = f >= 2, ks = it ? f - 2 : f;
-                        const int4 w0 = *reinterpret_cast<const int4 *>(whole + 16 * ks + 4 * hi), w1 = *reinterpret_cast<const int4 *>(whole + 16 * ks + 8 + 4 * hi);
-                        const int wj[8] = {w0.x, w0.y, w0.z, w0.w, w1.x, w1.y, w1.z, w1.w};
-                        float m[8];
-                        unpack8(m, gf[k]);
-#pragma unroll
-                        for (int e = 0; e < 8; ++e) m[e] = ldexpf(m[e], wi[it] - wj[e]);
-                        gf[k] = pack8(m);
-                    }
+                    for (int ph = 0; ph < PHW; ++ph) st[ph][k] = mfma32(bf[k][ks], xf[ph][ks], st[ph][k]);
+                    bf[k][ks] = next[(k * 4 + ks) * 64];
+                    __builtin_amdgcn_sched_barrier(0);
                 }
-            }
-            auto masked_products = [&](int half) __attribute__((always_inline)) {
-#pragma unroll
-                for (int k = 0; k < 3; ++k) {
-                    const int f = 3 * nh + k, it = f >= 2, ks = it ? f - 2 : f;
-                    if (ks / 2 == half) yt[it] = mfma32(xf[ks], gf[k], yt[it]);
-                }
-            };
-            const uint4 *next = item(c + 1);
-            auto load_b1 = [&](int k, int ks) __attribute__((always_inline)) { bfr[k][ks] = next[(4 * NT + (nt0 + k) * 4 + ks) * 64]; };
-            auto write_y = [&](int it, int q) __attribute__((always_inline)) {
-                *reinterpret_cast<float4 *>(y_wr + ((c - c_begin) & 1) * 2 * YB + it * 32 * 128 * PT + (((4 * ph + q + 4 * PT * hi) ^ (l32 & YM)) << 4)) =
-                    make_float4(yt[it][4 * q], yt[it][4 * q + 1], yt[it][4 * q + 2], yt[it][4 * q + 3]);
-            };
-            if (OUT) {
-                masked_products(0);
-                if (__builtin_expect(mode == 2, 0)) read_x(s_xs + slot * XB, 0, 2);
-            }
-            // Memory instructions go out one behind each MFMA: a wave that issues them in a row waits for the CU's address
-            // unit and LDS each time, with its matrix core idle.
-#pragma unroll
-            for (int k = 0; k < NTS; ++k)
-#pragma unroll
-                for (int ks = 0; ks < 2; ++ks) {
-                    st[k] = mfma32(bfr[k][ks], xf[ks], st[k]);
-                    load_b1(k, ks);
-                    if (OUT) write_y(0, (2 * k + ks) & 3);
-                }
-            if (OUT && NTS == 1) { write_y(0, 2); write_y(0, 3); }
-#pragma unroll
-            for (int i = 0; i < 2 * NTS; ++i) {
-                __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x20, 1, 0);
-                if (OUT) __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
-            }
-            if (__builtin_expect(mode == 1, 0)) {
-                // from the reference of the first 32 tokens to that of the others
-                const float over = ldexpf(1.f, ref_shift(pc));
-                if (OUT) {
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) yt[1][v] *= over;
-                }
-#pragma unroll
-                for (int k = 0; k < NTS; ++k)
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) st[k][v] *= over;
-            }
-            if (OUT) {
-                masked_products(1);
-            }
+            if (__builtin_expect(ref_mode(pc) == 1, 0)) scale(ldexpf(1.f, ref_shift(pc)));   // to the reference of the other 32 tokens
             int pn = __builtin_amdgcn_readfirstlane(rn.x);
-            const bool turn = flagged(rn.w);
-            if (__builtin_expect(turn || (OUT && mode == 2), 0)) {
-                if (OUT && mode == 2) read_x(s_xs + slot * XB, 2, 4);
-                if (turn) turn_direct(c + 1, next_slot, pn);
-            }
+            if (__builtin_expect(flagged(rn.w), 0)) turn_direct(c + 1, next_slot, pn);
             const float sc = ldexpf(__int_as_float(rc.y), ref_rem(pc) + (c + 1 < c_end ? ref_r0(pn) : 0));
-            if (OUT) load_g(c + 1);
-            __builtin_amdgcn_sched_barrier(0xf);
+            const unsigned char *base = x_base(pn, next_slot);
 #pragma unroll
-            for (int k = 0; k < NTS; ++k)
+            for (int ph = 0; ph < PHW; ++ph)
+#pragma unroll
+                for (int ks = 0; ks < 2; ++ks) xf[ph][ks] = read_x(base, ph0 + ph, ks);
+            // the state at the reference of the next step, a tile's behind the matrix work of the next
+            auto finish = [&](int i) __attribute__((always_inline)) {
+                const int k = i / PHW, ph = i % PHW;
+#pragma unroll
+                for (int v = 0; v < 16; ++v) st[ph][k][v] *= sc;
+                if (OUT) write_h((c + 1 - c_begin) & 1, ph, k);
+            };
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 0; i < NTS * PHW; ++i) {
+                const int k = i / PHW, ph = i % PHW;
 #pragma unroll
                 for (int ks = 2; ks < 4; ++ks) {
-                    st[k] = mfma32(bfr[k][ks], xf[ks], st[k]);
-                    load_b1(k, ks);
-                    if (OUT) write_y(1, (2 * k + ks) & 3);
+                    st[ph][k] = mfma32(bf[k][ks], xf[ph][ks], st[ph][k]);
+                    if (ph == PHW - 1) bf[k][ks] = next[(k * 4 + ks) * 64];
                 }
-            if (OUT && NTS == 1) { write_y(1, 0); write_y(1, 1); }
-            slot = next_slot;
-            read_x(s_x + slot * XB, 0, 4);
+                if (i == NTS * PHW - 1) {
 #pragma unroll
-            for (int i = 0; i < 2 * NTS; ++i) {
-                __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x20, 1, 0);
-                if (OUT) __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
-            }
-            __builtin_amdgcn_sched_group_barrier(0x100, 8, 0);
-            __builtin_amdgcn_sched_barrier(0);
-            // the state at the reference of the next step, and its share of that step's Y
-            const uint4 *after = item(c + 2);
+                    for (int q = 0; q < PHW; ++q)
 #pragma unroll
-            for (int it = 0; it < 2; ++it)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) yt[it][v] = 0.f;
-#pragma unroll
-            for (int k = 0; k < NTS; ++k) {
-                float m[16];
-#pragma unroll
-                for (int v = 0; v < 16; ++v) m[v] = (st[k][v] *= sc);
-                const uint4 hf[2] = {pack8(m), pack8(m + 8)};
-                if (OUT && on) {
-#pragma unroll
-                    for (int q = 0; q < 2; ++q)
-#pragma unroll
-                        for (int it = 0; it < 2; ++it) {
-                            yt[it] = mfma32(hf[q], cf[it][2 * k + q], yt[it]);
-                            cf[it][2 * k + q] = after[(it * 2 * NT + 2 * (nt0 + k) + q) * 64];
-                        }
+                        for (int ks = 2; ks < 4; ++ks) xf[q][ks] = read_x(base, ph0 + q, ks);
                 }
+                __builtin_amdgcn_sched_barrier(0);
+                if (i > 0) finish(i - 1);
+                __builtin_amdgcn_sched_barrier(0);
             }
+            finish(NTS * PHW - 1);
             rc = rn;
             pc = pn;
+            slot = next_slot;
+        };
+        int c = c_begin;
+        for (; c + DEPTH <= c_end; c += DEPTH) {         // no way from one of two operand sets to itself: the waits stay exact counts
+            step(c, bfr[0]);
+            if (DEPTH == 2) step(c + 1, bfr[DEPTH - 1]);
         }
+        if (DEPTH == 2 && c < c_end) step(c, bfr[0]);
         lds_barrier();
-        if (!OUT && on && sl * PT + ph < ptiles) {
-            float4 *dst = piece_frag(pieces, bh, nbh, seg, ptiles, sl * PT + ph, NT) + nt0 * 256 + lane;
+        if (!on) return;
 #pragma unroll
-            for (int k = 0; k < NTS; ++k)
+        for (int ph = 0; ph < PHW; ++ph) {
+            if (!OUT && sl * PT + ph0 + ph < ptiles) {
+                float4 *dst = piece_frag(pieces, bh, nbh, seg, ptiles, sl * PT + ph0 + ph, NT) + nt0 * 256 + lane;
 #pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    dst[(k * 4 + q) * 64] = make_float4(st[k][4 * q], st[k][4 * q + 1], st[k][4 * q + 2], st[k][4 * q + 3]);
-        }
-        if (OUT && h_final && seg == nseg - 1 && p < P && on) {
+                for (int k = 0; k < NTS; ++k)
 #pragma unroll
-            for (int k = 0; k < NTS; ++k)
+                    for (int q = 0; q < 4; ++q)
+                        dst[(k * 4 + q) * 64] = make_float4(st[ph][k][4 * q], st[ph][k][4 * q + 1], st[ph][k][4 * q + 2], st[ph][k][4 * q + 3]);
+            }
+            if (OUT && h_final && seg == nseg - 1 && p0 + 32 * ph + l32 < P) {
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int n = 32 * (nt0 + k) + 8 * q + 4 * hi;
-                    if (n < s.N)
-                        *reinterpret_cast<float4 *>(h_final + hoff + n) =
-                            make_float4(st[k][4 * q], st[k][4 * q + 1], st[k][4 * q + 2], st[k][4 * q + 3]);
-                }
+                for (int k = 0; k < NTS; ++k)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const int n = 32 * (nt0 + k) + 8 * q + 4 * hi;
+                        if (n < s.N)
+                            *reinterpret_cast<float4 *>(h_final + hoff(ph) + n) =
+                                make_float4(st[ph][k][4 * q], st[ph][k][4 * q + 1], st[ph][k][4 * q + 2], st[ph][k][4 * q + 3]);
+                    }
+            }
         }
     };
 
-    if (wave < PT) {
-        compute_wave(std::integral_constant<int, 0>{});
+    // ================= readout waves: Y of 32 tokens (one channel tile: of all 64), one step behind the state =================
+    auto readout_wave = [&](auto first_) __attribute__((always_inline)) {
+        constexpr int I0 = decltype(first_)::value, IW = CW == 2 ? 2 : 1;      // token tiles
+        constexpr int GF = IW == 2 ? 6 : 2 + 2 * I0, G0 = 2 * I0;              // operands of the masked products, from G0 on
+        constexpr int XK = I0 + IW == 2 ? 4 : 2;                               // k-steps of x
+        uint4 cf[DEPTH][IW][2 * NT], gf[DEPTH][GF], xf[PT][4];
+        auto load = [&](uint4 (&cv)[IW][2 * NT], uint4 (&gv)[GF], int c) __attribute__((always_inline)) {
+            const uint4 *src = item(c);
+#pragma unroll
+            for (int k = 0; k < 2 * NT; ++k)
+#pragma unroll
+                for (int i = 0; i < IW; ++i) {
+                    cv[i][k] = src[((I0 + i) * 2 * NT + k) * 64];
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+#pragma unroll
+            for (int k = 0; k < GF; ++k) {
+                gv[k] = src[(8 * NT + G0 + k) * 64];
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+#pragma unroll
+        for (int u = 0; u < DEPTH; ++u) load(cf[u], gf[u], c_begin + u);
+        lds_barrier();
+        int pc = __builtin_amdgcn_readfirstlane(s_ref[0].x);
+        if (__builtin_expect(flagged(s_ref[0].w), 0)) turn_direct(c_begin, 0, pc);
+        int slot = 0;
+        auto read_all_x = [&](int at) __attribute__((always_inline)) {
+#pragma unroll
+            for (int ph = 0; ph < PT; ++ph)
+#pragma unroll
+                for (int ks = 0; ks < XK; ++ks) xf[ph][ks] = read_x(s_x + at * XB, ph, ks);
+        };
+        read_all_x(0);
+        unsigned char *y_wr = s_y + (32 * I0 + l32) * (128 * PT);
+        auto step = [&](int c, uint4 (&cv)[IW][2 * NT], uint4 (&gv)[GF]) __attribute__((always_inline)) {
+            lds_barrier();
+            const int next_slot = slot == 2 ? 0 : slot + 1, par = (c - c_begin) & 1;
+            const int4 rn = s_ref[next_slot];
+            const int mode = ref_mode(pc);
+            const uint4 *hr = reinterpret_cast<const uint4 *>(s_h + par * HB) + lane;
+            constexpr int HF = PT == 1 && NT == 4 ? 2 : NT;      // operands of the state in flight
+            uint4 hf[HF];
+#pragma unroll
+            for (int k = 0; k < HF; ++k) hf[k] = hr[k * 64];
+            int wi[IW] = {};
+            if (__builtin_expect(mode == 2, 0)) {
+                const int *whole = s_whole + slot * CB_STEP;
+#pragma unroll
+                for (int i = 0; i < IW; ++i) wi[i] = whole[32 * (I0 + i) + l32];
+#pragma unroll
+                for (int k = 0; k < GF; ++k) {
+                    const int f = G0 + k, it = f >= 2, ks = it ? f - 2 : f;
+                    const int4 w0 = *reinterpret_cast<const int4 *>(whole + 16 * ks + 4 * hi), w1 = *reinterpret_cast<const int4 *>(whole + 16 * ks + 8 + 4 * hi);
+                    const int wj[8] = {w0.x, w0.y, w0.z, w0.w, w1.x, w1.y, w1.z, w1.w};
+                    float m[8];
+                    unpack8(m, gv[k]);
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) m[e] = ldexpf(m[e], wi[it - I0] - wj[e]);
+                    gv[k] = pack8(m);
+                }
+            }
+            const uint4 *next = item(c + DEPTH);
+            f32x16_t yt[PT][IW];
+            auto write_y = [&](int ph, int i, int q) __attribute__((always_inline)) {
+                *reinterpret_cast<float4 *>(y_wr + par * YB + i * 32 * 128 * PT + (((4 * ph + q + 4 * PT * hi) ^ (l32 & YM)) << 4)) =
+                    make_float4(yt[ph][i][4 * q], yt[ph][i][4 * q + 1], yt[ph][i][4 * q + 2], yt[ph][i][4 * q + 3]);
+            };
+            // one channel tile after the other: the first goes to LDS behind the matrix work of the second
+#pragma unroll
+            for (int ph = 0; ph < PT; ++ph) {
+#pragma unroll
+                for (int i = 0; i < IW; ++i)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) yt[ph][i][v] = 0.f;
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int k = 0; k < 2 * NT; ++k) {
+#pragma unroll
+                    for (int i = 0; i < IW; ++i) {
+                        yt[ph][i] = mfma32(hf[k % HF], cv[i][k], yt[ph][i]);
+                        if (ph == PT - 1) cv[i][k] = next[((I0 + i) * 2 * NT + k) * 64];
+                    }
+                    if (ph < PT - 1 || k < 2 * NT - HF) hf[k % HF] = hr[(ph * 2 * NT + k + HF) * 64];
+                    if (ph > 0 && k >= NT) write_y(ph - 1, 0, k - NT);           // NT = 4: the whole tile
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                if (__builtin_expect(mode == 2, 0)) {
+#pragma unroll
+                    for (int i = 0; i < IW; ++i)
+#pragma unroll
+                        for (int v = 0; v < 16; ++v) yt[ph][i][v] = ldexpf(yt[ph][i][v], wi[i]);
+                }
+                auto masked_products = [&](int half) __attribute__((always_inline)) {
+#pragma unroll
+                    for (int k = 0; k < GF; ++k) {
+                        const int f = G0 + k, it = f >= 2, ks = it ? f - 2 : f;
+                        if (ks / 2 == half) {
+                            yt[ph][it - I0] = mfma32(xf[ph][ks], gv[k], yt[ph][it - I0]);
+                            if (ph == PT - 1) gv[k] = next[(8 * NT + G0 + k) * 64];
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+                    }
+                };
+                masked_products(0);
+                if constexpr (I0 + IW == 2) {
+                    if (__builtin_expect(mode == 1, 0)) {
+                        // from the reference of the first 32 tokens to that of the others
+                        const float over = ldexpf(1.f, ref_shift(pc));
+#pragma unroll
+                        for (int v = 0; v < 16; ++v) yt[ph][IW - 1][v] *= over;
+                    }
+                    masked_products(1);
+                }
+            }
+            int pn = __builtin_amdgcn_readfirstlane(rn.x);
+            if (__builtin_expect(flagged(rn.w), 0)) turn_direct(c + 1, next_slot, pn);
+            read_all_x(next_slot);
+#pragma unroll
+            for (int ph = 0; ph < PT; ++ph)
+#pragma unroll
+                for (int i = 0; i < IW; ++i)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        if (ph == PT - 1 || q >= NT) write_y(ph, i, q);
+            pc = pn;
+            slot = next_slot;
+        };
+        int c = c_begin;
+        for (; c + DEPTH <= c_end; c += DEPTH) {         // no way from one of two operand sets to itself: the waits stay exact counts
+            step(c, cf[0], gf[0]);
+            if (DEPTH == 2) step(c + 1, cf[DEPTH - 1], gf[DEPTH - 1]);
+        }
+        if (DEPTH == 2 && c < c_end) step(c, cf[0], gf[0]);
+        lds_barrier();
+    };
+
+    if (wave < SW) {
+        state_wave(wave);
     } else if (wave < NW) {
-        compute_wave(std::integral_constant<int, 1>{});
+        if (CW == 2 || wave == SW) readout_wave(std::integral_constant<int, 0>{});
+        else readout_wave(std::integral_constant<int, CW == 2 ? 0 : 1>{});
     } else {
         // ================= i/o waves: two pieces of 8 channels of one token a thread =================
         const int iow = wave - NW;
-        int64_t xoff[2];
+        int xoff[2], yoff[2];
 #pragma unroll
-        for (int m = 0; m < 2; ++m) xoff[m] = (xj0 + 32 * m) * trow + (xin ? xp : 0);
+        for (int m = 0; m < 2; ++m) {
+            const int row = (xj0 + 32 * m) * (int)trow;
+            xoff[m] = (row + (xin ? xp : 0)) * 2;
+            yoff[m] = xin ? (row + xp) * 2 : (int)0x80000000;
+        }
         const float dsk = D ? D[h] : 0.f;
         const bool skip = D != nullptr;
-        // the next step's x and factors; past the end the last one's again
-        int xc = c_begin;
-        const uint16_t *xq = x + xbase + (int64_t)c_begin * CB_STEP * trow;
-        const float2 *fq = fe0 + (int64_t)c_begin * CB_STEP + xj0;
-        auto load_x = [&](uint4 (&v)[2], float2 (&fe)[2]) __attribute__((always_inline)) {
-            const int last = t_end - 1 - xc * CB_STEP;
-            int64_t o[2] = {xoff[0], xoff[1]};
-            if (last < CB_STEP - 1) {                    // a step that is not full
+        // x of step c, zeros past the segment's end, and its factors
+        auto load_x = [&](u32x4_t (&v)[2], float4 &fe, int c) __attribute__((always_inline)) {
+            const auto xrows = rows(x, c);
 #pragma unroll
-                for (int m = 0; m < 2; ++m) o[m] -= max(xj0 + 32 * m - last, 0) * trow;
-            }
-#pragma unroll
-            for (int m = 0; m < 2; ++m) {
-                v[m] = *reinterpret_cast<const uint4 *>(xq + o[m]);
-                fe[m] = fq[32 * m];
-            }
-            const bool more = xc < c_end - 1;
-            xc += more;
-            xq += more ? CB_STEP * trow : 0;
-            fq += more ? CB_STEP : 0;
+            for (int m = 0; m < 2; ++m) v[m] = __builtin_amdgcn_raw_buffer_load_b128(xrows, xoff[m], 0, 0);
+            fe = reinterpret_cast<const float4 *>(fe0 + min(c, c_end - 1) * CB_STEP)[xj0];
         };
+        auto unpack = [&](float (&a)[8], const u32x4_t &v) __attribute__((always_inline)) { unpack8(a, make_uint4(v[0], v[1], v[2], v[3])); };
         // x of step c (v) times its factor into LDS; of a direct step two copies, and fe turns into the factors.  Channels past
         // P hold something else's x, for rows of Y and columns of the state that go nowhere.
-        auto stage_x = [&](int c, int at, uint4 (&v)[2], float2 (&fe)[2], const cb_f32x4_t &ref) __attribute__((always_inline)) {
+        auto stage_x = [&](int c, int at, const u32x4_t (&v)[2], float4 &fe, const cb_f32x4_t &ref) __attribute__((always_inline)) {
             const int p = __float_as_int(ref[0]), left = t_end - c * CB_STEP;
-            if (__builtin_expect(left < CB_STEP, 0)) {   // tokens past the end hold another one's x
-#pragma unroll
-                for (int m = 0; m < 2; ++m)
-                    if (xj0 + 32 * m >= left) v[m] = make_uint4(0, 0, 0, 0);
-            }
             uint64_t in = ~0ull;
             if (__builtin_expect(ref_mode(p) == 2, 0)) {
 #pragma unroll
                 for (int m = 0; m < 2; ++m) {
-                    const float cs = fe[m].y, whole = rintf(cs), part = cs - whole;
-                    fe[m].x = cs == cs ? fe[m].x * fast_exp2(-part) : 0.f;
-                    fe[m].y = fast_exp2(part);
+                    float &f = m ? fe.z : fe.x, &e = m ? fe.w : fe.y;
+                    const float cs = e, whole = rintf(cs), part = cs - whole;
+                    f = cs == cs ? f * fast_exp2(-part) : 0.f;
+                    e = fast_exp2(part);
                     float a[8];
-                    unpack8(a, v[m]);
-                    stage_direct(at, m, a, fe[m].x, (int)whole, ref_shift(p));           // 0 of NaN
+                    unpack(a, v[m]);
+                    stage_direct(at, xj0 + 32 * m, xpc, a, f, (int)whole, ref_shift(p));   // 0 of NaN
                 }
             } else {
                 float most[2] = {0.f, 0.f};
 #pragma unroll
                 for (int m = 0; m < 2; ++m) {
                     float a[8];
-                    unpack8(a, v[m]);
+                    unpack(a, v[m]);
 #pragma unroll
-                    for (int q = 0; q < 8; ++q) a[q] *= fe[m].x;
+                    for (int q = 0; q < 8; ++q) a[q] *= m ? fe.z : fe.x;
 #pragma unroll
                     for (int q = 0; q < 8; ++q) most[m] = fmaxf(most[m], fabsf(a[q]));
-                    *reinterpret_cast<uint4 *>(s_x + at * XB + x_at + m * 32 * XROW) = pack8(a);
+                    *reinterpret_cast<uint4 *>(s_x + at * XB + x_at(xj0, xpc) + m * 32 * XROW) = pack8(a);
                 }
                 if (__builtin_expect(left < CB_STEP, 0)) {
 #pragma unroll
@@ -813,61 +894,39 @@ chain_bf16_kernel(const uint16_t *__restrict__ x, const float *__restrict__ D, c
             reinterpret_cast<unsigned char *>(&s_ref[at].w)[iow] = left > 0 && in != ~0ull;
         };
         const int ya0 = xj0 * (128 * PT) + ((xpc ^ (xj0 & YM)) << 4), ya1 = xj0 * (128 * PT) + (((xpc + 4 * PT) ^ (xj0 & YM)) << 4);
-        uint16_t *yq = y + xbase + (int64_t)c_begin * CB_STEP * trow;
         // stages step c + 2 (xn) and finishes step c - 1 (xo)
-        auto pass = [&](int c, int at, uint4 (&xn)[2], float2 (&fn)[2], const cb_f32x4_t &rn, const uint4 (&xo)[2], const float2 (&fo)[2], int ybuf) __attribute__((always_inline)) {
+        auto pass = [&](int c, int at, const u32x4_t (&xn)[2], float4 &fn, const cb_f32x4_t &rn, const u32x4_t (&xo)[2], const float4 &fo, int ybuf) __attribute__((always_inline)) {
             if (!OUT) {
                 stage_x(c + 2, at, xn, fn, rn);
                 return;
             }
-            const unsigned char *q = s_y + ybuf * 2 * YB;
-            float4 v[2][4];
+            const unsigned char *q = s_y + ybuf * YB;
+            float4 v[2][2];
 #pragma unroll
             for (int m = 0; m < 2; ++m) {
                 v[m][0] = *reinterpret_cast<const float4 *>(q + ya0 + m * 32 * 128 * PT);
-                v[m][1] = *reinterpret_cast<const float4 *>(q + YB + ya0 + m * 32 * 128 * PT);
-                v[m][2] = *reinterpret_cast<const float4 *>(q + ya1 + m * 32 * 128 * PT);
-                v[m][3] = *reinterpret_cast<const float4 *>(q + YB + ya1 + m * 32 * 128 * PT);
+                v[m][1] = *reinterpret_cast<const float4 *>(q + ya1 + m * 32 * 128 * PT);
             }
             stage_x(c + 2, at, xn, fn, rn);
-            float r[2][8];
+            const auto yrows = rows(y, c > c_begin ? c - 1 : nsteps);    // no step in front of the first
 #pragma unroll
-            for (int m = 0; m < 2; ++m)
-#pragma unroll
-                for (int k = 0; k < 2; ++k) {
-                    r[m][4 * k + 0] = (v[m][2 * k].x + v[m][2 * k + 1].x) * fo[m].y;
-                    r[m][4 * k + 1] = (v[m][2 * k].y + v[m][2 * k + 1].y) * fo[m].y;
-                    r[m][4 * k + 2] = (v[m][2 * k].z + v[m][2 * k + 1].z) * fo[m].y;
-                    r[m][4 * k + 3] = (v[m][2 * k].w + v[m][2 * k + 1].w) * fo[m].y;
-                }
-            if (skip) {
-#pragma unroll
-                for (int m = 0; m < 2; ++m) {
+            for (int m = 0; m < 2; ++m) {
+                const float e = m ? fo.w : fo.y;
+                float r[8] = {v[m][0].x * e, v[m][0].y * e, v[m][0].z * e, v[m][0].w * e, v[m][1].x * e, v[m][1].y * e, v[m][1].z * e, v[m][1].w * e};
+                if (skip) {
                     float a[8];
-                    unpack8(a, xo[m]);
+                    unpack(a, xo[m]);
 #pragma unroll
-                    for (int k = 0; k < 8; ++k) r[m][k] += dsk * a[k];
+                    for (int k = 0; k < 8; ++k) r[k] += dsk * a[k];
                 }
-            }
-            if (c > c_begin) {
-                const int left = t_end - (c - 1) * CB_STEP;
-                if (left >= CB_STEP) {
-                    if (xin) {
-                        store_nt(yq + xoff[0], pack8(r[0]));
-                        store_nt(yq + xoff[1], pack8(r[1]));
-                    }
-                } else {
-#pragma unroll
-                    for (int m = 0; m < 2; ++m)
-                        if (xin && xj0 + 32 * m < left) store_nt(yq + xoff[m], pack8(r[m]));
-                }
-                yq += CB_STEP * trow;
+                const uint4 o = pack8(r);
+                __builtin_amdgcn_raw_buffer_store_b128(u32x4_t{o.x, o.y, o.z, o.w}, yrows, yoff[m], 0, 2);
             }
         };
-        // x of step k in xr[(k - c_begin) % CB_RING]: loaded CB_RING - 4 steps before it is staged, kept until its y goes out
-        uint4 xr[CB_RING][2];
-        float2 fr[CB_RING][2];
-        // what all lanes take of a step comes through the scalar cache, three steps ahead
+        // x of step k in xr[(k - c_begin) % CB_RING]: loaded CB_RING - 3 steps before it is staged, kept until its y goes out
+        u32x4_t xr[CB_RING][2];
+        float4 fr[CB_RING];
+        // what all lanes take of a step comes through the scalar cache
         const cb_scalar_f32x2_t *refs = (const cb_scalar_f32x2_t *)tb.ref + bhs, *mags = (const cb_scalar_f32x2_t *)tb.mag + (int64_t)b * nsteps * s.G + g;
         auto load_ref = [&](int c) __attribute__((always_inline)) -> cb_f32x4_t {
             c = min(c, c_end - 1);
@@ -880,15 +939,15 @@ chain_bf16_kernel(const uint16_t *__restrict__ x, const float *__restrict__ D, c
         const cb_f32x4_t first = load_ref(c_begin), second = load_ref(c_begin + 1);
         cb_f32x4_t after = load_ref(c_begin + 2);
 #pragma unroll
-        for (int u = 0; u < CB_RING - 1; ++u) load_x(xr[u], fr[u]);
+        for (int u = 0; u < CB_RING - 1; ++u) load_x(xr[u], fr[u], c_begin + u);
         put_ref(0, first);
         put_ref(1, second);
         stage_x(c_begin, 0, xr[0], fr[0], first);
         lds_barrier();                                   // x of the first step
         // a step that the compute waves turn direct: its factor of y, and the barrier in turn_direct
-        auto turned = [&](float2 (&fe)[2]) __attribute__((always_inline)) {
-#pragma unroll
-            for (int m = 0; m < 2; ++m) fe[m].y = ldexpf(fe[m].y, -exponent(fe[m].y));
+        auto turned = [&](float4 &fe) __attribute__((always_inline)) {
+            fe.y = ldexpf(fe.y, -exponent(fe.y));
+            fe.w = ldexpf(fe.w, -exponent(fe.w));
             lds_barrier();
         };
         if (__builtin_expect(flagged(s_ref[0].w), 0)) turned(fr[0]);
@@ -899,11 +958,12 @@ chain_bf16_kernel(const uint16_t *__restrict__ x, const float *__restrict__ D, c
                 const int c = c0 + u, n1 = (u + 1) % CB_RING, n2 = (u + 2) % CB_RING, o = (u + CB_RING - 1) % CB_RING;
                 lds_barrier();
                 const int next = s_ref[(u + 1) % 3].w;
+                const cb_f32x4_t later = load_ref(c + 3);
                 pass(c, (u + 2) % 3, xr[n2], fr[n2], after, xr[o], fr[o], (u + 1) & 1);
                 if (c >= c_end) return;
                 put_ref((u + 2) % 3, after);
-                after = load_ref(c + 3);
-                load_x(xr[o], fr[o]);
+                load_x(xr[o], fr[o], c + CB_RING - 1);
+                after = later;
                 if (__builtin_expect(flagged(next), 0)) turned(fr[n1]);
             }
         }
@@ -1010,37 +1070,41 @@ static swimba_status launch_walk_t(const Shape &s, const void *x, const float *D
                                    const ChainScratch &scr, bool skip, hipStream_t st)
 {
     const int ncu = std::max(device_cus(), 1);
-    auto chain_shm = [](int PT, bool out) { return (size_t)(out ? 14 : 3) * CB_STEP * 64 * PT + 48 + (out ? 12 * CB_STEP : 0); };
+    auto chain_shm = [](int PT, bool out) { return (size_t)(out ? 10 + NT : 3) * CB_STEP * 64 * PT + 48 + (out ? 12 * CB_STEP : 0); };
     static std::atomic<uint64_t> done{0};
-    const swimba_status ok = allow_lds(done, {{(const void *)chain_bf16_kernel<NT, 1, true>, chain_shm(1, true)},
-                                              {(const void *)chain_bf16_kernel<NT, 2, true>, chain_shm(2, true)}});
+    const swimba_status ok = allow_lds(done, {{(const void *)chain_bf16_kernel<NT, 1, 2>, chain_shm(1, true)},
+                                              {(const void *)chain_bf16_kernel<NT, 1, 4>, chain_shm(1, true)},
+                                              {(const void *)chain_bf16_kernel<NT, 2, 4>, chain_shm(2, true)}});
     if (ok != SWIMBA_OK) return ok;
     ChainPlan plan = chain_plan(s, scr, skip, ncu);
     ChainPieces &pieces = plan.pieces;
     const size_t unit = chain_piece_bytes(s);
     int hblock = std::min(s.H, 8);
     while (s.H % hblock) --hblock;
-    // Both channel tiles of a head in one workgroup (one to a compute unit) where the heads fill at least three fifths of
-    // their rounds; else a workgroup per tile, two to a unit.
-    auto launch = [&](auto out_, int count, int steps) {
-        constexpr bool OUT = decltype(out_)::value;
+    // Workgroups of one channel tile where all of them find a compute unit at once; else of both tiles of a head, one to a unit,
+    // where the heads fill one round or three fifths of several; else (300 heads of 1024 tokens 45 / 48 us with both tiles in
+    // one), and for more heads of one tile than units (320 of 512 tokens, P = 64, N = 64: 29 / 38), of fewer waves, two to a unit.
+    auto launch = [&](bool out, int count, int steps) {
         const int64_t chains = (int64_t)s.B * s.H * count, rounds = (chains + ncu - 1) / ncu;
-        const int PT = s.P > 32 && 10 * chains >= 6 * rounds * ncu ? 2 : 1;
+        const int PT = s.P > 32 && 2 * chains > ncu && (rounds == 1 || 10 * chains >= 6 * rounds * ncu) ? 2 : 1;
+        const int CW = !out ? 0 : PT == 1 && chains * ((s.P + 31) / 32) > ncu ? 2 : 4;
         const int nslice = (s.P + 32 * PT - 1) / (32 * PT);
         const int total = (int)chains * nslice, nblocks = xcd_padded(total);
-        hipLaunchKernelGGL((PT == 2 ? chain_bf16_kernel<NT, 2, OUT> : chain_bf16_kernel<NT, 1, OUT>), dim3(nblocks), dim3(256 * PT),
-                           chain_shm(PT, OUT), st, (const uint16_t *)x, D, (const uint16_t *)scr.ops, chain_tables(s, scr), h0, h_final,
-                           (uint16_t *)y, s, plan.nsteps, nslice, count, steps, OUT ? s.H : hblock, pieces, total, nblocks);
+        const auto kernel = PT == 2 ? (out ? chain_bf16_kernel<NT, 2, 4> : chain_bf16_kernel<NT, 2, 0>)
+                                    : CW == 4 ? chain_bf16_kernel<NT, 1, 4> : CW == 2 ? chain_bf16_kernel<NT, 1, 2> : chain_bf16_kernel<NT, 1, 0>;
+        hipLaunchKernelGGL(kernel, dim3(nblocks), dim3(cb_threads(PT, CW)), chain_shm(PT, out), st, (const uint16_t *)x, D,
+                           (const uint16_t *)scr.ops, chain_tables(s, scr), h0, h_final, (uint16_t *)y, s, plan.nsteps, nslice, count, steps,
+                           out ? s.H : hblock, pieces, total, nblocks);
     };
     if (plan.nseg > 1) {
         // with the final state written over the initial one the first segment can start after the last one has ended
         if (h0 && h0 == h_final)
             pieces.h0_copy = pieces.npiece < pieces.n_a ? scr.a + pieces.npiece * (unit / 4) : scr.b + (pieces.npiece - pieces.n_a) * (unit / 4);
-        launch(std::false_type{}, pieces.npiece, pieces.steps);
+        launch(false, pieces.npiece, pieces.steps);
         SWIMBA_CHECK_LAUNCH();
         if (pieces.h0_copy) h0 = pieces.h0_copy;
     }
-    launch(std::true_type{}, plan.nseg, plan.steps_per_seg);
+    launch(true, plan.nseg, plan.steps_per_seg);
     SWIMBA_CHECK_LAUNCH();
     return SWIMBA_OK;
 }

@@ -29,6 +29,11 @@ CASES = [
     (2, 333, 4, 64, 128, 2, 5, 2, True, True, 40.0),      # mostly direct
     (1, 190, 160, 64, 128, 2, 5, 2, True, True, 10.0),    # all three
     (2, 333, 4, 64, 48, 2, 5, 2, True, True, 1e-3),
+    (2, 200, 160, 32, 72, 2, 4, 2, True, True, 4.0),      # 320 chains of one channel tile: two workgroups to a unit
+    (3, 130, 96, 16, 128, 1, 4, 2, True, False, 40.0),    # the same, mostly direct
+    (4, 67, 128, 24, 32, 4, 4, 1, False, True, 1.0),
+    (2, 130, 64, 64, 128, 1, 4, 2, True, True, 10.0),     # 128 chains: a workgroup per channel tile on every unit
+    (1, 130, 129, 64, 128, 1, 4, 2, True, True, 10.0),    # one more: both tiles in one
 ]
 
 
