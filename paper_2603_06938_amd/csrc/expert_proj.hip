@@ -90,33 +90,48 @@ __device__ __forceinline__ uint32_t pj_pack(float lo, float hi)
 
 // Workgroup = (share of one expert's list, block of 256 output columns), 8 waves: wave w owns
 // columns 64 (w & 3) .. + 63 of the block and one of two row groups.  The `nslots` workgroups
-// that fit on the chip at once (one per compute unit) are divided among the experts in
-// proportion to their list lengths (known on the device only), and a workgroup walks its share
-// in passes of up to 256 entries (2 to 4 row tiles of 32 per row group, one code path each): the
-// whole launch is one round of co-resident workgroups, whatever the routing.  The contraction
-// runs in stages of 64 features: both operands (256 weight rows, 64 per row tile of a group of
-// token rows, 128 bytes each) are read with fully coalesced 16-byte loads (8 lanes per row),
-// parked in registers while earlier stages are multiplied, and passed through one of two LDS
-// buffers, from where the lanes read their operand registers: one barrier a stage.
-// Against one code path of three row tiles per group, one LDS buffer and shares spread over the
-// XCDs: 8192 tokens x 1792 columns (130M-shaped layer with input streams) 86 -> 75 us, the whole
-// call 171 -> 164, of which the shares' place on the XCDs is 5; 16384 tokens x 256 columns 31 -> 30.
-// What is left there (us, 75 / 30): without the MFMAs and operand reads 45 / 19, without the writes
-// of a stage into LDS 50 / 20, without the stores of the results 60 / 25; the loads are hidden.
-// LDS is busy a quarter of the time, so its waits and the stages' order count, not its rate: the
-// barrier moved between the k-steps of a stage measured the same (75.6 / 31), results through LDS
-// to store whole lines worse (79 / 34).
+// that fit on the chip at once (one per compute unit) are divided among the experts by tiles of 32
+// entries (list lengths are known on the device only), and a workgroup walks its share in passes of
+// up to 256 entries (2 to 4 row tiles per row group, one code path each).  The contraction runs in
+// stages of 64 features: 256 weight rows and the pass's token rows, 128 bytes each, go from memory
+// straight into one of the LDS buffers (1 KB an instruction, 8 rows), a stage or, where three buffers
+// fit, two ahead, and from there into the lanes' operand registers: one barrier a stage.  A row's
+// 16-byte pieces lie exclusive-or'ed with half its number, so that the 16 rows that 16 lanes read lie
+// in different banks (with the number itself every read took twice as long).
+// Against the same stages through registers and padded LDS rows, and shares by rounded-down counts: 8192 tokens x 1792 columns
+// (130M-shaped layer with input streams) 78 -> 62 us, 16384 tokens x 256 columns 30 -> 26.  What is left there (us, 62 / 26):
+// without the MFMAs 46 / 19, without the stores of the results 51 / 20, without the copies 57 / 22; 2.3 until a workgroup has its
+// share.  Worse: all copies of a stage in front of its MFMAs (64 / 29), one behind each pair of MFMAs (66 / 31), the first wait
+// of a pass that counts the stores in front of it (64 / 26).
 constexpr int PJ_THREADS = 512;
 constexpr int PJ_KT = 64;             // features per stage
-constexpr int PJ_STR = PJ_KT + 8;     // LDS row stride (elements): rows stay 16-byte aligned
+constexpr int PJ_ROW = 2 * PJ_KT;     // bytes of a row in LDS
 constexpr int PJ_MAX_RT = 4;          // row tiles (of 32 list entries) per wave and pass
-constexpr int PJ_BUF = (PJ_COLS + 64 * PJ_MAX_RT) * PJ_STR;   // elements of an LDS buffer
-constexpr size_t PJ_SHM = 2 * PJ_BUF * sizeof(uint16_t);
+constexpr int PJ_WBYTES = PJ_COLS * PJ_ROW;
+constexpr int pj_buf(int RT) { return PJ_WBYTES + 64 * RT * PJ_ROW; }
+constexpr int pj_nbuf(int RT) { return RT == 2 ? 3 : 2; }
+constexpr size_t PJ_SHM = 3 * pj_buf(2);
+static_assert(PJ_SHM >= 2 * pj_buf(3) && PJ_SHM >= 2 * pj_buf(4), "LDS of the widest pass");
 
-// workgroups expert e gets out of nslots, given its list length
-__device__ __forceinline__ int proj_share(int cnt, int nslots, int64_t total)
+// 16 bytes a lane from memory to LDS byte address lds (uniform) + 16 lane.  The compiler does not see these loads: it keeps its
+// own waits exact or longer, and pj_wait waits for them.
+__device__ __forceinline__ void pj_copy(uint32_t lds, const void *base, uint32_t off)
 {
-    return cnt > 0 ? max(1, (int)((int64_t)nslots * cnt / total)) : 0;
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" :: "s"(__builtin_amdgcn_readfirstlane(lds)), "v"(off), "s"(base) : "memory");
+}
+__device__ __forceinline__ void pj_copy(uint32_t lds, const void *p)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" :: "s"(__builtin_amdgcn_readfirstlane(lds)), "v"(p) : "memory");
+}
+// until at most n vector memory operations of the wave are outstanding
+template <int n> __device__ __forceinline__ void pj_wait() { __builtin_amdgcn_s_waitcnt(0x0f70 | (n & 15) | (n >> 4) << 14); }
+
+// sum over the 64 lanes
+__device__ __forceinline__ int pj_wave_sum(int v)
+{
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) v += __shfl_xor(v, d);
+    return v;
 }
 
 __global__ void __launch_bounds__(PJ_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
@@ -124,36 +139,44 @@ proj_mfma_kernel(const uint16_t *__restrict__ u, ProjBlocks pb, const int32_t *_
                  const int32_t *__restrict__ lists, int64_t tokens, int E, int K, int Dm, int nslots,
                  int colblocks, int compact)
 {
-    extern __shared__ __align__(16) uint16_t s_buf[];        // [2] weight rows, then token rows
-    __shared__ int32_t s_share[SWIMBA_MAX_EXPERTS];
-    __shared__ int32_t s_sel[3];
+    extern __shared__ __align__(16) unsigned char s_buf[];   // weight rows, then token rows of each buffer
+    __shared__ int32_t s_sel[4];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int64_t total = tokens * K;
 
-    // ---- which expert, which part of its list: prefix sum of the shares (E <= 256 = 4 per lane) ----
+    // ---- which expert, which part of its list (E <= 256 = 4 per lane) ----
+    // Every workgroup gets the same number of tiles or less: the smallest even number, from the average on, with which the
+    // shares fit nslots.  Where that is not found (few slots an expert) there are up to E more shares, in a second round.
     // Workgroups of one XCD (ids equal mod 8) take neighbouring shares with all their column blocks, so
     // that its L2 holds the weights of about one expert and the token rows are read into it once.
-    if (tid < SWIMBA_MAX_EXPERTS) s_share[tid] = tid < E ? proj_share(counts[tid], nslots, total) : 0;
     if (tid == 0) s_sel[0] = -1;
     __syncthreads();
     if (wave == 0) {
-        int v[4], sum = 0;
+        int tiles[4], sum = 0, v[4];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) { v[q] = s_share[4 * lane + q]; sum += v[q]; }
+        for (int q = 0; q < 4; ++q) { tiles[q] = 4 * lane + q < E ? (counts[4 * lane + q] + 31) / 32 : 0; sum += tiles[q]; }
+        const int all = pj_wave_sum(sum);
+        int per = max(2, 2 * ((all + 2 * nslots - 1) / (2 * nslots)));
+        for (int tries = 0;; ++tries) {
+            sum = 0;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) { v[q] = (tiles[q] + per - 1) / per; sum += v[q]; }
+            if (tries == 6 || pj_wave_sum(sum) <= nslots) break;
+            per += max(2, per / 16 * 2);
+        }
         int incl = sum;
 #pragma unroll
         for (int d = 1; d < 64; d <<= 1) {
             const int t = __shfl_up(incl, d);
             if (lane >= d) incl += t;
         }
-        const int used = __builtin_amdgcn_readlane(incl, 63) * colblocks, per = (used + 7) / 8;
-        const int j = (int)blockIdx.x >> 3, lid = ((int)blockIdx.x & 7) * per + j;
+        const int used = __builtin_amdgcn_readlane(incl, 63) * colblocks, each = (used + 7) / 8;
+        const int j = (int)blockIdx.x >> 3, lid = ((int)blockIdx.x & 7) * each + j;
         int r = lid / colblocks - (incl - sum);
-        if (j < per && lid < used && r >= 0 && r < sum) {
+        if (j < each && lid < used && r >= 0 && r < sum) {
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                if (r >= 0 && r < v[q]) { s_sel[0] = 4 * lane + q; s_sel[1] = r; s_sel[2] = lid % colblocks; }
+                if (r >= 0 && r < v[q]) { s_sel[0] = 4 * lane + q; s_sel[1] = r; s_sel[2] = lid % colblocks; s_sel[3] = v[q]; }
                 r -= v[q];          // negative from the match on: no later q matches
             }
         }
@@ -161,9 +184,8 @@ proj_mfma_kernel(const uint16_t *__restrict__ u, ProjBlocks pb, const int32_t *_
     __syncthreads();
     const int e = __builtin_amdgcn_readfirstlane(s_sel[0]);
     if (e < 0) return;                                       // whole workgroup: no barrier is skipped
-    const int part = __builtin_amdgcn_readfirstlane(s_sel[1]);
+    const int part = __builtin_amdgcn_readfirstlane(s_sel[1]), nparts = __builtin_amdgcn_readfirstlane(s_sel[3]);
     const int cnt = counts[e];
-    const int nparts = proj_share(cnt, nslots, total);
     const int n32 = (cnt + 31) / 32;
     const int t_begin = (int)((int64_t)part * n32 / nparts), t_end = (int)((int64_t)(part + 1) * n32 / nparts);
     const int nt = t_end - t_begin;
@@ -176,152 +198,170 @@ proj_mfma_kernel(const uint16_t *__restrict__ u, ProjBlocks pb, const int32_t *_
     const bool active = col0 < pb.tot;                       // wave-uniform; idle waves still stage
     const int l32 = lane & 31, kg = lane >> 5;
 
-    // ---- staging map: lane -> 16-byte piece `piece` of rows row0 + 64 i ----
-    const int piece = tid & 7, row0 = tid >> 3;              // row0 = 32 rg + (row inside a 32-block)
-    // Every block has a multiple of 32 columns, so the 32 rows of a staging step of one wave lie in
-    // one weight tensor: a uniform base (scalar registers) + one per-lane offset for all four.
-    const uint16_t *wbase[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    // ---- staging map: a wave copies 8 rows an instruction, lane -> piece pieces[row / 8 % 2] of row r8 of them ----
+    const int r8 = lane >> 3, pieces[2] = {(lane & 7) ^ (r8 >> 1), (lane & 7) ^ (4 + (r8 >> 1))};
+    // A wave stages the 32 rows of one column tile, which lie in one weight tensor: a uniform base and a per-lane offset.
+    // Operand row r of a tile must hold column 16*((r>>2)&1) + 4*(r>>3) + (r&3) for accumulator register v of lane (l32, kg)
+    // to be column 16 kg + v of the tile: row 8 i + r8 is 4 i more than the lane's first.
+    const char *wbase;
+    {
         int cl;
-        const int sb = proj_block_of(pb, min(colblk + 64 * i + 32 * rg, pb.tot - 32), cl);   // past the end: the last rows again
-        wbase[i] = (const uint16_t *)pb.W[sb] + ((int64_t)e * pb.n[sb] + cl) * Dm;
+        const int sb = proj_block_of(pb, min(colblk + 32 * wave, pb.tot - 32), cl);   // past the end: the last rows again
+        wbase = (const char *)((const uint16_t *)pb.W[sb] + ((int64_t)e * pb.n[sb] + cl) * Dm);
     }
-    const int r32 = row0 & 31;
-    const int wlane = r32 * Dm;
-    const int k_last = ((Dm - 1) / PJ_KT) * PJ_KT;
-    // Operand row r of a 32-column weight tile must hold column 16*((r>>2)&1) + 4*(r>>3) + (r&3)
-    // for accumulator register v of lane (l32, kg) to be column 16 kg + v of the tile.  The
-    // permutation is applied when the rows are staged (column x goes to LDS row wrow), so the
-    // lanes of a wave read consecutive LDS rows: no bank conflicts.
-    const int wrow = 8 * ((r32 >> 2) & 3) + 4 * ((r32 >> 4) & 1) + (r32 & 3) + 32 * rg;
-    const int wr_at = wrow * PJ_STR + piece * 8, ur_at = (PJ_COLS + row0) * PJ_STR + piece * 8;
-    const int a_at = (cw * 64 + l32) * PJ_STR + 8 * kg;
+    const uint32_t wlane = (uint32_t)(16 * (r8 >> 2) + (r8 & 3)) * Dm * 2;
+    const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)s_buf);
+    const int stages = (Dm + PJ_KT - 1) / PJ_KT;
+    const int xo = kg ^ ((l32 >> 1) & 7);                           // of k-step s: pieces (2 s) ^ xo
     int cc;                                                  // column inside the row of the wave's block
     const int ob = proj_block_of(pb, min(col0, pb.tot - 64), cc);
     uint16_t *out = (uint16_t *)pb.out[ob];
     const int ncol = pb.n[ob];                               // row length of that output
+    const int32_t *list = lists + (int64_t)e * tokens;
 
-    // entries [32 p_begin, 32 p_end) of the list, at most 2 RT tiles.  SETS: stages parked in registers.
-    auto run_pass = [&](auto rt_, auto sets_, int p_begin, int p_end) __attribute__((always_inline)) {
-        constexpr int RT = decltype(rt_)::value, SETS = decltype(sets_)::value;
-        const int ptiles = p_end - p_begin;
-        const int half = (ptiles + 1) / 2;
-        const int tbase = rg ? half : 0;                                 // first tile of this wave's row group
-        const int nrt = rg ? ptiles - half : half;                       // its tiles, wave-uniform
-        const int nvalid = min(32 * p_end, cnt) - 32 * p_begin;          // entries of this pass
-        const int32_t *lst = lists + (int64_t)e * tokens + 32 * p_begin;
-        const uint16_t *usrc[RT];
+    auto run = [&](auto rt_) __attribute__((always_inline)) {
+        constexpr int RT = decltype(rt_)::value, BUF = pj_buf(RT), NBUF = pj_nbuf(RT), LOADS = 4 + RT;
+        auto first_tile = [&](int pass) __attribute__((always_inline)) { return t_begin + (int)((int64_t)pass * nt / npass); };
+        // the list entries whose token rows the lane copies
+        auto entries = [&](int32_t (&row)[RT], int pass) __attribute__((always_inline)) {
+            const int begin = 32 * first_tile(pass), last = min(32 * first_tile(pass + 1), cnt) - 1;
 #pragma unroll
-        for (int i = 0; i < RT; ++i) usrc[i] = u + (int64_t)(lst[min(row0 + 64 * i, nvalid - 1)] / K) * Dm;
-        const int b_at = (PJ_COLS + 32 * tbase + l32) * PJ_STR + 8 * kg;
-        // All loads are clamped and unconditional, so that the waits on them stay exact counts;
-        // the issues past the last stage re-read it and are not used.
-        uint4 wreg[SETS][4], ureg[SETS][RT];
-        auto load = [&](uint4 (&wr)[4], uint4 (&ur)[RT], int k0) __attribute__((always_inline)) {
-            const int kk = min(min(k0, k_last) + piece * 8, Dm - 8);   // a short last stage stays inside the row
-#pragma unroll
-            for (int i = 0; i < 4; ++i) wr[i] = *reinterpret_cast<const uint4 *>(wbase[i] + (wlane + kk));
-#pragma unroll
-            for (int i = 0; i < RT; ++i) ur[i] = *reinterpret_cast<const uint4 *>(usrc[i] + kk);
+            for (int i = 0; i < RT; ++i) row[i] = list[min(begin + 8 * (RT * wave + i) + r8, last)];
         };
-        // registers -> LDS; pieces past the end of a short last stage as zeros: every stage is 4 k-steps
-        auto put = [&](uint16_t *buf, const uint4 (&wr)[4], const uint4 (&ur)[RT], int k0) __attribute__((always_inline)) {
-            const uint32_t m = k0 + piece * 8 < Dm ? ~0u : 0u;
+        int32_t row[RT], next_row[RT];
+        int slot = 0;                                        // buffer of the next stage to be copied
+        auto copy_weights = [&](int st) __attribute__((always_inline)) {
+            uint32_t at_piece[2];
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-                *reinterpret_cast<uint4 *>(buf + wr_at + 64 * i * PJ_STR) = make_uint4(wr[i].x & m, wr[i].y & m, wr[i].z & m, wr[i].w & m);
+            for (int i = 0; i < 2; ++i) at_piece[i] = wlane + 2 * min(st * PJ_KT + pieces[i] * 8, Dm - 8);   // a short last stage stays inside the row
+            const uint32_t at = lds0 + slot * BUF + wave * (32 * PJ_ROW);
 #pragma unroll
-            for (int i = 0; i < RT; ++i)
-                *reinterpret_cast<uint4 *>(buf + ur_at + 64 * i * PJ_STR) = make_uint4(ur[i].x & m, ur[i].y & m, ur[i].z & m, ur[i].w & m);
+            for (int i = 0; i < 4; ++i) pj_copy(at + i * 8 * PJ_ROW, wbase + (int64_t)i * 8 * Dm, at_piece[i & 1]);
         };
-        pj_f32x16_t acc[2][RT];
+        auto copy_tokens = [&](int st) __attribute__((always_inline)) {
+            const int odd = (RT * wave) & 1;                 // of the wave's first 8 rows
+            const uint16_t *from[2] = {u + min(st * PJ_KT + pieces[0] * 8, Dm - 8), u + min(st * PJ_KT + pieces[1] * 8, Dm - 8)};
+            const uint32_t at = lds0 + slot * BUF + PJ_WBYTES + wave * (8 * RT * PJ_ROW);
 #pragma unroll
-        for (int ct = 0; ct < 2; ++ct)
-#pragma unroll
-            for (int rt = 0; rt < RT; ++rt) acc[ct][rt] = pj_f32x16_t{0};
-        auto read_ops = [&](const uint16_t *buf, uint4 (&a)[2], uint4 (&b)[RT], int s4) __attribute__((always_inline)) {
-#pragma unroll
-            for (int q = 0; q < 2; ++q) a[q] = *reinterpret_cast<const uint4 *>(buf + a_at + 32 * q * PJ_STR + 16 * s4);
-#pragma unroll
-            for (int rt = 0; rt < RT; ++rt)
-                b[rt] = *reinterpret_cast<const uint4 *>(buf + b_at + 32 * rt * PJ_STR + 16 * s4);
+            for (int i = 0; i < RT; ++i) pj_copy(at + i * 8 * PJ_ROW, ((i + odd) & 1 ? from[1] : from[0]) + (int64_t)row[i] * Dm);
+            slot = slot == NBUF - 1 ? 0 : slot + 1;
         };
-        auto mfmas = [&](const uint4 (&a)[2], const uint4 (&b)[RT]) __attribute__((always_inline)) {
+        auto to_tokens = [&](int32_t (&row)[RT]) __attribute__((always_inline)) {
 #pragma unroll
-            for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-                for (int ct = 0; ct < 2; ++ct)
-                    acc[ct][rt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                        __builtin_bit_cast(pj_bf16x8_t, a[ct]), __builtin_bit_cast(pj_bf16x8_t, b[rt]),
-                        acc[ct][rt], 0, 0, 0);
+            for (int i = 0; i < RT; ++i) row[i] /= K;
         };
-        // One stage: multiply buf; the next one's rows go into other, behind the first MFMAs, and its registers are
-        // refilled.  The operands of k-step s + 1 are read from LDS before the MFMAs of k-step s are issued (two sets
-        // rotated by name).  All RT row tiles are multiplied whether the wave has that many or not (the rows are staged
-        // clamped, the epilogue skips them): a branch per row tile would make every pair of MFMAs wait for its own read.
-        auto stage = [&](const uint16_t *buf, uint16_t *other, uint4 (&wr)[4], uint4 (&ur)[RT], int k0) __attribute__((always_inline)) {
-            lds_barrier();                       // buf is written; every wave is done with other
-            uint4 a0[2], b0[RT], a1[2], b1[RT];
-            read_ops(buf, a0, b0, 0);
-            read_ops(buf, a1, b1, 1);
-            __builtin_amdgcn_sched_barrier(0);
-            mfmas(a0, b0);
-            __builtin_amdgcn_sched_barrier(0);
-            read_ops(buf, a0, b0, 2);
-            __builtin_amdgcn_sched_barrier(0);
-            put(other, wr, ur, k0 + PJ_KT);
-            load(wr, ur, k0 + (1 + SETS) * PJ_KT);
-            __builtin_amdgcn_sched_barrier(0);
-            mfmas(a1, b1);
-            __builtin_amdgcn_sched_barrier(0);
-            read_ops(buf, a1, b1, 3);
-            __builtin_amdgcn_sched_barrier(0);
-            mfmas(a0, b0);
-            mfmas(a1, b1);
-        };
-        // prologue in the order the loop consumes (scheduling barriers keep the issue order)
-        load(wreg[0], ureg[0], 0);
-        __builtin_amdgcn_sched_barrier(0);
-        if (SETS == 2) load(wreg[SETS - 1], ureg[SETS - 1], PJ_KT);
-        __builtin_amdgcn_sched_barrier(0);
-        lds_barrier();                           // every wave is done with the pass in front
-        put(s_buf, wreg[0], ureg[0], 0);
-        load(wreg[0], ureg[0], SETS * PJ_KT);
-        // pairs of stages (an odd count runs an all-zero one): no branch between the buffers and register sets
-        for (int k0 = 0; k0 < Dm; k0 += 2 * PJ_KT) {
-            stage(s_buf, s_buf + PJ_BUF, wreg[SETS - 1], ureg[SETS - 1], k0);
-            stage(s_buf + PJ_BUF, s_buf, wreg[0], ureg[0], k0 + PJ_KT);
-        }
-        if (!active) return;
+        entries(row, 0);
+        to_tokens(row);
 #pragma unroll
-        for (int rt = 0; rt < RT; ++rt) {
-            const int prow = 32 * (tbase + rt) + l32;                         // entry inside the pass
-            if (rt < nrt && prow < nvalid) {
-                const int64_t ent = lst[prow];                                // t*K + r
-                const int64_t row = compact ? ent : (ent / K) * E + e;
+        for (int st = 0; st < NBUF - 1; ++st)
+            if (st < stages) {
+                copy_weights(st);
+                copy_tokens(st);
+            }
+        int buf = 0;                                         // of the stage that is multiplied
+        for (int pass = 0; pass < npass; ++pass) {
+            const int begin = first_tile(pass), end = first_tile(pass + 1);
+            const int ptiles = end - begin, half = (ptiles + 1) / 2;
+            const int tbase = rg ? half : 0;                                 // first tile of this wave's row group
+            const int nrt = rg ? ptiles - half : half;                       // its tiles, wave-uniform
+            const bool more = pass + 1 < npass;
+            if (more) entries(next_row, pass + 1);
+            const unsigned char *a_at = s_buf + (cw * 64 + l32) * PJ_ROW, *b_at = s_buf + PJ_WBYTES + (32 * tbase + l32) * PJ_ROW;
+            pj_f32x16_t acc[2][RT];
 #pragma unroll
-                for (int ct = 0; ct < 2; ++ct) {
-                    uint16_t *dst = out + row * ncol + cc + 32 * ct + 16 * kg;
-                    const pj_f32x16_t v = acc[ct][rt];
-                    *reinterpret_cast<uint4 *>(dst) =
-                        make_uint4(pj_pack(v[0], v[1]), pj_pack(v[2], v[3]), pj_pack(v[4], v[5]), pj_pack(v[6], v[7]));
-                    *reinterpret_cast<uint4 *>(dst + 8) = make_uint4(pj_pack(v[8], v[9]), pj_pack(v[10], v[11]),
-                                                                     pj_pack(v[12], v[13]), pj_pack(v[14], v[15]));
+            for (int ct = 0; ct < 2; ++ct)
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt) acc[ct][rt] = pj_f32x16_t{0};
+            auto stage = [&](int st, auto whole_) __attribute__((always_inline)) {
+                // the next stage may be under way; behind a pass's results nothing is counted
+                if (NBUF == 3 && (st > 0 || pass == 0) && (st + 1 < stages || more)) pj_wait<LOADS>();
+                else pj_wait<0>();
+                lds_barrier();                               // the stage is in LDS; every wave is done with the one in front
+                const int at = buf * BUF;
+                uint4 a0[2], b0[RT], a1[2], b1[RT];
+                auto read_ops = [&](uint4 (&a)[2], uint4 (&b)[RT], int s4) __attribute__((always_inline)) {
+                    const int o = at + (((2 * s4) ^ xo) << 4);
+#pragma unroll
+                    for (int k = 0; k < 2; ++k) a[k] = *reinterpret_cast<const uint4 *>(a_at + o + 32 * k * PJ_ROW);
+#pragma unroll
+                    for (int rt = 0; rt < RT; ++rt) b[rt] = *reinterpret_cast<const uint4 *>(b_at + o + 32 * rt * PJ_ROW);
+                };
+                // All RT row tiles are multiplied whether the wave has that many or not (the rows are staged clamped, the
+                // epilogue skips them): a branch per row tile would make every pair of MFMAs wait for its own read.
+                auto mfmas = [&](const uint4 (&a)[2], const uint4 (&b)[RT]) __attribute__((always_inline)) {
+#pragma unroll
+                    for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                        for (int ct = 0; ct < 2; ++ct)
+                            acc[ct][rt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(pj_bf16x8_t, a[ct]),
+                                                                                  __builtin_bit_cast(pj_bf16x8_t, b[rt]), acc[ct][rt], 0, 0, 0);
+                };
+                const int ahead = st + NBUF - 1;
+                const bool copies = ahead < stages || more;
+                const int ast = ahead < stages ? ahead : ahead - stages;
+                if (ahead == stages && more) {
+#pragma unroll
+                    for (int i = 0; i < RT; ++i) row[i] = next_row[i];
+                    to_tokens(row);
+                }
+                if constexpr (decltype(whole_)::value) {
+                    read_ops(a0, b0, 0);
+                    read_ops(a1, b1, 1);
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (copies) copy_weights(ast);
+                    mfmas(a0, b0);
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (copies) copy_tokens(ast);
+                    read_ops(a0, b0, 2);
+                    __builtin_amdgcn_sched_barrier(0);
+                    mfmas(a1, b1);
+                    __builtin_amdgcn_sched_barrier(0);
+                    read_ops(a1, b1, 3);
+                    __builtin_amdgcn_sched_barrier(0);
+                    mfmas(a0, b0);
+                    mfmas(a1, b1);
+                } else {
+                    if (copies) {
+                        copy_weights(ast);
+                        copy_tokens(ast);
+                    }
+#pragma unroll 1
+                    for (int s4 = 0; s4 < (Dm - st * PJ_KT) / 16; ++s4) {
+                        read_ops(a0, b0, s4);
+                        mfmas(a0, b0);
+                    }
+                }
+                buf = buf == NBUF - 1 ? 0 : buf + 1;
+            };
+            int st = 0;
+            for (; st < Dm / PJ_KT; ++st) stage(st, std::true_type{});
+            if (st < stages) stage(st, std::false_type{});
+            if (active) {
+                const int nvalid = min(32 * end, cnt) - 32 * begin;          // entries of this pass
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt) {
+                    const int prow = 32 * (tbase + rt) + l32;                    // entry inside the pass
+                    if (rt < nrt && prow < nvalid) {
+                        const int64_t ent = list[32 * begin + prow];             // t*K + r
+                        const int64_t row = compact ? ent : (ent / K) * E + e;
+#pragma unroll
+                        for (int ct = 0; ct < 2; ++ct) {
+                            uint16_t *dst = out + row * ncol + cc + 32 * ct + 16 * kg;
+                            const pj_f32x16_t v = acc[ct][rt];
+                            *reinterpret_cast<uint4 *>(dst) =
+                                make_uint4(pj_pack(v[0], v[1]), pj_pack(v[2], v[3]), pj_pack(v[4], v[5]), pj_pack(v[6], v[7]));
+                            *reinterpret_cast<uint4 *>(dst + 8) = make_uint4(pj_pack(v[8], v[9]), pj_pack(v[10], v[11]),
+                                                                             pj_pack(v[12], v[13]), pj_pack(v[14], v[15]));
+                        }
+                    }
                 }
             }
         }
     };
-    for (int pass = 0; pass < npass; ++pass) {
-        const int p_begin = t_begin + (int)((int64_t)pass * nt / npass);
-        const int p_end = t_begin + (int)((int64_t)(pass + 1) * nt / npass);
-        if (p_end - p_begin <= 4)
-            run_pass(std::integral_constant<int, 2>{}, std::integral_constant<int, 2>{}, p_begin, p_end);
-        else if (p_end - p_begin <= 6)
-            run_pass(std::integral_constant<int, 3>{}, std::integral_constant<int, 2>{}, p_begin, p_end);
-        else
-            run_pass(std::integral_constant<int, 4>{}, std::integral_constant<int, 1>{}, p_begin, p_end);
-    }
+    const int widest = (nt + npass - 1) / npass;
+    if (widest <= 4) run(std::integral_constant<int, 2>{});
+    else if (widest <= 6) run(std::integral_constant<int, 3>{});
+    else run(std::integral_constant<int, 4>{});
 }
 
 // any shape, fp32 arithmetic: block = (token, slot), the token's features in LDS, one lane
@@ -401,7 +441,7 @@ swimba_status launch_expert_proj(int64_t tokens, int E, int K, int GN, int Dm, i
         if (he != hipSuccess) { set_last_hip_error((int)he); return SWIMBA_ERR_HIP; }
         attr_set.fetch_or(bit, std::memory_order_release);
     }
-    // the shares sum to at most nslots + E
+    // the shares sum to at most nslots + E: each but one of an expert has the average of tiles a slot or more
     const unsigned grid = (unsigned)(((int64_t)(nslots + E) * colblocks + 7) / 8 * 8);
     hipLaunchKernelGGL(proj_mfma_kernel, dim3(grid), dim3(PJ_THREADS), PJ_SHM, st, (const uint16_t *)u, pb, counts, lists,
                        tokens, E, K, Dm, nslots, colblocks, compact);

@@ -38,6 +38,10 @@ SHAPES = [
     (1, 70, 64, 16, 8, 128, 3, "bf16"),     # MFMA: 2048 output columns (8 column blocks), k = 3
     (1, 5, 32, 16, 1, 64, 2, "bf16"),       # MFMA: most experts receive no token
     (1, 256, 768, 8, 1, 128, 2, "bf16"),    # MFMA: a 130M-sized model width
+    (1, 6200, 144, 1, 8, 128, 1, "bf16"),   # MFMA: one pass of 8 tiles a workgroup
+    (1, 9001, 80, 2, 8, 128, 1, "bf16"),    # MFMA: passes of 5 tiles, two a workgroup
+    (1, 12000, 32, 1, 8, 128, 1, "bf16"),   # MFMA: the same in less than one stage of features
+    (1, 600, 64, 64, 8, 128, 2, "bf16"),    # MFMA: more experts than workgroups at once
 ]
 
 
