@@ -48,7 +48,9 @@ swimba_status launch_router(int64_t tokens, int E, int K, int io_dtype, const vo
 // + 1 + 1 shuffles instead of 6 per sum), and lane 2i ends up with sum i, which makes the store
 // of a token's 8 logits one contiguous piece.  fp32 accumulation.
 // (First version: one expert at a time, token rows re-read per expert, 6 shuffles per sum:
-// 27 us on the 130M-shaped layer against a 4.5 us floor; rows in registers: 21 us.)
+// 27 us on the 130M-shaped layer against a 4.5 us floor; rows in registers: 21 us.)  Registers for as many pieces of a row as
+// the width has and no more, so that 16384 tokens x 768 features are one round of waves: 12.7 -> 11.6 us.  At most three waves
+// to a SIMD: with four the compiler keeps fewer loads in flight (8192 tokens 8.4 us for 7.1, 16384 10.8).
 constexpr int RL_TOK = 4;
 constexpr int RL_EXP = 8;
 
@@ -76,8 +78,8 @@ __device__ __forceinline__ void rl_halve(float (&v)[RL_TOK * RL_EXP], int lane, 
     }
 }
 
-template <typename T, bool VEC, bool REG>
-__global__ void __launch_bounds__(256)
+template <typename T, bool VEC, int REG>                   // REG: 16-byte pieces a lane keeps of a token row, 0 for none
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 3)))
 router_linear_kernel(const T *__restrict__ u, const T *__restrict__ Wg, T *__restrict__ logits, int64_t tokens,
                      int Dm, int E)
 {
@@ -88,10 +90,10 @@ router_linear_kernel(const T *__restrict__ u, const T *__restrict__ Wg, T *__res
     const T *ur[RL_TOK];
 #pragma unroll
     for (int q = 0; q < RL_TOK; ++q) ur[q] = u + min(t0 + q, tokens - 1) * Dm;
-    uint4 ureg[REG ? 4 : 1][RL_TOK];
-    if constexpr (VEC && REG) {
+    uint4 ureg[REG ? REG : 1][RL_TOK];
+    if constexpr (VEC && REG > 0) {
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
+        for (int c = 0; c < REG; ++c) {
             const int d = min(lane * 8 + 512 * c, Dm - 8);         // clamped: unused past the row end
 #pragma unroll
             for (int q = 0; q < RL_TOK; ++q) ureg[c][q] = *reinterpret_cast<const uint4 *>(ur[q] + d);
@@ -120,9 +122,9 @@ router_linear_kernel(const T *__restrict__ u, const T *__restrict__ Wg, T *__res
                         for (int i = 0; i < 8; ++i) v[q * RL_EXP + el] += wf[i] * uf[q][i];
                 }
             };
-            if constexpr (REG) {
+            if constexpr (REG > 0) {
 #pragma unroll
-                for (int c = 0; c < 4; ++c) {
+                for (int c = 0; c < REG; ++c) {
                     const int d = lane * 8 + 512 * c;
                     if (d < Dm) chunk(d, ureg[c]);
                 }
@@ -166,17 +168,12 @@ swimba_status launch_router_linear(int64_t tokens, int Dm, int E, int io_dtype, 
     const int64_t waves = (tokens + RL_TOK - 1) / RL_TOK;
     const unsigned grid = (unsigned)((waves + 3) / 4);
     if (io_dtype == SWIMBA_BF16) {
-        if (Dm % 8 == 0 && Dm <= 2048)
-            hipLaunchKernelGGL((router_linear_kernel<bf16, true, true>), dim3(grid), dim3(256), 0, st,
-                               (const bf16 *)u, (const bf16 *)Wg, (bf16 *)logits, tokens, Dm, E);
-        else if (Dm % 8 == 0)
-            hipLaunchKernelGGL((router_linear_kernel<bf16, true, false>), dim3(grid), dim3(256), 0, st,
-                               (const bf16 *)u, (const bf16 *)Wg, (bf16 *)logits, tokens, Dm, E);
-        else
-            hipLaunchKernelGGL((router_linear_kernel<bf16, false, false>), dim3(grid), dim3(256), 0, st,
-                               (const bf16 *)u, (const bf16 *)Wg, (bf16 *)logits, tokens, Dm, E);
+        const auto kernel = Dm % 8 ? router_linear_kernel<bf16, false, 0> : Dm <= 512 ? router_linear_kernel<bf16, true, 1>
+                            : Dm <= 1024 ? router_linear_kernel<bf16, true, 2> : Dm <= 2048 ? router_linear_kernel<bf16, true, 4>
+                                                                                          : router_linear_kernel<bf16, true, 0>;
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), 0, st, (const bf16 *)u, (const bf16 *)Wg, (bf16 *)logits, tokens, Dm, E);
     } else {
-        hipLaunchKernelGGL((router_linear_kernel<float, false, false>), dim3(grid), dim3(256), 0, st,
+        hipLaunchKernelGGL((router_linear_kernel<float, false, 0>), dim3(grid), dim3(256), 0, st,
                            (const float *)u, (const float *)Wg, (float *)logits, tokens, Dm, E);
     }
     SWIMBA_CHECK_LAUNCH();
