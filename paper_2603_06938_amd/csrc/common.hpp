@@ -120,6 +120,10 @@ swimba_status launch_expert_proj(int64_t tokens, int E, int K, int GN, int Dm, i
                                  int32_t *idx, float *w, int32_t *counts, int32_t *lists, int compact,
                                  hipStream_t st, const void *WX = nullptr, void *Xo = nullptr, int HP = 0);
 bool expert_proj_on_mfma(int io_dtype, int GN, int HP, int Dm);
+constexpr int PJ_SEG_EXPERTS = 32;     // most experts whose lists come in segments
+constexpr int PJ_MAX_SEGS = 256;       // most segments of a list
+constexpr int PJ_COUNTS = PJ_SEG_EXPERTS * PJ_MAX_SEGS;      // list lengths: of every segment, or of every expert
+static_assert(PJ_COUNTS >= SWIMBA_MAX_EXPERTS, "room for one length an expert");
 swimba_status launch_slot_ids(int32_t *idx, int64_t tokens, int K, hipStream_t st);
 // expert-specific input streams (xe.hip)
 swimba_status launch_xe_gather(const Shape &s, int io_dtype, int slot, const void *x_experts,
@@ -207,9 +211,41 @@ __device__ __forceinline__ void lds_barrier()
 // relative error of |v| * 2^-24, far inside the 1e-5 the routing weights are held to)
 __device__ __forceinline__ float route_exp(float v) { return __builtin_amdgcn_exp2f(v * 1.4426950408889634f); }
 
+// The same for E <= EM experts, their logits in registers: a loop that loads one after the other waits for each.
+template <int EM, typename Load>
+__device__ __forceinline__ void route_few(Load load, int E, int K, int32_t *idx, float *w)
+{
+    float v[EM], m = -INFINITY, Z = 0.f;
+#pragma unroll
+    for (int e = 0; e < EM; ++e) v[e] = load(min(e, E - 1));
+#pragma unroll
+    for (int e = 0; e < EM; ++e) m = fmaxf(m, v[e]);
+#pragma unroll
+    for (int e = 0; e < EM; ++e) Z += e < E ? route_exp(v[e] - m) : 0.f;
+    const float invZ = 1.0f / Z;
+    float pv = 0.f;
+    int pi = -1;
+    for (int r = 0; r < K; ++r) {
+        int best = -1;
+        float bv = 0.f;
+#pragma unroll
+        for (int e = 0; e < EM; ++e) {
+            const bool after = (r == 0) || (v[e] < pv) || (v[e] == pv && e > pi);
+            if (e < E && after && (best < 0 || v[e] > bv)) { best = e; bv = v[e]; }
+        }
+        if (best < 0) { best = (pi + 1) % E; bv = -INFINITY; }
+        idx[r] = best;
+        w[r] = route_exp(bv - m) * invZ;
+        pv = bv;
+        pi = best;
+    }
+}
+
 template <typename Load>
 __device__ __forceinline__ void route_token(Load load, int E, int K, int32_t *idx, float *w)
 {
+    if (E <= 8) return route_few<8>(load, E, K, idx, w);
+    if (E <= 16) return route_few<16>(load, E, K, idx, w);
     float m = -INFINITY;
     for (int e = 0; e < E; ++e) m = fmaxf(m, load(e));
     float Z = 0.f;

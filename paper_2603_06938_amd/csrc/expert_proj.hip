@@ -10,9 +10,8 @@
 //   x_t^(e)[c] = sum_d W_X[e][c][d] u_t[d],  c over (head, channel),
 // written the same way into (B,L,E,H,P) or (B,L,k,H,P).
 //
-// Three launches: clear the per-expert counters; route every token and append the entry
-// t*k + r to the list of its r-th expert (LDS counters per block, one global atomic per block
-// and expert); a grouped GEMM over (share of an expert's list, 256 output columns).
+// Two launches: route every token and append the entry t*k + r to the list of its r-th expert; a
+// grouped GEMM over (share of an expert's list, 256 output columns).
 // The GEMM is a dense contraction, so it runs on v_mfma_f32_32x32x16_bf16.  Both operands
 // are stored with the contraction index d contiguous (weights as (out, in), like a linear
 // layer), which is the 8-consecutive-k operand layout.  The product is computed transposed,
@@ -53,7 +52,45 @@ __global__ void proj_clear_kernel(int32_t *counts, int E)
     for (int e = threadIdx.x; e < E; e += blockDim.x) counts[e] = 0;
 }
 
-// one token per lane: top-k routing, then one list entry per active expert
+// Lists of the experts' entries t*k + r, in segments: block b of the routing (tb tokens) has the tb places from b*tb on of every
+// expert's list and says in counts[e][b] how many it filled, so nothing has to be cleared and no block waits for another.
+// One token per lane.  The logits of 256 tokens go through LDS: the routing reads them K + 2 times, one after the other.
+template <typename T>
+__global__ void __launch_bounds__(256)
+proj_route_segments_kernel(const T *__restrict__ logits, int32_t *__restrict__ idx, float *__restrict__ w,
+                           int32_t *__restrict__ counts, int32_t *__restrict__ lists, int64_t tokens, int E, int K, int tb)
+{
+    __shared__ int32_t s_cnt[PJ_SEG_EXPERTS];
+    extern __shared__ int32_t s_dyn[];
+    int32_t *s_idx = s_dyn;                                  // [256][K]
+    float *s_w = reinterpret_cast<float *>(s_idx + 256 * K); // [256][K]
+    float *s_l = s_w + 256 * K;                              // [256][E | 1]
+    const int tid = threadIdx.x;
+    const int64_t begin = (int64_t)blockIdx.x * tb, end = min(begin + tb, tokens);
+    if (tid < E) s_cnt[tid] = 0;
+    for (int64_t t0 = begin; t0 < end; t0 += 256) {
+        const int valid = (int)min((int64_t)256, end - t0);
+        __syncthreads();
+        for (int i = tid; i < valid * E; i += 256) s_l[i / E * (E | 1) + i % E] = to_float(logits[t0 * E + i]);
+        __syncthreads();
+        if (tid < valid) {
+            const float *row = s_l + tid * (E | 1);
+            int32_t *ix = s_idx + tid * K;
+            route_token([&](int e) { return row[e]; }, E, K, ix, s_w + tid * K);
+            for (int r = 0; r < K; ++r)
+                lists[ix[r] * tokens + begin + atomicAdd(&s_cnt[ix[r]], 1)] = (int32_t)((t0 + tid) * K + r);
+        }
+        __syncthreads();
+        for (int i = tid; i < valid * K; i += 256) {
+            idx[t0 * K + i] = s_idx[i];
+            w[t0 * K + i] = s_w[i];
+        }
+    }
+    __syncthreads();
+    if (tid < E) counts[tid * (int)gridDim.x + blockIdx.x] = s_cnt[tid];
+}
+
+// the same into whole lists, for many experts: counters cleared before, one global atomic per block and expert
 template <typename T>
 __global__ void __launch_bounds__(256)
 proj_route_kernel(const T *__restrict__ logits, int32_t *__restrict__ idx, float *__restrict__ w,
@@ -137,10 +174,13 @@ __device__ __forceinline__ int pj_wave_sum(int v)
 __global__ void __launch_bounds__(PJ_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
 proj_mfma_kernel(const uint16_t *__restrict__ u, ProjBlocks pb, const int32_t *__restrict__ counts,
                  const int32_t *__restrict__ lists, int64_t tokens, int E, int K, int Dm, int nslots,
-                 int colblocks, int compact)
+                 int colblocks, int compact, int nseg, int seg_len)
 {
     extern __shared__ __align__(16) unsigned char s_buf[];   // weight rows, then token rows of each buffer
     __shared__ int32_t s_sel[4];
+    __shared__ int32_t s_cnt[SWIMBA_MAX_EXPERTS];            // entries of every expert's list
+    __shared__ int32_t s_seg[PJ_MAX_SEGS + 1];               // of the workgroup's expert: entries in front of each segment
+    __shared__ int32_t s_ent[2][64 * PJ_MAX_RT];             // list entries of a pass
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
@@ -150,11 +190,24 @@ proj_mfma_kernel(const uint16_t *__restrict__ u, ProjBlocks pb, const int32_t *_
     // Workgroups of one XCD (ids equal mod 8) take neighbouring shares with all their column blocks, so
     // that its L2 holds the weights of about one expert and the token rows are read into it once.
     if (tid == 0) s_sel[0] = -1;
+    if (nseg == 1) {
+        if (tid < E) s_cnt[tid] = counts[tid];
+    } else {
+        for (int e = wave; e < E; e += PJ_THREADS / 64) {
+            int c[PJ_MAX_SEGS / 64], n = 0;
+#pragma unroll
+            for (int q = 0; q < PJ_MAX_SEGS / 64; ++q) c[q] = counts[e * nseg + min(64 * q + lane, nseg - 1)];
+#pragma unroll
+            for (int q = 0; q < PJ_MAX_SEGS / 64; ++q) n += 64 * q + lane < nseg ? c[q] : 0;
+            n = pj_wave_sum(n);
+            if (lane == 0) s_cnt[e] = n;
+        }
+    }
     __syncthreads();
     if (wave == 0) {
         int tiles[4], sum = 0, v[4];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) { tiles[q] = 4 * lane + q < E ? (counts[4 * lane + q] + 31) / 32 : 0; sum += tiles[q]; }
+        for (int q = 0; q < 4; ++q) { tiles[q] = 4 * lane + q < E ? (s_cnt[4 * lane + q] + 31) / 32 : 0; sum += tiles[q]; }
         const int all = pj_wave_sum(sum);
         int per = max(2, 2 * ((all + 2 * nslots - 1) / (2 * nslots)));
         for (int tries = 0;; ++tries) {
@@ -185,12 +238,39 @@ proj_mfma_kernel(const uint16_t *__restrict__ u, ProjBlocks pb, const int32_t *_
     const int e = __builtin_amdgcn_readfirstlane(s_sel[0]);
     if (e < 0) return;                                       // whole workgroup: no barrier is skipped
     const int part = __builtin_amdgcn_readfirstlane(s_sel[1]), nparts = __builtin_amdgcn_readfirstlane(s_sel[3]);
-    const int cnt = counts[e];
+    const int cnt = s_cnt[e];
     const int n32 = (cnt + 31) / 32;
     const int t_begin = (int)((int64_t)part * n32 / nparts), t_end = (int)((int64_t)(part + 1) * n32 / nparts);
     const int nt = t_end - t_begin;
     if (nt <= 0) return;
     const int npass = (nt + 2 * PJ_MAX_RT - 1) / (2 * PJ_MAX_RT);
+    if (nseg > 1) {
+        if (wave == 0) {
+            int c[PJ_MAX_SEGS / 64], n = 0;                  // four segments a lane
+#pragma unroll
+            for (int q = 0; q < 4; ++q) { c[q] = counts[e * nseg + min(4 * lane + q, nseg - 1)]; n += 4 * lane + q < nseg ? c[q] : 0; }
+            int in_front = n;
+#pragma unroll
+            for (int d = 1; d < 64; d <<= 1) {
+                const int t = __shfl_up(in_front, d);
+                if (lane >= d) in_front += t;
+            }
+            in_front -= n;
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (4 * lane + q < nseg) { s_seg[4 * lane + q] = in_front; in_front += c[q]; }
+        }
+        __syncthreads();
+    }
+    // entry r of the list
+    auto entry_at = [&](int r) __attribute__((always_inline)) {
+        if (nseg == 1) return r;
+        int seg = 0;                                         // the last one with at most r entries in front
+#pragma unroll
+        for (int d = PJ_MAX_SEGS / 2; d > 0; d >>= 1)
+            if (seg + d < nseg && s_seg[seg + d] <= r) seg += d;
+        return seg * seg_len + r - s_seg[seg];
+    };
 
     const int cw = wave & 3, rg = wave >> 2;                 // column group, row group of the wave
     const int colblk = __builtin_amdgcn_readfirstlane(s_sel[2]) * PJ_COLS;   // first column of the workgroup in [B | C | X]
@@ -226,7 +306,15 @@ proj_mfma_kernel(const uint16_t *__restrict__ u, ProjBlocks pb, const int32_t *_
         auto entries = [&](int32_t (&row)[RT], int pass) __attribute__((always_inline)) {
             const int begin = 32 * first_tile(pass), last = min(32 * first_tile(pass + 1), cnt) - 1;
 #pragma unroll
-            for (int i = 0; i < RT; ++i) row[i] = list[min(begin + 8 * (RT * wave + i) + r8, last)];
+            for (int i = 0; i < RT; ++i) row[i] = list[entry_at(min(begin + 8 * (RT * wave + i) + r8, last))];
+        };
+        // kept for the pass's results, and turned into tokens
+        auto to_tokens = [&](int32_t (&row)[RT], int pass) __attribute__((always_inline)) {
+#pragma unroll
+            for (int i = 0; i < RT; ++i) {
+                if ((lane & 7) == 0) s_ent[pass & 1][8 * (RT * wave + i) + r8] = row[i];
+                row[i] /= K;
+            }
         };
         int32_t row[RT], next_row[RT];
         int slot = 0;                                        // buffer of the next stage to be copied
@@ -246,12 +334,8 @@ proj_mfma_kernel(const uint16_t *__restrict__ u, ProjBlocks pb, const int32_t *_
             for (int i = 0; i < RT; ++i) pj_copy(at + i * 8 * PJ_ROW, ((i + odd) & 1 ? from[1] : from[0]) + (int64_t)row[i] * Dm);
             slot = slot == NBUF - 1 ? 0 : slot + 1;
         };
-        auto to_tokens = [&](int32_t (&row)[RT]) __attribute__((always_inline)) {
-#pragma unroll
-            for (int i = 0; i < RT; ++i) row[i] /= K;
-        };
         entries(row, 0);
-        to_tokens(row);
+        to_tokens(row, 0);
 #pragma unroll
         for (int st = 0; st < NBUF - 1; ++st)
             if (st < stages) {
@@ -302,7 +386,7 @@ proj_mfma_kernel(const uint16_t *__restrict__ u, ProjBlocks pb, const int32_t *_
                 if (ahead == stages && more) {
 #pragma unroll
                     for (int i = 0; i < RT; ++i) row[i] = next_row[i];
-                    to_tokens(row);
+                    to_tokens(row, pass + 1);
                 }
                 if constexpr (decltype(whole_)::value) {
                     read_ops(a0, b0, 0);
@@ -342,7 +426,7 @@ proj_mfma_kernel(const uint16_t *__restrict__ u, ProjBlocks pb, const int32_t *_
                 for (int rt = 0; rt < RT; ++rt) {
                     const int prow = 32 * (tbase + rt) + l32;                    // entry inside the pass
                     if (rt < nrt && prow < nvalid) {
-                        const int64_t ent = list[32 * begin + prow];             // t*K + r
+                        const int64_t ent = s_ent[pass & 1][prow];               // t*K + r
                         const int64_t row = compact ? ent : (ent / K) * E + e;
 #pragma unroll
                         for (int ct = 0; ct < 2; ++ct) {
@@ -420,10 +504,18 @@ swimba_status launch_expert_proj(int64_t tokens, int E, int K, int GN, int Dm, i
         SWIMBA_CHECK_LAUNCH();
         return SWIMBA_OK;
     }
-    hipLaunchKernelGGL(proj_clear_kernel, dim3(1), dim3(256), 0, st, counts, E);
-    SWIMBA_CHECK_LAUNCH();
-    hipLaunchKernelGGL(proj_route_kernel<bf16>, dim3(rgrid), dim3(256), (size_t)256 * K * sizeof(int32_t), st,
-                       (const bf16 *)logits, idx, w, counts, lists, tokens, E, K);
+    int nseg = 1, seg_len = 0;
+    if (E <= PJ_SEG_EXPERTS) {
+        seg_len = (int)((tokens + 256 * PJ_MAX_SEGS - 1) / (256 * PJ_MAX_SEGS)) * 256;
+        nseg = (int)((tokens + seg_len - 1) / seg_len);
+        hipLaunchKernelGGL(proj_route_segments_kernel<bf16>, dim3(nseg), dim3(256), (size_t)256 * (2 * K + (E | 1)) * 4, st,
+                           (const bf16 *)logits, idx, w, counts, lists, tokens, E, K, seg_len);
+    } else {
+        hipLaunchKernelGGL(proj_clear_kernel, dim3(1), dim3(256), 0, st, counts, E);
+        SWIMBA_CHECK_LAUNCH();
+        hipLaunchKernelGGL(proj_route_kernel<bf16>, dim3(rgrid), dim3(256), (size_t)256 * K * sizeof(int32_t), st,
+                           (const bf16 *)logits, idx, w, counts, lists, tokens, E, K);
+    }
     SWIMBA_CHECK_LAUNCH();
     // one place per compute unit (a workgroup is 8 waves with up to 256 registers each), shared
     // by the column blocks; the kernel divides them among the experts
@@ -444,7 +536,7 @@ swimba_status launch_expert_proj(int64_t tokens, int E, int K, int GN, int Dm, i
     // the shares sum to at most nslots + E: each but one of an expert has the average of tiles a slot or more
     const unsigned grid = (unsigned)(((int64_t)(nslots + E) * colblocks + 7) / 8 * 8);
     hipLaunchKernelGGL(proj_mfma_kernel, dim3(grid), dim3(PJ_THREADS), PJ_SHM, st, (const uint16_t *)u, pb, counts, lists,
-                       tokens, E, K, Dm, nslots, colblocks, compact);
+                       tokens, E, K, Dm, nslots, colblocks, compact, nseg, seg_len);
     SWIMBA_CHECK_LAUNCH();
     return SWIMBA_OK;
 }

@@ -41,7 +41,9 @@ SHAPES = [
     (1, 6200, 144, 1, 8, 128, 1, "bf16"),   # MFMA: one pass of 8 tiles a workgroup
     (1, 9001, 80, 2, 8, 128, 1, "bf16"),    # MFMA: passes of 5 tiles, two a workgroup
     (1, 12000, 32, 1, 8, 128, 1, "bf16"),   # MFMA: the same in less than one stage of features
-    (1, 600, 64, 64, 8, 128, 2, "bf16"),    # MFMA: more experts than workgroups at once
+    (1, 600, 64, 64, 8, 128, 2, "bf16"),    # MFMA: more experts than workgroups at once, lists in one piece
+    (1, 66001, 32, 3, 1, 64, 2, "bf16"),    # MFMA: segments of the lists of more than 256 tokens
+    (1, 300, 32, 32, 1, 64, 1, "bf16"),     # MFMA: most experts with segments, the second nearly empty
 ]
 
 
