@@ -159,7 +159,7 @@ __device__ __forceinline__ void chain_table(const ChainTables &t, int64_t bhs, f
     }
 }
 
-template <int NT>
+template <int NT, bool SEL>                              // SEL: rows of the selected experts and their weights
 __global__ void __launch_bounds__(CB_MIX_THREADS, 4)
 mix_steps_kernel(const bf16 *__restrict__ Be, const bf16 *__restrict__ Ce, const bf16 *__restrict__ logits,
                  int32_t *__restrict__ idx_out, float *__restrict__ w_out, const float *__restrict__ w_sel,
@@ -200,9 +200,9 @@ mix_steps_kernel(const bf16 *__restrict__ Be, const bf16 *__restrict__ Ce, const
     const int b = item / (gblocks * nsteps);
     const int valid = min(CB_STEP, s.L - c * CB_STEP);
     const int64_t tok0 = (int64_t)b * s.L + (int64_t)c * CB_STEP;
-    const bool sel = (w_sel != nullptr), is_c = wave >= CB_MIX_THREADS / 128;
+    const bool is_c = wave >= CB_MIX_THREADS / 128;
 
-    if (!sel) {
+    if (!SEL) {
         const int ES = s.E | 1;
         for (int i = tid; i < valid * s.E; i += CB_MIX_THREADS) s_l[i / s.E * ES + i % s.E] = to_float(logits[tok0 * s.E + i]);
         __syncthreads();
@@ -212,7 +212,7 @@ mix_steps_kernel(const bf16 *__restrict__ Be, const bf16 *__restrict__ Ce, const
         float *wx = s_w + tid * K;
         if (tid >= valid) {
             for (int r = 0; r < K; ++r) { ix[r] = 0; wx[r] = 0.f; }
-        } else if (sel) {
+        } else if (SEL) {
             for (int r = 0; r < K; ++r) { ix[r] = r; wx[r] = w_sel[(tok0 + tid) * K + r]; }
         } else {
             const float *row = s_l + tid * (s.E | 1);
@@ -223,7 +223,7 @@ mix_steps_kernel(const bf16 *__restrict__ Be, const bf16 *__restrict__ Ce, const
     }
     __syncthreads();
 
-    const int rowsE = sel ? K : s.E;
+    const int rowsE = SEL ? K : s.E;
     const int64_t estride = (int64_t)s.G * s.N, tokstride = rowsE * estride;
     const int l32 = lane & 31, hi = lane >> 5, s16 = lane & 15, half = (lane >> 4) & 1;
     for (int g = g_begin; g < g_begin + gpb; ++g) {
@@ -239,17 +239,19 @@ mix_steps_kernel(const bf16 *__restrict__ Be, const bf16 *__restrict__ Ce, const
                 const uint16_t *base = reinterpret_cast<const uint16_t *>(is_c ? Ce : Be);
                 const int j = min(row, valid - 1);
                 w = s_w[row * K + r];
-                return reinterpret_cast<const uint4 *>(base + (tok0 + j) * tokstride + s_idx[row * K + r] * estride +
-                                                       (int64_t)g * s.N + min(8 * pc, s.N - 8));
+                return base + (tok0 + j) * tokstride + s_idx[row * K + r] * estride + (int64_t)g * s.N + min(8 * pc, s.N - 8);
             };
+            // The experts' rows are read once and leave the last-level cache to what the walk reads next (130M-shaped layer 52.5 ->
+            // 47.0 us, two sequences of 16384 tokens 315 -> 309); selected rows have just been written by the projection.
+            auto row_piece = [&](const uint16_t *p) __attribute__((always_inline)) { return SEL ? *reinterpret_cast<const uint4 *>(p) : load_nt(p); };
             int r = 0;
             for (; r + 1 < K; r += 2) {
                 uint4 v0[NT], v1[NT];
                 float w0[NT], w1[NT];
 #pragma unroll
                 for (int m = 0; m < NT; ++m) {
-                    v0[m] = *source(m, r, w0[m]);
-                    v1[m] = *source(m, r + 1, w1[m]);
+                    v0[m] = row_piece(source(m, r, w0[m]));
+                    v1[m] = row_piece(source(m, r + 1, w1[m]));
                 }
 #pragma unroll
                 for (int m = 0; m < NT; ++m) {
@@ -261,7 +263,7 @@ mix_steps_kernel(const bf16 *__restrict__ Be, const bf16 *__restrict__ Ce, const
                 uint4 v0[NT];
                 float w0[NT];
 #pragma unroll
-                for (int m = 0; m < NT; ++m) v0[m] = *source(m, r, w0[m]);
+                for (int m = 0; m < NT; ++m) v0[m] = row_piece(source(m, r, w0[m]));
 #pragma unroll
                 for (int m = 0; m < NT; ++m) fma_bf16x8(acc[m], v0[m], w0[m]);
             }
@@ -350,7 +352,8 @@ __device__ __forceinline__ float4 *piece_frag(const ChainPieces &pc, int64_t bh,
 constexpr int cb_state_waves(int PT, int CW) { return CW ? CW / 2 : 2 * PT; }
 constexpr int cb_threads(int PT, int CW) { return 64 * (cb_state_waves(PT, CW) + CW / 2 + 2 * PT); }
 
-template <int NT, int PT, int CW>
+// XONCE: x passes by the caches
+template <int NT, int PT, int CW, bool XONCE = false>
 __global__ void __launch_bounds__(cb_threads(PT, CW), PT == 1 && CW == 4 ? 3 : 2)
 chain_bf16_kernel(const uint16_t *__restrict__ x, const float *__restrict__ D, const uint16_t *__restrict__ ops, ChainTables tb,
                   const float *h0, float *h_final, uint16_t *__restrict__ y, Shape s, int nsteps, int nslice, int nseg,
@@ -851,7 +854,7 @@ chain_bf16_kernel(const uint16_t *__restrict__ x, const float *__restrict__ D, c
         auto load_x = [&](u32x4_t (&v)[2], float4 &fe, int c) __attribute__((always_inline)) {
             const auto xrows = rows(x, c);
 #pragma unroll
-            for (int m = 0; m < 2; ++m) v[m] = __builtin_amdgcn_raw_buffer_load_b128(xrows, xoff[m], 0, 0);
+            for (int m = 0; m < 2; ++m) v[m] = __builtin_amdgcn_raw_buffer_load_b128(xrows, xoff[m], 0, XONCE ? 2 : 0);   // 2: non-temporal
             fe = reinterpret_cast<const float4 *>(fe0 + min(c, c_end - 1) * CB_STEP)[xj0];
         };
         auto unpack = [&](float (&a)[8], const u32x4_t &v) __attribute__((always_inline)) { unpack8(a, make_uint4(v[0], v[1], v[2], v[3])); };
@@ -1050,7 +1053,8 @@ static swimba_status launch_mix_t(const Shape &s, const void *dt, const float *A
     const int nsteps = (s.L + CB_STEP - 1) / CB_STEP, ncu = device_cus();
     auto mix_shm = [](int K, int E) { return (size_t)2 * CB_STEP * (64 * NT + 16) + (size_t)CB_STEP * K * 8 + (E ? (size_t)CB_STEP * (E | 1) * 4 : 0); };
     static std::atomic<uint64_t> done{0};
-    const swimba_status ok = allow_lds(done, {{(const void *)mix_steps_kernel<NT>, mix_shm(SWIMBA_MAX_TOPK, SWIMBA_MAX_EXPERTS)}});
+    const swimba_status ok = allow_lds(done, {{(const void *)mix_steps_kernel<NT, false>, mix_shm(SWIMBA_MAX_TOPK, SWIMBA_MAX_EXPERTS)},
+                                              {(const void *)mix_steps_kernel<NT, true>, mix_shm(SWIMBA_MAX_TOPK, 0)}});
     if (ok != SWIMBA_OK) return ok;
     // A workgroup routes its tokens once for as many groups as leave two workgroups to a compute unit.
     int gpb = 1;
@@ -1058,7 +1062,7 @@ static swimba_status launch_mix_t(const Shape &s, const void *dt, const float *A
         if (s.G % n == 0 && (int64_t)s.B * nsteps * s.G / n >= 2 * (int64_t)ncu) gpb = n;
     const int items = (int)((int64_t)s.B * nsteps * s.G / gpb);
     const int tblocks = (int)(((int64_t)s.B * nsteps * ((s.H + 7) / 8) + 7) / 8);
-    hipLaunchKernelGGL(mix_steps_kernel<NT>, dim3(items + tblocks), dim3(CB_MIX_THREADS), mix_shm(s.K, w_sel ? 0 : s.E), st,
+    hipLaunchKernelGGL((w_sel ? mix_steps_kernel<NT, true> : mix_steps_kernel<NT, false>), dim3(items + tblocks), dim3(CB_MIX_THREADS), mix_shm(s.K, w_sel ? 0 : s.E), st,
                        (const bf16 *)Be, (const bf16 *)Ce, (const bf16 *)logits, idx, w, w_sel, (uint16_t *)scr.ops,
                        (const bf16 *)dt, A, chain_tables(s, scr), s, nsteps, gpb, items);
     SWIMBA_CHECK_LAUNCH();
@@ -1074,7 +1078,8 @@ static swimba_status launch_walk_t(const Shape &s, const void *x, const float *D
     static std::atomic<uint64_t> done{0};
     const swimba_status ok = allow_lds(done, {{(const void *)chain_bf16_kernel<NT, 1, 2>, chain_shm(1, true)},
                                               {(const void *)chain_bf16_kernel<NT, 1, 4>, chain_shm(1, true)},
-                                              {(const void *)chain_bf16_kernel<NT, 2, 4>, chain_shm(2, true)}});
+                                              {(const void *)chain_bf16_kernel<NT, 2, 4>, chain_shm(2, true)},
+                                              {(const void *)chain_bf16_kernel<NT, 2, 4, true>, chain_shm(2, true)}});
     if (ok != SWIMBA_OK) return ok;
     ChainPlan plan = chain_plan(s, scr, skip, ncu);
     ChainPieces &pieces = plan.pieces;
@@ -1084,13 +1089,17 @@ static swimba_status launch_walk_t(const Shape &s, const void *x, const float *D
     // Workgroups of one channel tile where all of them find a compute unit at once; else of both tiles of a head, one to a unit,
     // where the heads fill one round or three fifths of several; else (300 heads of 1024 tokens 45 / 48 us with both tiles in
     // one), and for more heads of one tile than units (320 of 512 tokens, P = 64, N = 64: 29 / 38), of fewer waves, two to a unit.
+    // x and y that fill the last-level cache (256 MB) by themselves: x is not found there when it is read, and passes by it, too
+    // (370M-shaped layer, 268 MB: 101.7 -> 98 us; 130M-shaped, 100 MB: 47.0 -> 51.6), unless pieces of it are walked twice (two
+    // sequences of 16384 tokens 309 -> 320).
+    const bool x_once = plan.nseg == 1 && (int64_t)s.B * s.L * s.H * s.P * 4 >= 256 << 20;
     auto launch = [&](bool out, int count, int steps) {
         const int64_t chains = (int64_t)s.B * s.H * count, rounds = (chains + ncu - 1) / ncu;
         const int PT = s.P > 32 && 2 * chains > ncu && (rounds == 1 || 10 * chains >= 6 * rounds * ncu) ? 2 : 1;
         const int CW = !out ? 0 : PT == 1 && chains * ((s.P + 31) / 32) > ncu ? 2 : 4;
         const int nslice = (s.P + 32 * PT - 1) / (32 * PT);
         const int total = (int)chains * nslice, nblocks = xcd_padded(total);
-        const auto kernel = PT == 2 ? (out ? chain_bf16_kernel<NT, 2, 4> : chain_bf16_kernel<NT, 2, 0>)
+        const auto kernel = PT == 2 ? (!out ? chain_bf16_kernel<NT, 2, 0> : x_once ? chain_bf16_kernel<NT, 2, 4, true> : chain_bf16_kernel<NT, 2, 4>)
                                     : CW == 4 ? chain_bf16_kernel<NT, 1, 4> : CW == 2 ? chain_bf16_kernel<NT, 1, 2> : chain_bf16_kernel<NT, 1, 0>;
         hipLaunchKernelGGL(kernel, dim3(nblocks), dim3(cb_threads(PT, CW)), chain_shm(PT, out), st, (const uint16_t *)x, D,
                            (const uint16_t *)scr.ops, chain_tables(s, scr), h0, h_final, (uint16_t *)y, s, plan.nsteps, nslice, count, steps,
