@@ -17,7 +17,8 @@
 //                       M[i][j]   = G[i][j] dt_j exp(cs_i - cs_j)
 //                     The readout is split over the state columns, the 12 blocks of M over the waves, and
 //                     the four partial Y tiles are added in a fixed order: 76 MFMAs per wave and step
-//                     (N = 128) whatever the wave.
+//                     (N = 128) whatever the wave.  Where a tile has several waves (N <= 64) each keeps a part of the sum
+//                     over j of S (SPLIT).
 // Where batch x heads x slices alone would leave compute units idle, a sequence is walked as several
 // segments: one launch sums each segment's own contribution to the state (state part only), and a
 // segment of the output launch starts from the sum of those in front of it (the recurrence is linear
@@ -242,7 +243,11 @@ mix_ops_kernel(const T *__restrict__ Be, const T *__restrict__ Ce, const T *__re
 // 32 tokens).  OUT: y (and h_final); otherwise the state part only:
 // the segment's own contribution to the state (from zero) into hseg, its total decay (log2) into aseg; with an h_final
 // it is segment 0's copy of h0 for the output launch, whose own h_final is the caller's h0.
-template <typename T, int NTW, bool OUT, int ROWT>
+// SPLIT: waves that share a state tile where there are two or four waves to a tile (N <= 64, 32).  Each adds what its part of
+// a step's tokens contributes to a state of its own and reads it out; the readouts meet with the other partial sums of Y, the
+// states at the end.  N = 16: 36 MFMAs a wave and step for 76, four heads of 256 tokens 28.8 -> 23.7 us, 48 of 1000 tokens
+// 58.4 -> 50.5; N = 64: 60 MFMAs, 48 of 1000 tokens 66.2 -> 58.3.
+template <typename T, int NTW, bool OUT, int ROWT, int SPLIT>
 __global__ void __launch_bounds__(256, NTW == 1 ? (ROWT == 1 ? 3 : 2) : 1)
 chain_f32_kernel(const T *__restrict__ x, const T *__restrict__ dt, const float *__restrict__ A,
                  const float *__restrict__ D, const float *__restrict__ cop, const float *__restrict__ bop,
@@ -251,7 +256,9 @@ chain_f32_kernel(const T *__restrict__ x, const T *__restrict__ dt, const float 
                  int nrun, int nseg, int steps_per_seg, int total, int nblocks)
 {
     constexpr int QT = 4 * ROWT;                                 // 8-token blocks of a step
+    constexpr int QW = QT / SPLIT;                               // that the wave adds to its state
     static_assert(OUT || ROWT == 2, "segments are of whole steps");
+    static_assert(SPLIT == 1 || NTW == 1, "waves share a tile");
     __shared__ __align__(16) float s_x[2][32 * CF_XS];           // x^T of a step: [channel][token]
     __shared__ __align__(16) float s_cs[2][CF_STEP], s_dt[2][CF_STEP], s_c[2][CF_STEP];
     __shared__ int s_odd;                                        // an x or dt is not finite
@@ -268,6 +275,7 @@ chain_f32_kernel(const T *__restrict__ x, const T *__restrict__ dt, const float 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, kg = lane >> 5;
+    const int nt0 = SPLIT > 1 ? wave / SPLIT : wave * NTW, part = SPLIT > 1 ? wave % SPLIT : 0;      // first tile of the wave
     const int c_begin = seg * steps_per_seg, c_end = min(s.nc, c_begin + steps_per_seg);
     const int p0 = 32 * sl, P = s.P;
     const float Ah = A[h] * LOG2E;
@@ -284,13 +292,13 @@ chain_f32_kernel(const T *__restrict__ x, const T *__restrict__ dt, const float 
         const int n = 32 * nt + 8 * a + 4 * kg + q;
         return (p < P && n < s.N) ? base[(int64_t)p * s.N + n] : 0.f;
     };
-    if (!OUT && h_final && seg == 0 && p < P) {
+    if (!OUT && h_final && seg == 0 && p < P && part == 0) {
         const int64_t o = ((int64_t)b * s.H + h) * P * s.N;
 #pragma unroll
         for (int k = 0; k < NTW; ++k)
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
-                const int n = 32 * (wave * NTW + k) + 8 * (v >> 2) + 4 * kg + (v & 3);
+                const int n = 32 * (nt0 + k) + 8 * (v >> 2) + 4 * kg + (v & 3);
                 if (n < s.N) h_final[o + (int64_t)p * s.N + n] = h0[o + (int64_t)p * s.N + n];
             }
     }
@@ -298,16 +306,16 @@ chain_f32_kernel(const T *__restrict__ x, const T *__restrict__ dt, const float 
     auto initial = [&]() __attribute__((always_inline)) {
 #pragma unroll
         for (int k = 0; k < NTW; ++k) {
-            const int nt = wave * NTW + k;
+            const int nt = nt0 + k;
 #pragma unroll
             for (int v = 0; v < 16; ++v) st[k][v] = 0.f;
-            if (OUT && h0) {
+            if (OUT && h0 && part == 0) {
                 const float *hp = h0 + ((int64_t)b * s.H + h) * P * s.N;
 #pragma unroll
                 for (int v = 0; v < 16; ++v) st[k][v] = state_at(hp, nt, v >> 2, v & 3);
             }
         }
-        if (OUT) {
+        if (OUT && part == 0) {
             // the contributions of the segments in front, four requested together
             for (int q0 = 0; q0 < seg; q0 += 4) {
                 float dec[4];
@@ -320,7 +328,7 @@ chain_f32_kernel(const T *__restrict__ x, const T *__restrict__ dt, const float 
 #pragma unroll
                     for (int k = 0; k < NTW; ++k)
 #pragma unroll
-                        for (int a = 0; a < 4; ++a) v[u][k][a] = hp[(min(wave * NTW + k, NT - 1) * 4 + a) * 64];
+                        for (int a = 0; a < 4; ++a) v[u][k][a] = hp[(min(nt0 + k, NT - 1) * 4 + a) * 64];
                 }
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
@@ -361,7 +369,7 @@ chain_f32_kernel(const T *__restrict__ x, const T *__restrict__ dt, const float 
     };
     // In the state part alone the B operand of the next step has no readout to arrive behind: it gets registers of
     // its own (brn) and is requested a whole step ahead.
-    float4 cr[NTW][ROWT][4], br[NTW][QT], brn[NTW][QT], gr[ROWT == 2 ? 3 : 1];
+    float4 cr[NTW][ROWT][4], br[NTW][QW], brn[NTW][QW], gr[ROWT == 2 ? 3 : 1];
     const int64_t bg0 = ((int64_t)b * s.nc) * s.G + g;
     // of one tile row only the blocks with a token are there: the last of them comes for those behind it, to meet zeros
     const ChainOps ops = ROWT == 2 ? ChainOps{2, 8, CF_GBLK} : chain_ops(s.L);
@@ -374,14 +382,14 @@ chain_f32_kernel(const T *__restrict__ x, const T *__restrict__ dt, const float 
             for (int I = 0; I < ROWT; ++I)
 #pragma unroll
                 for (int a = 0; a < 4; ++a)
-                    cr[k][I][a] = src[((I * NT + min(wave * NTW + k, NT - 1)) * 4 + a) * 64];
+                    cr[k][I][a] = src[((I * NT + min(nt0 + k, NT - 1)) * 4 + a) * 64];
     };
-    auto load_b = [&](int c, float4 (&br)[NTW][QT]) __attribute__((always_inline)) {
+    auto load_b = [&](int c, float4 (&br)[NTW][QW]) __attribute__((always_inline)) {
         const float4 *src = reinterpret_cast<const float4 *>(bop) + (bg0 + (int64_t)c * s.G) * (NT * ops.QN * 64) + lane;
 #pragma unroll
         for (int k = 0; k < NTW; ++k)
 #pragma unroll
-            for (int q = 0; q < QT; ++q) br[k][q] = src[(min(wave * NTW + k, NT - 1) * ops.QN + min(q, ql)) * 64];
+            for (int q = 0; q < QW; ++q) br[k][q] = src[(min(nt0 + k, NT - 1) * ops.QN + min(part * QW + q, ql)) * 64];
     };
     auto load_g = [&](int c) __attribute__((always_inline)) {
         const float4 *src = reinterpret_cast<const float4 *>(gop) + (bg0 + (int64_t)c * s.G) * (ops.GB * 64) + lane;
@@ -407,7 +415,7 @@ chain_f32_kernel(const T *__restrict__ x, const T *__restrict__ dt, const float 
 
     float atot = 0.f;
     float odd = 0.f;                                     // NaN once zero times anything not finite has been added
-    auto step = [&](int c, float4 (&br)[NTW][QT], float4 (&brn)[NTW][QT], auto one_by_one) __attribute__((always_inline)) {
+    auto step = [&](int c, float4 (&br)[NTW][QW], float4 (&brn)[NTW][QW], auto one_by_one) __attribute__((always_inline)) {
         const int buf = (c - c_begin) & 1;
         const int cn = min(c + 1, c_end - 1);
         float xc[8];
@@ -431,9 +439,10 @@ chain_f32_kernel(const T *__restrict__ x, const T *__restrict__ dt, const float 
             const float ei[2] = {fast_exp2(ci[0]), fast_exp2(ci[1])};
 #pragma unroll
             for (int k = 0; k < NTW; ++k)
-                if (wave * NTW + k < NT) {               // wave-uniform
+                if (nt0 + k < NT) {                      // wave-uniform
 #pragma unroll
                     for (int a = 0; a < 4; ++a) {
+                        if (SPLIT == 4 && 8 * a >= s.N) break;           // columns that do not exist
                         const float4 u0 = cr[k][0][a], u1 = cr[k][ROWT - 1][a];
                         yt[0] = mfma_f32(st[k][4 * a + 0], u0.x * ei[0], yt[0]);
                         if (ROWT == 2) yt[ROWT - 1] = mfma_f32(st[k][4 * a + 0], u1.x * ei[1], yt[ROWT - 1]);
@@ -492,11 +501,12 @@ chain_f32_kernel(const T *__restrict__ x, const T *__restrict__ dt, const float 
                 for (int v = 0; v < 16; ++v) st[k][v] *= dec;
 #pragma unroll
             for (int k = 0; k < NTW; ++k) {
-                if (wave * NTW + k >= NT) continue;      // wave-uniform; outside the token loop, whose LDS reads overlap
+                if (nt0 + k >= NT) continue;             // wave-uniform; outside the token loop, whose LDS reads overlap
 #pragma unroll
-                for (int q = 0; q < QT; ++q) {
-                    const float4 cj = *reinterpret_cast<const float4 *>(&s_c[buf][8 * q + 4 * kg]);
-                    const float4 xv = *reinterpret_cast<const float4 *>(sx + 8 * q);
+                for (int q = 0; q < QW; ++q) {
+                    const int qb = part * QW + q;
+                    const float4 cj = *reinterpret_cast<const float4 *>(&s_c[buf][8 * qb + 4 * kg]);
+                    const float4 xv = *reinterpret_cast<const float4 *>(sx + 8 * qb);
                     st[k] = mfma_f32(br[k][q].x, xv.x * cj.x, st[k]);
                     st[k] = mfma_f32(br[k][q].y, xv.y * cj.y, st[k]);
                     st[k] = mfma_f32(br[k][q].z, xv.z * cj.z, st[k]);
@@ -576,14 +586,31 @@ chain_f32_kernel(const T *__restrict__ x, const T *__restrict__ dt, const float 
             __syncthreads();                             // every wave has read it
             walk(std::true_type{});
         }
+    if constexpr (SPLIT > 1) {
+        // the waves' states of a tile added up, in the first one of them
+        static_assert(sizeof(s_x) >= 4 * 1024 * sizeof(float), "room for four tiles");
+        float4 *tiles = reinterpret_cast<float4 *>(&s_x[0][0]) + lane;
+        __syncthreads();                                 // every wave is done with x
+#pragma unroll
+        for (int a = 0; a < 4; ++a) tiles[(wave * 4 + a) * 64] = make_float4(st[0][4 * a], st[0][4 * a + 1], st[0][4 * a + 2], st[0][4 * a + 3]);
+        __syncthreads();
+        if (part) return;
+#pragma unroll
+        for (int w = 1; w < SPLIT; ++w)
+#pragma unroll
+            for (int a = 0; a < 4; ++a) {
+                const float4 v = tiles[((wave + w) * 4 + a) * 64];
+                st[0][4 * a] += v.x; st[0][4 * a + 1] += v.y; st[0][4 * a + 2] += v.z; st[0][4 * a + 3] += v.w;
+            }
+    }
     if (!OUT) {
         float4 *dst = hseg_frag(seg);
 #pragma unroll
         for (int k = 0; k < NTW; ++k) {
-            if (wave * NTW + k >= NT) continue;          // wave-uniform
+            if (nt0 + k >= NT) continue;                 // wave-uniform
 #pragma unroll
             for (int a = 0; a < 4; ++a)
-                dst[((wave * NTW + k) * 4 + a) * 64] =
+                dst[((nt0 + k) * 4 + a) * 64] =
                     make_float4(st[k][4 * a], st[k][4 * a + 1], st[k][4 * a + 2], st[k][4 * a + 3]);
         }
     }
@@ -593,7 +620,7 @@ chain_f32_kernel(const T *__restrict__ x, const T *__restrict__ dt, const float 
         for (int k = 0; k < NTW; ++k)
 #pragma unroll
             for (int a = 0; a < 4; ++a) {
-                const int n = 32 * (wave * NTW + k) + 8 * a + 4 * kg;
+                const int n = 32 * (nt0 + k) + 8 * a + 4 * kg;
                 float *q = dst + (int64_t)p * s.N + n;
                 if (s.N % 4 == 0) {
                     if (n < s.N)
@@ -647,7 +674,7 @@ void chain_f32_sizes(const swimba_dims *d, size_t *cop, size_t *bop, size_t *g, 
     *init = nseg > 1 ? (size_t)d->batch * d->nheads * d->headdim * d->dstate * sizeof(float) : 0;
 }
 
-template <typename T, int NTW>
+template <typename T, int NTW, int SPLIT>
 static void launch_chain_t(const Shape &s, const void *x, const void *dt, const float *A, const float *D, const float *cop,
                            const float *bop, const float *gop, const float *h0, float *h_final, float *hseg,
                            float *aseg, float *hinit, void *y, int NT, int nseg, hipStream_t st)
@@ -659,13 +686,13 @@ static void launch_chain_t(const Shape &s, const void *x, const void *dt, const 
         // segment of a sequence can end before another one has started.
         float *copy = h0 && h0 == h_final ? hinit : nullptr;
         const int total = s.B * (used - 1) * s.H * nslice, nblocks = xcd_padded(total);
-        hipLaunchKernelGGL((chain_f32_kernel<T, NTW, false, 2>), dim3(nblocks), dim3(256), 0, st, (const T *)x, (const T *)dt,
+        hipLaunchKernelGGL((chain_f32_kernel<T, NTW, false, 2, SPLIT>), dim3(nblocks), dim3(256), 0, st, (const T *)x, (const T *)dt,
                            A, D, cop, bop, gop, h0, copy, hseg, aseg, (T *)y, s, NT, nslice, used - 1, used, sps, total, nblocks);
         if (copy) h0 = copy;
     }
     const int total = s.B * used * s.H * nslice, nblocks = xcd_padded(total);
     // at most 32 tokens: one tile row, 36 MFMAs for 76 and three workgroups per compute unit
-    auto out = s.L > 32 ? chain_f32_kernel<T, NTW, true, 2> : chain_f32_kernel<T, NTW, true, 1>;
+    auto out = s.L > 32 ? chain_f32_kernel<T, NTW, true, 2, SPLIT> : chain_f32_kernel<T, NTW, true, 1, SPLIT>;
     hipLaunchKernelGGL(out, dim3(nblocks), dim3(256), 0, st, (const T *)x, (const T *)dt, A, D, cop, bop, gop, h0, h_final,
                        hseg, aseg, (T *)y, s, NT, nslice, used, used, sps, total, nblocks);
 }
@@ -723,10 +750,8 @@ static swimba_status launch_f32_t(const Shape &s, const void *x, const void *dt,
                            (const T *)Ce, (const T *)logits, idx, w, w_sel, cop, bop, gop, s, NT, gpb);
     }
     SWIMBA_CHECK_LAUNCH();
-    if (NT <= 4)
-        launch_chain_t<T, 1>(s, x, dt, A, D, cop, bop, gop, h0, h_final, hseg, aseg, hinit, y, NT, nseg, st);
-    else
-        launch_chain_t<T, 2>(s, x, dt, A, D, cop, bop, gop, h0, h_final, hseg, aseg, hinit, y, NT, nseg, st);
+    const auto chain = NT > 4 ? launch_chain_t<T, 2, 1> : NT > 2 ? launch_chain_t<T, 1, 1> : NT == 2 ? launch_chain_t<T, 1, 2> : launch_chain_t<T, 1, 4>;
+    chain(s, x, dt, A, D, cop, bop, gop, h0, h_final, hseg, aseg, hinit, y, NT, nseg, st);
     SWIMBA_CHECK_LAUNCH();
     return SWIMBA_OK;
 }

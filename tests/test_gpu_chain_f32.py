@@ -57,6 +57,9 @@ def check(y, hf, p, k, h0, io):
     (2, 8200, 2, 33, 20, 1, 4, 2, "f32"),      # 129 steps in 32, a slice of one channel
     (2, 2050, 48, 8, 12, 2, 4, 2, "f32"),      # 96 chains in eight segments, more steps than mix in four parts
     (1, 600, 2, 24, 80, 1, 8, 2, "f32"),
+    (2, 30, 3, 40, 9, 1, 4, 2, "f32"),         # one tile row, a quarter of its blocks a wave
+    (3, 9, 2, 64, 64, 1, 4, 2, "f32"),         # two waves to a tile, blocks without a token
+    (1, 130, 2, 64, 65, 1, 4, 2, "f32"),       # three tiles: a wave each
     (1, 600, 2, 128, 60, 1, 8, 2, "bf16"),     # outside the bf16 kernels
     (1, 70, 2, 20, 160, 2, 8, 2, "bf16"),
 ], ids=lambda c: "B%dL%dH%dP%dN%dG%dE%dk%d%s" % c)
