@@ -352,9 +352,10 @@ __device__ __forceinline__ float4 *piece_frag(const ChainPieces &pc, int64_t bh,
 constexpr int cb_state_waves(int PT, int CW) { return CW ? CW / 2 : 2 * PT; }
 constexpr int cb_threads(int PT, int CW) { return 64 * (cb_state_waves(PT, CW) + CW / 2 + 2 * PT); }
 
-// XONCE: x passes by the caches
+// XONCE: x passes by the caches.  Registers for two workgroups to a unit where no Y is written: the pieces of two sequences of
+// 16384 tokens x 64 heads, 512 workgroups, are one round then (314 -> 309 us).
 template <int NT, int PT, int CW, bool XONCE = false>
-__global__ void __launch_bounds__(cb_threads(PT, CW), PT == 1 && CW == 4 ? 3 : 2)
+__global__ void __launch_bounds__(cb_threads(PT, CW), CW == 0 ? 4 : PT == 1 && CW == 4 ? 3 : 2)
 chain_bf16_kernel(const uint16_t *__restrict__ x, const float *__restrict__ D, const uint16_t *__restrict__ ops, ChainTables tb,
                   const float *h0, float *h_final, uint16_t *__restrict__ y, Shape s, int nsteps, int nslice, int nseg,
                   int steps_per_seg, int hblock, ChainPieces pieces, int total, int nblocks)
