@@ -202,12 +202,12 @@ static bool use_chunk_mix(const swimba_dims *d, bool selected)
 }
 
 // The bf16 forward as one walk over 64-token steps (chain_bf16.hip), two launches, or three where it cuts the sequence; its
-// scratch lies over cmix .. cb, states_lp, hmid and cs.  A chain's steps are serial, 0.7 us each (two workgroups to a compute unit)
-// to 1.6 (all units busy): ahead of the kernels above up to 16 steps (8 to 1024 chains, 64 to 1024 tokens: 0.5 to 0.98 of their
-// time; 4 and 8 chains of 1024 tokens are level, 22.7 / 22.6 us, 24.3 / 23.5 in 4 groups), from 40 chains on up to 24 (40 chains
-// of 20 steps 26.6 / 28.0, of 24 31.1 / 29.6; 48 of 24 32.9 / 34.7) and from 64 on up to 32 (64 chains 39.1 / 39.4, in 4 groups
-// 40.6 / 40.3; 48 chains 37.8 / 35.9), from 96 chains on up to 128 (96 chains of 6000 tokens 89 / 110) and where the chains fill
-// three fifths of their rounds at any length (256 of 4096 tokens 122 / 147), or where segments do (chain_bf16_segments).
+// scratch lies over cmix .. cb, states_lp, hmid and cs.  A chain's steps are serial, 0.7 us each (few chains) to 1.35 (all units
+// busy): ahead of the kernels above up to 16 steps (4 and 8 chains of 1024 tokens are level, 21.5 / 21.3 us and 21.7 / 21.7, in 4
+// groups 23.2 / 22.6 and 23.1 / 22.5), from 40 chains on up to 24 (40 chains of 20 steps 25.8 / 25.7, of 24 28.6 / 27.0; 48 of 24
+// 28.8 / 31.5; 32 of 20 26.0 / 24.9) and from 64 on up to 32 (64 chains 34.8 / 37.7, in 4 groups 35.6 / 40.6; 48 chains 34.3 /
+// 33.9), from 96 chains on up to 128 (96 chains of 6000 tokens 89 / 110 before the walk's waves parted) and where the chains fill
+// three fifths of their rounds at any length (256 of 4096 tokens 99 for the walk, 147 when the others were last timed), or where segments do (chain_bf16_segments).
 // Short of that the kernels that also parallelise over chunks stay ahead.
 // The walk addresses the 64 rows of a step by 31-bit offsets; past that, a row of 2^24 channels, the staged kernels take over.
 static bool chain_bf16_rows_fit(const swimba_dims *d) { return (int64_t)d->nheads * d->headdim < (1ll << 24); }

@@ -39,7 +39,7 @@ namespace swimba {
 constexpr int CB_STEP = 64;            // tokens per step
 constexpr int CB_MIX_THREADS = 512;
 constexpr float CB_RANGE = 120.f;      // most that cs falls under one reference (ChainTables)
-constexpr int CB_RING = 6;             // x tiles in an i/o wave's registers (a multiple of the 3 in LDS); 9 spill time: 130M 64.6 us
+constexpr int CB_RING = 6;             // x tiles in an i/o wave's registers (a multiple of the 3 in LDS)
 
 typedef __attribute__((ext_vector_type(4))) short cb_s16x4_t;
 typedef __attribute__((address_space(3))) cb_s16x4_t cb_lds_s16x4_t;
@@ -99,10 +99,9 @@ __host__ __device__ constexpr int cb_item_frags(int NT) { return 8 * NT + 6; }
 //           2^(whole_last - whole_j).
 // The parts go where they go in every mode, and the rest are whole powers of two: the modes round alike, and the bits of a
 // token do not depend on the tokens behind it, which choose the mode.
-// A direct step takes 0.1 to 0.3 us longer: all steps direct, 130M-shaped layer 56 -> 58 us, 370M-shaped layer 115 -> 121,
-// five sequences of 1237 tokens x 32 heads 37 -> 41 (x and cs gathered from memory by the compute waves: 155, 325, 96; the
-// staged kernels and the per-head pass, which know no modes: 71, 147, 50).  A smaller CB_RANGE makes more steps direct: 32
-// took 66, 122 and 45 us.
+// A direct step takes 0.1 to 0.3 us longer: all steps direct, 130M-shaped layer 52 -> 55 us, 370M-shaped layer 100 -> 104,
+// five sequences of 1237 tokens x 32 heads 32 -> 39.  A smaller CB_RANGE makes more steps direct: before the state and readout
+// waves parted, when these were 56 -> 58, 115 -> 121 and 37 -> 41, a range of 32 took 66, 122 and 45 us.
 // A step size or decay that is not finite makes the tokens from its own on and the state behind them NaN, those in front take
 // the direct step without it.  A token's cs falls by 300 at most, which leaves nothing of any fp32 value.
 // Factors of up to 2^60 either way could take a product that is in range by itself out of it.  So the waves that multiply x by
@@ -979,8 +978,9 @@ size_t chain_bf16_table_bytes(const Shape &s)
     return (size_t)s.B * ((s.L + CB_STEP - 1) / CB_STEP) * (s.H * (size_t)(2 * CB_STEP + 4) + 2 * s.G) * sizeof(float);
 }
 
-// Segments of a sequence, before the scratch is asked how many pieces it holds.  A compute unit takes 1.6 us for a step of a
-// head when all are busy, and a chain alone 0.75 a step, so short of a quarter as many chains as units the chip idles: as many
+// Segments of a sequence, before the scratch is asked how many pieces it holds.  A compute unit takes 1.35 us for a step of a
+// head when all are busy, and a chain alone 0.7 a step, so short of a quarter as many chains as units the chip idles (the times
+// below are from before the state and readout waves parted): as many
 // segments as fill it, of at least 12 steps each, or 8 where it stays half empty (24 chains of 256 steps: 1 segment 191 us, 5
 // 82, 10 70; 64 of 64: 58, 4 segments 48).  With less work than nine steps a unit the kernels that parallelise over chunks are
 // ahead (48 chains of 40 steps: 38.1 / 34.9, 32 of 64: 39.1 / 36.8; 48 of 56: 45.9 / 49.3, 8 of 217: 40 / 92).  From a quarter
