@@ -116,7 +116,8 @@ swimba_status swimba_mixer_workspace_layout(const swimba_dims *dims, swimba_ws_l
  * logits (including +0/-0) go to the lower expert index; the active set is
  * written in (logit descending, index ascending) order.  NaN or +inf logits, and
  * tokens whose logits are all -inf, are outside the contract: indices and weights are
- * then unspecified, but every index stays inside [0, E), so no call reads out of bounds.
+ * then unspecified, but every index stays inside [0, E) and no expert is named twice, so no call
+ * reads or writes out of bounds.
  *   logits   (tokens, E) io   [in]
  *   topk_idx (tokens, k) int32 [out]
  *   topk_w   (tokens, k) fp32  [out]

@@ -5,6 +5,7 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include "routing.hpp"
 #include "swimba.h"
 
 namespace swimba {
@@ -202,74 +203,6 @@ __device__ __forceinline__ void lds_barrier()
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
-// ---- device helper shared by the router kernel and the decode kernel -----------------
-// Top-k over E logits read through `load(e)`, in (logit descending, index
-// ascending) order; softmax over all E, no renormalisation.
-// exp(v) for v <= 0 through the hardware exp2 (about 1 ulp; the product v * log2(e) adds a
-// relative error of |v| * 2^-24, far inside the 1e-5 the routing weights are held to)
-__device__ __forceinline__ float route_exp(float v) { return __builtin_amdgcn_exp2f(v * 1.4426950408889634f); }
-
-// The same for E <= EM experts, their logits in registers: a loop that loads one after the other waits for each.
-template <int EM, typename Load>
-__device__ __forceinline__ void route_few(Load load, int E, int K, int32_t *idx, float *w)
-{
-    float v[EM], m = -INFINITY, Z = 0.f;
-#pragma unroll
-    for (int e = 0; e < EM; ++e) v[e] = load(min(e, E - 1));
-#pragma unroll
-    for (int e = 0; e < EM; ++e) m = fmaxf(m, v[e]);
-#pragma unroll
-    for (int e = 0; e < EM; ++e) Z += e < E ? route_exp(v[e] - m) : 0.f;
-    const float invZ = 1.0f / Z;
-    float pv = 0.f;
-    int pi = -1;
-    for (int r = 0; r < K; ++r) {
-        int best = -1;
-        float bv = 0.f;
-#pragma unroll
-        for (int e = 0; e < EM; ++e) {
-            const bool after = (r == 0) || (v[e] < pv) || (v[e] == pv && e > pi);
-            if (e < E && after && (best < 0 || v[e] > bv)) { best = e; bv = v[e]; }
-        }
-        if (best < 0) { best = (pi + 1) % E; bv = -INFINITY; }
-        idx[r] = best;
-        w[r] = route_exp(bv - m) * invZ;
-        pv = bv;
-        pi = best;
-    }
-}
-
-template <typename Load>
-__device__ __forceinline__ void route_token(Load load, int E, int K, int32_t *idx, float *w)
-{
-    if (E <= 8) return route_few<8>(load, E, K, idx, w);
-    if (E <= 16) return route_few<16>(load, E, K, idx, w);
-    float m = -INFINITY;
-    for (int e = 0; e < E; ++e) m = fmaxf(m, load(e));
-    float Z = 0.f;
-    for (int e = 0; e < E; ++e) Z += route_exp(load(e) - m);
-    const float invZ = 1.0f / Z;
-    float pv = 0.f;
-    int pi = -1;
-    for (int r = 0; r < K; ++r) {
-        int best = -1;
-        float bv = 0.f;
-        for (int e = 0; e < E; ++e) {
-            const float v = load(e);
-            // candidates are the experts that come after the previous pick in the order
-            const bool after = (r == 0) || (v < pv) || (v == pv && e > pi);
-            if (after && (best < 0 || v > bv)) { best = e; bv = v; }
-        }
-        // Only logits outside the contract (NaN, +inf, all -inf) leave no candidate.  The result is
-        // undefined then, but the index stays a valid one: it addresses the expert rows.
-        if (best < 0) { best = (pi + 1) % E; bv = -INFINITY; }
-        idx[r] = best;
-        w[r] = route_exp(bv - m) * invZ;
-        pv = bv;
-        pi = best;
-    }
 }
 
 }  // namespace swimba

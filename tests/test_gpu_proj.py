@@ -155,3 +155,32 @@ def test_expert_proj_shares_and_passes(T, Dm, E, k, skew):
         # half a unit in the last place of the bf16 result; fp32 sums in another order
         tol = 2.0 ** -8 * want.abs() + 1e-5 * Dm ** 0.5
         assert bool(((out[0, :, :, 0].float() - want).abs() <= tol).all())
+
+
+@pytest.mark.parametrize("T,k,bad", [
+    (257, 3, [3, 5] + [float("nan")] * 6),              # its pick by itself would repeat expert 1; a block of one token, the last one
+    (257, 4, [9, float("nan"), 3, 5]),                  # the last expert, whose list ends the workspace
+    (600, 4, [9] + [float("nan")] * 38 + [5]),          # lists in one piece
+], ids=["E8", "E4", "E40"])
+def test_a_token_without_an_order_leaves_the_others_alone(T, k, bad):
+    """Logits that are NaN give unspecified picks, but distinct ones: the other tokens' rows and what lies behind the workspace
+    stay as they are."""
+    E, Dm = len(bad), 32
+    gen = torch.Generator(device="cuda:0").manual_seed(T + E)
+    rnd = lambda *s: torch.randn(s, generator=gen, device="cuda:0")
+    u = rnd(1, T, Dm).bfloat16()
+    WB, WC = [(rnd(E, 1, 64, Dm) * Dm ** -0.5).bfloat16() for _ in range(2)]
+    logits = rnd(1, T, E).bfloat16()
+    logits[..., 1] += 8                              # an expert of every token: its list is full
+    logits[..., E - 1] += 8
+    size = sw.swimba_expert_proj_workspace_bytes(sw.make_dims(1, T, 1, 1, 64, 1, E, k, 1, torch.bfloat16), Dm)
+    ws = torch.full((size + 4096,), 171, dtype=torch.uint8, device="cuda:0")
+    want = sw.swimba_expert_proj_selected(u, WB, WC, logits, k)
+    logits[0, T - 1] = torch.tensor(bad)
+    got = sw.swimba_expert_proj_selected(u, WB, WC, logits, k, workspace=ws)
+    torch.cuda.synchronize()
+    assert bool((ws[size:] == 171).all())
+    for a, b in ((got.topk_idx, want.topk_idx), (got.B_experts, want.B_experts), (got.C_experts, want.C_experts)):
+        assert torch.equal(a[:, :-1], b[:, :-1])
+    picks = got.topk_idx[0, -1].sort().values
+    assert 0 <= int(picks[0]) and int(picks[-1]) < E and bool((picks.diff() > 0).all())
