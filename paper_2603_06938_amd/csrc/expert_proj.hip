@@ -505,11 +505,27 @@ swimba_status launch_expert_proj(int64_t tokens, int E, int K, int GN, int Dm, i
         SWIMBA_CHECK_LAUNCH();
         return SWIMBA_OK;
     }
+    int devid = 0, ncu = 0;
+    hipError_t he = hipGetDevice(&devid);
+    if (he == hipSuccess) he = hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, devid);
+    if (he != hipSuccess) { set_last_hip_error((int)he); return SWIMBA_ERR_HIP; }
+    // more than 64 KB of dynamic LDS has to be allowed once per device: the product's, and the lists' of 32 experts and 16 slots
+    auto route_shm = [](int K, int E) { return (size_t)256 * (2 * K + (E | 1)) * 4; };
+    static std::atomic<uint64_t> attr_set{0};                // one bit per device ordinal
+    const uint64_t bit = 1ull << (devid & 63);
+    if (!(attr_set.load(std::memory_order_acquire) & bit)) {
+        he = hipFuncSetAttribute((const void *)proj_mfma_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)PJ_SHM);
+        if (he == hipSuccess)
+            he = hipFuncSetAttribute((const void *)proj_route_segments_kernel<bf16>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                     (int)route_shm(SWIMBA_MAX_TOPK, PJ_SEG_EXPERTS));
+        if (he != hipSuccess) { set_last_hip_error((int)he); return SWIMBA_ERR_HIP; }
+        attr_set.fetch_or(bit, std::memory_order_release);
+    }
     int nseg = 1, seg_len = 0;
     if (E <= PJ_SEG_EXPERTS) {
         seg_len = (int)((tokens + 256 * PJ_MAX_SEGS - 1) / (256 * PJ_MAX_SEGS)) * 256;
         nseg = (int)((tokens + seg_len - 1) / seg_len);
-        hipLaunchKernelGGL(proj_route_segments_kernel<bf16>, dim3(nseg), dim3(256), (size_t)256 * (2 * K + (E | 1)) * 4, st,
+        hipLaunchKernelGGL(proj_route_segments_kernel<bf16>, dim3(nseg), dim3(256), route_shm(K, E), st,
                            (const bf16 *)logits, idx, w, counts, lists, tokens, E, K, seg_len);
     } else {
         hipLaunchKernelGGL(proj_clear_kernel, dim3(1), dim3(256), 0, st, counts, E);
@@ -520,20 +536,8 @@ swimba_status launch_expert_proj(int64_t tokens, int E, int K, int GN, int Dm, i
     SWIMBA_CHECK_LAUNCH();
     // one place per compute unit (a workgroup is 8 waves with up to 256 registers each), shared
     // by the column blocks; the kernel divides them among the experts
-    int devid = 0, ncu = 0;
-    hipError_t he = hipGetDevice(&devid);
-    if (he == hipSuccess) he = hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, devid);
-    if (he != hipSuccess) { set_last_hip_error((int)he); return SWIMBA_ERR_HIP; }
     const int colblocks = (pb.tot + PJ_COLS - 1) / PJ_COLS;
     const int nslots = max(1, ncu / colblocks);
-    // more than 64 KB of dynamic LDS has to be allowed once per device
-    static std::atomic<uint64_t> attr_set{0};                // one bit per device ordinal
-    const uint64_t bit = 1ull << (devid & 63);
-    if (!(attr_set.load(std::memory_order_acquire) & bit)) {
-        he = hipFuncSetAttribute((const void *)proj_mfma_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)PJ_SHM);
-        if (he != hipSuccess) { set_last_hip_error((int)he); return SWIMBA_ERR_HIP; }
-        attr_set.fetch_or(bit, std::memory_order_release);
-    }
     // the shares sum to at most nslots + E: each but one of an expert has the average of tiles a slot or more
     const unsigned grid = (unsigned)(((int64_t)(nslots + E) * colblocks + 7) / 8 * 8);
     hipLaunchKernelGGL(proj_mfma_kernel, dim3(grid), dim3(PJ_THREADS), PJ_SHM, st, (const uint16_t *)u, pb, counts, lists,

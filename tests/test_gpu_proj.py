@@ -44,6 +44,7 @@ SHAPES = [
     (1, 600, 64, 64, 8, 128, 2, "bf16"),    # MFMA: more experts than workgroups at once, lists in one piece
     (1, 66001, 32, 3, 1, 64, 2, "bf16"),    # MFMA: segments of the lists of more than 256 tokens
     (1, 300, 32, 32, 1, 64, 1, "bf16"),     # MFMA: most experts with segments, the second nearly empty
+    (1, 300, 32, 32, 1, 64, 16, "bf16"),    # MFMA: and most slots: the routing takes more than 64 KB of LDS
 ]
 
 
