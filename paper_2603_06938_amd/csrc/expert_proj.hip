@@ -152,15 +152,19 @@ constexpr size_t PJ_SHM = 3 * pj_buf(2);
 static_assert(PJ_SHM >= 2 * pj_buf(3) && PJ_SHM >= 2 * pj_buf(4), "LDS of the widest pass");
 
 // 16 bytes a lane from memory to LDS byte address lds (uniform) + 16 lane.  The compiler does not see these loads: it keeps its
-// own waits exact or longer, and pj_wait waits for them.
+// own waits exact or longer, and pj_wait waits for them.  m0, which holds the address, is no register that the compiler
+// allocates, and it warns at the name; named, no instruction that sets m0 for its own use is moved across.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 __device__ __forceinline__ void pj_copy(uint32_t lds, const void *base, uint32_t off)
 {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" :: "s"(__builtin_amdgcn_readfirstlane(lds)), "v"(off), "s"(base) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" :: "s"(__builtin_amdgcn_readfirstlane(lds)), "v"(off), "s"(base) : "memory", "m0");
 }
 __device__ __forceinline__ void pj_copy(uint32_t lds, const void *p)
 {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" :: "s"(__builtin_amdgcn_readfirstlane(lds)), "v"(p) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" :: "s"(__builtin_amdgcn_readfirstlane(lds)), "v"(p) : "memory", "m0");
 }
+#pragma clang diagnostic pop
 // until at most n vector memory operations of the wave are outstanding
 template <int n> __device__ __forceinline__ void pj_wait() { __builtin_amdgcn_s_waitcnt(0x0f70 | (n & 15) | (n >> 4) << 14); }
 
