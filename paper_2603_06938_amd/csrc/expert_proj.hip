@@ -11,7 +11,8 @@
 // written the same way into (B,L,E,H,P) or (B,L,k,H,P).
 //
 // Two launches: route every token and append the entry t*k + r to the list of its r-th expert; a
-// grouped GEMM over (share of an expert's list, 256 output columns).
+// grouped GEMM over (share of an expert's list, 256 output columns).  Above 32 experts a third one in
+// front of them clears the lists' lengths.
 // The GEMM is a dense contraction, so it runs on v_mfma_f32_32x32x16_bf16.  Both operands
 // are stored with the contraction index d contiguous (weights as (out, in), like a linear
 // layer), which is the 8-consecutive-k operand layout.  The product is computed transposed,
@@ -353,7 +354,7 @@ proj_mfma_kernel(const uint16_t *__restrict__ u, ProjBlocks pb, const int32_t *_
             const int ptiles = end - begin, half = (ptiles + 1) / 2;
             const int tbase = rg ? half : 0;                                 // first tile of this wave's row group
             const int nrt = rg ? ptiles - half : half;                       // its tiles, wave-uniform
-            const bool more = pass + 1 < npass;
+            const bool more = NBUF == 2 && pass + 1 < npass;                 // two tiles a group: one pass
             if (more) entries(next_row, pass + 1);
             const unsigned char *a_at = s_buf + (cw * 64 + l32) * PJ_ROW, *b_at = s_buf + PJ_WBYTES + (32 * tbase + l32) * PJ_ROW;
             pj_f32x16_t acc[2][RT];
@@ -362,8 +363,8 @@ proj_mfma_kernel(const uint16_t *__restrict__ u, ProjBlocks pb, const int32_t *_
 #pragma unroll
                 for (int rt = 0; rt < RT; ++rt) acc[ct][rt] = pj_f32x16_t{0};
             auto stage = [&](int st, auto whole_) __attribute__((always_inline)) {
-                // the next stage may be under way; behind a pass's results nothing is counted
-                if (NBUF == 3 && (st > 0 || pass == 0) && (st + 1 < stages || more)) pj_wait<LOADS>();
+                // with three buffers the next stage may be under way
+                if (NBUF == 3 && st + 1 < stages) pj_wait<LOADS>();
                 else pj_wait<0>();
                 lds_barrier();                               // the stage is in LDS; every wave is done with the one in front
                 const int at = buf * BUF;
@@ -447,8 +448,10 @@ proj_mfma_kernel(const uint16_t *__restrict__ u, ProjBlocks pb, const int32_t *_
             }
         }
     };
+    // Several passes have more than four tiles each, so two tiles a group are always one pass: its three buffers need not look
+    // past it.
     const int widest = (nt + npass - 1) / npass;
-    if (widest <= 4) run(std::integral_constant<int, 2>{});
+    if (nt <= 4) run(std::integral_constant<int, 2>{});
     else if (widest <= 6) run(std::integral_constant<int, 3>{});
     else run(std::integral_constant<int, 4>{});
 }
