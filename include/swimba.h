@@ -414,7 +414,8 @@ swimba_status swimba_router_linear(int64_t tokens, int32_t d_model, int32_t nexp
  * SWIMBA_MAX_DMODEL_GENERIC (the GEMM takes d_model up to 65536; beyond either limit the
  * workspace query returns 0 and the call SWIMBA_ERR_UNSUPPORTED).  The router's linear layer is not
  * part of this call: the logits are an input, so that the routing decision is the caller's.
- *   workspace >= swimba_expert_proj_workspace_bytes(dims, d_model), 256-byte aligned.
+ *   workspace >= swimba_expert_proj_workspace_bytes(dims, d_model), 256-byte aligned.  The size is this
+ *                 library's (another version may want a few KB more or less): ask, and keep none.
  */
 size_t swimba_expert_proj_workspace_bytes(const swimba_dims *dims, int32_t d_model);
 swimba_status swimba_expert_proj(const swimba_dims *dims, int32_t d_model, const void *u, const void *W_B,

@@ -1043,7 +1043,7 @@ static swimba_status proj_layout_of(const swimba_dims *d, int32_t d_model, ProjL
     size_t off = 0;
     o->idx = off;    off = align_up(off + (size_t)T * d->top_k * sizeof(int32_t), 256);
     o->w = off;      off = align_up(off + (size_t)T * d->top_k * sizeof(float), 256);
-    o->counts = off; off = align_up(off + PJ_COUNTS * sizeof(int32_t), 256);
+    o->counts = off; off = align_up(off + proj_counts_bytes(T, d->nexperts), 256);
     o->lists = off;  off = align_up(off + (size_t)T * d->nexperts * sizeof(int32_t), 256);
     o->total = off;
     return SWIMBA_OK;
@@ -1222,7 +1222,7 @@ static swimba_status mixproj_layout_of(const swimba_dims *d, int32_t d_model, Mi
     o->mixer = off;  off = align_up(off + lo.total, 256);
     o->bsel = off;   off = align_up(off + sel, 256);
     o->csel = off;   off = align_up(off + sel, 256);
-    o->counts = off; off = align_up(off + PJ_COUNTS * sizeof(int32_t), 256);
+    o->counts = off; off = align_up(off + proj_counts_bytes(T, d->nexperts), 256);
     o->lists = off;  off = align_up(off + T * d->nexperts * sizeof(int32_t), 256);
     o->total = off;
     return SWIMBA_OK;
@@ -1295,7 +1295,7 @@ static swimba_status xeproj_layout_of(const swimba_dims *d, int32_t d_model, XeP
     o->xsel = off;   off = align_up(off + T * d->top_k * d->nheads * d->headdim * io, 256);
     o->idx = off;    off = align_up(off + T * d->top_k * sizeof(int32_t), 256);
     o->w = off;      off = align_up(off + T * d->top_k * sizeof(float), 256);
-    o->counts = off; off = align_up(off + PJ_COUNTS * sizeof(int32_t), 256);
+    o->counts = off; off = align_up(off + proj_counts_bytes(T, d->nexperts), 256);
     o->lists = off;  off = align_up(off + T * d->nexperts * sizeof(int32_t), 256);
     o->total = off;
     return SWIMBA_OK;

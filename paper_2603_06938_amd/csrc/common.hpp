@@ -123,8 +123,18 @@ swimba_status launch_expert_proj(int64_t tokens, int E, int K, int GN, int Dm, i
 bool expert_proj_on_mfma(int io_dtype, int GN, int HP, int Dm);
 constexpr int PJ_SEG_EXPERTS = 32;     // most experts whose lists come in segments
 constexpr int PJ_MAX_SEGS = 256;       // most segments of a list
-constexpr int PJ_COUNTS = PJ_SEG_EXPERTS * PJ_MAX_SEGS;      // list lengths: of every segment, or of every expert
-static_assert(PJ_COUNTS >= SWIMBA_MAX_EXPERTS, "room for one length an expert");
+// Tokens of a segment, a multiple of 256, and segments of a list; one segment where the lists come in one piece.
+inline int64_t proj_seg_len(int64_t tokens) { return (tokens + 256 * PJ_MAX_SEGS - 1) / (256 * PJ_MAX_SEGS) * 256; }
+inline int proj_segments(int64_t tokens, int E)
+{
+    return E > PJ_SEG_EXPERTS || tokens == 0 ? 1 : (int)((tokens + proj_seg_len(tokens) - 1) / proj_seg_len(tokens));
+}
+// list lengths: one of every segment of every expert, and room for the most experts
+inline size_t proj_counts_bytes(int64_t tokens, int E)
+{
+    const size_t n = (size_t)E * proj_segments(tokens, E);
+    return (n > SWIMBA_MAX_EXPERTS ? n : SWIMBA_MAX_EXPERTS) * sizeof(int32_t);
+}
 swimba_status launch_slot_ids(int32_t *idx, int64_t tokens, int K, hipStream_t st);
 // expert-specific input streams (xe.hip)
 swimba_status launch_xe_gather(const Shape &s, int io_dtype, int slot, const void *x_experts,

@@ -528,10 +528,8 @@ swimba_status launch_expert_proj(int64_t tokens, int E, int K, int GN, int Dm, i
         if (he != hipSuccess) { set_last_hip_error((int)he); return SWIMBA_ERR_HIP; }
         attr_set.fetch_or(bit, std::memory_order_release);
     }
-    int nseg = 1, seg_len = 0;
+    const int nseg = proj_segments(tokens, E), seg_len = (int)proj_seg_len(tokens);
     if (E <= PJ_SEG_EXPERTS) {
-        seg_len = (int)((tokens + 256 * PJ_MAX_SEGS - 1) / (256 * PJ_MAX_SEGS)) * 256;
-        nseg = (int)((tokens + seg_len - 1) / seg_len);
         hipLaunchKernelGGL(proj_route_segments_kernel<bf16>, dim3(nseg), dim3(256), route_shm(K, E), st,
                            (const bf16 *)logits, idx, w, counts, lists, tokens, E, K, seg_len);
     } else {

@@ -66,6 +66,17 @@ def test_fp32_workspace_is_shared_and_no_larger_than_its_tokens_need(kw, most):
     assert lo.total <= max(lo.states_lp, lo.cs + most + 6 * 256)
 
 
+@pytest.mark.parametrize("tokens,nexperts,counts", [
+    (300, 8, 256), (8192, 8, 256), (100000, 33, 256), (100000, 256, 256),      # room for one length of the most experts
+    (16384, 8, 64 * 8), (300, 32, 256), (2305, 32, 10 * 32), (65536, 32, 256 * 32), (65537, 32, 129 * 32),
+])
+def test_projection_workspace_has_the_list_lengths_it_needs_and_no_more(tokens, nexperts, counts):
+    """Up to 32 experts the lists come in segments of a multiple of 256 tokens, 256 of them at most."""
+    up = lambda n: (n + 255) // 256 * 256
+    d = dims(batch=1, seqlen=tokens, nexperts=nexperts, io_dtype=1)
+    assert sw.swimba_expert_proj_workspace_bytes(d, 64) == 2 * up(tokens * 2 * 4) + up(counts * 4) + up(tokens * nexperts * 4)
+
+
 @pytest.mark.parametrize("kw,status", [
     (dict(io_dtype=7), 3),
     (dict(nheads=0), 2), (dict(top_k=0), 2), (dict(top_k=5), 2), (dict(ngroups=3), 2),
