@@ -158,7 +158,7 @@ __device__ __forceinline__ void chain_table(const ChainTables &t, int64_t bhs, f
     }
 }
 
-template <int NT, bool SEL>                              // SEL: rows of the selected experts and their weights
+template <int NT, bool SEL, bool ONCE>                   // SEL: rows of the selected experts and their weights; ONCE: row_piece
 __global__ void __launch_bounds__(CB_MIX_THREADS, 4)
 mix_steps_kernel(const bf16 *__restrict__ Be, const bf16 *__restrict__ Ce, const bf16 *__restrict__ logits,
                  int32_t *__restrict__ idx_out, float *__restrict__ w_out, const float *__restrict__ w_sel,
@@ -240,9 +240,7 @@ mix_steps_kernel(const bf16 *__restrict__ Be, const bf16 *__restrict__ Ce, const
                 w = s_w[row * K + r];
                 return base + (tok0 + j) * tokstride + s_idx[row * K + r] * estride + (int64_t)g * s.N + min(8 * pc, s.N - 8);
             };
-            // The experts' rows are read once and leave the last-level cache to what the walk reads next (130M-shaped layer 52.5 ->
-            // 47.0 us, two sequences of 16384 tokens 315 -> 309); selected rows have just been written by the projection.
-            auto row_piece = [&](const uint16_t *p) __attribute__((always_inline)) { return SEL ? *reinterpret_cast<const uint4 *>(p) : load_nt(p); };
+            auto row_piece = [&](const uint16_t *p) __attribute__((always_inline)) { return ONCE ? load_nt(p) : *reinterpret_cast<const uint4 *>(p); };
             int r = 0;
             for (; r + 1 < K; r += 2) {
                 uint4 v0[NT], v1[NT];
@@ -1054,8 +1052,9 @@ static swimba_status launch_mix_t(const Shape &s, const void *dt, const float *A
     const int nsteps = (s.L + CB_STEP - 1) / CB_STEP, ncu = device_cus();
     auto mix_shm = [](int K, int E) { return (size_t)2 * CB_STEP * (64 * NT + 16) + (size_t)CB_STEP * K * 8 + (E ? (size_t)CB_STEP * (E | 1) * 4 : 0); };
     static std::atomic<uint64_t> done{0};
-    const swimba_status ok = allow_lds(done, {{(const void *)mix_steps_kernel<NT, false>, mix_shm(SWIMBA_MAX_TOPK, SWIMBA_MAX_EXPERTS)},
-                                              {(const void *)mix_steps_kernel<NT, true>, mix_shm(SWIMBA_MAX_TOPK, 0)}});
+    const swimba_status ok = allow_lds(done, {{(const void *)mix_steps_kernel<NT, false, true>, mix_shm(SWIMBA_MAX_TOPK, SWIMBA_MAX_EXPERTS)},
+                                              {(const void *)mix_steps_kernel<NT, false, NT == 4>, mix_shm(SWIMBA_MAX_TOPK, SWIMBA_MAX_EXPERTS)},
+                                              {(const void *)mix_steps_kernel<NT, true, false>, mix_shm(SWIMBA_MAX_TOPK, 0)}});
     if (ok != SWIMBA_OK) return ok;
     // A workgroup routes its tokens once for as many groups as leave two workgroups to a compute unit.
     int gpb = 1;
@@ -1063,7 +1062,18 @@ static swimba_status launch_mix_t(const Shape &s, const void *dt, const float *A
         if (s.G % n == 0 && (int64_t)s.B * nsteps * s.G / n >= 2 * (int64_t)ncu) gpb = n;
     const int items = (int)((int64_t)s.B * nsteps * s.G / gpb);
     const int tblocks = (int)(((int64_t)s.B * nsteps * ((s.H + 7) / 8) + 7) / 8);
-    hipLaunchKernelGGL((w_sel ? mix_steps_kernel<NT, true> : mix_steps_kernel<NT, false>), dim3(items + tblocks), dim3(CB_MIX_THREADS), mix_shm(s.K, w_sel ? 0 : s.E), st,
+    // The experts' rows are read once and pass by the last-level cache (256 MB), which keeps x and the operands: of this call, or
+    // of calls on a few sets of inputs in turn, where these fit it then.  Plain loads / past the cache, us, 8 sequences x 24 heads
+    // x 2048 tokens, one group: one and two sets of inputs level (43.9 / 44.0), three 51.6 / 44.0, four and more 53.3 / 52.8; eight
+    // groups 85 / 77 and 97.6 / 90.3; two sequences of 16384 x 64 heads 312 / 306 with any.
+    // Rows of less than a line share it with other groups, for which it is fetched again: one, three and eight sets, N = 16 in
+    // eight groups 42.4 / 50.0, 52.8 / 58.8, 52.9 / 59.0, N = 48 56.1 / 61.1, 67.8 / 72.9, 68.0 / 73.6 (N = 64 54.5 / 56.1,
+    // 68.6 / 68.2, 69.1 / 68.5).  In four groups that counts for less, and three sets gain more: N = 16 38.5 / 41.4, 47.0 / 41.0,
+    // 48.6 / 50.9, N = 48 45.2 / 47.5, 57.5 / 50.8, 58.0 / 59.3.
+    // Selected rows have just been written by the projection.
+    const bool once = !(s.N < 64 && s.G >= 8);
+    const auto kernel = w_sel ? mix_steps_kernel<NT, true, false> : once ? mix_steps_kernel<NT, false, true> : mix_steps_kernel<NT, false, NT == 4>;
+    hipLaunchKernelGGL(kernel, dim3(items + tblocks), dim3(CB_MIX_THREADS), mix_shm(s.K, w_sel ? 0 : s.E), st,
                        (const bf16 *)Be, (const bf16 *)Ce, (const bf16 *)logits, idx, w, w_sel, (uint16_t *)scr.ops,
                        (const bf16 *)dt, A, chain_tables(s, scr), s, nsteps, gpb, items);
     SWIMBA_CHECK_LAUNCH();

@@ -34,6 +34,9 @@ CASES = [
     (4, 67, 128, 24, 32, 4, 4, 1, False, True, 1.0),
     (2, 130, 64, 64, 128, 1, 4, 2, True, True, 10.0),     # 128 chains: a workgroup per channel tile on every unit
     (1, 130, 129, 64, 128, 1, 4, 2, True, True, 10.0),    # one more: both tiles in one
+    (130, 40, 8, 8, 40, 8, 4, 2, False, True, 1.0),       # rows of less than a line in 8 groups, several groups a workgroup
+    (3, 70, 7, 8, 56, 7, 4, 3, False, True, 1.0),         # in fewer groups
+    (2, 70, 16, 8, 24, 16, 4, 3, False, True, 1.0),
 ]
 
 
