@@ -50,7 +50,9 @@ swimba_status launch_router(int64_t tokens, int E, int K, int io_dtype, const vo
 // (First version: one expert at a time, token rows re-read per expert, 6 shuffles per sum:
 // 27 us on the 130M-shaped layer against a 4.5 us floor; rows in registers: 21 us.)  Registers for as many pieces of a row as
 // the width has and no more, so that 16384 tokens x 768 features are one round of waves: 12.7 -> 11.6 us.  At most three waves
-// to a SIMD: with four the compiler keeps fewer loads in flight (8192 tokens 8.4 us for 7.1, 16384 10.8).
+// to a SIMD: with four the compiler keeps fewer loads in flight (8192 tokens 8.4 us for 7.1, 16384 10.8).  Rows of 1025 to 2048 features
+// take two waves' registers whatever it is told; told two to three, it orders their loads worse (4096 tokens x 1536 features
+// 8.3 us for 8.0, 300 tokens x 2048 x 64 experts 34.0 for 33.0).
 constexpr int RL_TOK = 4;
 constexpr int RL_EXP = 8;
 
@@ -79,7 +81,7 @@ __device__ __forceinline__ void rl_halve(float (&v)[RL_TOK * RL_EXP], int lane, 
 }
 
 template <typename T, bool VEC, int REG>                   // REG: 16-byte pieces a lane keeps of a token row, 0 for none
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 3)))
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(REG == 4 ? 1 : 2, REG == 4 ? 8 : 3)))
 router_linear_kernel(const T *__restrict__ u, const T *__restrict__ Wg, T *__restrict__ logits, int64_t tokens,
                      int Dm, int E)
 {

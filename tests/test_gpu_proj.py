@@ -76,6 +76,10 @@ ROUTER_LINEAR_SHAPES = [
     (2, 37, 24, 4, "f32"), (1, 50, 33, 5, "f32"), (1, 3, 700, 256, "f32"),
     (2, 40, 48, 4, "bf16"), (1, 130, 77, 8, "bf16"),          # 77 features: element-wise path
     (2, 300, 768, 8, "bf16"), (1, 9, 1024, 16, "bf16"), (1, 1, 8, 1, "bf16"),
+    # both sides of each width that a lane keeps in one, two and four pieces, and past it: piece ends inside the row and at its
+    # end, last tokens and last experts that fill no wave
+    (1, 7, 512, 9, "bf16"), (1, 6, 520, 8, "bf16"), (1, 5, 1032, 3, "bf16"), (2, 37, 1536, 8, "bf16"), (1, 33, 2048, 12, "bf16"),
+    (1, 10, 2056, 8, "bf16"), (1, 3, 4096, 17, "bf16"),
 ]
 
 
