@@ -31,40 +31,6 @@ constexpr int MC_ROW = MN + 8;       // LDS row stride of the mixed rows (elemen
 constexpr int MC_EMAX = 16;          // experts the in-register routing takes
 constexpr int MC_KMAX = 2;           // active experts per token the gather registers take
 
-// route_token with the logits in registers: the same comparisons and the same arithmetic in the same
-// order, every loop unrolled over MC_EMAX slots so that no index is dynamic
-__device__ __forceinline__ void route_token_regs(const float (&v)[MC_EMAX], int E, int K, int32_t *idx, float *w)
-{
-    float m = -INFINITY;
-#pragma unroll
-    for (int e = 0; e < MC_EMAX; ++e)
-        if (e < E) m = fmaxf(m, v[e]);
-    float Z = 0.f;
-#pragma unroll
-    for (int e = 0; e < MC_EMAX; ++e)
-        if (e < E) Z += route_exp(v[e] - m);
-    const float invZ = 1.0f / Z;
-    float pv = 0.f;
-    int pi = -1;
-#pragma unroll
-    for (int r = 0; r < MC_KMAX; ++r) {
-        if (r < K) {
-            int best = -1;
-            float bv = 0.f;
-#pragma unroll
-            for (int e = 0; e < MC_EMAX; ++e) {
-                const bool after = (r == 0) || (v[e] < pv) || (v[e] == pv && e > pi);
-                if (e < E && after && (best < 0 || v[e] > bv)) { best = e; bv = v[e]; }
-            }
-            if (best < 0) { best = (pi + 1) % E; bv = -INFINITY; }   // logits outside the contract: a valid index
-            idx[r] = best;
-            w[r] = route_exp(bv - m) * invZ;
-            pv = bv;
-            pi = best;
-        }
-    }
-}
-
 // 8 x 8 transpose of 16-bit values: in[r] holds 8 values of row r, out[c] the 8 values of column c
 __device__ __forceinline__ void transpose8x8_b16(const uint4 (&in)[8], uint4 (&out)[8])
 {
@@ -146,7 +112,7 @@ mix_chunk_kernel(const uint16_t *__restrict__ Be, const uint16_t *__restrict__ C
 #pragma unroll
                     for (int e = 0; e < MC_EMAX; ++e) v[e] = to_float(bf16{raw[e]});
                 }
-                route_token_regs(v, s.E, K, id, ww);
+                route_few<MC_EMAX, MC_KMAX>([&](int e) { return v[e]; }, s.E, K, id, ww);
                 if (g == 0 && tid < valid) {
 #pragma unroll
                     for (int r = 0; r < MC_KMAX; ++r)

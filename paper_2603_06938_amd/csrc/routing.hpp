@@ -30,8 +30,9 @@ __device__ __forceinline__ int route_open(const int32_t *idx, int r, int pi, int
     return e;
 }
 
-// E <= EM experts, their logits in registers: a loop that loads one after the other waits for each.
-template <int EM, typename Load>                       // EM < 32
+// E <= EM experts, their logits in registers: a loop that loads one after the other waits for each.  KM: most picks, where these
+// are registers, too.
+template <int EM, int KM = 0, typename Load>           // EM < 32
 __device__ __forceinline__ void route_few(Load load, int E, int K, int32_t *idx, float *w)
 {
     float v[EM], m = -INFINITY, Z = 0.f;
@@ -45,7 +46,7 @@ __device__ __forceinline__ void route_few(Load load, int E, int K, int32_t *idx,
     float pv = 0.f;
     int pi = -1;
     uint32_t picked = 0;
-    for (int r = 0; r < K; ++r) {
+    auto pick = [&](int r) __attribute__((always_inline)) {
         int best = -1;
         float bv = 0.f;
 #pragma unroll
@@ -59,6 +60,13 @@ __device__ __forceinline__ void route_few(Load load, int E, int K, int32_t *idx,
         w[r] = route_exp(bv - m) * invZ;
         pv = bv;
         pi = best;
+    };
+    if constexpr (KM > 0) {
+#pragma unroll
+        for (int r = 0; r < KM; ++r)
+            if (r < K) pick(r);
+    } else {
+        for (int r = 0; r < K; ++r) pick(r);
     }
 }
 
