@@ -251,8 +251,9 @@ int swimba_pass_segments(const swimba_dims *dims);
 int swimba_forward_path(const swimba_dims *dims);
 int swimba_forward_segments(const swimba_dims *dims);
 
-/* The launches behind SWIMBA_PATH_CHAIN_BF16, for any bf16 MFMA dims (SWIMBA_ERR_UNSUPPORTED otherwise), on scratch of
- * their own that lies over that of the other stages: run in this order they give swimba_mixer_fwd's bits.
+/* The launches behind SWIMBA_PATH_CHAIN_BF16, for any bf16 MFMA dims (SWIMBA_ERR_UNSUPPORTED otherwise; chain_walk also for
+ * nheads * headdim >= 2^24, whose forward takes another path), on scratch of their own that lies over that of the other
+ * stages: run in this order they give swimba_mixer_fwd's bits.
  *   chain_mix  : logits, B/C_experts, dt, A -> ws.topk_idx, ws.topk_w, mixed operands and decay tables of every 64-token step
  *   chain_walk : x, D, h0 -> y, h_final; one launch, or two where a sequence is cut into segments */
 swimba_status swimba_stage_chain_mix(const swimba_dims *dims, const void *dt, const float *A, const void *B_experts,

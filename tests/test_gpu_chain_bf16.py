@@ -294,3 +294,20 @@ def test_values_that_are_not_finite_reach_no_earlier_tile(value):
         assert torch.isfinite(got.y[:, :96, 1]).all()
         assert torch.equal(got.y[:, :, [0, 2, 3]], base[:, :, [0, 2, 3]])
         assert not torch.isfinite(got.y[:, 100:, 1]).all()
+
+
+def test_x_read_past_the_cache_changes_no_bit():
+    """Calls whose x and y fill the last-level cache read x past it.  Two sequences do here, either of them alone does not; a
+    last step of one token, heads narrower than two channel tiles."""
+    B, L, H, P, N, E = 2, 3777, 160, 56, 72, 4
+    assert B * L * H * P * 4 >= 256 << 20 > L * H * P * 4
+    gen = torch.Generator(device="cuda:0").manual_seed(3)
+    rnd = lambda *s: torch.randn(s, generator=gen, device="cuda:0").bfloat16()
+    x, Be, Ce, logits = rnd(B, L, H, P), rnd(B, L, E, 1, N), rnd(B, L, E, 1, N), rnd(B, L, E)
+    dt = torch.rand((B, L, H), generator=gen, device="cuda:0").mul_(0.1).bfloat16()
+    A, D = -torch.linspace(0.5, 16.0, H, device="cuda:0"), torch.linspace(-1.0, 1.0, H, device="cuda:0")
+    both = sw.swimba_mixer_fwd(x, dt, A, D, Be, Ce, logits, 2, 256)
+    assert bool(torch.isfinite(both.y).all())
+    for b in range(B):
+        one = sw.swimba_mixer_fwd(x[b:b + 1], dt[b:b + 1], A, D, Be[b:b + 1], Ce[b:b + 1], logits[b:b + 1], 2, 256)
+        assert torch.equal(one.y, both.y[b:b + 1]) and torch.equal(one.h_final, both.h_final[b:b + 1])

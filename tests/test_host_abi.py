@@ -77,6 +77,17 @@ def test_projection_workspace_has_the_list_lengths_it_needs_and_no_more(tokens, 
     assert sw.swimba_expert_proj_workspace_bytes(d, 64) == 2 * up(tokens * 2 * 4) + up(counts * 4) + up(tokens * nexperts * 4)
 
 
+@pytest.mark.parametrize("nheads,headdim,walks", [(262143, 64, True), (262144, 64, False), (300000, 56, False), (299593, 56, True)])
+def test_the_walk_takes_rows_of_less_than_2_24_channels(nheads, headdim, walks):
+    """It addresses the 64 rows of a step by 31-bit offsets; wider rows are the chunk kernels'."""
+    d = dims(seqlen=1, nheads=nheads, headdim=headdim, dstate=128, io_dtype=1)
+    size = sw.swimba_mixer_workspace_bytes(d)
+    assert size > 0
+    # valid workspace size, no tensors: NULL where the walk would run, UNSUPPORTED where it does not
+    st = sw._load().swimba_stage_chain_walk(ctypes.byref(d), None, None, None, None, None, 4096, size, None)
+    assert st == (1 if walks else 4)
+
+
 @pytest.mark.parametrize("kw,status", [
     (dict(io_dtype=7), 3),
     (dict(nheads=0), 2), (dict(top_k=0), 2), (dict(top_k=5), 2), (dict(ngroups=3), 2),
