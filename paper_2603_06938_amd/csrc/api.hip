@@ -203,12 +203,17 @@ static bool use_chunk_mix(const swimba_dims *d, bool selected)
 
 // The bf16 forward as one walk over 64-token steps (chain_bf16.hip), two launches, or three where it cuts the sequence; its
 // scratch lies over cmix .. cb, states_lp, hmid and cs.  A chain's steps are serial, 0.7 us each (few chains) to 1.35 (all units
-// busy): ahead of the kernels above up to 16 steps (4 and 8 chains of 1024 tokens are level, 21.5 / 21.3 us and 21.7 / 21.7, in 4
-// groups 23.2 / 22.6 and 23.1 / 22.5), from 40 chains on up to 24 (40 chains of 20 steps 25.8 / 25.7, of 24 28.6 / 27.0; 48 of 24
-// 28.8 / 31.5; 32 of 20 26.0 / 24.9) and from 64 on up to 32 (64 chains 34.8 / 37.7, in 4 groups 35.6 / 40.6; 48 chains 34.3 /
-// 33.9), from 96 chains on up to 128 (96 chains of 6000 tokens 89 / 110 before the walk's waves parted) and where the chains fill
-// three fifths of their rounds at any length (256 of 4096 tokens 99 for the walk, 147 when the others were last timed), or where segments do (chain_bf16_segments).
-// Short of that the kernels that also parallelise over chunks stay ahead.
+// busy).  Taken, walk / the kernels above in us (N = 128, three sets of inputs in turn):
+//   up to 16 steps                    4 and 8 chains of 16 21.4 / 21.4 and 21.8 / 21.8, in 4 groups 23.5 / 23.0 and 23.3 / 22.9;
+//                                     300 chains of 16 44.4 / 61.6
+//   up to 24 from 40 chains on        40 of 20 25.8 / 25.5, of 24 28.5 / 27.0, which the line loses; 44 and 48 of 24 28.5 / 31.4
+//                                     and 28.5 / 31.3 (32 of 20 26.2 / 24.8, of 24 28.5 / 26.2)
+//   up to 32 from 64 chains on        34.5 / 37.4, in 4 groups 34.9 / 39.3 (48 of 32 34.1 / 33.6)
+//   up to 128 from 96 chains on       of 40 40.8 / 55.9, of 64 57.5 / 75.0, of 94 96.6 / 114.7
+//   any from three fifths of their rounds on    160 chains of 32 43.0 / 68.2, 156 of 200 238 / 379, 256 of 64 99 / 197
+//   where segments fill the chip (chain_bf16_segments)
+// Short of that the kernels that also parallelise over chunks were ahead when the lines were drawn; the walk has become faster since
+// and would be now at 56 chains of 32 (34.2 / 35.4), 72 of 48 (45.3 / 53.5) and 88 of 48 (46.6 / 64.3), too.
 // The walk addresses the 64 rows of a step by 31-bit offsets; past that, a row of 2^24 channels, the staged kernels take over.
 static bool chain_bf16_rows_fit(const swimba_dims *d) { return (int64_t)d->nheads * d->headdim < (1ll << 24); }
 static bool use_chain_bf16(const swimba_dims *d)

@@ -350,7 +350,9 @@ constexpr int cb_state_waves(int PT, int CW) { return CW ? CW / 2 : 2 * PT; }
 constexpr int cb_threads(int PT, int CW) { return 64 * (cb_state_waves(PT, CW) + CW / 2 + 2 * PT); }
 
 // XONCE: x passes by the caches.  Registers for two workgroups to a unit where no Y is written: the pieces of two sequences of
-// 16384 tokens x 64 heads, 512 workgroups, are one round then (314 -> 309 us).
+// 16384 tokens x 64 heads, 512 workgroups, are one round then (314 -> 309 us).  With operands loaded two steps ahead the 128
+// registers of that are 21 too few at N = 128 (11 with one channel tile; one step ahead it was 106 without spills).  The walk of
+// one channel tile on four waves is 3 short.
 template <int NT, int PT, int CW, bool XONCE = false>
 __global__ void __launch_bounds__(cb_threads(PT, CW), CW == 0 ? 4 : PT == 1 && CW == 4 ? 3 : 2)
 chain_bf16_kernel(const uint16_t *__restrict__ x, const float *__restrict__ D, const uint16_t *__restrict__ ops, ChainTables tb,
@@ -977,14 +979,16 @@ size_t chain_bf16_table_bytes(const Shape &s)
 }
 
 // Segments of a sequence, before the scratch is asked how many pieces it holds.  A compute unit takes 1.35 us for a step of a
-// head when all are busy, and a chain alone 0.7 a step, so short of a quarter as many chains as units the chip idles (the times
-// below are from before the state and readout waves parted): as many
-// segments as fill it, of at least 12 steps each, or 8 where it stays half empty (24 chains of 256 steps: 1 segment 191 us, 5
-// 82, 10 70; 64 of 64: 58, 4 segments 48).  With less work than nine steps a unit the kernels that parallelise over chunks are
-// ahead (48 chains of 40 steps: 38.1 / 34.9, 32 of 64: 39.1 / 36.8; 48 of 56: 45.9 / 49.3, 8 of 217: 40 / 92).  From a quarter
-// as many chains on the extra launch pays from 128 steps on (128 of 256 steps: 396 / 345, 96 of 128: 148 / 139, 96 of 64:
-// 62 / 66), and two rounds of more segments where they are fuller by a sixth than one (96 chains of 256 steps: 2 segments
-// 262, 5 259).  Chains that fill three fifths of a round stay whole.
+// head when all are busy, and a chain alone 0.7 a step, so short of a quarter as many chains as units the chip idles: as many
+// segments as fill it, of at least 12 steps each, or 8 where it stays half empty (us; 24 chains of 256 steps: 1 segment 183, 5
+// 76, 10 68; 64 of 64: 56, 4 segments 47.6; 8 of 256: 179, 16 45).  With less work than nine steps a unit and less than 160
+// steps the kernels that parallelise over chunks are taken, segments / those: 48 chains of 40 36.2 / 34.8, 32 of 64 38.6 / 36.8,
+// 16 of 128 40.0 / 41.9, 8 of 128 33.7 / 34.3; past the line 48 of 48 40.0 / 44.5, 32 of 72 42.4 / 46.2, 8 of 217 41.2 / 48.7.
+// From a quarter as many chains on the extra launch pays from 128 steps on (1 segment / 2: 128 of 128 144 / 126, of 256 275 / 232,
+// 128 of 64 62 / 69, 96 of 64 58 / 64), and two rounds of more segments where these are fuller by a sixth than one: of 96 chains,
+// 2 segments / 5, 256 steps 230 / 228, 160 156 / 159, 128 119 / 129, so that it gains only at the longest.  Chains that fill three
+// fifths of a round stay whole (156 of 200: 238, 2 segments 314); 144 of 200, just short of that, are cut and lose (236, 3
+// segments 271).
 int chain_bf16_segments(int64_t chains, int64_t steps, int64_t ncu)
 {
     if (steps <= 32 || chains == 0 || 10 * chains >= 6 * ncu || (chains * steps < 9 * ncu && steps < 160)) return 1;
@@ -1100,9 +1104,12 @@ static swimba_status launch_walk_t(const Shape &s, const void *x, const float *D
     // Workgroups of one channel tile where all of them find a compute unit at once; else of both tiles of a head, one to a unit,
     // where the heads fill one round or three fifths of several; else (300 heads of 1024 tokens 45 / 48 us with both tiles in
     // one), and for more heads of one tile than units (320 of 512 tokens, P = 64, N = 64: 29 / 38), of fewer waves, two to a unit.
-    // x and y that fill the last-level cache (256 MB) by themselves: x is not found there when it is read, and passes by it, too
-    // (370M-shaped layer, 268 MB: 101.7 -> 98 us; 130M-shaped, 100 MB: 47.0 -> 51.6), unless pieces of it are walked twice (two
-    // sequences of 16384 tokens 309 -> 320).
+    // x and y that fill the last-level cache (256 MB) by themselves: x passes by it, unless pieces of it are walked twice (two
+    // sequences of 16384 tokens 309 -> 320 us).  On four and more sets of inputs in turn it is not found there, and passing by is
+    // ahead (x and y of 134 MB 57.7 -> 55.1 us, 201 MB 80.0 -> 77.7, 268 MB, the 370M-shaped layer, 100.4 -> 98.2, 402 MB 146.3 ->
+    // 143.9, 537 MB 190.8 -> 187.9).  An x that the cache still holds, because nothing else ran since it was written or read, is
+    // lost with it (one set of inputs again and again: 134 MB 48.8 -> 58.5, 201 MB 69 -> 80, 268 MB 87 -> 99, 402 MB 135 -> 144, 537 MB
+    // 189 -> 187).  The line lies where what a program ran before has left the less of x the larger it is.
     const bool x_once = plan.nseg == 1 && (int64_t)s.B * s.L * s.H * s.P * 4 >= 256 << 20;
     auto launch = [&](bool out, int count, int steps) {
         const int64_t chains = (int64_t)s.B * s.H * count, rounds = (chains + ncu - 1) / ncu;

@@ -137,9 +137,11 @@ __device__ __forceinline__ uint32_t pj_pack(float lo, float hi)
 // 16-byte pieces lie exclusive-or'ed with half its number, so that the 16 rows that 16 lanes read lie
 // in different banks (with the number itself every read took twice as long).
 // Against the same stages through registers and padded LDS rows, and shares by rounded-down counts: 8192 tokens x 1792 columns
-// (130M-shaped layer with input streams) 78 -> 65 to 67 us, 16384 tokens x 256 columns 30 -> 28 to 29 (kernel trace).  With the
-// reads' bank conflicts still there the whole call (lists and product) took 79.6 and 42.3 us, for 75.8 and 39.2 without; of the
-// former, left out one at a time: the MFMAs 20 / 6.5, the stores of the results 11.6 / 6, the copies 9 / 4; 2.3 until a
+// (130M-shaped layer with input streams) 78 -> 65 to 67 us, 16384 tokens x 256 columns 30 -> 27 to 29 (kernel trace).  Counters of
+// the two: matrix pipes busy 32 and 16 % of the kernel's time, no bank conflicts, operand reads 28 and 16 % of what LDS carries at
+// 128 bytes a clock, waves waiting for an instruction 44 and 35 % of theirs: no unit is near its rate, the waits between the
+// phases of a stage are what is left.  Left out one at a time, in a build whose reads still met in LDS banks, calls (lists and
+// product) of 79.6 and 42.3 us: the MFMAs 20 / 6.5, the stores of the results 11.6 / 6, the copies 9 / 4; 2.3 until a
 // workgroup has its share.  Worse: all copies of a stage in front of its MFMAs (2 / 3 us), one behind each pair of
 // MFMAs (4 / 5), the first wait of a pass that counts the stores in front of it (2 / 0).
 constexpr int PJ_THREADS = 512;
