@@ -103,9 +103,9 @@ mix_ops_kernel(const T *__restrict__ Be, const T *__restrict__ Ce, const T *__re
     const bool sel = (w_sel != nullptr);
     const ChainOps ops = chain_ops(s.L);
 
-    // more than 16 experts: the step's logits, one piece of memory, pass through LDS; up to 16 go through registers
+    // the step's logits, one piece of memory, pass through LDS where they do not fit registers
     const int ES = s.E | 1;                              // row stride
-    if (!sel && s.E > 16) {
+    if (!sel && s.E > ROUTE_FEW) {
         for (int i = tid; i < valid * s.E; i += CF_MIX_THREADS) s_B[i / s.E * ES + i % s.E] = to_float(logits[tok0 * s.E + i]);
         __syncthreads();
     }
@@ -116,17 +116,11 @@ mix_ops_kernel(const T *__restrict__ Be, const T *__restrict__ Ce, const T *__re
         if (sel) {
             for (int r = 0; r < K; ++r) { ix[r] = r; wx[r] = w_sel[t * K + r]; }
         } else {
-            float *row = s_B + tid * (s.E > 16 ? ES : 17);
-            if (s.E <= 16) {
-                const T *gl = logits + t * s.E;
-                float v[16];
-#pragma unroll
-                for (int e = 0; e < 16; ++e) v[e] = to_float(gl[min(e, s.E - 1)]);
-                // every load is in flight before the first is used
-#pragma unroll
-                for (int e = 0; e < 16; ++e) row[e] = v[e];
-            }
-            route_token([&](int e) { return row[e]; }, s.E, K, ix, wx);
+            const T *gl = logits + t * s.E;
+            const float *row = s_B + tid * ES;
+            if (s.E <= 8) route_few<8>([&](int e) { return to_float(gl[e]); }, s.E, K, ix, wx);
+            else if (s.E <= ROUTE_FEW) route_few<ROUTE_FEW>([&](int e) { return to_float(gl[e]); }, s.E, K, ix, wx);
+            else route_many([&](int e) { return row[e]; }, s.E, K, ix, wx);
             if (g_begin == 0 && tid >= r0 && tid < r0 + R)
                 for (int r = 0; r < K; ++r) { idx_out[t * K + r] = ix[r]; w_out[t * K + r] = wx[r]; }
         }

@@ -70,11 +70,11 @@ __device__ __forceinline__ void route_few(Load load, int E, int K, int32_t *idx,
     }
 }
 
+constexpr int ROUTE_FEW = 16;                          // most experts whose logits lie in registers
+
 template <typename Load>
-__device__ __forceinline__ void route_token(Load load, int E, int K, int32_t *idx, float *w)
+__device__ __forceinline__ void route_many(Load load, int E, int K, int32_t *idx, float *w)
 {
-    if (E <= 8) return route_few<8>(load, E, K, idx, w);
-    if (E <= 16) return route_few<16>(load, E, K, idx, w);
     float m = -INFINITY;
     for (int e = 0; e < E; ++e) m = fmaxf(m, load(e));
     float Z = 0.f;
@@ -97,6 +97,14 @@ __device__ __forceinline__ void route_token(Load load, int E, int K, int32_t *id
         pv = bv;
         pi = best;
     }
+}
+
+template <typename Load>
+__device__ __forceinline__ void route_token(Load load, int E, int K, int32_t *idx, float *w)
+{
+    if (E <= 8) return route_few<8>(load, E, K, idx, w);
+    if (E <= ROUTE_FEW) return route_few<ROUTE_FEW>(load, E, K, idx, w);
+    route_many(load, E, K, idx, w);
 }
 
 }  // namespace swimba
