@@ -204,7 +204,8 @@ def test_a_reference_changes_no_bit_in_front(s):
 
 
 @pytest.mark.parametrize("s", [1, 20, 31, 32, 33, 50, 63, 64, 100])
-@pytest.mark.parametrize("shape", [(24, 64, 128), (3, 40, 72), (160, 64, 16)], ids=["H24", "H3P40N72", "H160N16"])
+@pytest.mark.parametrize("shape", [(24, 64, 128), (3, 40, 72), (160, 64, 16), (300, 32, 72)],
+                         ids=["H24", "H3P40N72", "H160N16", "H300P32N72"])
 def test_a_direct_step_changes_no_bit_in_front(s, shape):
     """Step sizes from token s on that take its step from one reference, or one per half, to direct, to a rising cs, or to a
     value that is not finite: tokens in front keep their bits, and so do all others where the mode alone changes."""
@@ -265,7 +266,17 @@ def test_magnitudes(sx, sb, sc, L):
 @pytest.mark.parametrize("s", [0, 5, 40, 63, 64, 130])
 def test_one_tokens_magnitude_changes_no_bit_in_front(scale, s):
     """A token whose x no factor fits takes its step to direct: the tokens in front keep their bits, those behind it are right."""
-    p, h0 = inputs((1, 150, 24, 64, 128, 1, 4, 2, True, True, 1.0), 16)
+    one_token(scale, s, 24, 64, 128)
+
+
+@pytest.mark.parametrize("shape", [(160, 64, 128), (300, 32, 72)], ids=["both tiles", "two workgroups a unit"])
+@pytest.mark.parametrize("scale,s", [(1e30, 5), (1e30, 40), (5e37, 130), (0.0, 64)])
+def test_one_tokens_magnitude_however_the_waves_share_the_walk(scale, s, shape):
+    one_token(scale, s, *shape)
+
+
+def one_token(scale, s, H, P, N):
+    p, h0 = inputs((1, 150, H, P, N, 1, 4, 2, True, True, 1.0), 16)
     p["A"][::2] = -16.0
     p["dt"] = np.abs(p["dt"]) + np.float32(0.03125)       # most steps span 2^60 and more
     p["dt"] = torch.from_numpy(p["dt"]).to(torch.bfloat16).to(torch.float32).numpy()

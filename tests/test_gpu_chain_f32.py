@@ -123,13 +123,26 @@ def test_a_state_in_place_gives_the_same_bits(cfg):
     assert torch.equal(over.y, apart.y) and torch.equal(state, apart.h_final)
 
 
+WHICH = ["x_inf", "x_nan", "dt_inf", "dt_nan", "B_nan", "C_inf"]
+
+
 @pytest.mark.parametrize("L,j", [(600, 5), (600, 31), (600, 32), (600, 63), (600, 64), (600, 80), (600, 330), (20, 5)])
-@pytest.mark.parametrize("which", ["x_inf", "x_nan", "dt_inf", "dt_nan", "B_nan", "C_inf"])
+@pytest.mark.parametrize("which", WHICH)
 def test_values_that_are_not_finite_stay_causal(which, L, j):
     """Uninitialised padding behind a sequence, say: tokens in front of it, other channels (x), other heads (dt)
     and other sequences keep their values; its own token does not hide it."""
-    cfg = (2, L, 4, 40, 48, 1, 8, 2, "f32")                         # 600 tokens: five segments of two steps
-    B, _, H, P = cfg[:4]
+    stays_causal((2, L, 4, 40, 48, 1, 8, 2, "f32"), which, j)       # 600 tokens: five segments of two steps
+
+
+@pytest.mark.parametrize("N", [20, 65, 200], ids=["four waves a tile", "one", "two tiles a wave"])
+@pytest.mark.parametrize("L,j", [(600, 10), (600, 63), (600, 90), (20, 5)])
+@pytest.mark.parametrize("which", WHICH)
+def test_values_that_are_not_finite_stay_causal_however_the_waves_share_the_state(which, L, j, N):
+    stays_causal((2, L, 4, 40, N, 1, 8, 2, "f32"), which, j)
+
+
+def stays_causal(cfg, which, j):
+    B, L, H, P = cfg[:4]
     p, h0 = inputs(*cfg)
     d = to_device(p, "f32")
     names = ("x", "dt", "A", "D", "B_experts", "C_experts", "router_logits")
